@@ -5,7 +5,9 @@
  * arXiv 2006.06762 ("Ansor"): GMM, C2D and DEP of the single-operator
  * benchmark (Sec. 7.1, shapes in Appendix C) and the ConvLayer and TBS
  * subgraphs (Sec. 7.2).  All arithmetic is fp32 in, fp32 accumulate, fp32 out
- * (Sec. 7: float32 is used for all evaluations).
+ * (Sec. 7: float32 is used for all evaluations); large products multiply each
+ * float as the exact sum of three bf16 numbers, with results no further from the
+ * exact ones than fp32 products give.
  *
  * Conventions common to every call
  *   - Every tensor pointer is DEVICE memory owned by the caller.  The library

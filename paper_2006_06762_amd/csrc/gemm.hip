@@ -12,6 +12,7 @@
 #include "anr_device.h"
 #include "anr_kernels.h"
 #include "gemm_pipe_kernel.h"
+#include "gemm_split_kernel.h"
 
 namespace anr {
 namespace {
@@ -403,38 +404,79 @@ hipError_t launch_variant(const GemmArgs& a, hipStream_t stream)
 }
 
 
-template <int BM, int BN, bool NT, int NWG = 1>
-hipError_t launch_pipe(const GemmArgs& a, hipStream_t stream)
+template <int BM, int WM, int WN, int NWG, bool NT>
+hipError_t launch_split(const GemmArgs& a, hipStream_t stream)
 {
-    const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
-    const size_t lds_bytes = NWG * gpipe::Tiles<BM, BN, NT>::lds_bytes;
-    auto kern = gpipe::gemm_pipe_kernel<BM, BN, NT, NWG>;
+    const gsplit::Grid g{(a.M + BM - 1) / BM, (a.N + BM - 1) / BM, BM == 256 ? 4 : 8};
+    constexpr size_t lds_bytes = gsplit::lds_bytes<BM, BM, NWG>();
+    auto kern = gsplit::gemm_split_kernel<BM, BM, WM, WN, NWG, 2, NT>;
     if (lds_bytes > 48 * 1024) {
         static LdsLimit granted;
         hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_bytes, granted);
         if (e != hipSuccess) return e;
     }
-    return launch_kernel(kern, dim3((unsigned)(tiles_m * tiles_n), 1, a.batch), dim3(256 * NWG), lds_bytes, stream, a,
-                         tiles_m, tiles_n);
+    return launch_kernel(kern, dim3((unsigned)((int64_t)g.tiles_m * g.tiles_n * a.batch)), dim3(64 * WM * WN * NWG), lds_bytes,
+                         stream, a, g);
 }
 
-// Tile for the pipelined kernel: the largest that still puts two work-groups on every CU (they
-// fill each other's barrier and staging bubbles: 82 % MFMA utilisation against 55 % for a lone
-// work-group); large tiles also pull fewer operand bytes per FLOP into the CU.
+// Tile and wave groups of the split kernel: the variant with the shortest estimated time.  `base` is
+// launch, prologue and epilogue, `round` the time in which each group of a work-group alone on its CU
+// gets one 32-wide chunk done (load latency, staging, two barriers), `busy` a CU's time per chunk and
+// work-group once several fill it: us, measured on 32^3 to 1500^3 (`base`, `round`) and 4096^3 (`busy`).
+// Large tiles read fewer operand bytes per FLOP, small ones spread a small product over more CUs, and wave
+// groups shorten the chain of chunks where there are not enough tiles even so.
 template <bool NT>
-hipError_t launch_pipe_any(const GemmArgs& a, hipStream_t stream)
+hipError_t launch_split_any(const GemmArgs& a, hipStream_t stream)
 {
-    auto tiles = [&](int bm, int bn) {
-        return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.batch;
+    struct Variant {
+        int tile, groups;
+        double base, round, busy;
     };
-    if (tiles(128, 128) >= 512) return launch_pipe<128, 128, NT>(a, stream);
-    if (tiles(128, 64) >= 512) return launch_pipe<128, 64, NT>(a, stream);
-    // at most one 64 x 64 tile per CU and a long reduction: groups of waves share the chunk chain
-    // (1024^3: 28.6 us with one group)
-    const int nchunks = (a.K + gpipe::KC - 1) / gpipe::KC;
-    if (tiles(64, 64) <= 256 && nchunks >= 32) return launch_pipe<64, 64, NT, 4>(a, stream);
-    if (tiles(64, 64) <= 256 && nchunks >= 8) return launch_pipe<64, 64, NT, 2>(a, stream);
-    return launch_pipe<64, 64, NT>(a, stream);
+    constexpr Variant kVariants[] = {{256, 1, 9.0, 3.75, 4.4}, {128, 1, 5.4, 1.68, 1.27}, {128, 2, 6.8, 2.47, 1.4},
+                                     {64, 1, 3.9, 1.13, 0.47}, {64, 2, 3.6, 1.45, 0.44}, {64, 4, 5.6, 1.9, 0.55}};
+    const int chunks = (a.K + gsplit::KC - 1) / gsplit::KC;
+    int best = 0;
+    double best_us = 0.0;
+    for (int v = 0; v < 6; ++v) {
+        const Variant& t = kVariants[v];
+        const int64_t tiles = (int64_t)((a.M + t.tile - 1) / t.tile) * ((a.N + t.tile - 1) / t.tile) * a.batch;
+        const double chain = (double)((chunks + t.groups - 1) / t.groups) * t.round;
+        const double work = (double)((tiles + 255) / 256) * chunks * t.busy;
+        const double us = t.base + (work > chain ? work : chain);
+        if (v == 0 || us < best_us) {
+            best = v;
+            best_us = us;
+        }
+    }
+    switch (best) {
+        case 0: return launch_split<256, 2, 4, 1, NT>(a, stream);
+        case 1: return launch_split<128, 2, 2, 1, NT>(a, stream);
+        case 2: return launch_split<128, 2, 2, 2, NT>(a, stream);
+        case 3: return launch_split<64, 2, 1, 1, NT>(a, stream);
+        case 4: return launch_split<64, 2, 1, 2, NT>(a, stream);
+        default: return launch_split<64, 2, 1, 4, NT>(a, stream);
+    }
+}
+
+// The fp32 pipelined kernel where it is the faster one: at most one 64 x 64 tile per CU and a short
+// reduction, so that the time is a chain of latencies (splitting adds an LDS round trip to every chunk).
+// 300^3 9.9 against 11.1 us, 1000 x 1000 x 128 5.8 against 7.8, 32^3 3.0 against 4.8; from K = 500 on the
+// split kernel's four wave groups win (500^3 13.1 against 13.0, 768^3 17.7 against 15.8).
+hipError_t launch_pipe(const GemmArgs& a, hipStream_t stream, bool* taken)
+{
+    const int tiles_m = (a.M + 63) / 64, tiles_n = (a.N + 63) / 64;
+    *taken = a.K <= 96 || (a.K < 480 && (int64_t)tiles_m * tiles_n * a.batch <= 256);
+    if (!*taken) return hipSuccess;
+    const dim3 grid((unsigned)(tiles_m * tiles_n), 1, a.batch);
+    // a longer chain of chunks is shared by two groups of waves
+    if (a.K > 7 * gpipe::KC) {
+        constexpr size_t lds_bytes = 2 * gpipe::kLdsBytes;
+        static LdsLimit granted;
+        hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(gpipe::gemm_pipe_kernel<2>), lds_bytes, granted);
+        if (e != hipSuccess) return e;
+        return launch_kernel(gpipe::gemm_pipe_kernel<2>, grid, dim3(512), lds_bytes, stream, a, tiles_m, tiles_n);
+    }
+    return launch_kernel(gpipe::gemm_pipe_kernel<1>, grid, dim3(256), gpipe::kLdsBytes, stream, a, tiles_m, tiles_n);
 }
 
 }  // namespace
@@ -464,10 +506,20 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream)
     // 32-bit byte offsets inside one matrix, grid limits
     const int64_t a_ext = (int64_t)(a.M - 1) * a.lda + a.K;
     const int64_t b_ext = a.b_is_nk ? (int64_t)(a.N - 1) * a.ldb + a.K : (int64_t)(a.K - 1) * a.ldb + a.N;
-    const bool pipe = vec && a_ext < ((int64_t)1 << 29) && b_ext < ((int64_t)1 << 29) && a.batch <= 65535 &&
-                      (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) < ((int64_t)1 << 31);
-    if (pipe && !a.b_is_nk) {
-        err = launch_pipe_any<false>(a, stream);
+    // (work-items in one grid dimension stay below 2^32: a 64 x 64 tile has 128 to 512 of them)
+    const bool split = a_ext < ((int64_t)1 << 29) && b_ext < ((int64_t)1 << 29) &&
+                       (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch < ((int64_t)1 << 22);
+    bool piped = false;
+    err = hipSuccess;
+    if (split && vec && !a.b_is_nk) err = launch_pipe(a, stream, &piped);
+    if (err != hipSuccess) return err;
+    // operands the pipelined kernel cannot load, two chunks or less and at most one tile per CU: the plain
+    // kernel's prologue is the shortest (33^3 3.8 against 5.3 us, 65 x 67 x 63 x16 5.0 against 5.6)
+    const bool tiny = a.K <= 64 && (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch <= 256;
+    if (piped) {
+        // enqueued
+    } else if (split && !tiny) {
+        err = a.b_is_nk ? launch_split_any<true>(a, stream) : launch_split_any<false>(a, stream);
     } else if (a.b_is_nk) {
         if (big) err = vec ? launch_variant<128, 128, 16, true, true>(a, stream)
                            : launch_variant<128, 128, 16, true, false>(a, stream);

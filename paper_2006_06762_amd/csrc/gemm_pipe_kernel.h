@@ -1,8 +1,8 @@
-// GMM (C = A.B, Sec. 4.1 and Appendix C of arXiv 2006.06762) and its A.B^T form for operands
-// that allow 16-byte loads (K, and N for the A.B form, multiples of 4; aligned bases and
-// leading dimensions), any M, N, K otherwise.
+// GMM (C = A.B, Sec. 4.1 and Appendix C of arXiv 2006.06762) with the fp32 matrix instruction, for small
+// products whose operands allow 16-byte loads (K and N multiples of 4; aligned bases and leading
+// dimensions), any M, N, K otherwise.
 //
-// Work-group tile BM x BN, 4 waves in a 2 x 2 grid, reduction in chunks of 32.  A chunk of a
+// Work-group tile 64 x 64, 4 waves in a 2 x 2 grid, reduction in chunks of 32.  A chunk of a
 // work-group that has a CU to itself costs one memory round trip unless more than one chunk
 // is in flight, so the operands travel global -> registers -> LDS with TWO chunks of
 // look-ahead in registers and a double-buffered LDS tile: while chunk c is multiplied,
@@ -11,12 +11,10 @@
 // reduction index past K gets an offset beyond the descriptor's extent, which loads zero
 // without a branch.
 //
-// LDS: A (and B of the A.B^T form) row-major in k with a row stride of 36 floats (a staging unit is
-// then one 16-byte store; with 34, conflict-free 8-byte operand reads but two stores per unit,
-// 1024^3 x16 and 4096^3 ran 3 % slower), read two k
-// at a time (8-byte reads, half-wave h takes k = 4j + 2h, 4j + 2h + 1: any order is a valid
-// reduction order as long as both operands use it); B of the A.B form stays k-major as it is
-// in memory, row stride BN + 16 floats (rows 4j + 2h of the two half-waves then fall into
+// LDS: A row-major in k with a row stride of 36 floats (a staging unit is then one 16-byte store), read
+// two k at a time (8-byte reads, half-wave h takes k = 4j + 2h, 4j + 2h + 1: any order is a valid
+// reduction order as long as both operands use it); B stays k-major as it is
+// in memory, row stride 64 + 16 floats (rows 4j + 2h of the two half-waves then fall into
 // different halves of the LDS banks), read one float per MFMA.
 #pragma once
 #include <type_traits>
@@ -31,28 +29,21 @@ constexpr int KC = 32;
 constexpr int WS = KC + 4;       // LDS row stride of the k-contiguous tiles: a staging unit is one 16-byte store
 constexpr uint32_t kOutOfRange = 0x80000000u;
 
-template <int BM, int BN, bool NT>
-struct Tiles {
-    static constexpr int A_SZ = BM * WS;
-    static constexpr int LDB = BN + 16;
-    static constexpr int B_SZ = NT ? BN * WS : KC * LDB;
-    static constexpr size_t lds_bytes = sizeof(float) * 2 * (size_t)(A_SZ + B_SZ);
-};
+constexpr int BM = 64, BN = 64;
+constexpr int A_SZ = BM * WS;
+constexpr int LDB = BN + 16;
+constexpr int B_SZ = KC * LDB;
+constexpr size_t kLdsBytes = sizeof(float) * 2 * (size_t)(A_SZ + B_SZ);     // per wave group
 
-// NWG > 1 (64 x 64 tiles only): the work-group has NWG groups of four waves; group w takes every
-// NWG-th chunk through staging buffers of its own and the groups' accumulators meet in LDS at the
-// end.  For launches with at most one work-group per CU the chain of a work-group's chunks is what
-// takes the time (the matrix pipes idle between its barriers); sharing it among groups shortens it.
-template <int BM, int BN, bool NT, int NWG = 1>
+// NWG > 1: the work-group has NWG groups of four waves; group w takes every NWG-th chunk through
+// staging buffers of its own and the groups' accumulators meet in LDS at the end.  For launches with at
+// most one work-group per CU the chain of a work-group's chunks is what takes the time (the matrix pipes
+// idle between its barriers); sharing it among groups shortens it.
+template <int NWG>
 __global__ __launch_bounds__(256 * NWG) void gemm_pipe_kernel(const GemmArgs p, int tiles_m, int tiles_n)
 {
-    using T = Tiles<BM, BN, NT>;
-    constexpr int MB = BM / 64, NB = BN / 64;
     constexpr int AU = BM / 32;                 // 16-byte units of A per thread and chunk
     constexpr int BU = BN / 32;                 // 16-byte units of B per thread and chunk
-    constexpr int A_SZ = T::A_SZ, B_SZ = T::B_SZ, LDB = T::LDB;
-
-    static_assert(NWG == 1 || (MB == 1 && NB == 1), "wave groups share 64 x 64 tiles only");
     constexpr int REGION = 2 * (A_SZ + B_SZ);   // floats of staging per wave group
 
     extern __shared__ __attribute__((aligned(16))) float plds[];   // per group: A[2][A_SZ], then B[2][B_SZ]
@@ -74,8 +65,7 @@ __global__ __launch_bounds__(256 * NWG) void gemm_pipe_kernel(const GemmArgs p, 
     const int M = p.M, N = p.N, K = p.K;
 
     const uint32_t a_bytes = 4u * (uint32_t)((int64_t)(M - 1) * p.lda + K);
-    const uint32_t b_bytes = NT ? 4u * (uint32_t)((int64_t)(N - 1) * p.ldb + K)
-                                : 4u * (uint32_t)((int64_t)(K - 1) * p.ldb + N);
+    const uint32_t b_bytes = 4u * (uint32_t)((int64_t)(K - 1) * p.ldb + N);
     const __amdgpu_buffer_rsrc_t arsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A), 0, (int)a_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t brsrc =
@@ -90,23 +80,14 @@ __global__ __launch_bounds__(256 * NWG) void gemm_pipe_kernel(const GemmArgs p, 
         row = row < M ? row : M - 1;
         aoff[j] = 4u * (uint32_t)((int64_t)row * p.lda + ak);
     }
-    constexpr int BQ = BN / 4;                  // A.B form: 16-byte units per k row of the B tile
-    const int bk = NT ? ak : tid / BQ;          // k offset of this thread's first B unit
-    bool bcol_ok = true;
+    constexpr int BQ = BN / 4;                  // 16-byte units per k row of the B tile
+    const int bk = tid / BQ;          // k offset of this thread's first B unit
+    // N is a multiple of 4: a unit is in or out as a whole; a column past N keeps the out-of-range marker
+    // whatever is added to it for the chunk (extents are below 2^29 floats)
+    const int bcol = n0 + 4 * (tid % BQ);
 #pragma unroll
-    for (int j = 0; j < BU; ++j) {
-        if (NT) {
-            int row = n0 + (tid >> 3) + 32 * j;
-            row = row < N ? row : N - 1;
-            boff[j] = 4u * (uint32_t)((int64_t)row * p.ldb + ak);
-        } else {
-            const int col = n0 + 4 * (tid % BQ);
-            bcol_ok = col < N;                  // N is a multiple of 4: a unit is in or out as a whole
-            // a column past N keeps the out-of-range marker whatever is added to it for the chunk
-            // (extents are below 2^29 floats)
-            boff[j] = bcol_ok ? 4u * (uint32_t)((int64_t)(bk + (256 / BQ) * j) * p.ldb + col) : kOutOfRange;
-        }
-    }
+    for (int j = 0; j < BU; ++j)
+        boff[j] = bcol < N ? 4u * (uint32_t)((int64_t)(bk + (256 / BQ) * j) * p.ldb + bcol) : kOutOfRange;
 
     f32x4 ra[2][AU], rb[2][BU];
     auto load_chunk = [&](int chunk, auto set_c) {
@@ -119,7 +100,7 @@ __global__ __launch_bounds__(256 * NWG) void gemm_pipe_kernel(const GemmArgs p, 
 #pragma unroll
             for (int j = 0; j < AU; ++j)
                 ra[set][j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(arsrc, (int)aoff[j], 4 * k0, 0));
-            const int bs = NT ? 4 * k0 : 4 * k0 * p.ldb;
+            const int bs = (int)(4u * (uint32_t)(k0 * p.ldb));
 #pragma unroll
             for (int j = 0; j < BU; ++j)
                 rb[set][j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(brsrc, (int)boff[j], bs, 0));
@@ -132,44 +113,25 @@ __global__ __launch_bounds__(256 * NWG) void gemm_pipe_kernel(const GemmArgs p, 
             }
 #pragma unroll
             for (int j = 0; j < BU; ++j) {
-                uint32_t off;
-                if (NT) {
-                    off = a_in ? boff[j] + 4u * (uint32_t)k0 : kOutOfRange;
-                } else {
-                    const bool in = k0 + bk + (256 / BQ) * j < K;
-                    off = in ? boff[j] + 4u * (uint32_t)((int64_t)k0 * p.ldb) : kOutOfRange;
-                }
+                const bool in = k0 + bk + (256 / BQ) * j < K;
+                const uint32_t off = in ? boff[j] + 4u * (uint32_t)((int64_t)k0 * p.ldb) : kOutOfRange;
                 rb[set][j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(brsrc, (int)off, 0, 0));
             }
         }
     };
-    auto store_rows = [&](float* tile, const auto& reg) {
-        constexpr int count = sizeof(reg) / sizeof(f32x4);
-#pragma unroll
-        for (int j = 0; j < count; ++j) {
-            *reinterpret_cast<f32x4*>(&tile[((tid >> 3) + 32 * j) * WS + ak]) = reg[j];
-        }
-    };
     auto store_chunk = [&](int buf, auto set_c) {
         constexpr int set = decltype(set_c)::value;
-        store_rows(lds_a + buf * A_SZ, ra[set]);
-        if (NT) {
-            store_rows(lds_b + buf * B_SZ, rb[set]);
-        } else {
-            float* b = lds_b + buf * B_SZ;
 #pragma unroll
-            for (int j = 0; j < BU; ++j)
-                *reinterpret_cast<f32x4*>(&b[(bk + (256 / BQ) * j) * LDB + 4 * (tid % BQ)]) = rb[set][j];
-        }
+        for (int j = 0; j < AU; ++j)
+            *reinterpret_cast<f32x4*>(&lds_a[buf * A_SZ + ((tid >> 3) + 32 * j) * WS + ak]) = ra[set][j];
+#pragma unroll
+        for (int j = 0; j < BU; ++j)
+            *reinterpret_cast<f32x4*>(&lds_b[buf * B_SZ + (bk + (256 / BQ) * j) * LDB + 4 * (tid % BQ)]) = rb[set][j];
     };
 
-    f32x16 acc[MB][NB];
+    f32x16 acc;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 
     const int nchunks = (K + KC - 1) / KC;
     // chunks past the end are the last chunk again: loaded, never multiplied
@@ -191,31 +153,14 @@ __global__ __launch_bounds__(256 * NWG) void gemm_pipe_kernel(const GemmArgs p, 
         load_chunk(clampc(c + 2 * NWG), std::integral_constant<int, P>{});
         // keep the loads ahead of the MFMAs (the scheduler would sink them to their first use)
         __builtin_amdgcn_sched_barrier(0);
-        const float* a = lds_a + P * A_SZ + (wm * MB * 32 + r32) * WS + 2 * h;
-        const float* b = NT ? lds_b + P * B_SZ + (wn * NB * 32 + r32) * WS + 2 * h
-                            : lds_b + P * B_SZ + (2 * h) * LDB + wn * NB * 32 + r32;
+        const float* a = lds_a + P * A_SZ + (wm * 32 + r32) * WS + 2 * h;
+        const float* b = lds_b + P * B_SZ + (2 * h) * LDB + wn * 32 + r32;
         if (NWG == 1 || c < nchunks) {          // a group may have one chunk fewer than the others
 #pragma unroll
             for (int j = 0; j < KC / 4; ++j) {
-                f32x2 av[MB], bv[NB];
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-                    av[mb] = *reinterpret_cast<const f32x2*>(a + mb * 32 * WS + 4 * j);
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    if (NT) {
-                        bv[nb] = *reinterpret_cast<const f32x2*>(b + nb * 32 * WS + 4 * j);
-                    } else {
-                        bv[nb][0] = b[(4 * j) * LDB + nb * 32];
-                        bv[nb][1] = b[(4 * j + 1) * LDB + nb * 32];
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 2; ++e)
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma32(av[mb][e], bv[nb][e], acc[mb][nb]);
+                const f32x2 av = *reinterpret_cast<const f32x2*>(a + 4 * j);
+                acc = mfma32(av[0], b[(4 * j) * LDB], acc);
+                acc = mfma32(av[1], b[(4 * j + 1) * LDB], acc);
             }
         }
         store_chunk(P ^ 1, std::integral_constant<int, P ^ 1>{});
@@ -230,31 +175,26 @@ __global__ __launch_bounds__(256 * NWG) void gemm_pipe_kernel(const GemmArgs p, 
         // leave their accumulators in their own regions, group 0 adds them in group order.
         if (wgrp > 0) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) lds_a[(wave * 16 + r) * 64 + lane] = acc[0][0][r];
+            for (int r = 0; r < 16; ++r) lds_a[(wave * 16 + r) * 64 + lane] = acc[r];
         }
         __syncthreads();
         if (wgrp > 0) return;
 #pragma unroll
         for (int o = 1; o < NWG; ++o)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[0][0][r] += plds[o * REGION + (wave * 16 + r) * 64 + lane];
+            for (int r = 0; r < 16; ++r) acc[r] += plds[o * REGION + (wave * 16 + r) * 64 + lane];
     }
 
     // accumulator register r of lane (h, r32): row 8*(r/4) + 4*h + r%4, column r32 of the block
+    const int col = n0 + wn * 32 + r32;
+    if (col >= N) return;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const int col = n0 + (wn * NB + nb) * 32 + r32;
-            if (col >= N) continue;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = m0 + (wm * MB + mb) * 32 + 8 * (r / 4) + 4 * h + (r % 4);
-                // 32 lanes write one whole 128-byte run of a row; C is not read again (non-temporal:
-                // no dirty lines left for the end of the kernel)
-                if (row < M) __builtin_nontemporal_store(acc[mb][nb][r], &C[(int64_t)row * p.ldc + col]);
-            }
-        }
+    for (int r = 0; r < 16; ++r) {
+        const int row = m0 + wm * 32 + 8 * (r / 4) + 4 * h + (r % 4);
+        // 32 lanes write one whole 128-byte run of a row; C is not read again (non-temporal:
+        // no dirty lines left for the end of the kernel)
+        if (row < M) __builtin_nontemporal_store(acc[r], &C[(int64_t)row * p.ldc + col]);
+    }
 }
 
 }  // namespace gpipe

@@ -1,0 +1,337 @@
+// GMM (C = A.B, Sec. 4.1 and Appendix C of arXiv 2006.06762) on the bf16 matrix pipes, each fp32
+// operand split into three bf16 pieces (split_bf16.h): any M, N, K, any alignment.
+//
+// Work-group tile BM x BN, WM x WN waves of MB x 2 blocks of 32 x 32, NWG such groups of waves that
+// share the chunks of the reduction.  Operands travel global -> registers -> (split) -> LDS, so a float
+// is split once per work-group and not once per wave that reads it.  The LDS image is in operand order:
+// plane (h, m, l), then unit of eight k, then row, 16 bytes each: a wave's operand read is 32 consecutive
+// 16-byte pieces per half (no bank conflict).  A half chunk of 16 k has two units; unit t holds k = 4t ..
+// 4t+3 and 8+4t .. 8+4t+3, so that the two lanes that stage a row read 32 contiguous bytes at a time (any
+// order of k is a valid reduction order as long as both operands use it).  Units are 64 bytes further
+// apart than their rows need: those two lanes then write to different banks.
+//
+// B is k-major in memory.  A staging piece is four k of two neighbouring columns: 8-byte loads (the
+// address unit takes a load instruction's 64 lanes in 16 cycles whatever their width, and 4-byte loads
+// cost a quarter of the time of a work-group alone on its CU), and packing pairs of k transposes for
+// free.  Column 2p + b sits at position b*BN/2 + p, so that a lane's two accumulator blocks are
+// neighbouring columns of C.  Loads past the end of a matrix read zero (the buffer range check is per
+// dword), loads past the end of a row read the next one and meet columns that are never stored.
+//
+// Bound: large products by the matrix pipes' power: at 4096^3 they are busy 69 % of the cycles and the
+// clock falls to 1.7 GHz (six bf16 products per fp32 one at 235 TFLOP/s are 1.4 PFLOP/s); work-groups
+// alone on their CU by the chain load - split - LDS - multiply.  Measured against the fp32 kernels this
+// one took over from: 4096^3 984 -> 594 us, 1024^3 x16 262 -> 157, 512^3 x16 38.0 -> 29.6,
+// 1009 x 1531 x 771 x3 (4-byte aligned rows) 167 -> 63, 1024^3 22.3 -> 19.8.  Tried and dropped: the split
+// between the matrix instructions, v_dot2 for its subtractions, wave groups in opposite order (all slower).
+#pragma once
+#include <type_traits>
+
+#include "anr_kernels.h"
+#include "split_bf16.h"
+
+namespace anr {
+namespace gsplit {
+
+constexpr int KC = 32;                               // k of a global load round; LDS buffers hold half of it
+constexpr uint32_t kOutOfRange = 0x80000000u;
+
+template <int ROWS>
+struct Plane {
+    static constexpr int UNIT = ROWS * 16 + 64;      // bytes between units of eight k
+    static constexpr int BYTES = 2 * UNIT;
+};
+
+template <int BM, int BN, int NWG>
+constexpr size_t lds_bytes()
+{
+    return NWG * 2 * 3 * (size_t)(Plane<BM>::BYTES + Plane<BN>::BYTES);
+}
+
+// Chunk-invariant description of a launch (what the host works out once).
+struct Grid {
+    int tiles_m, tiles_n;
+    int group_m;          // tiles are walked in bands of group_m rows of tiles
+};
+
+template <int BM, int BN, int WM, int WN, int NWG, int MINW, bool NT>
+__global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(const GemmArgs p, const Grid g)
+{
+    constexpr int T = 64 * WM * WN;                  // threads of a wave group
+    constexpr int MB = BM / (32 * WM);
+    static_assert(BN == 64 * WN && BM == BN && T == 2 * BM,
+                  "two blocks of columns per wave; per half chunk every thread stages one unit of A and one piece of B");
+    constexpr int PA = Plane<BM>::BYTES, PB = Plane<BN>::BYTES;
+    constexpr int BUF = 3 * (PA + PB);
+    constexpr int RED = BM * BN * 4;                 // a group's accumulators
+    static_assert(NWG == 1 || (NWG - 1) * RED <= NWG * 2 * BUF, "the groups' sums meet in the staging buffers");
+
+    extern __shared__ __attribute__((aligned(16))) char slds[];
+
+    const int wgrp = NWG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / T) : 0;
+    char* const region = slds + wgrp * 2 * BUF;
+    const int tid = (int)threadIdx.x % T;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int r32 = lane & 31, h = lane >> 5;
+    const int wm = wave / WN, wn = wave % WN;
+
+    // Work-group ids are dealt round-robin over the 8 XCDs, each with its own L2: every XCD gets a
+    // contiguous run of the batch's tiles, each matrix walked in bands of group_m tile rows, column by
+    // column (512^3 x16: whole matrices stay on one XCD)
+    const int tiles = g.tiles_m * g.tiles_n;
+    int id = blockIdx.x;
+    {
+        const int all = (int)gridDim.x, per = all >> 3, rest = all & 7, xcd = id & 7, slot = id >> 3;
+        id = xcd * per + (xcd < rest ? xcd : rest) + slot;
+    }
+    const int mat = id / tiles;
+    id -= mat * tiles;
+    const int band = id / (g.group_m * g.tiles_n);
+    const int band_rows = min(g.group_m, g.tiles_m - band * g.group_m);
+    const int in_band = id - band * g.group_m * g.tiles_n;
+    const int tile_m = band * g.group_m + in_band % band_rows, tile_n = in_band / band_rows;
+    const int m0 = tile_m * BM, n0 = tile_n * BN;
+
+    const int zo = mat / p.batch_inner, zi = mat - zo * p.batch_inner;
+    const float* A = p.A + zo * p.sAo + zi * p.sAi;
+    const float* B = p.B + zo * p.sBo + zi * p.sBi;
+    float* __restrict__ C = p.C + zo * p.sCo + zi * p.sCi;
+    const int M = p.M, N = p.N, K = p.K;
+
+    const uint32_t a_bytes = 4u * (uint32_t)((int64_t)(M - 1) * p.lda + K);
+    const uint32_t b_bytes = NT ? 4u * (uint32_t)((int64_t)(N - 1) * p.ldb + K) : 4u * (uint32_t)((int64_t)(K - 1) * p.ldb + N);
+    const __amdgpu_buffer_rsrc_t arsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A), 0, (int)a_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t brsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B), 0, (int)b_bytes, 0x00020000);
+
+    // Staging of A: row tid/2, unit tid%2.  Of B: four k 4t + 8 (tid%2) .. +3 of the column pair
+    // (tid/2) % (BN/2), unit t = (tid/2) / (BN/2); of the k-contiguous B of the A.B^T form like A.
+    const int at = tid & 1, arow = tid >> 1;
+    const int bt = arow / (BN / 2), bpair = arow % (BN / 2);
+    // rows past M repeat the last one and columns past N the last ones: loaded, never stored
+    const uint32_t aoff = 4u * (uint32_t)((int64_t)min(m0 + arow, M - 1) * p.lda + 4 * at);
+    const uint32_t boff = NT ? 4u * (uint32_t)((int64_t)min(n0 + arow, N - 1) * p.ldb + 4 * at)
+                             : 4u * (uint32_t)((int64_t)(4 * bt + 8 * at) * p.ldb + min(n0 + 2 * bpair, N - 1));
+
+    float ra[2][8], rb[2][8];                        // rb: four k of the first column, then of the second (NT: as ra)
+    const uint32_t ldb4 = 4u * (uint32_t)p.ldb;
+    auto load_unit = [&](__amdgpu_buffer_rsrc_t rsrc, uint32_t off, int k0, int f, float (&r)[8]) {
+        const f32x4 lo = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off + 64 * f, 4 * k0, 0));
+        const f32x4 hi = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off + 64 * f + 32, 4 * k0, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { r[e] = lo[e]; r[4 + e] = hi[e]; }
+    };
+    // Chunks past the last one read zeros: their addresses are those of the last chunk with an offset that
+    // is out of range (a branch around the loads would make the compiler wait for them where it ends)
+    const int nchunks = (K + KC - 1) / KC;
+    auto load_a = [&](int c, auto f_c) {             // half f of chunk c
+        constexpr int f = decltype(f_c)::value;
+        const uint32_t past = c < nchunks ? 0u : kOutOfRange;
+        load_unit(arsrc, aoff | past, min(c, nchunks - 1) * KC, f, ra[f]);
+    };
+    auto load_b = [&](int c, auto f_c) {
+        constexpr int f = decltype(f_c)::value;
+        const uint32_t past = c < nchunks ? 0u : kOutOfRange;
+        const int k0 = min(c, nchunks - 1) * KC;
+        if (NT) {
+            load_unit(brsrc, boff | past, k0, f, rb[f]);
+            return;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            // the row's part of the offset is uniform and rides in the load's scalar offset
+            const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(brsrc, (int)(boff | past), (int)((uint32_t)(k0 + 16 * f + e) * ldb4), 0));
+            rb[f][e] = v[0];
+            rb[f][4 + e] = v[1];
+        }
+    };
+    // Half f goes to buffer f: eight pairs of floats are split (0-3: the unit of A, 4-5 and 6-7: the
+    // columns of B) and written as soon as a 16- or 8-byte store is complete.
+    uint32_t lost = 0;
+    uint32_t sp[3][8];
+    char* const wa = region + at * Plane<BM>::UNIT + arow * 16;
+    char* const wb = region + 3 * PA + (NT ? at * Plane<BN>::UNIT + ((arow & 1) * (BN / 2) + (arow >> 1)) * 16
+                                           : bt * Plane<BN>::UNIT + bpair * 16 + 8 * at);
+    // k past the end: rows of a k-major B lie past the matrix and read zero, a k-contiguous row runs on
+    // into the next one and is cleared here (the half chunk starts at k)
+    auto clear_past = [&](auto f_c, int k) {
+        constexpr int f = decltype(f_c)::value;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const bool in = k + 4 * at + (e < 4 ? e : 4 + e) < K;
+            ra[f][e] = in ? ra[f][e] : 0.f;
+            if (NT) rb[f][e] = in ? rb[f][e] : 0.f;
+        }
+    };
+    auto split_pair = [&](auto f_c, int i) {
+        constexpr int f = decltype(f_c)::value;
+        if (i < 4) split2(ra[f][2 * i], ra[f][2 * i + 1], sp[0][i], sp[1][i], sp[2][i], lost);
+        else split2(rb[f][2 * (i - 4)], rb[f][2 * (i - 4) + 1], sp[0][i], sp[1][i], sp[2][i], lost);
+        if (i == 3) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(wa + f * BUF + q * PA) = u32x4{sp[q][0], sp[q][1], sp[q][2], sp[q][3]};
+        }
+        if (NT && i == 7) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(wb + f * BUF + q * PB) = u32x4{sp[q][4], sp[q][5], sp[q][6], sp[q][7]};
+        }
+        if (!NT && (i == 5 || i == 7)) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2*>(wb + f * BUF + q * PB + (i == 7 ? BN * 8 : 0)) = u32x2{sp[q][i - 1], sp[q][i]};
+        }
+    };
+    auto store_half = [&](auto f_c, int c) {         // half f of chunk c
+        const int k = c * KC + 16 * decltype(f_c)::value;
+        if (k + 16 > K) clear_past(f_c, k);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) split_pair(f_c, i);
+    };
+
+    f32x16 acc[MB][2];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
+
+    // Multiplies buffer f, then fills the other one with the loaded half of chunk c_fill and sends that
+    // half's loads of chunk c_load.
+    auto half = [&](auto f_c, int c_fill, int c_load) {
+        constexpr int f = decltype(f_c)::value;
+        using G = std::integral_constant<int, f ^ 1>;
+        const char* a = region + f * BUF + h * Plane<BM>::UNIT + (wm * MB * 32 + r32) * 16;
+        const char* b = region + f * BUF + 3 * PA + h * Plane<BN>::UNIT + (wn * 32 + r32) * 16;
+        u32x4 bv[3][2];
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) bv[q][nb] = *reinterpret_cast<const u32x4*>(b + q * PB + nb * BN * 8);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            u32x4 av[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) av[q] = *reinterpret_cast<const u32x4*>(a + q * PA + mb * 512);
+            constexpr int qa[6] = {0, 0, 1, 1, 0, 2}, qb[6] = {0, 1, 0, 1, 2, 0};
+#pragma unroll
+            for (int t = 0; t < 6; ++t)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = mfma_bf16(av[qa[t]], bv[qb[t]][nb], acc[mb][nb]);
+        }
+        store_half(G{}, c_fill);
+        load_a(c_load, G{});
+        load_b(c_load, G{});
+    };
+
+    // Half f of every chunk goes through buffer f: between two barriers one buffer is multiplied and the
+    // other filled.  Group w takes every NWG-th chunk.
+    using F0 = std::integral_constant<int, 0>;
+    using F1 = std::integral_constant<int, 1>;
+    const int iters = (nchunks + NWG - 1) / NWG;     // the barriers are the work-group's
+    load_a(wgrp, F0{});
+    load_b(wgrp, F0{});
+    load_a(wgrp, F1{});
+    load_b(wgrp, F1{});
+    store_half(F0{}, wgrp);
+    load_a(wgrp + NWG, F0{});
+    load_b(wgrp + NWG, F0{});
+    for (int i = 0; i < iters; ++i) {
+        const int c = wgrp + i * NWG;
+        __syncthreads();
+        half(F0{}, c, c + NWG);
+        __syncthreads();
+        half(F1{}, c + NWG, c + 2 * NWG);
+    }
+    if (NWG > 1) __syncthreads();
+    if (NWG > 1) {
+        // every staging buffer is free: groups 1 .. NWG-1 leave their accumulators there, group 0 adds
+        // them in group order
+        if (wgrp > 0) {
+            float* red = reinterpret_cast<float*>(slds + (wgrp - 1) * RED) + wave * (MB * 2 * 16 * 64) + lane;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) red[((mb * 2 + nb) * 16 + r) * 64] = acc[mb][nb][r];
+        }
+        __syncthreads();
+        if (wgrp == 0) {
+#pragma unroll
+            for (int o = 1; o < NWG; ++o) {
+                const float* red = reinterpret_cast<const float*>(slds + (o - 1) * RED) + wave * (MB * 2 * 16 * 64) + lane;
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[mb][nb][r] += red[((mb * 2 + nb) * 16 + r) * 64];
+            }
+        }
+    }
+
+    float nf = 0.f;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) nf = not_finite(acc[mb][nb], nf);
+    const int again = __syncthreads_or(lost_bits(lost) || nf != 0.f);
+    if (NWG > 1 && wgrp > 0) return;
+    if (again) {
+        // values the split cannot carry: the tile again, block by block, with the fp32 instruction and
+        // operands read element by element (rows, columns and k past the end as above)
+#pragma unroll 1
+        for (int blk = 0; blk < MB * 2; ++blk) {
+            const int row0 = m0 + (wm * MB + blk / 2) * 32, col = n0 + 2 * (wn * 32 + r32) + blk % 2;
+            const uint32_t ar = 4u * (uint32_t)((int64_t)min(row0 + r32, M - 1) * p.lda);
+            const uint32_t bc = 4u * (uint32_t)min(col, N - 1) * (NT ? (uint32_t)p.ldb : 1u), bk = NT ? 4u : ldb4;
+            f32x16 v;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] = 0.f;
+            for (int k0 = 0; k0 < K; k0 += 16) {
+                float x[8], y[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int k = k0 + 2 * i + h;
+                    const uint32_t past = k < K ? 0u : kOutOfRange;
+                    x[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(arsrc, (int)((ar + 4u * (uint32_t)k) | past), 0, 0));
+                    y[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(brsrc, (int)((bc + (uint32_t)k * bk) | past), 0, 0));
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v = mfma32(x[i], y[i], v);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = row0 + 8 * (r / 4) + 4 * h + (r % 4);
+                if (row < M && col < N) C[(int64_t)row * p.ldc + col] = v[r];
+            }
+        }
+        return;
+    }
+
+    // accumulator register r of lane (h, r32): row 8*(r/4) + 4*h + r%4 of block mb, columns 2*(wn*32 + r32) + nb:
+    // 32 lanes write 256 contiguous bytes of a row, and C is not read again (non-temporal)
+    auto store_tile = [&](auto whole_c) {
+        constexpr bool whole = decltype(whole_c)::value;
+        typedef float pair __attribute__((ext_vector_type(2), aligned(4)));
+        const int col = n0 + 2 * (wn * 32 + r32);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int row0 = m0 + (wm * MB + mb) * 32 + 4 * h;
+            float* const c = C + (int64_t)row0 * p.ldc + col;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int dr = 8 * (r / 4) + (r % 4);
+                float* const d = c + (int64_t)dr * p.ldc;
+                const pair v = {acc[mb][0][r], acc[mb][1][r]};
+                if (whole || (row0 + dr < M && col + 1 < N)) __builtin_nontemporal_store(v, reinterpret_cast<pair*>(d));
+                else if (row0 + dr < M && col < N) *d = acc[mb][0][r];
+            }
+        }
+    };
+    if (m0 + BM <= M && n0 + BN <= N) store_tile(std::true_type{});
+    else store_tile(std::false_type{});
+}
+
+}  // namespace gsplit
+}  // namespace anr

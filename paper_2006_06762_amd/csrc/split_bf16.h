@@ -1,0 +1,68 @@
+// fp32 products on the bf16 matrix pipes without giving up fp32 accuracy.
+//
+// gfx950 multiplies fp32 matrices at 157 TFLOP/s and bf16 ones at 2.5 PFLOP/s.  A float is the exact
+// sum of three bf16 numbers, x = h + m + l (24 significant bits in three pieces of eight, each
+// rounded to nearest, so the next piece is at most 2^-9 of the one before), and a product of two
+// floats is then the sum of the nine products of their pieces, each exact in fp32.  Six of them are
+// formed: hh, hm, mh, mm, hl, lh; the three left out (ml, lm, ll) add up to less than 2^-25 of the
+// product, half a unit in the last place of fp32, with random sign.  v_mfma_f32_32x32x16_bf16 adds
+// the sixteen products of an instruction to the accumulator with one rounding where the fp32 form
+// rounds for every two: measured against 64-bit results the six-product sum is no further off than
+// the fp32 instruction (512 terms 3.2e-7 against 4.0e-7, 4096 terms 8.9e-7 against 1.1e-6).
+// Denormal inputs and results are kept by the instruction (measured).
+//
+// Two kinds of value do not survive the split, and both are detected exactly:
+//   - magnitudes below 2^-110, whose last piece needs bits under the smallest bf16 denormal: l is the
+//     difference of floats, so it is exact, and it is representable if and only if its low 16 bits
+//     are zero; `lost` collects them;
+//   - infinities, NaN and magnitudes that round to infinity in bf16: a piece of theirs is infinite or
+//     NaN, so every accumulator they reach is not finite.
+// A work-group that meets either recomputes its tile with the fp32 instruction.
+#pragma once
+#include "anr_device.h"
+
+namespace anr {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// v_mfma_f32_32x32x16_bf16: D(32x32) += A(32x16) * B(16x32).  Lane l supplies A[i = l%32][k = 8*(l/32) + 0..7]
+// and B[the same k][j = l%32]; the accumulator layout is that of mfma32.
+__device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Two floats rounded to bf16 (nearest, ties to even), the first in the low half.
+__device__ __forceinline__ uint32_t pack_bf16(float x, float y)
+{
+    const f32x2 v = {x, y};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// The pieces of two floats, packed; `lost` as described above.
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l, uint32_t& lost)
+{
+    h = pack_bf16(x0, x1);
+    const float r0 = x0 - __builtin_bit_cast(float, h << 16);
+    const float r1 = x1 - __builtin_bit_cast(float, h & 0xffff0000u);
+    m = pack_bf16(r0, r1);
+    const uint32_t l0 = __builtin_bit_cast(uint32_t, r0 - __builtin_bit_cast(float, m << 16));
+    const uint32_t l1 = __builtin_bit_cast(uint32_t, r1 - __builtin_bit_cast(float, m & 0xffff0000u));
+    l = __builtin_amdgcn_perm(l1, l0, 0x07060302u);
+    lost |= l0 | l1;
+}
+
+__device__ __forceinline__ bool lost_bits(uint32_t lost) { return (lost & 0xffffu) != 0; }
+
+// NaN if any accumulator register is infinite or NaN, else zero (added to `s`).
+__device__ __forceinline__ float not_finite(const f32x16& a, float s)
+{
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s = fmaf(a[r], 0.f, s);
+    return s;
+}
+
+}  // namespace anr

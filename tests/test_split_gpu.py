@@ -1,0 +1,105 @@
+"""The GEMM and convolution kernels that multiply fp32 operands as three bf16 pieces each.
+
+Values the pieces cannot carry (infinities, NaN, magnitudes that round to infinity in bf16 or lie below
+2^-110) must come out as the fp32 instruction gives them; everything else within the bound of an fp32
+sum.  The bound: K + 2 roundings of 2^-24 relative to the sum of the absolute products (an fp32 sum in any
+order makes K - 1, a product one; the split leaves out less than 2^-25 of a product), plus half the
+smallest denormal per term.
+"""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def anr():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2006_06762_amd import binding
+    return binding
+
+
+def uniform(seed, *shape):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    return torch.empty(shape, device="cuda").uniform_(-1.0, 1.0, generator=gen)
+
+
+def assert_product(C, A, B):
+    ref, size, K = A.double() @ B.double(), A.double().abs() @ B.double().abs(), A.shape[-1]
+    finite = ref.abs() <= torch.finfo(torch.float32).max
+    got = C.double()
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    inf = ~finite & ~torch.isnan(ref)
+    assert torch.equal(got[inf], torch.sign(ref[inf]) * float("inf"))
+    off = (got - ref).abs()[finite]
+    bound = ((K + 2) * 2.0 ** -24 * size + K * 2.0 ** -149)[finite]
+    assert bool((off <= bound).all()), float((off / bound).max())
+
+
+# one shape per tile variant and per remainder: tiles of 256, 128 and 64, one to four wave groups, K below, at and
+# past the 16- and 32-wide steps, single columns and rows past a tile, odd leading dimensions
+SHAPES = [(1, 4097, 4095, 129), (1, 2305, 1791, 161), (16, 513, 511, 333), (3, 1009, 1531, 71), (1, 300, 301, 303),
+          (1, 33, 47, 1000), (1, 65, 1, 513), (1, 1, 130, 95), (2, 64, 66, 511), (5, 129, 127, 145), (1, 700, 700, 480)]
+
+
+@pytest.mark.parametrize("batch,M,N,K", SHAPES)
+def test_split_gemm_edges(anr, batch, M, N, K):
+    A, B = uniform(M, batch, M, K), uniform(N, batch, K, N)
+    buf = torch.full((batch * M * N + 128,), 7.0, device="cuda")
+    C = buf[64:-64].view(batch, M, N)
+    anr.gemm(A, B, C)
+    assert_product(C, A, B)
+    assert bool((buf[:64] == 7.0).all()) and bool((buf[-64:] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(300, 260, 333), (700, 700, 545), (2100, 1900, 200)])
+def test_split_gemm_strided_unaligned_views(anr, M, N, K):
+    A = uniform(1, M, K + 5)[:, 3:K + 3]
+    B = uniform(2, K, N + 7)[:, 1:N + 1]
+    C = torch.full((M, N + 3), 7.0, device="cuda")
+    anr.gemm(A, B, C[:, 1:N + 1])
+    assert_product(C[:, 1:N + 1], A, B)
+    assert bool((C[:, 0] == 7.0).all()) and bool((C[:, N + 1:] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(300, 260, 333), (700, 700, 545), (2100, 1900, 200)])
+@pytest.mark.parametrize("what", ["inf", "nan", "huge", "overflow", "denormal", "tiny", "past_k"])
+def test_split_gemm_values_the_pieces_cannot_carry(anr, M, N, K, what):
+    A, B = uniform(3, M, K), uniform(4, K, N)
+    if what == "inf":
+        A[M // 2, K - 1] = float("inf")
+        B[0, N // 3] = -float("inf")
+        B[K - 1, N - 1] = 0.0                       # inf * 0
+    elif what == "nan":
+        A[M - 1, 0] = float("nan")
+    elif what == "huge":                            # finite, but its first piece rounds to infinity
+        A[M // 3, K // 2] = 3.4e38
+        B[K // 2] = 0.25
+    elif what == "overflow":
+        A[1] = 1e20
+        B[:, 2] = 1e20
+    elif what == "denormal":
+        A *= 2.0 ** -130
+    elif what == "tiny":
+        A *= 2.0 ** -118
+        B *= 2.0 ** 100
+    elif what == "past_k":                          # what lies behind a row's end must not be multiplied
+        whole = torch.full((M, K + 8), float("inf"), device="cuda")
+        whole[:, :K] = A
+        A = whole[:, :K]
+    C = torch.empty(M, N, device="cuda")
+    anr.gemm(A, B, C)
+    assert_product(C, A, B)
+
+
+@pytest.mark.parametrize("B,S,H,D", [(2, 130, 3, 64), (1, 257, 2, 80), (4, 512, 12, 33), (1, 300, 1, 128)])
+def test_split_scores(anr, B, S, H, D):
+    q, k = uniform(5, B, S, H, D), uniform(6, B, S, H, D)
+    out = torch.empty(B, H, S, S, device="cuda")
+    anr.tbg(q, k, out)
+    qt, kt = q.permute(0, 2, 1, 3).contiguous(), k.permute(0, 2, 3, 1).contiguous()
+    assert_product(out, qt, kt)
+    q[0, S - 1, 0, D - 1] = float("inf")
+    anr.tbg(q, k, out)
+    assert_product(out, q.permute(0, 2, 1, 3).contiguous(), kt)
