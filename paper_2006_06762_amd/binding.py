@@ -7,6 +7,7 @@ been built, importing this module raises.
 """
 import ctypes
 import os
+import struct
 
 # torch ships its own HIP runtime (libamdhip64.so.7).  It must be in the process before
 # libanr.so is opened, so that the library binds to that same runtime instance: streams
@@ -132,14 +133,41 @@ def _check(status, where):
         raise AnrError(status, where)
 
 
+# The operators' own handle on the library: the same functions with plain pointer arguments, so that a call
+# passes integers and a packed descriptor as they are.  With ctypes structures, pointer objects and torch's
+# Stream object around every call, the host took 8 us per launch, more than most of the small kernels run.
+_fast = ctypes.CDLL(LIB_PATH)
+_sz, _fl, _vp4 = ctypes.c_size_t, ctypes.c_float, [_vp] * 4
+_fast.anr_gemm.argtypes = _vp4 + [_vp, _sz, _vp]
+_fast.anr_conv2d.argtypes = _vp4 + [_vp, _sz, _vp]
+_fast.anr_conv2d_noalloc.argtypes = _vp4 + [_vp]
+_fast.anr_conv2d_packed.argtypes = _vp4 + [_vp, _sz, _vp]
+_fast.anr_conv_bn_relu_packed.argtypes = _vp4 + [_vp, _sz, _vp]
+_fast.anr_conv_bn_relu.argtypes = [_vp] * 7 + [_fl, _vp, _vp, _sz, _vp]
+_fast.anr_dwconv.argtypes = _vp4 + [_vp, _sz, _vp]
+_fast.anr_tbg.argtypes = _vp4 + [_vp, _sz, _vp]
+_fast.anr_tbs.argtypes = _vp4 + [_vp, _sz, _vp]
+_fast.anr_nrm.argtypes = [_vp] * 3 + [_vp, _sz, _vp]
+
+_pack_gemm = struct.Struct("@10q").pack
+_pack_conv = struct.Struct("@14i8q2i").pack
+_pack_tbg = struct.Struct("@4i12q").pack
+_pack_nrm = struct.Struct("@5q").pack
+assert [struct.calcsize(f) for f in ("@10q", "@14i8q2i", "@4i12q", "@5q")] == \
+    [ctypes.sizeof(t) for t in (GemmDesc, ConvDesc, TbgDesc, NrmDesc)]
+_NO_STRIDES = (0, 0, 0, 0)
+_f32 = torch.float32
+
+
 def _ptr(t):
-    if not isinstance(t, torch.Tensor) or t.dtype != torch.float32 or not t.is_cuda:
+    if not isinstance(t, torch.Tensor) or t.dtype is not _f32 or not t.is_cuda:
         raise TypeError("expected a float32 CUDA tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """torch's current stream on the current device, as the integer the library takes."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def conv_desc(x_shape, K, R, S, stride=(1, 1), pad=(0, 0), x_stride=None, y_stride=None, dil=(1, 1),
@@ -178,55 +206,77 @@ def conv2d_route(desc: ConvDesc) -> ConvRoute:
 _workspaces = {}
 
 
-def _workspace(op: int, desc, ws):
-    """(pointer, bytes) of the workspace for one call: the caller's tensor, else a buffer kept
-    per (device, stream) and grown on demand (calls on one stream run in order, so they can
-    share it; a call never synchronises)."""
-    need = workspace_size(op, desc)
-    if need == 0:
-        return None, 0
+def _with_workspace(fn, name, op, desc, args, ws, desc_type=ConvDesc):
+    """Calls fn(desc, *args, workspace, bytes, stream).  The workspace is the caller's tensor, else a buffer
+    kept per (device, stream) and grown on demand (calls on one stream run in order, so they can share it; a
+    call never synchronises).  Without the caller's tensor the call itself says whether the buffer it is
+    handed will do: a refused call has had no effect, and is made again with one that is large enough."""
+    stream = _stream()
     if ws is None:
-        key = (torch.cuda.current_device(), torch.cuda.current_stream().cuda_stream)
+        key = (torch._C._cuda_getDevice(), stream)
         ws = _workspaces.get(key)
-        if ws is None or ws.numel() < need:
-            ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+        if ws is None:
+            status = fn(desc, *args, None, 0, stream)
+        else:
+            status = fn(desc, *args, ws.data_ptr(), ws.numel(), stream)
+        if status == ANR_ERR_WORKSPACE:
+            ws = torch.empty(workspace_size(op, desc_type.from_buffer_copy(desc)), dtype=torch.uint8, device="cuda")
             _workspaces[key] = ws
-    if not ws.is_cuda or not ws.is_contiguous() or ws.numel() * ws.element_size() < need:
-        raise ValueError("workspace must be a contiguous CUDA tensor of at least %d bytes" % need)
-    return ctypes.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size()
+            status = fn(desc, *args, ws.data_ptr(), ws.numel(), stream)
+    else:
+        need = workspace_size(op, desc_type.from_buffer_copy(desc))
+        if need == 0:
+            status = fn(desc, *args, None, 0, stream)
+        else:
+            if not ws.is_cuda or not ws.is_contiguous() or ws.numel() * ws.element_size() < need:
+                raise ValueError("workspace must be a contiguous CUDA tensor of at least %d bytes" % need)
+            status = fn(desc, *args, ws.data_ptr(), ws.numel() * ws.element_size(), stream)
+    if status != ANR_OK:
+        raise AnrError(status, name)
 
 
 def gemm(A, B, C):
     """C = A.B.  A [M,K] / [b,M,K], B [K,N] / [b,K,N], C [M,N] / [b,M,N]; last dim contiguous."""
-    if A.dim() == 2:
+    sa, sb, sc = A.stride(), B.stride(), C.stride()
+    if len(sa) == 2:
         M, K = A.shape
         N = B.shape[1]
-        d = GemmDesc(M, N, K, A.stride(0), B.stride(0), C.stride(0), 1, 0, 0, 0)
+        d = _pack_gemm(M, N, K, sa[0], sb[0], sc[0], 1, 0, 0, 0)
     else:
         b, M, K = A.shape
         N = B.shape[2]
-        d = GemmDesc(M, N, K, A.stride(1), B.stride(1), C.stride(1), b,
-                     A.stride(0), B.stride(0), C.stride(0))
-    if A.stride(-1) != 1 or B.stride(-1) != 1 or C.stride(-1) != 1:
+        d = _pack_gemm(M, N, K, sa[1], sb[1], sc[1], b, sa[0], sb[0], sc[0])
+    if sa[-1] != 1 or sb[-1] != 1 or sc[-1] != 1:
         raise ValueError("innermost dimension must be contiguous")
-    _check(_lib.anr_gemm(ctypes.byref(d), _ptr(A), _ptr(B), _ptr(C), None, 0, _stream()), "anr_gemm")
+    status = _fast.anr_gemm(d, _ptr(A), _ptr(B), _ptr(C), None, 0, _stream())
+    if status != ANR_OK:
+        raise AnrError(status, "anr_gemm")
     return C
 
 
 def _conv_strides(t):
-    return None if t.is_contiguous() else tuple(t.stride())
+    return _NO_STRIDES if t.is_contiguous() else tuple(t.stride())
+
+
+def _conv_packed_desc(x, w, y, stride, pad, dil, groups, route):
+    """The descriptor of a call on x, w and y, as the bytes of an anr_conv_desc."""
+    K, _, R, S = w.shape
+    if not w.is_contiguous():
+        raise ValueError("weights must be packed")
+    N, C, H, W = x.shape
+    xs, ys = _conv_strides(x), _conv_strides(y)
+    try:
+        return _pack_conv(N, C, H, W, K, R, S, stride[0], stride[1], pad[0], pad[1], dil[0], dil[1], ANR_LAYOUT_NCHW,
+                          *xs, *ys, groups, route)
+    except struct.error:        # numbers beyond the fields' range: as the structure takes them
+        return bytes(conv_desc((N, C, H, W), K, R, S, stride, pad, xs, ys, dil=dil, groups=groups, route=route))
 
 
 def conv2d(x, w, y, stride=(1, 1), pad=(0, 0), ws=None, dil=(1, 1), groups=1, route=ANR_CONV_ROUTE_AUTO):
     """y = conv2d(x, w); x [N,C,H,W], w [K,C/groups,R,S] packed, y [N,K,OH,OW] (may be strided views).
     ws: optional workspace tensor of at least workspace_size(ANR_OP_CONV2D, desc) bytes."""
-    K, _, R, S = w.shape
-    if not w.is_contiguous():
-        raise ValueError("weights must be packed")
-    d = conv_desc(tuple(x.shape), K, R, S, stride, pad, _conv_strides(x), _conv_strides(y), dil=dil, groups=groups,
-                  route=route)
-    wp, wb = _workspace(ANR_OP_CONV2D, d, ws)
-    _check(_lib.anr_conv2d(ctypes.byref(d), _ptr(x), _ptr(w), _ptr(y), wp, wb, _stream()), "anr_conv2d")
+    d = _conv_packed_desc(x, w, y, stride, pad, dil, groups, route)
+    _with_workspace(_fast.anr_conv2d, "anr_conv2d", ANR_OP_CONV2D, d, (_ptr(x), _ptr(w), _ptr(y)), ws)
     return y
 
 
@@ -235,12 +285,8 @@ STATIC_SCRATCH_BYTES = 16 << 20
 
 def conv2d_noalloc(x, w, y, stride=(1, 1), pad=(0, 0), dil=(1, 1), groups=1, route=ANR_CONV_ROUTE_AUTO):
     """conv2d without a workspace argument: split reductions use the library's static scratch array."""
-    K, _, R, S = w.shape
-    if not w.is_contiguous():
-        raise ValueError("weights must be packed")
-    d = conv_desc(tuple(x.shape), K, R, S, stride, pad, _conv_strides(x), _conv_strides(y), dil=dil, groups=groups,
-                  route=route)
-    _check(_lib.anr_conv2d_noalloc(ctypes.byref(d), _ptr(x), _ptr(w), _ptr(y), _stream()), "anr_conv2d_noalloc")
+    d = _conv_packed_desc(x, w, y, stride, pad, dil, groups, route)
+    _check(_fast.anr_conv2d_noalloc(d, _ptr(x), _ptr(w), _ptr(y), _stream()), "anr_conv2d_noalloc")
     return y
 
 
@@ -267,76 +313,58 @@ def conv2d_pack_weights(x_shape, w, stride=(1, 1), pad=(0, 0), bn=None, eps=0.0,
     return d, pack
 
 
-def _run_packed(fn, name, desc, x, pack, y, ws):
+def _run_packed(fn, name, op, desc, x, pack, y, ws):
     d = ConvDesc.from_buffer_copy(desc)
-    xs, ys = _conv_strides(x), _conv_strides(y)
-    d.x_stride = (ctypes.c_int64 * 4)(*(xs or (0, 0, 0, 0)))
-    d.y_stride = (ctypes.c_int64 * 4)(*(ys or (0, 0, 0, 0)))
-    op = ANR_OP_CONV2D if fn is _lib.anr_conv2d_packed else ANR_OP_CONV_BN_RELU
-    wp, wb = _workspace(op, d, ws)
-    _check(fn(ctypes.byref(d), _ptr(x), ctypes.c_void_p(pack.data_ptr()), _ptr(y), wp, wb, _stream()), name)
+    d.x_stride = _conv_strides(x)
+    d.y_stride = _conv_strides(y)
+    _with_workspace(fn, name, op, bytes(d), (_ptr(x), pack.data_ptr(), _ptr(y)), ws)
     return y
 
 
 def conv2d_packed(desc, x, pack, y, ws=None):
     """conv2d with weights from conv2d_pack_weights (desc: the descriptor it returned)."""
-    return _run_packed(_lib.anr_conv2d_packed, "anr_conv2d_packed", desc, x, pack, y, ws)
+    return _run_packed(_fast.anr_conv2d_packed, "anr_conv2d_packed", ANR_OP_CONV2D, desc, x, pack, y, ws)
 
 
 def conv_bn_relu_packed(desc, x, pack, y, ws=None):
     """conv + batch norm + ReLU with a pack made with bn=(gamma, beta, mean, var)."""
-    return _run_packed(_lib.anr_conv_bn_relu_packed, "anr_conv_bn_relu_packed", desc, x, pack, y, ws)
+    return _run_packed(_fast.anr_conv_bn_relu_packed, "anr_conv_bn_relu_packed", ANR_OP_CONV_BN_RELU, desc, x, pack, y, ws)
 
 
 def conv_bn_relu(x, w, gamma, beta, mean, var, eps, y, stride=(1, 1), pad=(0, 0), ws=None, dil=(1, 1), groups=1,
                  route=ANR_CONV_ROUTE_AUTO):
-    K, _, R, S = w.shape
     if not w.is_contiguous():
         raise ValueError("weights must be packed")
+    K = w.shape[0]
     for v in (gamma, beta, mean, var):
-        if tuple(v.shape) != (K,) or not v.is_contiguous():
+        if v.shape != (K,) or not v.is_contiguous():
             raise ValueError("batch-norm vectors must be packed [K]")
-    d = conv_desc(tuple(x.shape), K, R, S, stride, pad, _conv_strides(x), _conv_strides(y), dil=dil, groups=groups,
-                  route=route)
-    wp, wb = _workspace(ANR_OP_CONV_BN_RELU, d, ws)
-    _check(_lib.anr_conv_bn_relu(ctypes.byref(d), _ptr(x), _ptr(w), _ptr(gamma), _ptr(beta), _ptr(mean),
-                                 _ptr(var), ctypes.c_float(eps), _ptr(y), wp, wb, _stream()),
-           "anr_conv_bn_relu")
+    d = _conv_packed_desc(x, w, y, stride, pad, dil, groups, route)
+    args = (_ptr(x), _ptr(w), _ptr(gamma), _ptr(beta), _ptr(mean), _ptr(var), eps, _ptr(y))
+    _with_workspace(_fast.anr_conv_bn_relu, "anr_conv_bn_relu", ANR_OP_CONV_BN_RELU, d, args, ws)
     return y
 
 
 def dwconv(x, w, y, stride=(1, 1), pad=(0, 0), dil=(1, 1)):
-    C, _, R, S = w.shape
-    if not w.is_contiguous():
-        raise ValueError("weights must be packed")
-    d = conv_desc(tuple(x.shape), C, R, S, stride, pad, _conv_strides(x), _conv_strides(y), dil=dil)
-    _check(_lib.anr_dwconv(ctypes.byref(d), _ptr(x), _ptr(w), _ptr(y), None, 0, _stream()), "anr_dwconv")
+    d = _conv_packed_desc(x, w, y, stride, pad, dil, 1, ANR_CONV_ROUTE_AUTO)
+    _check(_fast.anr_dwconv(d, _ptr(x), _ptr(w), _ptr(y), None, 0, _stream()), "anr_dwconv")
     return y
 
 
-def _tbg_desc(q, k, out) -> TbgDesc:
+def _tbg_desc(q, k, out):
     B, S, H, D = q.shape
-    d = TbgDesc(B, S, H, D)
-    if not q.is_contiguous():
-        d.q_stride = (ctypes.c_int64 * 4)(*q.stride())
-    if not k.is_contiguous():
-        d.k_stride = (ctypes.c_int64 * 4)(*k.stride())
-    if not out.is_contiguous():
-        d.o_stride = (ctypes.c_int64 * 4)(*out.stride())
-    return d
+    return _pack_tbg(B, S, H, D, *_conv_strides(q), *_conv_strides(k), *_conv_strides(out))
 
 
 def tbg(q, k, out):
     """out[b,h,i,j] = sum_d q[b,i,h,d] k[b,j,h,d]; q,k [B,S,H,D], out [B,H,S,S]."""
-    d = _tbg_desc(q, k, out)
-    _check(_lib.anr_tbg(ctypes.byref(d), _ptr(q), _ptr(k), _ptr(out), None, 0, _stream()), "anr_tbg")
+    _check(_fast.anr_tbg(_tbg_desc(q, k, out), _ptr(q), _ptr(k), _ptr(out), None, 0, _stream()), "anr_tbg")
     return out
 
 
 def tbs(q, k, out):
     """tbg followed by a softmax over the last axis."""
-    d = _tbg_desc(q, k, out)
-    _check(_lib.anr_tbs(ctypes.byref(d), _ptr(q), _ptr(k), _ptr(out), None, 0, _stream()), "anr_tbs")
+    _check(_fast.anr_tbs(_tbg_desc(q, k, out), _ptr(q), _ptr(k), _ptr(out), None, 0, _stream()), "anr_tbs")
     return out
 
 
@@ -344,12 +372,12 @@ def nrm(x, out, ws=None):
     """out[b] = sqrt(sum of squares of x[b]).  x [N,M] or [b,N,M] with unit column stride, out [1] / [b]."""
     if x.dim() == 2:
         N, M = x.shape
-        d = NrmDesc(N, M, x.stride(0), 1, 0)
+        b, st = 1, (0,) + tuple(x.stride())
     else:
         b, N, M = x.shape
-        d = NrmDesc(N, M, x.stride(1), b, x.stride(0) if b > 1 else 0)
-    if x.stride(-1) != 1 or not out.is_contiguous() or out.numel() != d.batch:
+        st = x.stride()
+    if st[2] != 1 or not out.is_contiguous() or out.numel() != b:
         raise ValueError("x needs unit column stride and out one packed float per matrix")
-    wp, wb = _workspace(ANR_OP_NRM, d, ws)
-    _check(_lib.anr_nrm(ctypes.byref(d), _ptr(x), _ptr(out), wp, wb, _stream()), "anr_nrm")
+    d = _pack_nrm(N, M, st[1], b, st[0] if b > 1 else 0)
+    _with_workspace(_fast.anr_nrm, "anr_nrm", ANR_OP_NRM, d, (_ptr(x), _ptr(out)), ws, NrmDesc)
     return out
