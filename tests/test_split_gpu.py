@@ -103,3 +103,77 @@ def test_split_scores(anr, B, S, H, D):
     q[0, S - 1, 0, D - 1] = float("inf")
     anr.tbg(q, k, out)
     assert_product(out, q.permute(0, 2, 1, 3).contiguous(), kt)
+
+
+def conv_reference(x, w, stride, pad, dil=1, groups=1):
+    """Convolution and the convolution of the absolute values, in 64 bits, tap by tap."""
+    N, C, H, W = x.shape
+    K, Cg, R, S = w.shape
+    OH, OW = (H + 2 * pad - dil * (R - 1) - 1) // stride + 1, (W + 2 * pad - dil * (S - 1) - 1) // stride + 1
+    out = []
+    for f in (lambda t: t, torch.abs):
+        xp = f(torch.nn.functional.pad(x.double(), (pad,) * 4))
+        wd = f(w.double()).view(groups, K // groups, Cg, R, S)
+        y = torch.zeros(N, groups, K // groups, OH * OW, dtype=torch.float64, device=x.device)
+        for r in range(R):
+            for s in range(S):
+                tap = xp[:, :, r * dil:r * dil + stride * (OH - 1) + 1:stride, s * dil:s * dil + stride * (OW - 1) + 1:stride]
+                y += wd[:, :, :, r, s].contiguous() @ tap.reshape(N, groups, Cg, OH * OW)
+        out.append(y.view(N, K, OH, OW))
+    return out[0], out[1], Cg * R * S
+
+
+def assert_conv(y, x, w, stride, pad, dil=1, groups=1):
+    ref, size, terms = conv_reference(x, w, stride, pad, dil, groups)
+    got = y.double()
+    finite = ref.abs() <= torch.finfo(torch.float32).max
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    inf = ~finite & ~torch.isnan(ref)
+    assert torch.equal(got[inf], torch.sign(ref[inf]) * float("inf"))
+    off = (got - ref).abs()[finite]
+    bound = ((terms + 2) * 2.0 ** -24 * size + terms * 2.0 ** -149)[finite]
+    assert bool((off <= bound).all()), float((off / bound).max())
+
+
+# (N, C, H, W, K, R, stride, pad): two and three channels, ragged tiles, channels past a tile of 64, no padding
+STEMS = [(64, 3, 64, 64, 64, 7, 2, 3), (11, 2, 129, 95, 100, 7, 2, 3), (4, 2, 131, 133, 64, 7, 1, 3), (4, 3, 130, 129, 49, 7, 1, 2),
+         (3, 3, 225, 222, 190, 7, 2, 0), (33, 3, 40, 63, 64, 7, 1, 6)]
+
+
+@pytest.mark.parametrize("N,C,H,W,K,R,stride,pad", STEMS)
+@pytest.mark.parametrize("what", ["plain", "inf", "tiny", "huge_weight"])
+def test_stem_convolution(anr, N, C, H, W, K, R, stride, pad, what):
+    x, w = uniform(7, N, C, H, W), uniform(8, K, C, R, R)
+    if what == "inf":
+        x[N - 1, C - 1, H // 2, W - 1] = float("inf")
+        x[0, 0, 0, 0] = float("nan")
+    elif what == "tiny":
+        x[N // 2] *= 2.0 ** -125
+    elif what == "huge_weight":
+        w[K - 1, 0, R - 1, 0] = 3.4e38
+        x *= 0.5
+    r = anr.conv2d_route(anr.conv_desc(x.shape, K, R, R, (stride, stride), (pad, pad)))
+    assert (r.kernel, r.tile_m, r.ksplit) == (anr.ANR_CONV_KERNEL_BIGTAPS, 256, 1)
+    OH, OW = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
+    buf = torch.full((N * K * OH * OW + 128,), 7.0, device="cuda")
+    y = buf[64:-64].view(N, K, OH, OW)
+    anr.conv2d(x, w, y, (stride, stride), (pad, pad))
+    assert_conv(y, x, w, stride, pad)
+    assert bool((buf[:64] == 7.0).all()) and bool((buf[-64:] == 7.0).all())
+
+
+def test_stem_conv_bn_relu_on_strided_views(anr):
+    N, C, H, W, K = 10, 3, 100, 110, 100
+    x = uniform(9, N, C, H + 2, W + 5)[:, :, 1:H + 1, 2:W + 2]
+    w, gamma, beta, mean = uniform(10, K, C, 7, 7), uniform(11, K), uniform(12, K), uniform(13, K)
+    var = uniform(14, K) + 1.5
+    OH, OW = (H - 1) // 2 + 1, (W - 1) // 2 + 1
+    y = torch.empty(N, K, OH, OW + 3, device="cuda")[..., 1:OW + 1]
+    anr.conv_bn_relu(x, w, gamma, beta, mean, var, 1e-5, y, (2, 2), (3, 3))
+    ref, size, terms = conv_reference(x, w, 2, 3)
+    c = lambda v: v.double().view(1, K, 1, 1)
+    scale = c(gamma) / torch.sqrt(c(var) + 1e-5)
+    want = torch.relu((ref - c(mean)) * scale + c(beta))
+    # the sum's bound scaled, and a handful of roundings of the batch norm's own terms
+    bound = (terms + 2) * 2.0 ** -24 * size * scale.abs() + 8 * 2.0 ** -24 * (ref.abs() * scale.abs() + (c(mean) * scale).abs() + c(beta).abs())
+    assert bool(((y.double() - want).abs() <= bound).all())
