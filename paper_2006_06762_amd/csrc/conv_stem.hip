@@ -288,7 +288,8 @@ bool plan_stem(const ConvArgs& a, Geom* g)
     // half-empty tiles (14 x 14 and smaller maps leave a quarter and more of a tile unused)
     if ((double)a.OH * a.OW < 0.7 * g->tiles_x * g->tiles_y * TP * TP) return false;
     g->tiles = (int)tiles;
-    g->per_n = (kCUs + tiles_n - 1) / tiles_n;
+    // no more work-groups than CUs: each takes a CU's LDS, one too many would wait for a whole round
+    g->per_n = tiles_n < kCUs ? kCUs / tiles_n : 1;
     if (g->per_n > g->tiles) g->per_n = g->tiles;
     g->x_bytes = (uint32_t)(4 * x_extent);
     g->w_bytes = (uint32_t)(4 * w_extent);

@@ -177,3 +177,36 @@ def test_stem_conv_bn_relu_on_strided_views(anr):
     # the sum's bound scaled, and a handful of roundings of the batch norm's own terms
     bound = (terms + 2) * 2.0 ** -24 * size * scale.abs() + 8 * 2.0 ** -24 * (ref.abs() * scale.abs() + (c(mean) * scale).abs() + c(beta).abs())
     assert bool(((y.double() - want).abs() <= bound).all())
+
+
+# (N, C, H, W, K, pad): tiles of 64 and of 32 channels, patches of up to 512 and up to 1024 pixels, tiles that straddle
+# images, channels past the last tile, a single chunk of sixteen channels
+PATCHES = [(16, 64, 56, 56, 64, 1), (16, 16, 56, 56, 50, 1), (16, 48, 28, 28, 100, 1), (5, 32, 112, 112, 96, 1), (9, 32, 56, 60, 64, 0),
+           (8, 16, 28, 56, 256, 2)]
+
+
+def patch_case(anr, N, C, H, W, K, pad):
+    x, w = uniform(15, N, C, H, W), uniform(16, K, C, 3, 3)
+    r = anr.conv2d_route(anr.conv_desc(x.shape, K, 3, 3, (1, 1), (pad, pad), route=anr.ANR_CONV_ROUTE_PATCH))
+    assert r.kernel == anr.ANR_CONV_KERNEL_PATCH and r.tile_m == 224, (r.kernel, r.tile_m)
+    return x, w, torch.full((N, K, H + 2 * pad - 2, W + 2 * pad - 2), 7.0, device="cuda")
+
+
+@pytest.mark.parametrize("N,C,H,W,K,pad", PATCHES)
+@pytest.mark.parametrize("what", ["plain", "inf", "tiny", "huge_weight"])
+def test_patch_convolution(anr, N, C, H, W, K, pad, what):
+    x, w, y = patch_case(anr, N, C, H, W, K, pad)
+    if what == "inf":
+        x[N - 1, C - 1, H // 2, W - 1] = float("inf")
+        x[0, 0, 0, 0] = float("nan")
+    elif what == "tiny":
+        x[N // 2] *= 2.0 ** -125
+    elif what == "huge_weight":
+        w[K - 1, 0, 2, 0] = 3.4e38
+        x *= 0.5
+    anr.conv2d(x, w, y, (1, 1), (pad, pad), route=anr.ANR_CONV_ROUTE_PATCH)
+    assert_conv(y, x, w, 1, pad)
+    desc, pack = anr.conv2d_pack_weights(x.shape, w, (1, 1), (pad, pad), route=anr.ANR_CONV_ROUTE_PATCH)
+    z = torch.empty_like(y)
+    anr.conv2d_packed(desc, x, pack, z)
+    assert torch.equal(y.nan_to_num(1.5), z.nan_to_num(1.5))
