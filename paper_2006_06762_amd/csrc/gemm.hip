@@ -437,19 +437,21 @@ hipError_t launch_split_any(const GemmArgs& a, hipStream_t stream)
     const int chunks = (a.K + gsplit::KC - 1) / gsplit::KC;
     int best = 0;
     double best_us = 0.0;
-    for (int v = 0; v < 6; ++v) {
+    for (int v = NT ? 1 : 0; v < 6; ++v) {      // (the 256-wide tile leaves no registers for a second set of sums)
         const Variant& t = kVariants[v];
         const int64_t tiles = (int64_t)((a.M + t.tile - 1) / t.tile) * ((a.N + t.tile - 1) / t.tile) * a.batch;
         const double chain = (double)((chunks + t.groups - 1) / t.groups) * t.round;
         const double work = (double)((tiles + 255) / 256) * chunks * t.busy;
         const double us = t.base + (work > chain ? work : chain);
-        if (v == 0 || us < best_us) {
+        if (v == (NT ? 1 : 0) || us < best_us) {
             best = v;
             best_us = us;
         }
     }
     switch (best) {
-        case 0: return launch_split<256, 2, 4, 1, NT>(a, stream);
+        case 0:
+            if constexpr (!NT) return launch_split<256, 2, 4, 1, NT>(a, stream);
+            [[fallthrough]];
         case 1: return launch_split<128, 2, 2, 1, NT>(a, stream);
         case 2: return launch_split<128, 2, 2, 2, NT>(a, stream);
         case 3: return launch_split<64, 2, 1, 1, NT>(a, stream);

@@ -56,7 +56,15 @@ hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
                       (a.sBo % 4 == 0) && (a.sBi % 4 == 0);
     const int tiles = (a.M + tbg::kTile - 1) / tbg::kTile;
     const int64_t blocks = (int64_t)a.batch * tiles * tiles;
-    if (!fast || blocks >= ((int64_t)1 << 31)) {
+    // Enough 128 x 128 tiles to fill the chip twice, mostly full: the bf16-split GEMM (32 x 12 heads of 512 x
+    // 512 x 128 239 -> 187 us, 16 x 12 of 200 x 200 x 80 36 -> 23).  With fewer or half-empty tiles the kernels
+    // below are the faster ones (166 x 166 x 64 14.3 against 16.3 us), and the fused softmax keeps its sizes.
+    const bool fused = a.softmax_rows && a.M <= tbg::kMaxKeys && a.K <= 1024 && (a.K % 8 == 0);
+    const int64_t tiles128 = (a.M + 127) / 128;
+    const bool split = a.M > tbg::kMaxKeys && !fused && tiles128 * tiles128 * a.batch >= 512 &&
+                       (double)a.M * a.M >= 0.6 * tiles128 * tiles128 * 128 * 128 && (a.K >= 48 || a.M % tbg::kTile == 0) &&
+                       (int64_t)(a.M - 1) * a.lda + a.K < ((int64_t)1 << 29) && (int64_t)(a.N - 1) * a.ldb + a.K < ((int64_t)1 << 29);
+    if (!fast || split || blocks >= ((int64_t)1 << 31)) {
         GemmArgs g = a;
         return launch_gemm(g, stream);
     }
@@ -68,7 +76,7 @@ hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
     t.os_b = a.sCo; t.os_h = a.sCi; t.os_i = a.ldc;
     t.tiles_i = tiles; t.tiles_j = tiles;
     t.xcd_chunk = (blocks % 8 == 0) ? (int)(blocks / 8) : 0;
-    if (a.softmax_rows && a.M <= tbg::kMaxKeys && a.K <= 1024 && (a.K % 8 == 0)) {
+    if (fused) {
         // fused TBS: a block of query rows x all keys per work-group
         const int vec_store = is_aligned16(a.C) && (a.ldc % 4 == 0) && (a.sCo % 4 == 0) && (a.sCi % 4 == 0);
         if (a.M <= 32) return launch_tbs_by_d<1>(t, a.batch, vec_store, stream);

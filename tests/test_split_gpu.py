@@ -93,7 +93,8 @@ def test_split_gemm_values_the_pieces_cannot_carry(anr, M, N, K, what):
     assert_product(C, A, B)
 
 
-@pytest.mark.parametrize("B,S,H,D", [(2, 130, 3, 64), (1, 257, 2, 80), (4, 512, 12, 33), (1, 300, 1, 128)])
+@pytest.mark.parametrize("B,S,H,D", [(2, 130, 3, 64), (1, 257, 2, 80), (4, 512, 12, 33), (1, 300, 1, 128), (16, 256, 8, 128),
+                                     (8, 200, 16, 80), (8, 192, 16, 32)])
 def test_split_scores(anr, B, S, H, D):
     q, k = uniform(5, B, S, H, D), uniform(6, B, S, H, D)
     out = torch.empty(B, H, S, S, device="cuda")
