@@ -547,7 +547,8 @@ def main():
             traffic = None
     traffic_source = "stored: profiles/hbm_traffic.json (rocprofv3 --pmc FETCH_SIZE, WRITE_SIZE)" if traffic else None
     # the kernel behind each operator's benchmark launch (with --only, the roofline is that operator's)
-    kernels = {"GMM": "gemm_tile32_ksplit_kernel", "C2D": "conv_igemm_kernel", "ConvLayer": "conv_igemm_kernel",
+    kernels = {"GMM": "gemm_tile32_ksplit_kernel", "C2D": "conv_patch_split_kernel",
+               "ConvLayer": "conv_patch_split_kernel",
                "C2D_S2": "conv_igemm_kernel", "TBG": "tbg_tile64_kernel", "TBS": "tbs_rows32_kernel",
                "DEP": "dwconv3x3_stream_kernel"}
     if dom["bound"] == "hbm":

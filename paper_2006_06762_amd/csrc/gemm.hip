@@ -1,8 +1,11 @@
 // fp32 GEMM on the MFMA units of gfx950: the GMM operator (C = A.B, Sec. 4.1 of
 // arXiv 2006.06762) and the batch matmul of the TBS subgraph (Sec. 7.2) in its
-// A.B^T form.
+// A.B^T form.  Four kernels, chosen in launch_gemm: the wave-split-K kernel below for small
+// products of K = 128, 256 and 512, gemm_pipe_kernel for other small aligned ones,
+// gemm_split_kernel for everything larger, and gemm_kernel for what those leave (extents beyond
+// 32-bit offsets, tiny unaligned products).
 //
-// Work-group tile BM x BN, 256 threads = 4 waves in a 2 x 2 grid; every wave
+// gemm_kernel: work-group tile BM x BN, 256 threads = 4 waves in a 2 x 2 grid; every wave
 // owns a (BM/2) x (BN/2) block of C as 32x32 MFMA accumulators.  Operand tiles
 // go HBM/L2 -> registers -> LDS (double buffered, one barrier per K step), and
 // LDS -> registers with 16-byte reads: the 32x32x2 MFMA takes, from lane l,
