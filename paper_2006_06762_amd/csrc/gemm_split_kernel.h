@@ -139,7 +139,10 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            // the row's part of the offset is uniform and rides in the load's scalar offset
+            // the row's part of the offset is uniform and rides in the load's scalar offset.  In the last chunk
+            // that part alone may lie past the extent: the range check counts it and the load reads zero
+            // (measured with scalar offsets up to 1000 times the extent; keeping it on the last row instead
+            // costs 2 %: 4096^3 604 against 589 us)
             const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(brsrc, (int)(boff | past), (int)((uint32_t)(k0 + 16 * f + e) * ldb4), 0));
             rb[f][e] = v[0];
             rb[f][4 + e] = v[1];
