@@ -486,8 +486,14 @@ hipError_t launch_pipe(const GemmArgs& a, hipStream_t stream, bool* taken)
 
 }  // namespace
 
-hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream)
+hipError_t launch_gemm(const GemmArgs& args, hipStream_t stream)
 {
+    GemmArgs a = args;
+    // a packed column is a k-contiguous row of the A.B^T form
+    if (!a.b_is_nk && a.N == 1 && a.ldb == 1) {
+        a.b_is_nk = true;
+        a.ldb = a.K;
+    }
     const bool strides4 = (a.sAo % 4 == 0) && (a.sAi % 4 == 0) && (a.sBo % 4 == 0) &&
                           (a.sBi % 4 == 0) && (a.sCo % 4 == 0) && (a.sCi % 4 == 0);
     bool vec = is_aligned16(a.A) && is_aligned16(a.B) && is_aligned16(a.C) && strides4 &&
@@ -512,7 +518,8 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream)
     const int64_t a_ext = (int64_t)(a.M - 1) * a.lda + a.K;
     const int64_t b_ext = a.b_is_nk ? (int64_t)(a.N - 1) * a.ldb + a.K : (int64_t)(a.K - 1) * a.ldb + a.N;
     // (work-items in one grid dimension stay below 2^32: a 64 x 64 tile has 128 to 512 of them)
-    const bool split = a_ext < ((int64_t)1 << 29) && b_ext < ((int64_t)1 << 29) &&
+    // (and the split kernel reads pairs of columns)
+    const bool split = (a.b_is_nk || a.N >= 2) && a_ext < ((int64_t)1 << 29) && b_ext < ((int64_t)1 << 29) &&
                        (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch < ((int64_t)1 << 22);
     bool piped = false;
     err = hipSuccess;

@@ -14,8 +14,7 @@
 // address unit takes a load instruction's 64 lanes in 16 cycles whatever their width, and 4-byte loads
 // cost a quarter of the time of a work-group alone on its CU), and packing pairs of k transposes for
 // free.  Column 2p + b sits at position b*BN/2 + p, so that a lane's two accumulator blocks are
-// neighbouring columns of C.  Loads past the end of a matrix read zero (the buffer range check is per
-// dword), loads past the end of a row read the next one and meet columns that are never stored.
+// neighbouring columns of C.  Which rows, columns and k a thread reads at the edges: gemm_split_plan.h.
 //
 // Bound: large products by the matrix pipes' power: at 4096^3 they are busy 69 % of the cycles and the
 // clock falls to 1.7 GHz (six bf16 products per fp32 one at 235 TFLOP/s are 1.4 PFLOP/s); work-groups
@@ -27,13 +26,11 @@
 #include <type_traits>
 
 #include "anr_kernels.h"
+#include "gemm_split_plan.h"
 #include "split_bf16.h"
 
 namespace anr {
 namespace gsplit {
-
-constexpr int KC = 32;                               // k of a global load round; LDS buffers hold half of it
-constexpr uint32_t kOutOfRange = 0x80000000u;
 
 template <int ROWS>
 struct Plane {
@@ -108,10 +105,9 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
     // (tid/2) % (BN/2), unit t = (tid/2) / (BN/2); of the k-contiguous B of the A.B^T form like A.
     const int at = tid & 1, arow = tid >> 1;
     const int bt = arow / (BN / 2), bpair = arow % (BN / 2);
-    // rows past M repeat the last one and columns past N the last ones: loaded, never stored
-    const uint32_t aoff = 4u * (uint32_t)((int64_t)min(m0 + arow, M - 1) * p.lda + 4 * at);
-    const uint32_t boff = NT ? 4u * (uint32_t)((int64_t)min(n0 + arow, N - 1) * p.ldb + 4 * at)
-                             : 4u * (uint32_t)((int64_t)(4 * bt + 8 * at) * p.ldb + min(n0 + 2 * bpair, N - 1));
+    const uint32_t aoff = 4u * (uint32_t)((int64_t)unit_row(m0 + arow, M) * p.lda + unit_k(at, 0, 0));
+    const uint32_t boff = NT ? 4u * (uint32_t)((int64_t)unit_row(n0 + arow, N) * p.ldb + unit_k(at, 0, 0))
+                             : 4u * (uint32_t)((int64_t)piece_k(bt, at) * p.ldb + piece_col(n0 + 2 * bpair, N));
 
     float ra[2][8], rb[2][8];                        // rb: four k of the first column, then of the second (NT: as ra)
     const uint32_t ldb4 = 4u * (uint32_t)p.ldb;
@@ -121,29 +117,43 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
 #pragma unroll
         for (int e = 0; e < 4; ++e) { r[e] = lo[e]; r[4 + e] = hi[e]; }
     };
-    // Chunks past the last one read zeros: their addresses are those of the last chunk with an offset that
-    // is out of range (a branch around the loads would make the compiler wait for them where it ends)
+    // Chunks past the last one read zeros: their offset is out of range (a branch around the loads would make
+    // the compiler wait for them where it ends)
     const int nchunks = (K + KC - 1) / KC;
     auto load_a = [&](int c, auto f_c) {             // half f of chunk c
         constexpr int f = decltype(f_c)::value;
         const uint32_t past = c < nchunks ? 0u : kOutOfRange;
-        load_unit(arsrc, aoff | past, min(c, nchunks - 1) * KC, f, ra[f]);
+        load_unit(arsrc, aoff | past, chunk_k0(c, K), f, ra[f]);
     };
     auto load_b = [&](int c, auto f_c) {
         constexpr int f = decltype(f_c)::value;
         const uint32_t past = c < nchunks ? 0u : kOutOfRange;
-        const int k0 = min(c, nchunks - 1) * KC;
+        const int k0 = chunk_k0(c, K);
         if (NT) {
             load_unit(brsrc, boff | past, k0, f, rb[f]);
             return;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            // the row's part of the offset is uniform and rides in the load's scalar offset.  In the last chunk
-            // that part alone may lie past the extent: the range check counts it and the load reads zero
-            // (measured with scalar offsets up to 1000 times the extent; keeping it on the last row instead
-            // costs 2 %: 4096^3 604 against 589 us)
-            const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(brsrc, (int)(boff | past), (int)((uint32_t)(k0 + 16 * f + e) * ldb4), 0));
+            // the row's part of the offset is uniform and rides in the load's scalar offset
+            const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(brsrc, (int)(boff | past), (int)((uint32_t)(k0 + piece_step(f, e)) * ldb4), 0));
+            rb[f][e] = v[0];
+            rb[f][4 + e] = v[1];
+        }
+    };
+    // The first chunk of a group, and the only one of a K below 32, whose rows past K are kept out lane by lane
+    auto load_b_first = [&](auto f_c) {
+        constexpr int f = decltype(f_c)::value;
+        if (NT) {
+            load_b(wgrp, f_c);
+            return;
+        }
+        const int k0 = chunk_k0(wgrp, K);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool in = wgrp < nchunks && k0 + piece_k(bt, at) + piece_step(f, e) < K;
+            const uint32_t off = in ? boff + (uint32_t)(k0 + piece_step(f, e)) * ldb4 : kOutOfRange;
+            const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(brsrc, (int)off, 0, 0));
             rb[f][e] = v[0];
             rb[f][4 + e] = v[1];
         }
@@ -155,13 +165,14 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
     char* const wa = region + at * Plane<BM>::UNIT + arow * 16;
     char* const wb = region + 3 * PA + (NT ? at * Plane<BN>::UNIT + ((arow & 1) * (BN / 2) + (arow >> 1)) * 16
                                            : bt * Plane<BN>::UNIT + bpair * 16 + 8 * at);
-    // k past the end: rows of a k-major B lie past the matrix and read zero, a k-contiguous row runs on
-    // into the next one and is cleared here (the half chunk starts at k)
-    auto clear_past = [&](auto f_c, int k) {
+    // k that an earlier chunk has counted and, of a K below 32, k past the end (of B, loaded zeros or, where a
+    // k-contiguous row runs on into the next one, cleared as well)
+    auto clear_uncounted = [&](auto f_c, int c) {
         constexpr int f = decltype(f_c)::value;
+        const int k0 = chunk_k0(c, K);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const bool in = k + 4 * at + (e < 4 ? e : 4 + e) < K;
+            const bool in = counts(c, k0 + unit_k(at, f, e), K);
             ra[f][e] = in ? ra[f][e] : 0.f;
             if (NT) rb[f][e] = in ? rb[f][e] : 0.f;
         }
@@ -184,8 +195,7 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
         }
     };
     auto store_half = [&](auto f_c, int c) {         // half f of chunk c
-        const int k = c * KC + 16 * decltype(f_c)::value;
-        if (k + 16 > K) clear_past(f_c, k);
+        if (c * KC + KC > K) clear_uncounted(f_c, c);
 #pragma unroll
         for (int i = 0; i < 8; ++i) split_pair(f_c, i);
     };
@@ -239,9 +249,9 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
     using F1 = std::integral_constant<int, 1>;
     const int iters = (nchunks + NWG - 1) / NWG;     // the barriers are the work-group's
     load_a(wgrp, F0{});
-    load_b(wgrp, F0{});
+    load_b_first(F0{});
     load_a(wgrp, F1{});
-    load_b(wgrp, F1{});
+    load_b_first(F1{});
     store_half(F0{}, wgrp);
     load_a(wgrp + NWG, F0{});
     load_b(wgrp + NWG, F0{});
@@ -343,7 +353,7 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
                 float* const d = c + (int64_t)dr * p.ldc;
                 const pair v = {acc[mb][0][r], acc[mb][1][r]};
                 if (whole || (row0 + dr < M && col + 1 < N)) __builtin_nontemporal_store(v, reinterpret_cast<pair*>(d));
-                else if (row0 + dr < M && col < N) *d = acc[mb][0][r];
+                else if (row0 + dr < M && col < N) *d = acc[mb][!NT && second_of_pair(col, N)][r];
             }
         }
     };

@@ -1,0 +1,27 @@
+"""The bf16-split GEMM's staging, walked thread by thread on the CPU with the kernel's own index arithmetic: every
+load inside its matrix (or past the extent by the lane's part of the offset alone), every k counted once."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2006_06762_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def staging(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "staging")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-I", CSRC, os.path.join(HERE, "gemm_split_staging.cpp"), "-o", exe],
+                   check=True)
+    return lambda *args: subprocess.run([exe, *map(str, args)], capture_output=True, text=True)
+
+
+# tails of K of every kind (below a chunk, one past, one short), odd and even N, one pair of columns, single rows
+@pytest.mark.parametrize("tile,groups", [(64, 1), (64, 2), (64, 4), (128, 1), (128, 2), (256, 1)])
+@pytest.mark.parametrize("M,N,K", [(65, 3, 33), (1, 2, 31), (70, 129, 1), (63, 66, 95), (3, 65, 64), (66, 64, 17), (2, 67, 161)])
+@pytest.mark.parametrize("pad", [0, 3])
+@pytest.mark.parametrize("nt", [0, 1])
+def test_split_gemm_staging_stays_inside_and_counts_once(staging, tile, groups, M, N, K, pad, nt):
+    res = staging(tile, groups, M, N, K, pad, nt)
+    assert res.returncode == 0, res.stdout + res.stderr
