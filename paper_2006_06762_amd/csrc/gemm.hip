@@ -410,7 +410,7 @@ hipError_t launch_variant(const GemmArgs& a, hipStream_t stream)
 template <int BM, int WM, int WN, int NWG, bool NT>
 hipError_t launch_split(const GemmArgs& a, hipStream_t stream)
 {
-    const gsplit::Grid g{(a.M + BM - 1) / BM, (a.N + BM - 1) / BM, BM == 256 ? 4 : 8};
+    const gsplit::Grid g{(a.M + BM - 1) / BM, (a.N + BM - 1) / BM, 8};
     constexpr size_t lds_bytes = gsplit::lds_bytes<BM, BM, NWG>();
     auto kern = gsplit::gemm_split_kernel<BM, BM, WM, WN, NWG, 2, NT>;
     if (lds_bytes > 48 * 1024) {
@@ -422,43 +422,15 @@ hipError_t launch_split(const GemmArgs& a, hipStream_t stream)
                          stream, a, g);
 }
 
-// Tile and wave groups of the split kernel: the variant with the shortest estimated time.  `base` is
-// launch, prologue and epilogue, `round` the time in which each group of a work-group alone on its CU
-// gets one 32-wide chunk done (load latency, staging, two barriers), `busy` a CU's time per chunk and
-// work-group once several fill it: us, measured on 32^3 to 1500^3 (`base`, `round`) and 4096^3 (`busy`).
-// Large tiles read fewer operand bytes per FLOP, small ones spread a small product over more CUs, and wave
-// groups shorten the chain of chunks where there are not enough tiles even so.
 template <bool NT>
 hipError_t launch_split_any(const GemmArgs& a, hipStream_t stream)
 {
-    struct Variant {
-        int tile, groups;
-        double base, round, busy;
-    };
-    constexpr Variant kVariants[] = {{256, 1, 9.0, 3.75, 4.4}, {128, 1, 5.4, 1.68, 1.27}, {128, 2, 6.8, 2.47, 1.4},
-                                     {64, 1, 3.9, 1.13, 0.47}, {64, 2, 3.6, 1.45, 0.44}, {64, 4, 5.6, 1.9, 0.55}};
-    const int chunks = (a.K + gsplit::KC - 1) / gsplit::KC;
-    int best = 0;
-    double best_us = 0.0;
-    for (int v = NT ? 1 : 0; v < 6; ++v) {      // (the 256-wide tile leaves no registers for a second set of sums)
-        const Variant& t = kVariants[v];
-        const int64_t tiles = (int64_t)((a.M + t.tile - 1) / t.tile) * ((a.N + t.tile - 1) / t.tile) * a.batch;
-        const double chain = (double)((chunks + t.groups - 1) / t.groups) * t.round;
-        const double work = (double)((tiles + 255) / 256) * chunks * t.busy;
-        const double us = t.base + (work > chain ? work : chain);
-        if (v == (NT ? 1 : 0) || us < best_us) {
-            best = v;
-            best_us = us;
-        }
-    }
-    switch (best) {
-        case 0:
-            if constexpr (!NT) return launch_split<256, 2, 4, 1, NT>(a, stream);
-            [[fallthrough]];
-        case 1: return launch_split<128, 2, 2, 1, NT>(a, stream);
-        case 2: return launch_split<128, 2, 2, 2, NT>(a, stream);
-        case 3: return launch_split<64, 2, 1, 1, NT>(a, stream);
-        case 4: return launch_split<64, 2, 1, 2, NT>(a, stream);
+    static_assert(gsplit::kVariantCount == 5, "one launch per variant");
+    switch (gsplit::choose_variant(a.M, a.N, a.K, a.batch)) {
+        case 0: return launch_split<128, 2, 2, 1, NT>(a, stream);
+        case 1: return launch_split<128, 2, 2, 2, NT>(a, stream);
+        case 2: return launch_split<64, 2, 1, 1, NT>(a, stream);
+        case 3: return launch_split<64, 2, 1, 2, NT>(a, stream);
         default: return launch_split<64, 2, 1, 4, NT>(a, stream);
     }
 }

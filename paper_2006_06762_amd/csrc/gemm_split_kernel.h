@@ -16,12 +16,14 @@
 // free.  Column 2p + b sits at position b*BN/2 + p, so that a lane's two accumulator blocks are
 // neighbouring columns of C.  Which rows, columns and k a thread reads at the edges: gemm_split_plan.h.
 //
-// Bound: large products by the matrix pipes' power: at 4096^3 they are busy 69 % of the cycles and the
-// clock falls to 1.7 GHz (six bf16 products per fp32 one at 235 TFLOP/s are 1.4 PFLOP/s); work-groups
-// alone on their CU by the chain load - split - LDS - multiply.  Measured against the fp32 kernels this
-// one took over from: 4096^3 984 -> 594 us, 1024^3 x16 262 -> 157, 512^3 x16 38.0 -> 29.6,
-// 1009 x 1531 x 771 x3 (4-byte aligned rows) 167 -> 63, 1024^3 22.3 -> 19.8.  Tried and dropped: the split
-// between the matrix instructions, v_dot2 for its subtractions, wave groups in opposite order (all slower).
+// Bound: large products by the matrix pipes' power (eight bf16 products per fp32 one at 181 TFLOP/s are
+// 1.45 PFLOP/s, what a large bf16 product of the library reaches on the card is 1.3); work-groups alone on their
+// CU by the chain load - split - LDS - multiply.  Measured against the fp32 kernels this one took over from:
+// 4096^3 976 -> 761-799 us (by box), 2048^3 133 -> 113, 1024^3 x16 257 -> 204, 512^3 x16 38.6 -> 33.3,
+// 1009 x 1531 x 771 x3 (4-byte aligned rows) 167 -> 70, 1024^3 22.7 -> 22.4.  Tried and dropped: the split
+// between the matrix instructions, v_dot2 for its subtractions, wave groups in opposite order (all slower);
+// 256 x 256 tiles, which leave no registers for the second set of sums (six products in one set, 4096^3 in
+// 600 us, but up to five full-size roundings where a single non-zero term needs one).
 #pragma once
 #include <type_traits>
 
@@ -200,17 +202,14 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
         for (int i = 0; i < 8; ++i) split_pair(f_c, i);
     };
 
-    // The short reductions of the A.B^T form (head sizes) keep the five small products in accumulators of
-    // their own: the large sum is then rounded once per sixteen k instead of six times (D = 32: 3.9e-8 from
-    // the 64-bit results; 1.0e-7 with one accumulator, 7.9e-8 with the fp32 instruction)
-    constexpr bool LOW = NT;
-    f32x16 acc[MB][2], low[LOW ? MB : 1][2];
+    // the products of the first pieces, and the other seven
+    f32x16 acc[MB][2], low[MB][2];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mb][nb][r] = low[LOW ? mb : 0][nb][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[mb][nb][r] = low[mb][nb][r] = 0.f;
 
     // Multiplies buffer f, then fills the other one with the loaded half of chunk c_fill and sends that
     // half's loads of chunk c_load.
@@ -229,13 +228,12 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
             u32x4 av[3];
 #pragma unroll
             for (int q = 0; q < 3; ++q) av[q] = *reinterpret_cast<const u32x4*>(a + q * PA + mb * 512);
-            constexpr int qa[6] = {0, 0, 1, 1, 0, 2}, qb[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll
-            for (int t = 0; t < 6; ++t)
+            for (int t = 0; t < kProducts; ++t)
 #pragma unroll
                 for (int nb = 0; nb < 2; ++nb) {
-                    f32x16& sum = LOW && t > 0 ? low[LOW ? mb : 0][nb] : acc[mb][nb];
-                    sum = mfma_bf16(av[qa[t]], bv[qb[t]][nb], sum);
+                    f32x16& sum = t < kProducts - 1 ? low[mb][nb] : acc[mb][nb];
+                    sum = mfma_bf16(av[kPieceA[t]], bv[kPieceB[t]][nb], sum);
                 }
         }
         store_half(G{}, c_fill);
@@ -262,14 +260,12 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
         __syncthreads();
         half(F1{}, c + NWG, c + 2 * NWG);
     }
-    if (LOW) {
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
+        for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[mb][nb][r] += low[LOW ? mb : 0][nb][r];
-    }
+            for (int r = 0; r < 16; ++r) acc[mb][nb][r] += low[mb][nb][r];
     if (NWG > 1) __syncthreads();
     if (NWG > 1) {
         // every staging buffer is free: groups 1 .. NWG-1 leave their accumulators there, group 0 adds

@@ -1,15 +1,18 @@
 // fp32 products on the bf16 matrix pipes without giving up fp32 accuracy.
 //
 // gfx950 multiplies fp32 matrices at 157 TFLOP/s and bf16 ones at 2.5 PFLOP/s.  A float is the exact
-// sum of three bf16 numbers, x = h + m + l (24 significant bits in three pieces of eight, each
-// rounded to nearest, so the next piece is at most 2^-9 of the one before), and a product of two
-// floats is then the sum of the nine products of their pieces, each exact in fp32.  Six of them are
-// formed: hh, hm, mh, mm, hl, lh; the three left out (ml, lm, ll) add up to less than 2^-25 of the
-// product, half a unit in the last place of fp32, with random sign.  v_mfma_f32_32x32x16_bf16 adds
-// the sixteen products of an instruction to the accumulator with one rounding where the fp32 form
-// rounds for every two: measured against 64-bit results the six-product sum is no further off than
-// the fp32 instruction (512 terms 3.2e-7 against 4.0e-7, 4096 terms 8.9e-7 against 1.1e-6).
-// Denormal inputs and results are kept by the instruction (measured).
+// sum of three bf16 numbers, x = h + m + l (24 significant bits in three pieces of eight, each rounded to
+// nearest, so m is at most 2^-8 and l at most 2^-17 of the leading bit of x), and a product of two floats
+// is then the sum of the nine products of their pieces, each exact in fp32.  Eight of them are formed; ll,
+// the ninth, is at most 2^-34 of the product.  (Six, without ml and lm, would leave out up to 2^-24 of the
+// product: as much again as rounding it to fp32.)
+//
+// v_mfma_f32_32x32x16_bf16 adds the sixteen products of an instruction to the accumulator with one rounding.
+// The seven small products, 2^-8 of hh and less, go to an accumulator of their own, so that the large sum is
+// rounded once per sixteen k where the fp32 instruction rounds once per two: a single non-zero term comes out
+// as one fp32 rounding of the product (measured 1.004 units of 2^-24 at most, the fp32 instruction 1.000; one
+// accumulator for all products and six of them 4.99), sums of 1024 terms of one sign 2.6 units rms against
+// 7.2, of random sign 0.12 against 0.40.  Denormal inputs and results are kept by the instruction (measured).
 //
 // Two kinds of value do not survive the split, and both are detected exactly:
 //   - magnitudes below 2^-110, whose last piece needs bits under the smallest bf16 denormal: l is the
@@ -54,6 +57,11 @@ __device__ __forceinline__ void split2(float x0, float x1, uint32_t& h, uint32_t
     l = __builtin_amdgcn_perm(l1, l0, 0x07060302u);
     lost |= l0 | l1;
 }
+
+// The products, smallest first: pieces of the two operands (0 h, 1 m, 2 l).  The last one is the large one.
+constexpr int kProducts = 8;
+constexpr int kPieceA[kProducts] = {1, 2, 0, 2, 1, 0, 1, 0};
+constexpr int kPieceB[kProducts] = {2, 1, 2, 0, 1, 1, 0, 0};
 
 __device__ __forceinline__ bool lost_bits(uint32_t lost) { return (lost & 0xffffu) != 0; }
 

@@ -25,3 +25,23 @@ def staging(tmp_path_factory):
 def test_split_gemm_staging_stays_inside_and_counts_once(staging, tile, groups, M, N, K, pad, nt):
     res = staging(tile, groups, M, N, K, pad, nt)
     assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_variant_shapes_select_their_variants(tmp_path):
+    """The GPU tests' shapes run the tile and wave groups they are listed for, and every variant has one."""
+    torch_tests = pytest.importorskip("test_split_gpu")
+    src = tmp_path / "choose.cpp"
+    src.write_text("""
+#include <cstdio>
+#include <cstdlib>
+#include "gemm_split_plan.h"
+int main(int, char** v)
+{
+    const auto& c = anr::gsplit::kVariants[anr::gsplit::choose_variant(atoi(v[2]), atoi(v[3]), atoi(v[4]), atoi(v[1]))];
+    printf("%d %d %d", c.tile, c.groups, anr::gsplit::kVariantCount);
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-I", CSRC, str(src), "-o", str(tmp_path / "choose")], check=True)
+    choose = lambda shape: tuple(map(int, subprocess.check_output([str(tmp_path / "choose"), *map(str, shape)]).split()))
+    for variant, shape in torch_tests.VARIANTS.items():
+        assert choose(shape) == (*variant, len(torch_tests.VARIANTS))

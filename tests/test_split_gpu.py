@@ -106,6 +106,50 @@ def test_split_scores(anr, B, S, H, D):
     assert_product(out, q.permute(0, 2, 1, 3).contiguous(), kt)
 
 
+# one shape per variant of the split GEMM (tile, wave groups), each with remainders in M, N and K
+VARIANTS = {(128, 1): (1, 3971, 4033, 545), (128, 2): (8, 505, 900, 515), (64, 1): (8, 257, 900, 161), (64, 2): (12, 505, 511, 1509),
+            (64, 4): (1, 257, 511, 515)}
+
+# Units of 2^-24 of a product: what the products add beside the roundings of the large sum.  The seven small ones
+# make at most 2^-7 of a product, rounded seven times; ll, which is left out, at most 2^-10 of a unit.
+SMALL = 7 * 2.0 ** -7 + 2.0 ** -10
+
+
+def few_terms(seed, terms, batch, M, K):
+    """A with `terms` non-zeros of 1 to 2 and either sign in every row."""
+    A = uniform(seed, batch, M, K)
+    A = torch.where(A < 0, A * 0.5 - 1.0, A * 0.5 + 1.0)
+    A.scatter_(2, uniform(seed + 1, batch, M, K).argsort(2)[:, :, terms:], 0.0)
+    return A
+
+
+@pytest.mark.parametrize("variant", VARIANTS)
+@pytest.mark.parametrize("terms", [1, 4])
+def test_split_gemm_of_few_terms_is_rounded_once_per_term(anr, variant, terms):
+    batch, M, N, K = VARIANTS[variant]
+    A, B = few_terms(20, terms, batch, M, K), uniform(22, batch, K, N)
+    B[:, :, : N // 2] = 1.0 + 2.0 ** -8 - 2.0 ** -17          # both small pieces as large as they get
+    C = torch.empty(batch, M, N, device="cuda")
+    anr.gemm(A, B, C)
+    units = (C.double() - A.double() @ B.double()).abs() / (A.double().abs() @ B.double().abs()) * 2.0 ** 24
+    # the first term's large product is exact; every further one and the small products' sum are a rounding each
+    assert float(units.max()) <= terms + SMALL, float(units.max())
+
+
+@pytest.mark.parametrize("variant", VARIANTS)
+def test_split_gemm_of_one_sign_is_rounded_once_per_sixteen_terms(anr, variant):
+    batch, M, N, K = VARIANTS[variant]
+    A, B = uniform(24, batch, M, K).abs(), uniform(25, batch, K, N).abs()
+    C = torch.empty(batch, M, N, device="cuda")
+    anr.gemm(A, B, C)
+    ref = A.double() @ B.double()
+    rms = float(((C.double() - ref) / ref * 2.0 ** 24).square().mean().sqrt())
+    # n roundings of a sum that grows evenly, each evenly spread over at most a unit of it: sqrt(n / 9); the last
+    # chunk repeats up to half of its steps with zeros, which round nothing.  The fp32 instruction has 8 n.
+    n = -(-K // 16) + 1
+    assert rms <= 1.1 * (n / 9.0) ** 0.5 + SMALL, (rms, n)
+
+
 def conv_reference(x, w, stride, pad, dil=1, groups=1):
     """Convolution and the convolution of the absolute values, in 64 bits, tap by tap."""
     N, C, H, W = x.shape
