@@ -3,7 +3,7 @@
 // A.B^T form.  Four kernels, chosen in launch_gemm: the wave-split-K kernel below for small
 // products of K = 128, 256 and 512, gemm_pipe_kernel for other small aligned ones,
 // gemm_split_kernel for everything larger, and gemm_kernel for what those leave (extents beyond
-// 32-bit offsets, tiny unaligned products).
+// 32-bit offsets, unaligned products of few tiles and a short reduction).
 //
 // gemm_kernel: work-group tile BM x BN, 256 threads = 4 waves in a 2 x 2 grid; every wave
 // owns a (BM/2) x (BN/2) block of C as 32x32 MFMA accumulators.  Operand tiles
@@ -435,14 +435,18 @@ hipError_t launch_split_any(const GemmArgs& a, hipStream_t stream)
     }
 }
 
-// The fp32 pipelined kernel where it is the faster one: at most one 64 x 64 tile per CU and a short
-// reduction, so that the time is a chain of latencies (splitting adds an LDS round trip to every chunk).
-// 300^3 9.9 against 11.1 us, 1000 x 1000 x 128 5.8 against 7.8, 32^3 3.0 against 4.8; from K = 500 on the
-// split kernel's four wave groups win (500^3 13.1 against 13.0, 768^3 17.7 against 15.8).
+// The fp32 pipelined kernel where it is the faster one: a short reduction over few 64 x 64 tiles, so that the
+// time is a chain of latencies (splitting adds an LDS round trip to every chunk).  At most one tile per CU:
+// 512^2 x 96 5.1 against 7.3 us, 1024^2 x 480 12.8 against 13.9, x 608 15.3 against 16.2 (past 704 four
+// wave groups of the split kernel come level, and only they keep up with a longer chain).  Up to three tiles
+// per CU and the seven chunks of one wave group: 1536 x 1024 x 160 9.2 against 10.7, 1536^2 x 224 15.3 against
+// 16.1; x 256 18.6 against 17.1, and 16 x 512^2 x 128 14.3 against 12.7.  Up to four and two chunks: 2048^2 x 64
+// 10.6 against 12.7.  The split kernel starts at one chunk.
 hipError_t launch_pipe(const GemmArgs& a, hipStream_t stream, bool* taken)
 {
     const int tiles_m = (a.M + 63) / 64, tiles_n = (a.N + 63) / 64;
-    *taken = a.K <= 96 || (a.K < 480 && (int64_t)tiles_m * tiles_n * a.batch <= 256);
+    const int64_t tiles = (int64_t)tiles_m * tiles_n * a.batch;
+    *taken = tiles <= 256 ? a.K <= 704 : tiles <= 768 ? a.K <= 7 * gpipe::KC : tiles <= 1024 ? a.K <= 64 : a.K < gsplit::KC;
     if (!*taken) return hipSuccess;
     const dim3 grid((unsigned)(tiles_m * tiles_n), 1, a.batch);
     // a longer chain of chunks is shared by two groups of waves
@@ -490,19 +494,21 @@ hipError_t launch_gemm(const GemmArgs& args, hipStream_t stream)
     const int64_t a_ext = (int64_t)(a.M - 1) * a.lda + a.K;
     const int64_t b_ext = a.b_is_nk ? (int64_t)(a.N - 1) * a.ldb + a.K : (int64_t)(a.K - 1) * a.ldb + a.N;
     // (work-items in one grid dimension stay below 2^32: a 64 x 64 tile has 128 to 512 of them)
-    // (and the split kernel reads pairs of columns)
-    const bool split = (a.b_is_nk || a.N >= 2) && a_ext < ((int64_t)1 << 29) && b_ext < ((int64_t)1 << 29) &&
-                       (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch < ((int64_t)1 << 22);
+    const int64_t tiles64 = (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch;
+    const bool offsets32 = a_ext < ((int64_t)1 << 29) && b_ext < ((int64_t)1 << 29) && tiles64 < ((int64_t)1 << 22);
     bool piped = false;
     err = hipSuccess;
-    if (split && vec && !a.b_is_nk) err = launch_pipe(a, stream, &piped);
+    if (offsets32 && vec && !a.b_is_nk) err = launch_pipe(a, stream, &piped);
     if (err != hipSuccess) return err;
-    // operands the pipelined kernel cannot load, two chunks or less and at most one tile per CU: the plain
-    // kernel's prologue is the shortest (33^3 3.8 against 5.3 us, 65 x 67 x 63 x16 5.0 against 5.6)
-    const bool tiny = a.K <= 64 && (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch <= 256;
+    // A k-major B is read a whole chunk of rows and a pair of columns at a time.  Operands the pipelined kernel
+    // cannot load, few tiles and a short reduction: the plain kernel's prologue is the shortest (up to a tile per
+    // CU K = 32 to 47 0.73 of the split kernel's time, 81 to 96 0.82, 129 to 160 0.94, 161 to 224 1.11; up to two
+    // 48 to 80 0.89, 81 to 96 0.97, 129 to 160 1.16; three to four tiles per CU 48 to 64 1.13).
+    const bool split = offsets32 && (a.b_is_nk || (a.N >= 2 && a.K >= gsplit::KC)) &&
+                       a.K > (tiles64 <= 256 ? 160 : tiles64 <= 512 ? 96 : 0);
     if (piped) {
         // enqueued
-    } else if (split && !tiny) {
+    } else if (split) {
         err = a.b_is_nk ? launch_split_any<true>(a, stream) : launch_split_any<false>(a, stream);
     } else if (a.b_is_nk) {
         if (big) err = vec ? launch_variant<128, 128, 16, true, true>(a, stream)

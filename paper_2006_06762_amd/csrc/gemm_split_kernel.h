@@ -143,23 +143,6 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
             rb[f][4 + e] = v[1];
         }
     };
-    // The first chunk of a group, and the only one of a K below 32, whose rows past K are kept out lane by lane
-    auto load_b_first = [&](auto f_c) {
-        constexpr int f = decltype(f_c)::value;
-        if (NT) {
-            load_b(wgrp, f_c);
-            return;
-        }
-        const int k0 = chunk_k0(wgrp, K);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const bool in = wgrp < nchunks && k0 + piece_k(bt, at) + piece_step(f, e) < K;
-            const uint32_t off = in ? boff + (uint32_t)(k0 + piece_step(f, e)) * ldb4 : kOutOfRange;
-            const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(brsrc, (int)off, 0, 0));
-            rb[f][e] = v[0];
-            rb[f][4 + e] = v[1];
-        }
-    };
     // Half f goes to buffer f: eight pairs of floats are split (0-3: the unit of A, 4-5 and 6-7: the
     // columns of B) and written as soon as a 16- or 8-byte store is complete.
     uint32_t lost = 0;
@@ -167,8 +150,8 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
     char* const wa = region + at * Plane<BM>::UNIT + arow * 16;
     char* const wb = region + 3 * PA + (NT ? at * Plane<BN>::UNIT + ((arow & 1) * (BN / 2) + (arow >> 1)) * 16
                                            : bt * Plane<BN>::UNIT + bpair * 16 + 8 * at);
-    // k that an earlier chunk has counted and, of a K below 32, k past the end (of B, loaded zeros or, where a
-    // k-contiguous row runs on into the next one, cleared as well)
+    // k that an earlier chunk has counted and, of a K below 32, k past the end (in B's rows too: they run on into
+    // the next one)
     auto clear_uncounted = [&](auto f_c, int c) {
         constexpr int f = decltype(f_c)::value;
         const int k0 = chunk_k0(c, K);
@@ -247,9 +230,9 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
     using F1 = std::integral_constant<int, 1>;
     const int iters = (nchunks + NWG - 1) / NWG;     // the barriers are the work-group's
     load_a(wgrp, F0{});
-    load_b_first(F0{});
+    load_b(wgrp, F0{});
     load_a(wgrp, F1{});
-    load_b_first(F1{});
+    load_b(wgrp, F1{});
     store_half(F0{}, wgrp);
     load_a(wgrp + NWG, F0{});
     load_b(wgrp + NWG, F0{});

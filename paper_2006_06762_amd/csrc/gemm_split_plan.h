@@ -13,8 +13,8 @@ constexpr uint32_t kOutOfRange = 0x80000000u;        // byte offset beyond any d
 constexpr int smaller(int a, int b) { return a < b ? a : b; }
 
 // First k that chunk c loads.  The last chunk of a K that is no multiple of 32 starts at K - 32, inside the
-// matrix, and what an earlier chunk has counted is cleared in A (`counts`); of a K below 32 the only chunk
-// starts at zero and rows and columns past K are kept out lane by lane.
+// matrix, and what an earlier chunk has counted is cleared in A (`counts`).  A K below 32 comes in the A.B^T form
+// only: the chunk starts at zero, and what its rows read past K is cleared in both operands.
 constexpr int chunk_k0(int c, int K) { return K < KC ? 0 : smaller(c * KC, K - KC); }
 constexpr bool counts(int c, int k, int K) { return k >= c * KC && k < K; }
 
@@ -24,7 +24,7 @@ constexpr int unit_k(int at, int f, int e) { return 16 * f + 4 * at + (e < 4 ? e
 // The row such a unit reads: rows past the end repeat the last one (loaded, never stored).
 constexpr int unit_row(int row, int rows) { return smaller(row, rows - 1); }
 
-// Row e (0..3) of half f of a staging piece of k-major B, offset from the chunk's start: the part that differs
+// Row e (0..3) of half f of a staging piece of k-major B (K >= 32), offset from the chunk's start: the part that differs
 // between lanes and the part that rides in the scalar offset.
 constexpr int piece_k(int bt, int at) { return 4 * bt + 8 * at; }
 constexpr int piece_step(int f, int e) { return 16 * f + e; }

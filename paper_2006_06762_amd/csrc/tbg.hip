@@ -56,14 +56,20 @@ hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
                       (a.sBo % 4 == 0) && (a.sBi % 4 == 0);
     const int tiles = (a.M + tbg::kTile - 1) / tbg::kTile;
     const int64_t blocks = (int64_t)a.batch * tiles * tiles;
-    // Enough 128 x 128 tiles to fill the chip twice, mostly full: the bf16-split GEMM (32 x 12 heads of 512 x
-    // 512 x 128 239 -> 187 us, 16 x 12 of 200 x 200 x 80 36 -> 23).  With fewer or half-empty tiles the kernels
-    // below are the faster ones (166 x 166 x 64 14.3 against 16.3 us), and the fused softmax keeps its sizes.
     const bool fused = a.softmax_rows && a.M <= tbg::kMaxKeys && a.K <= 1024 && (a.K % 8 == 0);
+    const bool offsets32 = (int64_t)(a.M - 1) * a.lda + a.K < ((int64_t)1 << 29) && (int64_t)(a.N - 1) * a.ldb + a.K < ((int64_t)1 << 29);
+    // whole tiles, whole chunks and 32-bit byte offsets inside one (b, h) view: the lean form
+    const bool whole = (a.M % tbg::kTile == 0) && (a.K % tbg::kChunk == 0) && offsets32 &&
+                       (int64_t)(a.M - 1) * a.ldc + a.N < ((int64_t)1 << 29);
+    // Enough 128 x 128 tiles to fill the chip twice, mostly full: the bf16-split GEMM (32 x 12 heads of 512 x
+    // 512 x 128 231 -> 200 us, 16 x 12 of 200 x 200 x 80 36 -> 26).  With fewer or half-empty tiles the kernels
+    // below are the faster ones (8 x 8 of 312 x 312 x 64 15.0 against 16.5 us), and so they are with a single
+    // chunk in the lean form (24 x 8 of 256 x 256 x 64 18.4 against 20.6, 48 x 8 of 512 x 512 x 64 129.7 against
+    // 128.7).  The fused softmax keeps its sizes.
     const int64_t tiles128 = (a.M + 127) / 128;
-    const bool split = a.M > tbg::kMaxKeys && !fused && tiles128 * tiles128 * a.batch >= 512 &&
-                       (double)a.M * a.M >= 0.6 * tiles128 * tiles128 * 128 * 128 && (a.K >= 48 || a.M % tbg::kTile == 0) &&
-                       (int64_t)(a.M - 1) * a.lda + a.K < ((int64_t)1 << 29) && (int64_t)(a.N - 1) * a.ldb + a.K < ((int64_t)1 << 29);
+    const bool split = a.M > tbg::kMaxKeys && !fused && offsets32 && tiles128 * tiles128 * a.batch >= 512 &&
+                       (double)a.M * a.M >= 0.6 * tiles128 * tiles128 * 128 * 128 && (double)a.M * a.M * a.batch >= 384.0 * 128 * 128 &&
+                       (a.K >= 48 || a.M % tbg::kTile == 0) && !(whole && a.K <= tbg::kChunk);
     if (!fast || split || blocks >= ((int64_t)1 << 31)) {
         GemmArgs g = a;
         return launch_gemm(g, stream);
@@ -83,11 +89,6 @@ hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
         if (a.M <= 64) return launch_tbs_by_d<2>(t, a.batch, vec_store, stream);
         return launch_tbs_by_d<4>(t, a.batch, vec_store, stream);
     }
-    // whole tiles, whole chunks and 32-bit byte offsets inside one (b, h) view: the lean form
-    const bool whole = (a.M % tbg::kTile == 0) && (a.K % tbg::kChunk == 0) &&
-                       (int64_t)(a.M - 1) * a.lda + a.K < ((int64_t)1 << 29) &&
-                       (int64_t)(a.N - 1) * a.ldb + a.K < ((int64_t)1 << 29) &&
-                       (int64_t)(a.M - 1) * a.ldc + a.N < ((int64_t)1 << 29);
     t.d_tiles_j = make_fastdiv(t.tiles_j);
     t.d_tiles_i = make_fastdiv(t.tiles_i);
     t.d_h = make_fastdiv(t.H);

@@ -65,13 +65,7 @@ int main(int argc, char** argv)
                                 for (int b = 0; b < 2; ++b) {
                                     const int64_t lane = (int64_t)piece_k(bt, at) * ldb + piece_col(n0 + 2 * pair, N) + b;
                                     const int step = k0 + piece_step(f, e);
-                                    int v;
-                                    if (i == 0) {                             // the form of a group's first chunk
-                                        const bool in = g < nchunks && step + piece_k(bt, at) < K;
-                                        v = in ? load(B, lane + (int64_t)step * ldb, 0) : 0;
-                                    } else {
-                                        v = load(B, lane + (c < nchunks ? 0 : (int64_t)1 << 40), (int64_t)step * ldb);
-                                    }
+                                    const int v = load(B, lane + (c < nchunks ? 0 : (int64_t)1 << 40), (int64_t)step * ldb);
                                     sb[(size_t)(2 * pair + b) * KC + piece_k(bt, at) + piece_step(f, e)] = v;
                                 }
                         }
