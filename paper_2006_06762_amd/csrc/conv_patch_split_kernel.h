@@ -12,12 +12,12 @@
 // channel.  Eight waves: with 64 channels two halves of them by four groups of two blocks of 32 pixels (the
 // last group has one: seven blocks), with 32 channels a block of pixels each (one wave only stages).
 //
-// Bound: a chunk takes 5.3 us where its matrix instructions take 2.8; the rest is the split of the next
-// chunk (about 240 vector-ALU instructions per wave, and they hold up the matrix pipe) and its LDS stores,
-// which one staging buffer keeps apart from the products (two do not fit).  Against the fp32 form, batch 16:
-// 56x56 64 -> 64 34.0 -> 28.0 us, 28x28 256 -> 256 132 -> 91, 28x28 128 -> 128 33.7 -> 29.2, 112x112
-// 128 -> 64 249 -> 195.  Dealing the taps to the waves instead of the blocks (all waves on all blocks, sums
-// meeting in LDS) took 31.0 us for the first.
+// Bound: a chunk takes 5.3 us (56x56, 64 and 256 channels to 64) where its matrix instructions take 3.8; the
+// rest is the split of the next chunk (about 240 vector-ALU instructions per wave, and they hold up the matrix
+// pipe) and its LDS stores, which one staging buffer keeps apart from the products.  Against the fp32 form,
+// batch 16: 56x56 64 -> 64 34.0 -> 29.7 us, 28x28 256 -> 256 133 -> 100, 112x112 128 -> 64 251 -> 225, 28x28
+// 16 -> 128 11.1 -> 8.5; 28x28 128 -> 128 and 512 -> 128 come out level (37, 121).  Dealing the taps to the
+// waves instead of the blocks (all waves on all blocks, sums meeting in LDS) was slower.
 #pragma once
 #include "conv_fp32_block.h"
 #include "conv_igemm_kernel.h"
@@ -180,14 +180,20 @@ __global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p
         xa[b] = (uint32_t)(((n * g.HV + oh * p.stride_h - v0) * wp + ow * p.stride_w) * 16 + h * XKQ);
     }
     const char* const wa = lw + h * WKQ + (32 * wn + r32) * 16;
-    // The products of the first pieces and the other five, each at most 2^-8 of those, in accumulators of
-    // their own: a chunk rounds the large sum nine times instead of 54 (56x56, 64 -> 64: 1.3e-7 from the
-    // 64-bit results; 3.7e-7 with one accumulator, 3.0e-7 with the fp32 instruction).
-    f32x16 acc[BLK], low[BLK];
+    // The products of the first pieces, and the other seven, at most 2^-7 of those: a chunk rounds the large sum
+    // nine times.  Tiles of 32 channels, whose fp32 kernel adds up four parts, have registers for a large sum per
+    // kernel row (28x28, 128 -> 128, inputs and weights of one sign: 1.2 units of 2^-24 rms; 3.0 with one sum, 2.2
+    // with the fp32 kernel.  Tiles of 64, one sum: 56x56, 64 -> 64 2.2 against 3.0).
+    constexpr int SUMS = BLK == 1 ? 3 : 1;
+    f32x16 acc[BLK][SUMS], low[BLK];
 #pragma unroll
     for (int b = 0; b < BLK; ++b)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[b][r] = low[b][r] = 0.f;
+        for (int r = 0; r < 16; ++r) {
+            low[b][r] = 0.f;
+#pragma unroll
+            for (int i = 0; i < SUMS; ++i) acc[b][i][r] = 0.f;
+        }
 
     auto multiply = [&](auto blocks_c) {
         constexpr int blocks = decltype(blocks_c)::value;
@@ -201,13 +207,12 @@ __global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p
 #pragma unroll
                 for (int b = 0; b < blocks; ++b) xv[q][b] = *reinterpret_cast<const u32x4*>(xt + xa[b] + q * XPLANE);
             }
-            constexpr int qw[6] = {0, 0, 1, 1, 0, 2}, qx[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll
-            for (int i = 0; i < 6; ++i)
+            for (int i = 0; i < kProducts; ++i)
 #pragma unroll
                 for (int b = 0; b < blocks; ++b) {
-                    f32x16& sum = i == 0 ? acc[b] : low[b];
-                    sum = mfma_bf16(wv[qw[i]], xv[qx[i]][b], sum);
+                    f32x16& sum = i < kProducts - 1 ? low[b] : acc[b][t / 3 % SUMS];
+                    sum = mfma_bf16(wv[kPieceA[i]], xv[kPieceB[i]][b], sum);
                 }
         }
     };
@@ -226,8 +231,10 @@ __global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p
 #pragma unroll
     for (int b = 0; b < BLK; ++b) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[b][r] += low[b][r];
-        nf = not_finite(acc[b], nf);
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int i = 0; i < SUMS; ++i) low[b][r] += acc[b][i][r];
+        nf = not_finite(low[b], nf);
     }
     const int again = __syncthreads_or(lost_bits(lost) || nf != 0.f);
 
@@ -294,7 +301,7 @@ __global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p
     }
 #pragma unroll
     for (int b = 0; b < BLK; ++b)
-        if (BLK * mg + b < MB) store_block(BLK * mg + b, acc[b], g.vec_store != 0);
+        if (BLK * mg + b < MB) store_block(BLK * mg + b, low[b], g.vec_store != 0);
 }
 
 }  // namespace psplit

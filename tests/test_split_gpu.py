@@ -255,3 +255,31 @@ def test_patch_convolution(anr, N, C, H, W, K, pad, what):
     z = torch.empty_like(y)
     anr.conv2d_packed(desc, x, pack, z)
     assert torch.equal(y.nan_to_num(1.5), z.nan_to_num(1.5))
+
+
+@pytest.mark.parametrize("N,C,H,W,K,pad", PATCHES)
+@pytest.mark.parametrize("terms", [1, 4])
+def test_patch_convolution_of_few_terms_is_rounded_once_per_term(anr, N, C, H, W, K, pad, terms):
+    x, _, y = patch_case(anr, N, C, H, W, K, pad)
+    x[: N // 2] = 1.0 + 2.0 ** -8 - 2.0 ** -17          # both small pieces as large as they get
+    w = few_terms(30, terms, 1, K, C * 9).view(K, C, 3, 3)
+    w[: K // 2] *= (1.0 + 2.0 ** -8 - 2.0 ** -17) / w[: K // 2].abs().clamp_min(1.0)
+    anr.conv2d(x, w, y, (1, 1), (pad, pad), route=anr.ANR_CONV_ROUTE_PATCH)
+    ref, size, _ = conv_reference(x, w, 1, pad)
+    units = ((y.double() - ref).abs() / size.clamp_min(1e-300) * 2.0 ** 24)[size > 0]
+    assert float(units.max()) <= terms + SMALL, float(units.max())
+
+
+@pytest.mark.parametrize("N,C,H,W,K,pad", PATCHES)
+def test_patch_convolution_of_one_sign_is_rounded_nine_times_per_chunk(anr, N, C, H, W, K, pad):
+    x, w, y = patch_case(anr, N, C, H, W, K, pad)
+    sums = 3 if anr.conv2d_route(anr.conv_desc(x.shape, K, 3, 3, (1, 1), (pad, pad), route=anr.ANR_CONV_ROUTE_PATCH)).tile_n == 32 else 1
+    x, w = x.abs(), w.abs()
+    anr.conv2d(x, w, y, (1, 1), (pad, pad), route=anr.ANR_CONV_ROUTE_PATCH)
+    ref = conv_reference(x, w, 1, pad)[0]
+    units = ((y.double() - ref) / ref.clamp_min(1e-300) * 2.0 ** 24)[ref > 0]
+    # n roundings of `sums` sums that grow evenly to that share of the result, each evenly spread over at most a unit
+    # of its sum, and the additions of the sums
+    n = 9 * C // 16
+    ends = (sum((i + 1) ** 2 for i in range(sums)) / sums ** 2 / 3.0) ** 0.5
+    assert float(units.square().mean().sqrt()) <= 1.1 * (n / 9.0) ** 0.5 / sums + ends + SMALL
