@@ -12,9 +12,9 @@
 // writes whole 64-byte runs.
 //
 // Kernel rows of a channel are padded to an even number (two units make one matrix instruction): 7 x 7
-// does 8 x 8 / 49 = 1.3 times the products, at 2.7 times the fp32 rate.  Bound: the matrix pipes are busy 42 %
-// of a work-group's time, the rest is staging and stores, which its two barriers a round keep apart from the
-// products.  Batch 16: 224x224x3 -> 64, stride 2, 48.1 -> 36.3 us, stride 1 166 -> 102 us.
+// does 8 x 8 / 49 = 1.3 times the products, at twice the fp32 rate.  Bound: half of a work-group's time is
+// staging and stores, which its two barriers a round keep apart from the products.  Batch 16: 224x224x3 -> 64,
+// stride 2, 48.2 -> 46.2 us, stride 1 160 -> 132 us; 96 channels, batch 32 162 -> 132.
 #include <type_traits>
 
 #include "conv_fp32_block.h"
@@ -178,17 +178,18 @@ __global__ __launch_bounds__(T * G) void conv_stem_kernel(const ConvArgs p, cons
         // keep the loads ahead of the matrix instructions
         __builtin_amdgcn_sched_barrier(0);
         if (t < g.tiles) {
-            f32x16 acc[2];
+            // the products of the first pieces, and the other seven
+            f32x16 acc[2], low[2];
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
+                for (int r = 0; r < 16; ++r) acc[cb][r] = low[cb][r] = 0.f;
             for (int c = 0; c < C; ++c) {
                 const char* wc = wl + c * D::RP * 1024;
                 const char* xc = lx + grp * D::XBUF + xoff + c * D::PR * D::PW * 2;
 #pragma unroll
                 for (int j = 0; j < D::RP / 2; ++j) {
-                    u32x4 wv[3][2], xv[3];
+                    u32x4 xv[3];
 #pragma unroll
                     for (int q = 0; q < 3; ++q) {
                         const uint32_t* s = reinterpret_cast<const uint32_t*>(xc + q * D::PLANE + 2 * j * D::PW * 2);
@@ -202,17 +203,24 @@ __global__ __launch_bounds__(T * G) void conv_stem_kernel(const ConvArgs p, cons
 #pragma unroll
                             for (int e = 0; e < 4; ++e) xv[q][e] = s[e];
                         }
-#pragma unroll
-                        for (int cb = 0; cb < 2; ++cb)
-                            wv[q][cb] = *reinterpret_cast<const u32x4*>(wc + q * D::WPLANE + 2 * j * 1024 + cb * 512);
                     }
-                    constexpr int qw[6] = {0, 0, 1, 1, 0, 2}, qx[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll
-                    for (int i = 0; i < 6; ++i)
+                    for (int cb = 0; cb < 2; ++cb) {
+                        u32x4 wv[3];
 #pragma unroll
-                        for (int cb = 0; cb < 2; ++cb) acc[cb] = mfma_bf16(wv[qw[i]][cb], xv[qx[i]], acc[cb]);
+                        for (int q = 0; q < 3; ++q) wv[q] = *reinterpret_cast<const u32x4*>(wc + q * D::WPLANE + 2 * j * 1024 + cb * 512);
+#pragma unroll
+                        for (int i = 0; i < kProducts; ++i) {
+                            f32x16& sum = i < kProducts - 1 ? low[cb] : acc[cb];
+                            sum = mfma_bf16(wv[kPieceA[i]], xv[kPieceB[i]], sum);
+                        }
+                    }
                 }
             }
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[cb][r] += low[cb][r];
             int n, oh0, ow0;
             origin(t, n, oh0, ow0);
             const int oh = oh0 + py, ow = ow0 + px;
