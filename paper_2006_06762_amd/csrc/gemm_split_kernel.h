@@ -43,7 +43,7 @@ struct Plane {
 template <int BM, int BN, int NWG>
 constexpr size_t lds_bytes()
 {
-    return NWG * 2 * 3 * (size_t)(Plane<BM>::BYTES + Plane<BN>::BYTES);
+    return NWG * 2 * 3 * (size_t)(Plane<BM>::BYTES + Plane<BN>::BYTES) + 16;      // and a flag
 }
 
 // Chunk-invariant description of a launch (what the host works out once).
@@ -52,8 +52,10 @@ struct Grid {
     int group_m;          // tiles are walked in bands of group_m rows of tiles
 };
 
-template <int BM, int BN, int WM, int WN, int NWG, int MINW, bool NT>
-__global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(const GemmArgs p, const Grid g)
+// One tile of a work-group: as bf16 pieces, or PLAIN, with the fp32 instruction.  False if it met a value that the
+// pieces cannot carry: then nothing is stored.
+template <int BM, int BN, int WM, int WN, int NWG, bool NT, bool PLAIN>
+__device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, const int thread)
 {
     constexpr int T = 64 * WM * WN;                  // threads of a wave group
     constexpr int MB = BM / (32 * WM);
@@ -66,9 +68,10 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
 
     extern __shared__ __attribute__((aligned(16))) char slds[];
 
-    const int wgrp = NWG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / T) : 0;
+    const int wgrp = NWG > 1 ? __builtin_amdgcn_readfirstlane(thread / T) : 0;
     char* const region = slds + wgrp * 2 * BUF;
-    const int tid = (int)threadIdx.x % T;
+    int* const flag = reinterpret_cast<int*>(slds + NWG * 2 * BUF);     // a value was met that the pieces cannot carry
+    const int tid = thread % T;
     const int lane = tid & 63, wave = tid >> 6;
     const int r32 = lane & 31, h = lane >> 5;
     const int wm = wave / WN, wn = wave % WN;
@@ -179,13 +182,28 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2*>(wb + f * BUF + q * PB + (i == 7 ? BN * 8 : 0)) = u32x2{sp[q][i - 1], sp[q][i]};
         }
     };
+    // For the fp32 instruction the half goes as it is: units of four k, 16 bytes a row
+    constexpr int QA = BM * 16 + 64, QB = BN * 16 + 64;
+    static_assert(4 * QA <= 3 * PA && 4 * QB <= 3 * PB, "fits the room of the pieces");
+    char* const fa = region + at * QA + arow * 16;
+    char* const fb = region + 3 * PA + (NT ? at * QB + ((arow & 1) * (BN / 2) + (arow >> 1)) * 16 : (bt + 2 * at) * QB + bpair * 16);
     auto store_half = [&](auto f_c, int c) {         // half f of chunk c
+        constexpr int f = decltype(f_c)::value;
         if (c * KC + KC > K) clear_uncounted(f_c, c);
+        if constexpr (PLAIN) {
+            const float* const x = ra[f];
+            const float* const y = rb[f];
+            *reinterpret_cast<f32x4*>(fa + f * BUF) = f32x4{x[0], x[1], x[2], x[3]};
+            *reinterpret_cast<f32x4*>(fa + f * BUF + 2 * QA) = f32x4{x[4], x[5], x[6], x[7]};
+            *reinterpret_cast<f32x4*>(fb + f * BUF) = f32x4{y[0], y[1], y[2], y[3]};
+            *reinterpret_cast<f32x4*>(fb + f * BUF + (NT ? 2 * QB : BN * 8)) = f32x4{y[4], y[5], y[6], y[7]};
+        } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) split_pair(f_c, i);
+            for (int i = 0; i < 8; ++i) split_pair(f_c, i);
+        }
     };
 
-    // the products of the first pieces, and the other seven
+    // the products of the first pieces (or of the floats themselves), and the other seven
     f32x16 acc[MB][2], low[MB][2];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -194,41 +212,63 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[mb][nb][r] = low[mb][nb][r] = 0.f;
 
-    // Multiplies buffer f, then fills the other one with the loaded half of chunk c_fill and sends that
-    // half's loads of chunk c_load.
-    auto half = [&](auto f_c, int c_fill, int c_load) {
+    auto multiply = [&](auto f_c) {
         constexpr int f = decltype(f_c)::value;
-        using G = std::integral_constant<int, f ^ 1>;
-        const char* a = region + f * BUF + h * Plane<BM>::UNIT + (wm * MB * 32 + r32) * 16;
-        const char* b = region + f * BUF + 3 * PA + h * Plane<BN>::UNIT + (wn * 32 + r32) * 16;
-        u32x4 bv[3][2];
+        if constexpr (PLAIN) {
+            // the wave's half h takes the units 2q + h, element by element
+            const char* a = region + f * BUF + h * QA + (wm * MB * 32 + r32) * 16;
+            const char* b = region + f * BUF + 3 * PA + h * QB + (wn * 32 + r32) * 16;
 #pragma unroll
-        for (int q = 0; q < 3; ++q)
+            for (int q = 0; q < 2; ++q) {
+                f32x4 av[MB], bv[2];
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb) bv[q][nb] = *reinterpret_cast<const u32x4*>(b + q * PB + nb * BN * 8);
+                for (int mb = 0; mb < MB; ++mb) av[mb] = *reinterpret_cast<const f32x4*>(a + 2 * q * QA + mb * 512);
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            u32x4 av[3];
+                for (int nb = 0; nb < 2; ++nb) bv[nb] = *reinterpret_cast<const f32x4*>(b + 2 * q * QB + nb * BN * 8);
 #pragma unroll
-            for (int q = 0; q < 3; ++q) av[q] = *reinterpret_cast<const u32x4*>(a + q * PA + mb * 512);
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int t = 0; t < kProducts; ++t)
+                    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    f32x16& sum = t < kProducts - 1 ? low[mb][nb] : acc[mb][nb];
-                    sum = mfma_bf16(av[kPieceA[t]], bv[kPieceB[t]][nb], sum);
-                }
+                        for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = mfma32(av[mb][e], bv[nb][e], acc[mb][nb]);
+            }
+        } else {
+            const char* a = region + f * BUF + h * Plane<BM>::UNIT + (wm * MB * 32 + r32) * 16;
+            const char* b = region + f * BUF + 3 * PA + h * Plane<BN>::UNIT + (wn * 32 + r32) * 16;
+            u32x4 bv[3][2];
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) bv[q][nb] = *reinterpret_cast<const u32x4*>(b + q * PB + nb * BN * 8);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                u32x4 av[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) av[q] = *reinterpret_cast<const u32x4*>(a + q * PA + mb * 512);
+#pragma unroll
+                for (int t = 0; t < kProducts; ++t)
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb) {
+                        f32x16& sum = t < kProducts - 1 ? low[mb][nb] : acc[mb][nb];
+                        sum = mfma_bf16(av[kPieceA[t]], bv[kPieceB[t]][nb], sum);
+                    }
+            }
         }
+    };
+
+    // Half f of every chunk goes through buffer f: between two barriers one buffer is multiplied, the other filled
+    // with the loaded half of the next chunk and that half's loads of the chunk after it sent.  Group w takes every
+    // NWG-th chunk.
+    using F0 = std::integral_constant<int, 0>;
+    using F1 = std::integral_constant<int, 1>;
+    auto half = [&](auto f_c, int c_fill, int c_load) {
+        using G = std::integral_constant<int, decltype(f_c)::value ^ 1>;
+        multiply(f_c);
         store_half(G{}, c_fill);
         load_a(c_load, G{});
         load_b(c_load, G{});
     };
-
-    // Half f of every chunk goes through buffer f: between two barriers one buffer is multiplied and the
-    // other filled.  Group w takes every NWG-th chunk.
-    using F0 = std::integral_constant<int, 0>;
-    using F1 = std::integral_constant<int, 1>;
-    const int iters = (nchunks + NWG - 1) / NWG;     // the barriers are the work-group's
+    if (!PLAIN && thread == 0) *flag = 0;
     load_a(wgrp, F0{});
     load_b(wgrp, F0{});
     load_a(wgrp, F1{});
@@ -236,23 +276,30 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
     store_half(F0{}, wgrp);
     load_a(wgrp + NWG, F0{});
     load_b(wgrp + NWG, F0{});
-    for (int i = 0; i < iters; ++i) {
-        const int c = wgrp + i * NWG;
+    int end = (nchunks + NWG - 1) / NWG * NWG;       // the barriers are the work-group's
+#pragma unroll 1
+    for (int c = wgrp; c < end; c += NWG) {
         __syncthreads();
+        // set between the barriers of a round and read behind the second, so every wave reads the same
+        if (!PLAIN && lost_bits(lost)) *flag = 1;
         half(F0{}, c, c + NWG);
         __syncthreads();
+        const int stop = PLAIN ? 0 : *flag;
         half(F1{}, c + NWG, c + 2 * NWG);
+        if (!PLAIN && __builtin_amdgcn_readfirstlane(stop)) end = 0;
     }
+    if (!PLAIN) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
+            for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mb][nb][r] += low[mb][nb][r];
-    if (NWG > 1) __syncthreads();
+                for (int r = 0; r < 16; ++r) acc[mb][nb][r] += low[mb][nb][r];
+    }
     if (NWG > 1) {
         // every staging buffer is free: groups 1 .. NWG-1 leave their accumulators there, group 0 adds
         // them in group order
+        __syncthreads();
         if (wgrp > 0) {
             float* red = reinterpret_cast<float*>(slds + (wgrp - 1) * RED) + wave * (MB * 2 * 16 * 64) + lane;
 #pragma unroll
@@ -277,44 +324,15 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
         }
     }
 
-    float nf = 0.f;
+    if (!PLAIN) {
+        float nf = 0.f;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) nf = not_finite(acc[mb][nb], nf);
-    const int again = __syncthreads_or(lost_bits(lost) || nf != 0.f);
-    if (NWG > 1 && wgrp > 0) return;
-    if (again) {
-        // values the split cannot carry: the tile again, block by block, with the fp32 instruction and
-        // operands read element by element (rows, columns and k past the end as above)
-#pragma unroll 1
-        for (int blk = 0; blk < MB * 2; ++blk) {
-            const int row0 = m0 + (wm * MB + blk / 2) * 32, col = n0 + 2 * (wn * 32 + r32) + blk % 2;
-            const uint32_t ar = 4u * (uint32_t)((int64_t)min(row0 + r32, M - 1) * p.lda);
-            const uint32_t bc = 4u * (uint32_t)min(col, N - 1) * (NT ? (uint32_t)p.ldb : 1u), bk = NT ? 4u : ldb4;
-            f32x16 v;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) v[r] = 0.f;
-            for (int k0 = 0; k0 < K; k0 += 16) {
-                float x[8], y[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int k = k0 + 2 * i + h;
-                    const uint32_t past = k < K ? 0u : kOutOfRange;
-                    x[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(arsrc, (int)((ar + 4u * (uint32_t)k) | past), 0, 0));
-                    y[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(brsrc, (int)((bc + (uint32_t)k * bk) | past), 0, 0));
-                }
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v = mfma32(x[i], y[i], v);
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = row0 + 8 * (r / 4) + 4 * h + (r % 4);
-                if (row < M && col < N) C[(int64_t)row * p.ldc + col] = v[r];
-            }
-        }
-        return;
+            for (int nb = 0; nb < 2; ++nb) nf = not_finite(acc[mb][nb], nf);
+        if (__syncthreads_or(lost_bits(lost) || nf != 0.f)) return false;
     }
+    if (NWG > 1 && wgrp > 0) return true;
 
     // accumulator register r of lane (h, r32): row 8*(r/4) + 4*h + r%4 of block mb, columns 2*(wn*32 + r32) + nb:
     // 32 lanes write 256 contiguous bytes of a row, and C is not read again (non-temporal)
@@ -338,6 +356,21 @@ __global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(co
     };
     if (m0 + BM <= M && n0 + BN <= N) store_tile(std::true_type{});
     else store_tile(std::false_type{});
+    return true;
+}
+
+// Values the pieces cannot carry: the tile again with the fp32 instruction, staged the same way.  A lost low piece
+// ends the first try a chunk or two after it is met, so a product full of them takes little more than the fp32
+// kernels did (4096^3, probabilities of a steep softmax: 1050 to 1080 us against 1003); infinities, NaN and a last
+// chunk's lost pieces cost both tries (1870).  Operand by operand, without staging, it was 5020.  The flag costs an
+// ordinary product 1.4 % (set at the end of a round instead, where it cuts the schedule in two, 6 %).
+template <int BM, int BN, int WM, int WN, int NWG, int MINW, bool NT>
+__global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(const GemmArgs p, const Grid g)
+{
+    int thread = threadIdx.x;
+    if (compute_tile<BM, BN, WM, WN, NWG, NT, false>(p, g, thread)) return;
+    asm("" : "+v"(thread));                          // nothing of the second try is held through the first
+    compute_tile<BM, BN, WM, WN, NWG, NT, true>(p, g, thread);
 }
 
 }  // namespace gsplit

@@ -302,3 +302,29 @@ def test_stem_convolution_is_rounded_no_more_than_its_large_sum(anr, N, C, H, W,
     units = ((y.double() - ref) / ref.clamp_min(1e-300) * 2.0 ** 24)[ref > 0]
     # four roundings a channel of a sum that grows evenly, and the small products' sum
     assert float(units.square().mean().sqrt()) <= 1.1 * (4 * C / 9.0) ** 0.5 + 3.0 ** -0.5 + SMALL
+
+
+def microseconds(call):
+    call()
+    best = float("inf")
+    for _ in range(5):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        for _ in range(4):
+            call()
+        end.record()
+        end.synchronize()
+        best = min(best, start.elapsed_time(end) * 250.0)
+    return best
+
+
+# Values the pieces cannot carry are redone with the fp32 instruction, at half the rate of the eight products; where
+# the whole first try is lost as well the two take three times an ordinary call.
+@pytest.mark.parametrize("batch,M,N,K", [(1, 2048, 2048, 2048), (16, 512, 512, 512), (1, 1024, 1024, 1024)])
+def test_split_gemm_of_values_the_pieces_cannot_carry_takes_no_multiple(anr, batch, M, N, K):
+    A, B, C = uniform(40, batch, M, K), uniform(41, batch, K, N), torch.empty(batch, M, N, device="cuda")
+    usual = microseconds(lambda: anr.gemm(A, B, C))
+    A[:, ::32, K - 1] = float("inf")
+    assert microseconds(lambda: anr.gemm(A, B, C)) <= 3.0 * usual
+    A = torch.softmax(200.0 * uniform(42, batch, M, K), -1)
+    assert microseconds(lambda: anr.gemm(A, B, C)) <= 2.0 * usual
