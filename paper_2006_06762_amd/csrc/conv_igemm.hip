@@ -98,7 +98,9 @@ int split_patch(const ConvArgs& a, const Geom& g, int most, int* wp)
 {
     *wp = (a.OW - 1) * a.stride_w + a.S;
     const int64_t px = (int64_t)g.VR * *wp;
-    if (a.C % 16 != 0 || a.stride_h != 1 || a.stride_w != 1 || px > most || g.x_bytes >= kPastExtent || g.w_bytes >= kPastExtent || g.wpack_bytes >= kPastExtent) return 0;
+    if (a.C % 16 != 0 || a.stride_h != 1 || a.stride_w != 1 || px > most || g.x_bytes >= psplit::kPastExtent || g.w_bytes >= psplit::kPastExtent ||
+        g.wpack_bytes >= psplit::kPastExtent)
+        return 0;
     return px <= 512 ? 512 : 1024;
 }
 

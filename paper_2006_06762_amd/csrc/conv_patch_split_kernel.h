@@ -19,12 +19,14 @@
 // 16 -> 128 11.1 -> 8.5; 28x28 128 -> 128 and 512 -> 128 come out level (37, 121).  Dealing the taps to the
 // waves instead of the blocks (all waves on all blocks, sums meeting in LDS) was slower.
 #pragma once
-#include "conv_fp32_block.h"
 #include "conv_igemm_kernel.h"
+#include "conv_internal.h"
+#include "split_bf16.h"
 
 namespace anr {
 namespace psplit {
 
+constexpr uint32_t kPastExtent = 0x80000000u;       // byte offset beyond any descriptor extent
 constexpr int T = 512;
 constexpr int MB = 7, BM = 32 * MB;
 
@@ -35,12 +37,17 @@ struct Lds {
     // the six lanes that stage one channel's unit rows, and three channels, fall on different banks
     static constexpr int WKQ = BN * 16 + 48, WTAP = (2 * WKQ + 255) / 256 * 256 + 32, WPLANE = 9 * WTAP;
     static constexpr size_t kStaging = 3 * XPLANE + 3 * WPLANE;
-    static constexpr size_t kBytes = kStaging + 2 * BN * sizeof(float);
+    static constexpr size_t kBytes = kStaging + 2 * BN * sizeof(float);                // and the batch norm
+    // the floats themselves: units of four channels in the room of the pieces
+    static constexpr int FTAP = 2 * WTAP;
+    static_assert(4 * WKQ <= FTAP && 9 * FTAP <= 3 * WPLANE && 4 * XKQ <= 3 * XPLANE, "fits the room of the pieces");
     static_assert(kBytes <= 160 * 1024, "LDS");
 };
 
-template <int BN, int CAP, bool PACKED>
-__global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p, const igemm::Geom g, int wp)
+// One tile of a work-group: as bf16 pieces, or PLAIN, with the fp32 instruction.  False if it met a value that the
+// pieces cannot carry: then nothing is stored.
+template <int BN, int CAP, bool PACKED, bool PLAIN>
+__device__ __forceinline__ bool compute_tile(const ConvArgs& p, const igemm::Geom& g, const int wp, const int tid)
 {
     using L = Lds<BN, CAP>;
     constexpr int XKQ = L::XKQ, XPLANE = L::XPLANE, WKQ = L::WKQ, WTAP = L::WTAP, WPLANE = L::WPLANE;
@@ -51,7 +58,7 @@ __global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p
     char* const lw = plds + 3 * XPLANE;
     float* const lbn = reinterpret_cast<float*>(plds + L::kStaging);
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, h = lane >> 5;
     const int wn = wave % NB, mg = wave / NB;
@@ -102,7 +109,7 @@ __global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p
         wstep = 4u * 16 * 9;
     }
     char* const dx = lx + px0 * 16;
-    char* const dw = lw + 3 * wr * WTAP + wk * WKQ + wc * 16;
+    char* const dw = PLAIN ? lw + 3 * wr * L::FTAP + 2 * wk * WKQ + wc * 16 : lw + 3 * wr * WTAP + wk * WKQ + wc * 16;
 
     float rx[PX][2][8], rw[8][3];
     const uint32_t xs1b = 4u * (uint32_t)p.xs[1];
@@ -124,6 +131,24 @@ __global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p
     };
     uint32_t lost = 0;
     auto store_chunk = [&] {
+        if constexpr (PLAIN) {
+            // units of four channels
+#pragma unroll
+            for (int i = 0; i < PX; ++i)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float* const v = rx[i][u / 2] + 4 * (u % 2);
+                    *reinterpret_cast<f32x4*>(dx + u * XKQ + T * 16 * i) = f32x4{v[0], v[1], v[2], v[3]};
+                }
+            if (has_w) {
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        *reinterpret_cast<f32x4*>(dw + t * L::FTAP + u * WKQ) = f32x4{rw[4 * u][t], rw[4 * u + 1][t], rw[4 * u + 2][t], rw[4 * u + 3][t]};
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < PX; ++i)
 #pragma unroll
@@ -200,6 +225,21 @@ __global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p
 #pragma unroll
         for (int t = 0; t < 9; ++t) {
             const char* const xt = lx + ((t / 3) * wp + t % 3) * 16;
+            if constexpr (PLAIN) {
+                // the wave's half h takes the units 2u + h, channel by channel
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const f32x4 wv = *reinterpret_cast<const f32x4*>(wa + t * L::FTAP + 2 * u * WKQ);
+                    f32x4 xv[blocks];
+#pragma unroll
+                    for (int b = 0; b < blocks; ++b) xv[b] = *reinterpret_cast<const f32x4*>(xt + xa[b] + 2 * u * XKQ);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int b = 0; b < blocks; ++b) acc[b][t / 3 % SUMS] = mfma32(wv[e], xv[b][e], acc[b][t / 3 % SUMS]);
+                }
+                continue;
+            }
             u32x4 wv[3], xv[3][blocks];
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
@@ -236,7 +276,7 @@ __global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p
             for (int i = 0; i < SUMS; ++i) low[b][r] += acc[b][i][r];
         nf = not_finite(low[b], nf);
     }
-    const int again = __syncthreads_or(lost_bits(lost) || nf != 0.f);
+    if (!PLAIN && __syncthreads_or(lost_bits(lost) || nf != 0.f)) return false;
 
     // register r of lane (h, r32): channel 8*(r/4) + 4*h + r%4 of the half, pixel r32 of the block
     auto store_block = [&](int mb, f32x16 v, bool runs) {
@@ -262,46 +302,23 @@ __global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p
             }
         }
     };
-    if (again) {
-        // values the split cannot carry: the wave's blocks again with the fp32 instruction
-        if (PACKED) {
-            // out of the pack's order: tap by tap from its images
-#pragma unroll 1
-            for (int mb = BLK * mg; mb < min(BLK * mg + BLK, MB); ++mb) {
-                f32x16 v;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) v[r] = 0.f;
-                const int m = min(m0 + 32 * mb + r32, g.Mtot - 1);
-                const int gr = g.d_ow.div(m), ow = m - gr * p.OW;
-                const int n = g.d_oh.div(gr), oh = gr - n * p.OH;
-                for (int c0 = 0; c0 < p.C; c0 += 2) {
-                    const int c = c0 + h;
-                    const uint32_t wb = 4u * (uint32_t)(((tile_n * (p.C / 8) + c / 8) * BN + 32 * wn + r32) * 76 + c % 8 * 9);
-                    for (int t = 0; t < 9; ++t) {
-                        const int ih = oh * p.stride_h - p.pad_h + t / 3, iw = ow * p.stride_w - p.pad_w + t % 3;
-                        const bool in = ((unsigned)ih < (unsigned)p.H) & ((unsigned)iw < (unsigned)p.W);
-                        const uint32_t xo = in ? 4u * (uint32_t)(n * p.xs[0] + c * p.xs[1] + ih * p.xs[2] + iw) : kPastExtent;
-                        const float x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)xo, 0, 0));
-                        const float w = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wrsrc, (int)(wb + 4u * t), 0, 0));
-                        v = mfma32(w, x, v);
-                    }
-                }
-                store_block(mb, v, false);
-            }
-        } else {
-#pragma unroll 1
-            for (int mb = BLK * mg; mb < min(BLK * mg + BLK, MB); ++mb) {
-                const int m = min(m0 + 32 * mb + r32, g.Mtot - 1);
-                const int gr = g.d_ow.div(m), ow = m - gr * p.OW;
-                const int n = g.d_oh.div(gr), oh = gr - n * p.OH;
-                store_block(mb, conv_block_fp32(p, xrsrc, wrsrc, n, oh, ow, min(co0 + 32 * wn + r32, p.K - 1), 0, 0, p.C), false);
-            }
-        }
-        return;
-    }
 #pragma unroll
     for (int b = 0; b < BLK; ++b)
         if (BLK * mg + b < MB) store_block(BLK * mg + b, low[b], g.vec_store != 0);
+    return true;
+}
+
+// Values the pieces cannot carry: the tile again with the fp32 instruction, staged the same way.  The two tries
+// take 71 us for 56x56, 64 -> 64, batch 16, with such a value in every tile (without 30 to 34; element by element,
+// without staging, 168), and 250 us for 28x28, 256 -> 256 (105; 685).  Ending the first try early, as the GEMM
+// does, costs ordinary values 2 %.
+template <int BN, int CAP, bool PACKED>
+__global__ __launch_bounds__(T, 2) void conv_patch_split_kernel(const ConvArgs p, const igemm::Geom g, int wp)
+{
+    int tid = threadIdx.x;
+    if (compute_tile<BN, CAP, PACKED, false>(p, g, wp, tid)) return;
+    asm("" : "+v"(tid));                             // nothing of the second try is held through the first
+    compute_tile<BN, CAP, PACKED, true>(p, g, wp, tid);
 }
 
 }  // namespace psplit

@@ -328,3 +328,15 @@ def test_split_gemm_of_values_the_pieces_cannot_carry_takes_no_multiple(anr, bat
     assert microseconds(lambda: anr.gemm(A, B, C)) <= 3.0 * usual
     A = torch.softmax(200.0 * uniform(42, batch, M, K), -1)
     assert microseconds(lambda: anr.gemm(A, B, C)) <= 2.0 * usual
+
+
+@pytest.mark.parametrize("C,H,K", [(64, 56, 64), (256, 28, 256)])
+def test_patch_convolution_of_values_the_pieces_cannot_carry_takes_no_multiple(anr, C, H, K):
+    x, w, y = patch_case(anr, 16, C, H, H, K, 1)
+    call = lambda: anr.conv2d(x, w, y, (1, 1), (1, 1), route=anr.ANR_CONV_ROUTE_PATCH)
+    usual = microseconds(call)
+    x[:, 0, ::2] *= 2.0 ** -120
+    assert microseconds(call) <= 3.0 * usual
+    x.uniform_(-1.0, 1.0)
+    w[::8] *= 2.0 ** -120
+    assert microseconds(call) <= 3.0 * usual
