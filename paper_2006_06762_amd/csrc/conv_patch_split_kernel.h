@@ -267,16 +267,16 @@ __device__ __forceinline__ bool compute_tile(const ConvArgs& p, const igemm::Geo
         __syncthreads();
     }
 
-    float nf = 0.f;
+    SumCheck sums;
 #pragma unroll
     for (int b = 0; b < BLK; ++b) {
 #pragma unroll
         for (int r = 0; r < 16; ++r)
 #pragma unroll
             for (int i = 0; i < SUMS; ++i) low[b][r] += acc[b][i][r];
-        nf = not_finite(low[b], nf);
+        if (BLK * mg + b < MB) sums.check(low[b]);
     }
-    if (!PLAIN && __syncthreads_or(lost_bits(lost) || nf != 0.f)) return false;
+    if (!PLAIN && __syncthreads_or(lost_bits(lost) || sums.refused())) return false;
 
     // register r of lane (h, r32): channel 8*(r/4) + 4*h + r%4 of the half, pixel r32 of the block
     auto store_block = [&](int mb, f32x16 v, bool runs) {

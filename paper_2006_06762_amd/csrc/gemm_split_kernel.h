@@ -325,12 +325,12 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
     }
 
     if (!PLAIN) {
-        float nf = 0.f;
+        SumCheck sums;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb) nf = not_finite(acc[mb][nb], nf);
-        if (__syncthreads_or(lost_bits(lost) || nf != 0.f)) return false;
+            for (int nb = 0; nb < 2; ++nb) sums.check(acc[mb][nb]);
+        if (__syncthreads_or(lost_bits(lost) || sums.refused())) return false;
     }
     if (NWG > 1 && wgrp > 0) return true;
 

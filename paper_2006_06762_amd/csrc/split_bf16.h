@@ -14,13 +14,15 @@
 // accumulator for all products and six of them 4.99), sums of 1024 terms of one sign 2.6 units rms against
 // 7.2, of random sign 0.12 against 0.40.  Denormal inputs and results are kept by the instruction (measured).
 //
-// Two kinds of value do not survive the split, and both are detected exactly:
+// Three kinds of value do not survive the split, and all are detected:
 //   - magnitudes below 2^-110, whose last piece needs bits under the smallest bf16 denormal: l is the
 //     difference of floats, so it is exact, and it is representable if and only if its low 16 bits
 //     are zero; `lost` collects them;
 //   - infinities, NaN and magnitudes that round to infinity in bf16: a piece of theirs is infinite or
-//     NaN, so every accumulator they reach is not finite.
-// A work-group that meets either recomputes its tile with the fp32 instruction.
+//     NaN, so every accumulator they reach is not finite;
+//   - sums below 2^-118 other than zero: there the roundings of the small products, at 2^-150, are no longer
+//     small beside that of the result.
+// A work-group that meets one recomputes its tile with the fp32 instruction.
 #pragma once
 #include "anr_device.h"
 
@@ -65,12 +67,24 @@ constexpr int kPieceB[kProducts] = {2, 1, 2, 0, 1, 1, 0, 0};
 
 __device__ __forceinline__ bool lost_bits(uint32_t lost) { return (lost & 0xffffu) != 0; }
 
-// NaN if any accumulator register is infinite or NaN, else zero (added to `s`).
-__device__ __forceinline__ float not_finite(const f32x16& a, float s)
-{
+// The bits that tell whether accumulators can be kept: start from {}, check every one, ask once.
+struct SumCheck {
+    float not_finite = 0.f;                // NaN once a register is infinite or NaN
+    uint32_t smallest = 0xffffffffu;       // smallest magnitude other than zero, as 2 * bits - 1
+
+    __device__ __forceinline__ void check(const f32x16& a)
+    {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s = fmaf(a[r], 0.f, s);
-    return s;
-}
+        for (int r = 0; r < 16; ++r) {
+            not_finite = fmaf(a[r], 0.f, not_finite);
+            smallest = min(smallest, (__builtin_bit_cast(uint32_t, a[r]) << 1) - 1u);
+        }
+    }
+    __device__ __forceinline__ bool refused() const
+    {
+        constexpr uint32_t kSmall = (uint32_t)(127 - 118) << 23;      // 2^-118
+        return not_finite != 0.f || smallest < (kSmall << 1) - 1u;
+    }
+};
 
 }  // namespace anr

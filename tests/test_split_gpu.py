@@ -150,6 +150,19 @@ def test_split_gemm_of_one_sign_is_rounded_once_per_sixteen_terms(anr, variant):
     assert rms <= 1.1 * (n / 9.0) ** 0.5 + SMALL, (rms, n)
 
 
+@pytest.mark.parametrize("variant", VARIANTS)
+def test_split_gemm_results_near_the_smallest_normal(anr, variant):
+    batch, M, N, K = VARIANTS[variant]
+    A, B = few_terms(27, 1, batch, M, K), uniform(29, batch, K, N)
+    A *= 2.0 ** -64
+    B = torch.where(B < 0, B * 0.5 - 1.0, B * 0.5 + 1.0) * 2.0 ** -60       # products of 2^-124 to 2^-122
+    C = torch.empty(batch, M, N, device="cuda")
+    anr.gemm(A, B, C)
+    ref = A.double() @ B.double()
+    units = (C.double() - ref).abs() / ref.abs() * 2.0 ** 24
+    assert float(units.max()) <= 1.0 + SMALL, float(units.max())
+
+
 def conv_reference(x, w, stride, pad, dil=1, groups=1):
     """Convolution and the convolution of the absolute values, in 64 bits, tap by tap."""
     N, C, H, W = x.shape
@@ -319,3 +332,13 @@ def test_patch_convolution_of_values_the_pieces_cannot_carry_takes_no_multiple(a
     x.uniform_(-1.0, 1.0)
     w[::8] *= 2.0 ** -120
     assert microseconds(call) <= 3.0 * usual
+
+
+def test_patch_convolution_results_near_the_smallest_normal(anr):
+    x, _, y = patch_case(anr, 16, 64, 56, 56, 64, 1)
+    x = torch.where(x < 0, x * 0.5 - 1.0, x * 0.5 + 1.0) * 2.0 ** -60
+    w = few_terms(37, 1, 1, 64, 64 * 9).view(64, 64, 3, 3) * 2.0 ** -64
+    anr.conv2d(x, w, y, (1, 1), (1, 1), route=anr.ANR_CONV_ROUTE_PATCH)
+    ref = conv_reference(x, w, 1, 1)[0]
+    units = ((y.double() - ref).abs() / ref.abs() * 2.0 ** 24)[ref != 0]
+    assert float(units.max()) <= 1.0 + SMALL, float(units.max())
