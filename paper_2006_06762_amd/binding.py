@@ -353,7 +353,11 @@ def dwconv(x, w, y, stride=(1, 1), pad=(0, 0), dil=(1, 1)):
 
 def _tbg_desc(q, k, out):
     B, S, H, D = q.shape
-    return _pack_tbg(B, S, H, D, *_conv_strides(q), *_conv_strides(k), *_conv_strides(out))
+    strides = _conv_strides(q), _conv_strides(k), _conv_strides(out)
+    try:
+        return _pack_tbg(B, S, H, D, *strides[0], *strides[1], *strides[2])
+    except struct.error:        # numbers beyond the fields' range: as the structure takes them
+        return bytes(TbgDesc(B, S, H, D, *strides))
 
 
 def tbg(q, k, out):

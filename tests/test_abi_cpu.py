@@ -436,3 +436,11 @@ def test_conv_route_validation():
     assert B.raw().anr_conv2d_route(ctypes.byref(d), None) == B.ANR_ERR_NULL
     d.stride_h = 0
     assert B.raw().anr_conv2d_route(ctypes.byref(d), ctypes.byref(r)) == B.ANR_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("fn", ["anr_tbg", "anr_tbs"])
+def test_tbg_sizes_beyond_the_descriptor_are_refused_by_the_library(fn):
+    import torch
+    q = torch.empty((2 ** 31, 1, 1, 4), device="meta")
+    d = B.TbgDesc.from_buffer_copy(B._tbg_desc(q, q, torch.empty((2 ** 31, 1, 1, 1), device="meta")))
+    assert getattr(B.raw(), fn)(ctypes.byref(d), DUMMY, DUMMY, DUMMY, None, 0, None) == B.ANR_ERR_INVALID_ARG
