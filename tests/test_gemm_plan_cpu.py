@@ -45,3 +45,5 @@ int main(int, char** v)
     choose = lambda shape: tuple(map(int, subprocess.check_output([str(tmp_path / "choose"), *map(str, shape)]).split()))
     for variant, shape in torch_tests.VARIANTS.items():
         assert choose(shape) == (*variant, len(torch_tests.VARIANTS))
+    for variant, (B, S, H, D) in torch_tests.SCORES.items():
+        assert choose((B * H, S, S, D)) == (*variant, len(torch_tests.SCORES)) and D % 4 != 0

@@ -3,8 +3,8 @@
 Values the pieces cannot carry (infinities, NaN, magnitudes that round to infinity in bf16 or lie below
 2^-110) must come out as the fp32 instruction gives them; everything else within the bound of an fp32
 sum.  The bound: K + 2 roundings of 2^-24 relative to the sum of the absolute products (an fp32 sum in any
-order makes K - 1, a product one; the split leaves out less than 2^-25 of a product), plus half the
-smallest denormal per term.
+order makes K - 1, a product one; the split's small products and what it leaves out add less than one), plus half the
+smallest denormal per term.  Tighter bounds for few terms and for sums of one sign stand beside their tests.
 """
 import pytest
 
@@ -37,8 +37,8 @@ def assert_product(C, A, B):
     assert bool((off <= bound).all()), float((off / bound).max())
 
 
-# one shape per tile variant and per remainder: tiles of 256, 128 and 64, one to four wave groups, K below, at and
-# past the 16- and 32-wide steps, single columns and rows past a tile, odd leading dimensions
+# K below, at and past the 16- and 32-wide steps, single columns and rows past a tile, odd leading dimensions (what
+# each variant of tile and wave groups does at its edges: VARIANTS below)
 SHAPES = [(1, 4097, 4095, 129), (1, 2305, 1791, 161), (16, 513, 511, 333), (3, 1009, 1531, 71), (1, 300, 301, 303),
           (1, 33, 47, 1000), (1, 65, 1, 513), (1, 1, 130, 95), (2, 64, 66, 511), (5, 129, 127, 145), (1, 700, 700, 480)]
 
@@ -121,6 +121,53 @@ def few_terms(seed, terms, batch, M, K):
     A = torch.where(A < 0, A * 0.5 - 1.0, A * 0.5 + 1.0)
     A.scatter_(2, uniform(seed + 1, batch, M, K).argsort(2)[:, :, terms:], 0.0)
     return A
+
+
+# the same of the A.B^T form, as (B, S, H, D) of scores that no other kernel takes (D is no multiple of four)
+SCORES = {(128, 1): (4, 512, 12, 33), (128, 2): (2, 397, 8, 515), (64, 1): (4, 292, 8, 65), (64, 2): (2, 300, 8, 257),
+          (64, 4): (1, 300, 8, 257)}
+
+
+@pytest.mark.parametrize("variant", VARIANTS)
+@pytest.mark.parametrize("what", ["plain", "inf", "huge", "tiny", "denormal"])
+def test_split_gemm_variants(anr, variant, what):
+    batch, M, N, K = VARIANTS[variant]
+    A, B = uniform(43, batch, M, K), uniform(44, batch, K, N)
+    if what == "inf":                               # in the last row, column and k of a matrix
+        A[batch // 2, M - 1, K - 1] = float("inf")
+        B[0, K - 1, N - 1] = float("nan")
+    elif what == "huge":
+        A[batch - 1, M // 3, K // 2] = 3.4e38
+        B[:, K // 2] = 0.25
+    elif what == "tiny":                            # in the first chunk of some tiles, in the last of others
+        A[:, ::301, 0] *= 2.0 ** -112
+        A[:, 150::301, K - 1] *= 2.0 ** -130
+    elif what == "denormal":
+        A *= 2.0 ** -130
+    buf = torch.full((batch * M * N + 128,), 7.0, device="cuda")
+    C = buf[64:-64].view(batch, M, N)
+    anr.gemm(A, B, C)
+    assert_product(C, A, B)
+    assert bool((buf[:64] == 7.0).all()) and bool((buf[-64:] == 7.0).all())
+
+
+# ... and scores that the dispatch takes from the tile kernels: heads of 256 and more in whole chunks, parts of one
+# (K below the 32 of a chunk) and a ragged last tile
+@pytest.mark.parametrize("B,S,H,D", [*SCORES.values(), (16, 256, 8, 32), (16, 256, 8, 24), (16, 256, 8, 128), (16, 360, 8, 96)])
+def test_split_scores_variants(anr, B, S, H, D):
+    q, k = uniform(45, B, S, H, D), uniform(46, B, S, H, D)
+    out, soft = torch.empty(2, B, H, S, S, device="cuda")
+    for tiny in (False, True):
+        if tiny:
+            q[:, ::5, :, D - 1] *= 2.0 ** -115
+        anr.tbg(q, k, out)
+        assert_product(out, q.permute(0, 2, 1, 3).contiguous(), k.permute(0, 2, 3, 1).contiguous())
+        # softmax over the same scores: an exponential and a division of a few units, at most 16 additions in a lane
+        # and 6 between lanes, and the exponent, the distance from the row's maximum, rounded as it is subtracted and
+        # as it is scaled to a power of two
+        anr.tbs(q, k, soft)
+        want, below = torch.softmax(out.double(), -1), out.amax(-1, keepdim=True).double() - out.double()
+        assert bool(((soft.double() - want).abs() <= (32 + 2 * below) * 2.0 ** -24 * want + 2.0 ** -148).all())
 
 
 @pytest.mark.parametrize("variant", VARIANTS)
