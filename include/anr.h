@@ -280,7 +280,7 @@ anr_status anr_workspace_size(int op, const void *desc, size_t *bytes);
 enum {
     ANR_CONV_KERNEL_PATCH = 1,     /* 3x3 patch-staging kernel tuned on the ResNet-style layers   */
     ANR_CONV_KERNEL_TAPS = 2,      /* 3x3 / 1x1 gather kernel with compile-time taps              */
-    ANR_CONV_KERNEL_BIGTAPS = 3,   /* 5x5 / 7x7 gather kernel, one channel per chunk              */
+    ANR_CONV_KERNEL_BIGTAPS = 3,   /* 5x5 / 7x7 kernels: one channel per chunk, or the stem kernel  */
     ANR_CONV_KERNEL_GATHER = 4,    /* any-geometry gather kernel                                  */
     ANR_CONV_KERNEL_DIRECT = 5,    /* one thread per output (extents beyond 32-bit offsets)       */
     ANR_CONV_KERNEL_POINTWISE = 6  /* streaming 1x1 kernel for layers with few channels           */

@@ -24,6 +24,9 @@ size_t conv2d_gather_workspace_bytes(const ConvArgs& a);
 // Streaming kernel for pointwise layers with few channels (conv_pointwise_kernel.h); same contract.
 hipError_t launch_conv2d_pointwise(const ConvArgs& a, hipStream_t stream, bool* taken);
 
+// Kernel for images of two or three channels with 7 x 7 kernels (conv_stem.hip); same contract.
+hipError_t launch_conv2d_stem(const ConvArgs& a, hipStream_t stream, bool* taken);
+
 // What a launch would do, for introspection (nothing is launched).
 struct ConvRoute {
     int kernel;          // 1 patch-staging, 2 taps, 3 bigtaps, 4 gather, 5 direct, 6 pointwise stream (the public ANR_CONV_KERNEL_* values)
@@ -33,6 +36,7 @@ struct ConvRoute {
 bool describe_conv2d_igemm(const ConvArgs& a, ConvRoute* r);
 bool describe_conv2d_gather(const ConvArgs& a, ConvRoute* r);
 bool describe_conv2d_pointwise(const ConvArgs& a, ConvRoute* r);
+bool describe_conv2d_stem(const ConvArgs& a, ConvRoute* r);
 void describe_conv2d(const ConvArgs& a, ConvRoute* r);
 
 // Register-sliding 3x3 / stride 1 / pad 1 depthwise kernel; same contract.

@@ -257,6 +257,8 @@ def test_stem_convolution(anr, N, C, H, W, K, R, stride, pad, what):
     elif what == "huge_weight":
         w[K - 1, 0, R - 1, 0] = 3.4e38
         x *= 0.5
+    r = anr.conv2d_route(anr.conv_desc(x.shape, K, R, R, (stride, stride), (pad, pad)))
+    assert (r.kernel, r.tile_m, r.ksplit) == (anr.ANR_CONV_KERNEL_BIGTAPS, 256, 1)
     OH, OW = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
     buf = torch.full((N * K * OH * OW + 128,), 7.0, device="cuda")
     y = buf[64:-64].view(N, K, OH, OW)
@@ -341,6 +343,25 @@ def test_patch_convolution_of_one_sign_is_rounded_nine_times_per_chunk(anr, N, C
     n = 9 * C // 16
     ends = (sum((i + 1) ** 2 for i in range(sums)) / sums ** 2 / 3.0) ** 0.5
     assert float(units.square().mean().sqrt()) <= 1.1 * (n / 9.0) ** 0.5 / sums + ends + SMALL
+
+
+@pytest.mark.parametrize("N,C,H,W,K,R,stride,pad", STEMS)
+def test_stem_convolution_is_rounded_no_more_than_its_large_sum(anr, N, C, H, W, K, R, stride, pad):
+    x, y = uniform(33, N, C, H, W), torch.empty(N, K, (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1, device="cuda")
+    x[: N // 2] = 1.0 + 2.0 ** -8 - 2.0 ** -17          # both small pieces as large as they get
+    for terms in (1, 4):
+        w = few_terms(34, terms, 1, K, C * R * R).view(K, C, R, R)
+        w[: K // 2] *= (1.0 + 2.0 ** -8 - 2.0 ** -17) / w[: K // 2].abs().clamp_min(1.0)
+        anr.conv2d(x, w, y, (stride, stride), (pad, pad))
+        ref, size, _ = conv_reference(x, w, stride, pad)
+        units = ((y.double() - ref).abs() / size.clamp_min(1e-300) * 2.0 ** 24)[size > 0]
+        assert float(units.max()) <= terms + SMALL, (terms, float(units.max()))
+    x, w = uniform(35, N, C, H, W).abs(), uniform(36, K, C, R, R).abs()
+    anr.conv2d(x, w, y, (stride, stride), (pad, pad))
+    ref = conv_reference(x, w, stride, pad)[0]
+    units = ((y.double() - ref) / ref.clamp_min(1e-300) * 2.0 ** 24)[ref > 0]
+    # four roundings a channel of a sum that grows evenly, and the small products' sum
+    assert float(units.square().mean().sqrt()) <= 1.1 * (4 * C / 9.0) ** 0.5 + 3.0 ** -0.5 + SMALL
 
 
 def microseconds(call):
