@@ -14,14 +14,16 @@
 // Kernel rows of a channel are padded to an even number (two units make one matrix instruction): 7 x 7
 // does 8 x 8 / 49 = 1.3 times the products, at twice the fp32 rate.  Bound: half of a work-group's time is
 // staging and stores, which its two barriers a round keep apart from the products.  Batch 16: 224x224x3 -> 64,
-// stride 2, 48.2 -> 46.2 us, stride 1 160 -> 132 us; 96 channels, batch 32 162 -> 132.
+// stride 2, 48.2 -> 46.0 us, stride 1 160 -> 134; 128 channels 87 -> 80, 96 at batch 32 163 -> 133.
 #include <type_traits>
 
-#include "conv_fp32_block.h"
+#include "conv_internal.h"
+#include "split_bf16.h"
 
 namespace anr {
 namespace stem {
 
+constexpr uint32_t kPastExtent = 0x80000000u;       // byte offset beyond any descriptor extent
 constexpr int TP = 16;                  // tile edge, pixels
 constexpr int T = 512;                  // threads of a tile
 constexpr int G = 2;                    // tiles a work-group has in hand
@@ -143,27 +145,45 @@ __global__ __launch_bounds__(T * G) void conv_stem_kernel(const ConvArgs p, cons
     auto tile_of = [&](int i) { return first + (G * i + grp) * g.per_n; };
     load_patch(min(tile_of(0), g.tiles - 1));
     __syncthreads();                                 // the flags are set
+    auto load_weights = [&](int i, uint32_t (&w)[8]) {
+        const int unit = i >> 6, co = co0 + (i & 63), c = unit / D::RP, r = unit - c * D::RP;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const bool ok = (s < R_) & (r < R_) & (c < C) & (co < p.K);
+            w[s] = __builtin_amdgcn_raw_buffer_load_b32(wrsrc, (int)((uint32_t)(4 * ((co * C + c) * R_ * R_ + r * R_ + s)) | (ok ? 0u : kPastExtent)), 0, 0);
+        }
+    };
     {
         uint32_t lost = 0;
+        bool huge = false;
         for (int i = threadIdx.x; i < D::WUNITS * 64; i += T * G) {
-            const int unit = i >> 6, co = co0 + (i & 63), c = unit / D::RP, r = unit - c * D::RP;
-            float w[8];
-#pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                const bool ok = (s < R_) & (r < R_) & (c < C) & (co < p.K);
-                w[s] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wrsrc, (int)((uint32_t)(4 * ((co * C + c) * R_ * R_ + r * R_ + s)) | (ok ? 0u : kPastExtent)), 0, 0));
-            }
+            uint32_t w[8];
+            load_weights(i, w);
             u32x4 s[3];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 uint32_t hh, mm, ll;
-                split2(w[2 * e], w[2 * e + 1], hh, mm, ll, lost);
+                split2(__builtin_bit_cast(float, w[2 * e]), __builtin_bit_cast(float, w[2 * e + 1]), hh, mm, ll, lost);
                 s[0][e] = hh; s[1][e] = mm; s[2][e] = ll;
+                huge |= (w[2 * e] << 1) > 0xfefe0000u || (w[2 * e + 1] << 1) > 0xfefe0000u;      // above the largest bf16
             }
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(lw + q * D::WPLANE + i * 16) = s[q];
         }
-        if (lost_bits(lost)) flag[G] = 1;
+        if (lost_bits(lost) || huge) flag[G] = 1;
+    }
+    // Weights the pieces cannot carry: as floats in their place, the halves of the word in the first two planes
+    __syncthreads();
+    const bool whole_weights = flag[G] == 1;
+    if (whole_weights) {
+        for (int i = threadIdx.x; i < D::WUNITS * 64; i += T * G) {
+            uint32_t w[8];
+            load_weights(i, w);
+            *reinterpret_cast<u32x4*>(lw + i * 16) = u32x4{w[0] >> 16 | (w[1] & 0xffff0000u), w[2] >> 16 | (w[3] & 0xffff0000u),
+                                                           w[4] >> 16 | (w[5] & 0xffff0000u), w[6] >> 16 | (w[7] & 0xffff0000u)};
+            *reinterpret_cast<u32x4*>(lw + D::WPLANE + i * 16) = u32x4{(w[0] & 0xffffu) | w[1] << 16, (w[2] & 0xffffu) | w[3] << 16,
+                                                                       (w[4] & 0xffffu) | w[5] << 16, (w[6] & 0xffffu) | w[7] << 16};
+        }
     }
 
     const int py = 2 * wave + (r32 >> 4), px = r32 & 15;
@@ -224,15 +244,55 @@ __global__ __launch_bounds__(T * G) void conv_stem_kernel(const ConvArgs p, cons
             int n, oh0, ow0;
             origin(t, n, oh0, ow0);
             const int oh = oh0 + py, ow = ow0 + px;
-            const float nf = not_finite(acc[0], not_finite(acc[1], 0.f));
-            if (__any(nf != 0.f) || flag[grp] == t || flag[G] == 1) {
+            SumCheck sums;
+            sums.check(acc[0]);
+            sums.check(acc[1]);
+            if (whole_weights || flag[grp] == t || __any(sums.refused())) {
+                // Values the pieces cannot carry: the wave's block again with the fp32 instruction.  Its half h supplies
+                // the input channels c with c % 2 == h; inputs come straight from memory, a kernel row's in flight at a
+                // time, weights are the sums of their pieces (exact) or the floats themselves.  In every tile that is
+                // 2.3 times an ordinary call (with weights from memory as well 3.8).
+                int l = lane;
+                asm("" : "+v"(l));               // nothing of this is held through the ordinary rounds
+                const int hc = l >> 5;
+                const char* const wbase = lw + (l & 31) * 16;
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
+                const int iw = min(ow, p.OW - 1) * ST - p.pad_w, ih0 = min(oh, p.OH - 1) * ST - p.pad_h;
+                for (int c0 = 0; c0 < C; c0 += 2) {
+                    const int c = min(c0 + hc, C - 1);
+                    const uint32_t past = c0 + hc < C ? 0u : kPastExtent;
+                    const int xc = (int)(n * p.xs[0] + c * p.xs[1]) + iw;
 #pragma unroll 1
-                for (int cb = 0; cb < 2; ++cb) {
-                    const f32x16 v = conv_block_fp32(p, xrsrc, wrsrc, n, min(oh, p.OH - 1), min(ow, p.OW - 1),
-                                                     min(co0 + 32 * cb + r32, p.K - 1), 0, 0, C);
-                    if (cb == 0) acc[0] = v;
-                    else acc[1] = v;
+                    for (int r = 0; r < R_; ++r) {
+                        const uint32_t row = ((unsigned)(ih0 + r) < (unsigned)p.H ? 0u : kPastExtent) | past;
+                        float x[R_];
+#pragma unroll
+                        for (int s = 0; s < R_; ++s) {
+                            const uint32_t ok = (unsigned)(iw + s) < (unsigned)p.W ? row : kPastExtent;
+                            x[s] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)((uint32_t)(4 * (xc + (ih0 + r) * (int)p.xs[2] + s)) | ok), 0, 0));
+                        }
+#pragma unroll
+                        for (int cb = 0; cb < 2; ++cb) {
+                            u32x4 w[3];
+#pragma unroll
+                            for (int q = 0; q < 3; ++q) w[q] = *reinterpret_cast<const u32x4*>(wbase + q * D::WPLANE + ((c * D::RP + r) * 64 + 32 * cb) * 16);
+#pragma unroll
+                            for (int s = 0; s < R_; ++s) {
+                                uint32_t b[3];
+#pragma unroll
+                                for (int q = 0; q < 3; ++q) b[q] = s % 2 ? w[q][s / 2] & 0xffff0000u : w[q][s / 2] << 16;
+                                const float sum = (__builtin_bit_cast(float, b[0]) + __builtin_bit_cast(float, b[1])) + __builtin_bit_cast(float, b[2]);
+                                const float v = whole_weights ? __builtin_bit_cast(float, b[0] | b[1] >> 16) : sum;
+                                acc[cb] = mfma32(v, x[s], acc[cb]);
+                            }
+                        }
+                    }
                 }
+                // once more, so that their registers are free for this
+                load_patch(min(tile_of(i + 1), g.tiles - 1));
             }
             // register r of lane (h, r32): channel 8*(r/4) + 4*h + r%4 of the block, pixel r32
             if (p.gamma) {
@@ -273,10 +333,12 @@ using namespace stem;
 
 // Where it is the faster one: 7 x 7 (5 x 5 pads 25 taps to 48: 11.8 against 12.9 us for 64x64x3 -> 64 at batch
 // 16), two or three channels (with one there is too little to multiply per store: 16.2 against 18.7 us for
-// 112x112x1 -> 64 at batch 32), a channel tile at least three quarters full, and a tile of pixels for every
-// CU (294 tiles 22.9 against 21.9 us, 343 24.0 against 19.8; at batch 1 the 49 tiles of 112 x 112 leave the
-// chip idle, and the reduction split over work-groups takes 8 us).
+// 112x112x1 -> 64 at batch 32), a channel tile at least three quarters full, and of the 512 tiles that the chip
+// has in hand at a time enough that are there: a round takes what the gather kernel does 370 tiles in (stride 2:
+// 256 tiles 21.2 against 17.9 us, 392 27.9 against 27.8, 784 46.2 against 48.2, 1568 80 against 87; stride 1:
+// 3136 132 against 160).
 constexpr int kCUs = 256;
+constexpr int kTilesWorthARound = 380;
 
 bool plan_stem(const ConvArgs& a, Geom* g)
 {
@@ -292,13 +354,15 @@ bool plan_stem(const ConvArgs& a, Geom* g)
     if (4 * a.K < 3 * 64 * tiles_n) return false;
     // (the lane's part of an output offset is 32 bits)
     if (a.ys[1] >= ((int64_t)1 << 27) || a.ys[2] >= ((int64_t)1 << 16) || a.ys[2] * a.OH >= ((int64_t)1 << 30)) return false;
-    if (tiles * tiles_n < kCUs || tiles >= ((int64_t)1 << 30)) return false;
+    if (tiles >= ((int64_t)1 << 30)) return false;
     // half-empty tiles (14 x 14 and smaller maps leave a quarter and more of a tile unused)
     if ((double)a.OH * a.OW < 0.7 * g->tiles_x * g->tiles_y * TP * TP) return false;
     g->tiles = (int)tiles;
     // no more work-groups than CUs: each takes a CU's LDS, one too many would wait for a whole round
     g->per_n = tiles_n < kCUs ? kCUs / tiles_n : 1;
     if (g->per_n > g->tiles) g->per_n = g->tiles;
+    const int64_t rounds = (tiles + G * g->per_n - 1) / (G * g->per_n);
+    if (tiles * tiles_n < rounds * kTilesWorthARound) return false;
     g->x_bytes = (uint32_t)(4 * x_extent);
     g->w_bytes = (uint32_t)(4 * w_extent);
     g->d_x = make_fastdiv(g->tiles_x);
