@@ -34,6 +34,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_MFMA_F32_TFLOPS = 157.3      # 256 CU x 2.4 GHz x 256 flop/clk/CU
+PEAK_MFMA_BF16_TFLOPS = 2500.0
+SPLIT_PRODUCTS = 8                # bf16 products per fp32 product, in the operators that run on the bf16 pipes:
+SPLIT_OPS = ("C2D", "ConvLayer", "C2D_packed", "ConvLayer_packed")
 PEAK_HBM_GBS = 8000.0
 METRIC = "achieved TFLOP/s and % of fp32 MFMA peak per operator; DEP HBM GB/s"
 # the paper's own headline figures, printed beside the throughput as context (other hardware,
@@ -525,6 +528,9 @@ def main():
         rec["frac_mfma_peak_warm"] = rec["tflops_warm"] / PEAK_MFMA_F32_TFLOPS
         rec["frac_mfma_peak_cold"] = rec["tflops_cold"] / PEAK_MFMA_F32_TFLOPS
         rec["frac_hbm_peak_cold"] = rec["gbs_cold"] / PEAK_HBM_GBS
+        # share of the matrix pipes that the operator's kernel uses
+        rec["frac_pipe_peak_cold"] = (SPLIT_PRODUCTS * rec["tflops_cold"] / PEAK_MFMA_BF16_TFLOPS if n in SPLIT_OPS
+                                      else rec["frac_mfma_peak_cold"])
         rec["in_step"] = n in names
         per_op.append(rec)
 
