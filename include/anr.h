@@ -5,9 +5,11 @@
  * arXiv 2006.06762 ("Ansor"): GMM, C2D and DEP of the single-operator
  * benchmark (Sec. 7.1, shapes in Appendix C) and the ConvLayer and TBS
  * subgraphs (Sec. 7.2).  All arithmetic is fp32 in, fp32 accumulate, fp32 out
- * (Sec. 7: float32 is used for all evaluations); large products multiply each
- * float as the exact sum of three bf16 numbers, with results no further from the
- * exact ones than fp32 products give.
+ * (Sec. 7: float32 is used for all evaluations).  Large products multiply each
+ * float as the exact sum of three bf16 numbers: of the nine products of the
+ * pieces only the smallest, below 2^-34 of the product, is left out.  A result of
+ * one term is then at most 1.06 x 2^-24 of it off (an fp32 product 1.00), one of n
+ * terms at most (n + 0.06) x 2^-24 of the sum of their magnitudes.
  *
  * Conventions common to every call
  *   - Every tensor pointer is DEVICE memory owned by the caller.  The library

@@ -123,6 +123,7 @@ hipError_t launch_igemm_plan(const ConvArgs& a, const IgemmPlan& p, hipStream_t 
     int wp = 0;
     switch (p.variant) {
         case 0:
+            // (left to the fp32 forms: channel counts of 8 mod 16, wider patches, offsets beyond 31 bits)
             if (split_patch(a, g, 512, &wp)) return launch_patch_split<64, 512>(a, g, wp, stream);
             if (try_fixed<V224x64, 3, 64, 384, 3>(a, g, lds, stream, &err)) return err;     // 56x56 maps, stride 1
             return V224x64::launch(a, g, lds, stream);
