@@ -19,7 +19,7 @@
 // Bound: large products by the matrix pipes' power (eight bf16 products per fp32 one at 181 TFLOP/s are
 // 1.45 PFLOP/s, what a large bf16 product of the library reaches on the card is 1.3); work-groups alone on their
 // CU by the chain load - split - LDS - multiply.  Measured against the fp32 kernels this one took over from:
-// 4096^3 976 -> 765-889 us (by box), 2048^3 133 -> 113, 1024^3 x16 257 -> 204, 512^3 x16 38.6 -> 33.3,
+// 4096^3 976 -> 765-889 us (by card), 2048^3 133 -> 113, 1024^3 x16 257 -> 204, 512^3 x16 38.6 -> 33.3,
 // 1009 x 1531 x 771 x3 (4-byte aligned rows) 167 -> 70, 1024^3 22.7 -> 22.4.  Tried and dropped: the split
 // between the matrix instructions, v_dot2 for its subtractions, wave groups in opposite order (all slower);
 // 256 x 256 tiles, which leave no registers for the second set of sums (six products in one set, 4096^3 in
