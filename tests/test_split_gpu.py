@@ -63,6 +63,18 @@ def test_split_gemm_strided_unaligned_views(anr, M, N, K):
     assert bool((C[:, 0] == 7.0).all()) and bool((C[:, N + 1:] == 7.0).all())
 
 
+# a packed column is a row of the A.B^T form, a strided one is not; K below a chunk, around the plain kernel's range
+@pytest.mark.parametrize("M,K", [(65, 1), (130, 31), (65, 100), (700, 160), (40000, 24), (300, 161), (70, 513)])
+@pytest.mark.parametrize("batch", [1, 3])
+@pytest.mark.parametrize("ldb,ldc", [(1, 1), (3, 1), (1, 4)])
+def test_gemm_of_a_single_column(anr, batch, M, K, ldb, ldc):
+    A, B = uniform(50, batch, M, K), uniform(51, batch, K, ldb)[:, :, :1]
+    C = torch.full((batch, M, ldc), 7.0, device="cuda")
+    anr.gemm(A, B, C[:, :, :1])
+    assert_product(C[:, :, :1], A, B.contiguous())
+    assert bool((C[:, :, 1:] == 7.0).all())
+
+
 @pytest.mark.parametrize("M,N,K", [(300, 260, 333), (700, 700, 545), (2100, 1900, 200)])
 @pytest.mark.parametrize("what", ["inf", "nan", "huge", "overflow", "denormal", "tiny", "past_k"])
 def test_split_gemm_values_the_pieces_cannot_carry(anr, M, N, K, what):
