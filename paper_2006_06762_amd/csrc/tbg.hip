@@ -46,6 +46,25 @@ hipError_t launch_tbs_by_d(const tbg::Args& t, int batch, int vec_store, hipStre
     return launch_tbs_rows32<(rows * 16 + 255) / 256, KB>(t, batch, vec_store, stream);
 }
 
+template <int KW, int KBW>
+hipError_t launch_tbs_long(const tbg::Args& t0, int batch, int vec_store, hipStream_t stream)
+{
+    tbg::Args t = t0;
+    t.tiles_i = (t.S + 31) / 32;
+    const int64_t items = (int64_t)batch * t.tiles_i;
+    t.xcd_chunk = (items % 8 == 0) ? (int)(items / 8) : 0;
+    t.d_tiles_i = make_fastdiv(t.tiles_i);
+    t.d_h = make_fastdiv(t.H);
+    const size_t lds_bytes = sizeof(float) * tbg::long_lds_floats<KW>(t.D);
+    auto kern = tbg::tbs_long_kernel<KW, KBW>;
+    if (lds_bytes > 48 * 1024) {
+        static LdsLimit granted;
+        hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_bytes, granted);
+        if (e != hipSuccess) return e;
+    }
+    return launch_kernel(kern, dim3((unsigned)items), dim3(64 * KW), lds_bytes, stream, t, vec_store);
+}
+
 }  // namespace
 
 hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
@@ -70,6 +89,18 @@ hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
     const bool split = a.M > tbg::kMaxKeys && !fused && offsets32 && tiles128 * tiles128 * a.batch >= 512 &&
                        (double)a.M * a.M >= 0.6 * tiles128 * tiles128 * 128 * 128 && (double)a.M * a.M * a.batch >= 384.0 * 128 * 128 &&
                        (a.K >= 48 || a.M % tbg::kTile == 0) && !(whole && a.K <= tbg::kChunk);
+    // What is left with a softmax and up to 512 keys: one kernel that keeps the scores on the chip (16 x 16 heads, two
+    // kernels / one: 160 x 160 x 64 52 / 29 us, 256 x 256 x 64 71 / 39, 481 x 481 x 32 203 / 128, 512 x 512 x 64 209 /
+    // 152).  The split GEMM keeps its sizes: its scores are the closer ones, and those tbg gives for them.  A
+    // work-group walks the keys in a row, so with few work-groups and a long walk the two kernels are faster (8 heads of
+    // 300 x 300 x 128 11.1 / 16.1, x 64 9.8 / 10.4, x 32 9.7 / 8.5; 12 heads of 492 x 492 x 128 19.4 / 21.9, 16 of 400 x
+    // 400 x 128 23.8 / 21.0), and so they
+    // are for wide heads with a third of the last keys missing (64 of 300 x 300 x 128 39.0 / 41.7).
+    const int64_t long_items = (int64_t)a.batch * ((a.M + 31) / 32);
+    const int long_chunks = (a.M + 127) / 128;
+    const bool long_pays = (long_items > (a.K > 96 ? 200 : 160) || long_chunks * a.K <= 128) && !(a.K > 96 && long_chunks == 3 && long_items < 1024);
+    const bool rows_long = long_pays && !split && a.softmax_rows && a.M > tbg::kMaxKeys && a.M <= tbg::kLongKeys &&
+                           a.K <= tbg::kLongD && (a.K % 8 == 0) && offsets32;
     if (!fast || split || blocks >= ((int64_t)1 << 31)) {
         GemmArgs g = a;
         return launch_gemm(g, stream);
@@ -88,6 +119,15 @@ hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
         if (a.M <= 32) return launch_tbs_by_d<1>(t, a.batch, vec_store, stream);
         if (a.M <= 64) return launch_tbs_by_d<2>(t, a.batch, vec_store, stream);
         return launch_tbs_by_d<4>(t, a.batch, vec_store, stream);
+    }
+    if (rows_long) {
+        // 1: rows of 16-byte units, 2: and every store a whole line (see stg4_nt)
+        const bool units = is_aligned16(a.C) && (a.ldc % 4 == 0) && (a.sCo % 4 == 0) && (a.sCi % 4 == 0);
+        const bool lines = units && (reinterpret_cast<uintptr_t>(a.C) & 127) == 0 && (a.ldc % 32 == 0) && (a.sCo % 32 == 0) && (a.sCi % 32 == 0);
+        const int vec_store = lines ? 2 : units ? 1 : 0;
+        if (t.S <= 256) return launch_tbs_long<4, 2>(t, a.batch, vec_store, stream);
+        if (t.S <= 384) return launch_tbs_long<4, 3>(t, a.batch, vec_store, stream);
+        return launch_tbs_long<4, 4>(t, a.batch, vec_store, stream);
     }
     t.d_tiles_j = make_fastdiv(t.tiles_j);
     t.d_tiles_i = make_fastdiv(t.tiles_i);

@@ -473,5 +473,216 @@ __global__ __launch_bounds__(256) void tbs_rows32_kernel(const Args p, int ld, i
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// Full TBS for 128 < S <= 512: scores, softmax and probabilities in one launch, so that the
+// scores never go to memory (as two kernels they are written, read and written again).
+//
+// Work-group = 32 queries x all keys of one (b, h), KW waves; KBW chunks of 32 * KW keys, of which a wave
+// owns one block of 32 keys each.  As above a wave computes the transposed block, so a lane holds 16
+// keys of one query per chunk and a softmax row reduces inside the lane, across the two half-waves
+// and, through LDS, across the waves.  q sits in LDS whole, the key chunks pass through it 64
+// columns at a time with the next one waiting in registers.
+//
+// A block of scores adds up four accumulators per 32 columns (chains of four instructions; relative error of the
+// probabilities, D = 64 / 80 / 128: 3.9e-7 / 4.1e-7 / 4.7e-7, the 64 x 64 tile kernels 10e-7 for D = 64; per 64 columns
+// 3 % faster, 4.4e-7 / 4.5e-7 / 5.0e-7).
+//
+// Bound: bringing the keys to every work-group's LDS.  16 x 16 heads of 512 x 512 x 64: 148 us, 110 of them
+// without the products, 108 without the stores; the 268 MB of probabilities alone take 40.  Two query blocks
+// per work-group halve that traffic but leave one work-group per CU, whose phases then overlap with nothing: the
+// same time.  Eight waves with half the scores each need more registers than 128 per lane.
+//
+// Probabilities go out through a private corner of LDS per wave: 32 keys of a query are a run of 128 bytes,
+// written two (4-byte stores) or eight (16-byte stores, rows that are aligned) at a time, without a barrier.
+constexpr int kLongKeys = 512;
+constexpr int kLongD = 256;
+
+template <int KW>
+constexpr size_t long_lds_floats(int D)
+{
+    return 32 * KW * (size_t)kLds + 32 * (size_t)(D + 4);
+}
+
+template <int KW, int KBW>
+__global__ __launch_bounds__(64 * KW, 2) void tbs_long_kernel(const Args p, int vec_store)
+{
+    constexpr int T = 64 * KW, KEYS = 32 * KW, UK = KEYS * 16 / T, ROWS = T / 16;      // staging units of a thread, rows they step over
+    extern __shared__ __attribute__((aligned(16))) float panel[];
+    __shared__ float red[2][KW][32];
+    const int ldq = p.D + 4;
+    float* const ks = panel;                       // a chunk of keys x 64 columns
+    float* const qs = panel + KEYS * kLds;          // the queries, all columns
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // key block of a chunk
+    const int r32 = lane & 31, h2 = lane >> 5;
+    // every XCD gets a contiguous range of items: the query blocks of a head share its keys in one L2
+    int item = blockIdx.x;
+    if (p.xcd_chunk > 0) item = (item & 7) * p.xcd_chunk + (item >> 3);
+    const int bh = p.d_tiles_i.div(item), ti = item - bh * p.tiles_i;
+    const int b = p.d_h.div(bh), hh = bh - b * p.H;
+    const int i0 = ti * 32;
+
+    const float* __restrict__ qb = p.q + b * p.qs_b + hh * p.qs_h;
+    const float* __restrict__ kb = p.k + b * p.ks_b + hh * p.ks_h;
+    const int ks_s = (int)p.ks_s;
+
+    const int krow = tid >> 4, kcol = (tid & 15) * 4;
+    const float* rowp[UK];
+    auto key_rows = [&](int kc) {                  // keys past S repeat the last one and are masked
+#pragma unroll
+        for (int u = 0; u < UK; ++u) {
+            const int key = KEYS * kc + krow + ROWS * u;
+            rowp[u] = kb + (key < p.S ? key : p.S - 1) * ks_s;
+        }
+    };
+    f32x4 rg[UK];
+    auto load_chunk = [&](int d0) {                // columns past D repeat the last four and are not read
+        const int col = d0 + kcol < p.D ? d0 + kcol : p.D - 4;
+#pragma unroll
+        for (int u = 0; u < UK; ++u) rg[u] = ldg4(rowp[u] + col);
+    };
+    key_rows(0);
+    load_chunk(0);
+    {
+        const int dq = p.D >> 2;
+        for (int u = tid; u < 32 * dq; u += T) {
+            const int row = u / dq, col = 4 * (u - row * dq);
+            const int i = i0 + row < p.S ? i0 + row : p.S - 1;
+            *reinterpret_cast<f32x4*>(&qs[row * ldq + col]) = ldg4(qb + i * p.qs_s + col);
+        }
+    }
+
+    const float* const arow = ks + (32 * wave + r32) * kLds + 4 * h2;
+    const float* const brow = qs + r32 * ldq + 4 * h2;
+    f32x16 sc[KBW];
+#pragma unroll
+    for (int kc = 0; kc < KBW; ++kc) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sc[kc][r] = 0.f;
+        const bool any = KEYS * kc + 32 * wave < p.S;             // uniform over the wave
+#pragma unroll 1
+        for (int d0 = 0; d0 < p.D; d0 += kChunk) {
+            __syncthreads();                                     // the chunk before is consumed
+#pragma unroll
+            for (int u = 0; u < UK; ++u) *reinterpret_cast<f32x4*>(&ks[(krow + ROWS * u) * kLds + kcol]) = rg[u];
+            __syncthreads();
+            if (d0 + kChunk < p.D) {
+                load_chunk(d0 + kChunk);
+            } else if (kc + 1 < KBW) {
+                key_rows(kc + 1);
+                load_chunk(0);
+            }
+            __builtin_amdgcn_sched_barrier(0);                   // the loads stay ahead of the products
+            if (any) {
+                auto part = [&](int d1, int steps_c) {
+                    f32x16 acc[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[e][r] = 0.f;
+                    auto step = [&](int d) {
+                        const f32x4 a = *reinterpret_cast<const f32x4*>(arow + d);
+                        const f32x4 bq = *reinterpret_cast<const f32x4*>(brow + d0 + d);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[e] = mfma32(a[e], bq[e], acc[e]);
+                    };
+                    if (steps_c == 4) {
+#pragma unroll
+                        for (int d = 0; d < 32; d += 8) step(d1 + d);
+                    } else {
+                        for (int d = 0; d < 8 * steps_c; d += 8) step(d1 + d);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sc[kc][r] += (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]);
+                };
+                const int left = (p.D - d0) / 8;                 // D is a multiple of 8
+#pragma unroll
+                for (int d1 = 0; d1 < kChunk; d1 += 32) {
+                    if (left >= d1 / 8 + 4) part(d1, 4);
+                    else if (left > d1 / 8) part(d1, left - d1 / 8);
+                }
+            }
+        }
+    }
+
+    // register r of lane (h2, r32), chunk kc: key KEYS*kc + 32*wave + 8*(r/4) + 4*h2 + r%4, query i0 + r32
+    const int key0 = 32 * wave + 4 * h2;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kc = 0; kc < KBW; ++kc)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            if (kc == KBW - 1) sc[kc][r] = KEYS * kc + key0 + 8 * (r / 4) + (r % 4) < p.S ? sc[kc][r] : -INFINITY;
+            mx = fmaxf(mx, sc[kc][r]);
+        }
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    if (h2 == 0) red[0][wave][r32] = mx;
+    __syncthreads();
+    mx = red[0][0][r32];
+#pragma unroll
+    for (int w = 1; w < KW; ++w) mx = fmaxf(mx, red[0][w][r32]);
+    constexpr float kLog2e = 1.44269504088896340736f;
+    float sum = 0.f;
+#pragma unroll
+    for (int kc = 0; kc < KBW; ++kc) {
+        float part = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            sc[kc][r] = __builtin_amdgcn_exp2f((sc[kc][r] - mx) * kLog2e);      // 2^(-inf) = 0 for masked keys
+            part += sc[kc][r];
+        }
+        sum += part;
+    }
+    sum += __shfl_xor(sum, 32);
+    if (h2 == 0) red[1][wave][r32] = sum;
+    __syncthreads();
+    sum = red[1][0][r32];
+#pragma unroll
+    for (int w = 1; w < KW; ++w) sum += red[1][w][r32];
+    const float inv = 1.0f / sum;
+
+    // every wave is done with ks and qs: each takes 32 rows of 36 floats of them
+    float* const ps = panel + wave * (32 * 36);
+    float* __restrict__ ob = p.out + b * p.os_b + hh * p.os_h;
+#pragma unroll
+    for (int kc = 0; kc < KBW; ++kc) {
+        const int k0 = KEYS * kc + 32 * wave;
+        if (kc == KBW - 1 && k0 >= p.S) break;                   // uniform over the wave
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 v = {sc[kc][4 * g] * inv, sc[kc][4 * g + 1] * inv, sc[kc][4 * g + 2] * inv, sc[kc][4 * g + 3] * inv};
+            *reinterpret_cast<f32x4*>(&ps[r32 * 36 + 8 * g + 4 * h2]) = v;
+        }
+        // the region is the wave's own and its LDS accesses run in order; the fences only hold the compiler
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (vec_store && k0 + 32 <= p.S) {
+            const int col = 4 * (lane & 7);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = 8 * i + (lane >> 3);
+                const f32x4 v = *reinterpret_cast<const f32x4*>(&ps[row * 36 + col]);
+                if (i0 + row < p.S) {
+                    float* const o = ob + (i0 + row) * p.os_i + k0 + col;
+                    if (vec_store == 2) stg4_nt(o, v);
+                    else stg4(o, v);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int row = 2 * i + h2;
+                const float v = ps[row * 36 + r32];
+                if (i0 + row < p.S && k0 + r32 < p.S) ob[(i0 + row) * p.os_i + k0 + r32] = v;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
+
 }  // namespace tbg
 }  // namespace anr
