@@ -112,6 +112,68 @@ hipError_t launch_small_planes(const ConvArgs& a, hipStream_t stream, bool* take
     return launch_kernel(dw::dwconv_small_planes_kernel<0, 0>, grid, dim3(256), (size_t)lds_floats * 4, stream, a, g);
 }
 
+// Bands of rows or groups of planes: see dwconv_band_kernel.
+template <int K_, int ST>
+hipError_t launch_bands_as(const ConvArgs& a, hipStream_t stream, bool* taken)
+{
+    const int64_t planes = (int64_t)a.N * a.C;
+    const int64_t wl = (int64_t)(a.OW - 1) * ST + K_, x_plane = (int64_t)(a.H - 1) * a.xs[2] + a.W;
+    auto rows_in = [&](int rows) { return (int64_t)(rows - 1) * ST + K_; };
+    constexpr int64_t kRoom = 7 * 1024;                      // floats: five work-groups per CU
+    if (planes >= ((int64_t)1 << 30) || x_plane >= ((int64_t)1 << 28) || a.xs[2] >= ((int64_t)1 << 28) ||
+        wl * rows_in(dw::kBandRows) > 2 * kRoom || a.OH > (1 << 20))
+        return hipSuccess;
+    // One thread per output needs no second trip (load, LDS, weights, store): below some four million products it is
+    // the faster one (335 planes of 58 x 58, stride 2, 5.2 against 5.7 us; 408 of 29 x 29 5.1 against 5.9; 636 of 77 x
+    // 77, stride 2, 11.4 against 7.8).
+    if (planes * a.OH * a.OW * (K_ * K_) < 4000000) return hipSuccess;
+    dw::Band g{};
+    // the fewest bands that fit, and smaller ones until the chip has four work-groups per CU
+    int bands = 1;
+    auto rows_of = [&](int b) { return ((a.OH + b - 1) / b + dw::kBandRows - 1) / dw::kBandRows * dw::kBandRows; };
+    while (rows_of(bands) > dw::kBandRows &&
+           (wl * rows_in(rows_of(bands)) > kRoom || planes * ((a.OH + rows_of(bands) - 1) / rows_of(bands)) < 1024))
+        ++bands;
+    g.rows = rows_of(bands);
+    g.bands = (a.OH + g.rows - 1) / g.rows;
+    g.strips = g.rows / dw::kBandRows;
+    g.wl = (int)wl;
+    g.rows_in = (int)rows_in(g.rows);
+    g.per_plane = g.rows_in * g.wl;
+    g.planes = (int)planes;
+    g.G = 1;
+    const bool dense = a.xs[1] == a.xs[2] * a.H && a.xs[0] == a.xs[1] * a.C;
+    if (g.bands == 1 && dense) {
+        // whole planes: as many as fill the threads twice, while they leave four work-groups per CU
+        const int per = g.strips * a.OW;
+        g.G = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(512 / per, kRoom / g.per_plane), planes / 1024));
+        if ((g.G - 1) * a.xs[1] + x_plane >= ((int64_t)1 << 28)) g.G = 1;
+    }
+    g.x_bytes = (uint32_t)(4 * ((g.G - 1) * (g.G > 1 ? a.xs[1] : 0) + x_plane));
+    const int64_t groups = (planes + g.G - 1) / g.G;
+    if (groups * g.bands >= ((int64_t)1 << 31)) return hipSuccess;
+    g.d_bands = make_fastdiv(g.bands);
+    g.d_wl = make_fastdiv(g.wl);
+    g.d_plane = make_fastdiv(g.per_plane);
+    g.d_ow = make_fastdiv(a.OW);
+    g.d_strips = make_fastdiv(g.strips);
+    g.d_c = make_fastdiv(a.C);
+    *taken = true;
+    return launch_kernel(dw::dwconv_band_kernel<K_, ST>, dim3((unsigned)(groups * g.bands)), dim3(256),
+                         sizeof(float) * (size_t)g.G * g.per_plane, stream, a, g);
+}
+
+hipError_t launch_bands(const ConvArgs& a, hipStream_t stream, bool* taken)
+{
+    *taken = false;
+    if (a.R != a.S || a.dil_h != 1 || a.dil_w != 1 || a.stride_h != a.stride_w) return hipSuccess;
+    if (a.R == 3 && a.stride_h == 1) return launch_bands_as<3, 1>(a, stream, taken);
+    if (a.R == 3 && a.stride_h == 2) return launch_bands_as<3, 2>(a, stream, taken);
+    if (a.R == 5 && a.stride_h == 1) return launch_bands_as<5, 1>(a, stream, taken);
+    if (a.R == 5 && a.stride_h == 2) return launch_bands_as<5, 2>(a, stream, taken);
+    return hipSuccess;
+}
+
 }  // namespace
 
 hipError_t launch_dwconv3x3(const ConvArgs& a, hipStream_t stream, bool* taken)
@@ -158,6 +220,8 @@ hipError_t launch_dwconv(const ConvArgs& a, hipStream_t stream)
     hipError_t err = launch_dwconv3x3(a, stream, &taken);
     if (taken || err != hipSuccess) return err;
     err = launch_small_planes(a, stream, &taken);
+    if (taken || err != hipSuccess) return err;
+    err = launch_bands(a, stream, &taken);
     if (taken || err != hipSuccess) return err;
     return launch_dwconv_direct(a, stream);
 }

@@ -375,5 +375,101 @@ __global__ __launch_bounds__(256) void dwconv_small_planes_kernel(const ConvArgs
     }
 }
 
+// Bands of rows (3 x 3 and 5 x 5, stride 1 and 2, any width, padding, alignment and row stride): the shapes the
+// kernels above leave, formerly one thread per output with R * S loads each.  A work-group takes a band of one plane's
+// output rows (or G whole planes), brings the input rows they need to LDS with their padding as zeros, every element
+// once and by consecutive lanes, and a thread walks down kBandRows outputs of one column, so that an output costs
+// S + (R - stride) * S / kBandRows LDS reads.  The taps of an output are added in the order of the direct kernel
+// (same bits).  Bound: memory for 3 x 3, LDS reads for 5 x 5.  One thread per output / this: 141 x 141 x 104, batch
+// 32, 564 / 150 us; 115 x 115 x 343, batch 16, 616 / 156 (3.7 TB/s); 95 x 95 x 304, stride 2, batch 32, 228 / 106;
+// 68 x 68 x 924, 5 x 5, batch 16, 1094 / 175.
+constexpr int kBandRows = 8;          // outputs of a thread's walk
+
+struct Band {
+    int G;                  // planes per work-group (bands == 1 if more than one)
+    int bands, rows;        // bands per plane, output rows of a band (a multiple of kBandRows)
+    int strips;             // rows / kBandRows
+    int wl, per_plane;      // LDS row and plane, floats
+    int rows_in;            // input rows of a band that reach its last output row
+    int planes;             // N * C
+    uint32_t x_bytes;       // what a work-group's loads may reach from its first plane
+    FastDiv d_bands, d_wl, d_plane, d_ow, d_strips, d_c;
+};
+
+template <int K_, int ST>
+__global__ __launch_bounds__(256) void dwconv_band_kernel(const ConvArgs p, const Band g)
+{
+    extern __shared__ __attribute__((aligned(16))) float dlds[];
+    constexpr int U = 8;                                     // loads in flight per thread
+    const int tid = threadIdx.x;
+    const int item = blockIdx.x;
+    const int first = g.d_bands.div(item), band = item - first * g.bands;
+    const int plane0 = first * g.G;
+    const int nplanes = min(g.G, g.planes - plane0);
+    const int n0 = g.d_c.div(plane0), c0 = plane0 - n0 * p.C;
+    const int oh0 = band * g.rows;
+    const float* const xp = p.x + n0 * p.xs[0] + c0 * p.xs[1];
+    const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xp), 0, (int)g.x_bytes, 0x00020000);
+
+    const int count = nplanes * g.per_plane;
+    const int row0 = oh0 * ST - p.pad_h;
+    const int xs1 = (int)p.xs[1], xs2 = (int)p.xs[2];
+    for (int base = tid; base < count; base += 256 * U) {
+        float v[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int u = base + 256 * i;
+            const int pl = g.G > 1 ? g.d_plane.div(u) : 0;
+            const int e = u - pl * g.per_plane;
+            const int r = g.d_wl.div(e);
+            const int ih = row0 + r, iw = e - r * g.wl - p.pad_w;
+            const bool in = (u < count) & ((unsigned)ih < (unsigned)p.H) & ((unsigned)iw < (unsigned)p.W);
+            const uint32_t off = in ? 4u * (uint32_t)(pl * xs1 + ih * xs2 + iw) : 0x80000000u;
+            v[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)off, 0, 0));
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            if (base + 256 * i < count) dlds[base + 256 * i] = v[i];
+    }
+    __syncthreads();
+
+    const int units = nplanes * g.strips * p.OW;
+    for (int u = tid; u < units; u += 256) {
+        const int v = g.d_ow.div(u), ow = u - v * p.OW;
+        const int pl = g.G > 1 ? g.d_strips.div(v) : 0;
+        const int oh = (v - pl * g.strips) * kBandRows;      // in the band
+        const int plane = plane0 + pl;
+        const int n = g.G > 1 ? g.d_c.div(plane) : n0, c = g.G > 1 ? plane - n * p.C : c0;
+        const float* const wp = p.w + (int64_t)c * (K_ * K_);
+        float w[K_ * K_];
+#pragma unroll
+        for (int i = 0; i < K_ * K_; ++i) w[i] = wp[i];
+        const float* const in = dlds + pl * g.per_plane + oh * ST * g.wl + ow * ST;
+        float* const out = p.y + n * p.ys[0] + c * p.ys[1] + (int64_t)(oh0 + oh) * p.ys[2] + ow;
+        const int left = min(g.rows, p.OH - oh0) - oh;       // outputs of this walk
+        float win[K_][K_];
+#pragma unroll
+        for (int r = 0; r < K_ - ST; ++r)
+#pragma unroll
+            for (int s = 0; s < K_; ++s) win[r][s] = in[r * g.wl + s];
+#pragma unroll
+        for (int i = 0; i < kBandRows; ++i) {
+            if (i < left) {
+                // input row i * ST + r of the walk sits in win[(i * ST + r) % K_]
+#pragma unroll
+                for (int r = K_ - ST; r < K_; ++r)
+#pragma unroll
+                    for (int s = 0; s < K_; ++s) win[(i * ST + r) % K_][s] = in[(i * ST + r) * g.wl + s];
+                float acc = 0.f;
+#pragma unroll
+                for (int r = 0; r < K_; ++r)
+#pragma unroll
+                    for (int s = 0; s < K_; ++s) acc = fmaf(win[(i * ST + r) % K_][s], w[r * K_ + s], acc);
+                out[i * p.ys[2]] = acc;
+            }
+        }
+    }
+}
+
 }  // namespace dw
 }  // namespace anr

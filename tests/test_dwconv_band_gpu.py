@@ -1,0 +1,44 @@
+"""Depthwise layers that run in bands of rows: odd widths and heights around the eight outputs of a thread's walk,
+both strides, both kernel sizes, any padding, several planes per work-group, views; small integers, so bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2006_06762_amd import inputs as I
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+GUARD = 12345.0
+
+
+def run(s, seed, start=0, gap=0):
+    """start: floats x and y begin past an aligned address; gap: floats between the rows of x and of y."""
+    from paper_2006_06762_amd import binding as anr
+    x, w = I.dwconv_inputs(s, seed, ints=True)
+    xbuf = torch.full((s.N * s.C * s.H * (s.W + gap) + 8,), float("nan"), device="cuda")
+    xv = xbuf[start:start + s.N * s.C * s.H * (s.W + gap)].view(s.N, s.C, s.H, s.W + gap)[..., :s.W]
+    xv.copy_(torch.from_numpy(x))
+    n = s.N * s.C * s.OH * (s.OW + gap)
+    ybuf = torch.full((n + 128,), GUARD, device="cuda")
+    wide = ybuf[64 + start:64 + start + n].view(s.N, s.C, s.OH, s.OW + gap)
+    anr.dwconv(xv, torch.from_numpy(w).cuda(), wide[..., :s.OW], s.stride, s.pad)
+    assert np.array_equal(wide[..., :s.OW].cpu().numpy().astype(np.float64), oracle.dwconv(x, w, s.stride, s.pad)), s
+    assert bool((wide[..., s.OW:] == GUARD).all()) and bool((ybuf[:64 + start] == GUARD).all())
+    assert bool((ybuf[64 + start + n:] == GUARD).all())
+
+
+@pytest.mark.parametrize("R", [3, 5])
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("H, W, planes", [(47, 61, 400), (64, 67, 400), (65, 50, 350), (150, 21, 330), (9, 259, 900), (57, 57, 1100)])
+def test_bands(R, stride, H, W, planes):
+    planes *= stride * stride
+    run(I.ConvShape(2, planes // 2, H, W, planes // 2, R, R, (stride, stride), (R // 2, R // 2)), 3000 + H + R)
+
+
+@pytest.mark.parametrize("H, W, R, stride, pad, start, gap", [(13, 13, 3, 1, 1, 1, 0), (14, 14, 5, 1, 2, 3, 0), (7, 9, 3, 1, 1, 2, 0),
+                                                              (20, 20, 3, 1, 0, 0, 3), (30, 31, 3, 2, 3, 0, 1), (16, 12, 5, 2, 4, 1, 0)])
+def test_planes_in_groups_views_and_padding(H, W, R, stride, pad, start, gap):
+    """Planes that are unaligned or whose rows lie apart: several to a work-group, or one."""
+    s = I.ConvShape(5, 3001 if H * W < 300 else 901, H, W, 3001 if H * W < 300 else 901, R, R, (stride, stride), (pad, pad))
+    run(s, 3100 + H, start, gap)
