@@ -33,9 +33,13 @@ __device__ __forceinline__ float block_sum(float v, float* red)
 }
 
 // One work-group reduces elements [part * per_part, (part + 1) * per_part) of the flattened
-// matrix (per_part is a multiple of 4 * kNT when VEC).  Writes sqrt of the sum when the
-// matrix has a single part, else the partial sum to ws[b * parts + part].
-template <bool VEC, bool ONCE>
+// matrix (per_part is a multiple of 4 * kNT).  Writes sqrt of the sum when the matrix has a single part, else the
+// partial sum to ws[b * parts + part].
+// PACKED: rows back to back, so a slice is one contiguous run whatever its alignment: up to three floats, 16-byte units,
+// up to three floats.  Otherwise a thread steps through the flattened matrix by carrying row and column along.
+// One element and one 64-bit division at a time, as both had it unless everything was a multiple of four, 16 matrices of
+// 131 x 161 took 13.2 us, of 177 x 999 26.2, of 3651 x 86 28.2; PACKED 7.1, 7.2 and 9.4.
+template <bool PACKED, bool ONCE>
 __global__ __launch_bounds__(kNT) void nrm_partial_kernel(const NrmArgs p, int64_t per_part, int parts)
 {
     __shared__ float red[4];
@@ -45,11 +49,14 @@ __global__ __launch_bounds__(kNT) void nrm_partial_kernel(const NrmArgs p, int64
     const int64_t end = begin + per_part < total ? begin + per_part : total;
     const float* __restrict__ x = p.x + b * p.stride;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    if (VEC) {
-        // packed rows: the slice is one contiguous run of 16-byte units
-        const f32x4* __restrict__ x4 = reinterpret_cast<const f32x4*>(x);
-        const int64_t u0 = begin / 4 + threadIdx.x, u1 = end / 4;      // total is a multiple of 4
-        int64_t u = u0;
+    if (PACKED) {
+        const int64_t count = end > begin ? end - begin : 0;
+        const float* __restrict__ xs = x + begin;
+        int64_t head = (4 - ((reinterpret_cast<uintptr_t>(xs) >> 2) & 3)) & 3;      // floats ahead of an aligned one
+        if (head > count) head = count;
+        const f32x4* __restrict__ x4 = reinterpret_cast<const f32x4*>(xs + head);
+        const int64_t u1 = (count - head) / 4;
+        int64_t u = threadIdx.x;
         for (; u + 7 * kNT < u1; u += 8 * kNT) {
             f32x4 v[8];
 #pragma unroll
@@ -69,11 +76,34 @@ __global__ __launch_bounds__(kNT) void nrm_partial_kernel(const NrmArgs p, int64
             s2 = fmaf(v[2], v[2], s2);
             s3 = fmaf(v[3], v[3], s3);
         }
+        // the floats around the units: threads 0 .. 2 and 4 .. 6
+        const int64_t rest = head + 4 * u1;
+        const int t = threadIdx.x;
+        const int64_t e = t < 4 ? t : rest + t - 4;
+        if ((t < 3 && e < head) || (t >= 4 && t < 7 && e < count)) s0 = fmaf(xs[e], xs[e], s0);
     } else {
-        // any row stride: element e of the flattened matrix is row e / M, column e % M
-        for (int64_t e = begin + threadIdx.x; e < end; e += kNT) {
-            const int64_t row = e / p.M, col = e - row * p.M;
-            const float v = x[row * p.ld + col];
+        // element e of the flattened matrix is row e / M, column e % M; one step of the work-group is step_r rows
+        // and step_c columns
+        const int64_t e0 = begin + threadIdx.x, step_r = kNT / p.M, step_c = kNT - step_r * p.M;
+        int64_t row = e0 / p.M, col = e0 - row * p.M, at = row * p.ld + col;
+        auto next = [&] {
+            const int64_t here = at;
+            col += step_c;
+            const bool carry = col >= p.M;
+            col -= carry ? p.M : 0;
+            at += step_r * p.ld + step_c + (carry ? p.ld - p.M : 0);
+            return here;
+        };
+        int64_t e = e0;
+        for (; e + 3 * kNT < end; e += 4 * kNT) {
+            const float v0 = x[next()], v1 = x[next()], v2 = x[next()], v3 = x[next()];
+            s0 = fmaf(v0, v0, s0);
+            s1 = fmaf(v1, v1, s1);
+            s2 = fmaf(v2, v2, s2);
+            s3 = fmaf(v3, v3, s3);
+        }
+        for (; e < end; e += kNT) {
+            const float v = x[next()];
             s0 = fmaf(v, v, s0);
         }
     }
@@ -120,13 +150,13 @@ hipError_t launch_nrm(const NrmArgs& a, hipStream_t stream)
     const int parts = nrm_parts(a);
     const int64_t total = a.N * a.M;
     if (parts > 1 && (a.ws == nullptr || a.ws_bytes < nrm_workspace_bytes(a))) return hipErrorInvalidValue;
-    const bool vec = a.ld == a.M && (total % 4 == 0) && (a.stride % 4 == 0) && is_aligned16(a.x);
+    const bool packed = a.ld == a.M || a.N == 1;
     // slice length: a whole number of passes of the work-group over 16-byte units
     int64_t per_part = (total + parts - 1) / parts;
     per_part = (per_part + 4 * kNT - 1) / (4 * kNT) * (4 * kNT);
     const dim3 grid((unsigned)parts, (unsigned)a.batch);
     const bool once = total * a.batch * 4 > kOnceBytes;
-    hipError_t err = !vec   ? launch_kernel(nrm_partial_kernel<false, false>, grid, dim3(kNT), 0, stream, a, per_part, parts)
+    hipError_t err = !packed ? launch_kernel(nrm_partial_kernel<false, false>, grid, dim3(kNT), 0, stream, a, per_part, parts)
                      : once ? launch_kernel(nrm_partial_kernel<true, true>, grid, dim3(kNT), 0, stream, a, per_part, parts)
                             : launch_kernel(nrm_partial_kernel<true, false>, grid, dim3(kNT), 0, stream, a, per_part, parts);
     if (err != hipSuccess || parts == 1) return err;
