@@ -15,6 +15,7 @@
 #include "anr_device.h"
 #include "anr_kernels.h"
 #include "gemm_pipe_kernel.h"
+#include "gemm_rows32_kernel.h"
 #include "gemm_split_kernel.h"
 
 namespace anr {
@@ -460,6 +461,33 @@ hipError_t launch_pipe(const GemmArgs& a, hipStream_t stream, bool* taken)
     return launch_kernel(gpipe::gemm_pipe_kernel<1>, grid, dim3(256), gpipe::kLdsBytes, stream, a, tiles_m, tiles_n);
 }
 
+template <int NW, int FOLDS>
+hipError_t launch_rows32_as(const GemmArgs& a, hipStream_t stream)
+{
+    const int tiles_m = (a.M + 31) / 32, tiles_n = (a.N + 31) / 32;
+    constexpr size_t lds_bytes = sizeof(float) * NW * grows::kStage;
+    auto kern = grows::gemm_rows32_kernel<NW, FOLDS>;
+    if (lds_bytes > 48 * 1024) {
+        static LdsLimit granted;
+        hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_bytes, granted);
+        if (e != hipSuccess) return e;
+    }
+    return launch_kernel(kern, dim3((unsigned)((int64_t)tiles_m * tiles_n * a.batch)), dim3(64 * NW), lds_bytes, stream, a, tiles_m, tiles_n);
+}
+
+// Eight waves to a work-group, with more than one work-group per CU and a short reduction four (1422 x 200 x 510 12.1
+// against 12.7 us); the number of folds by K as their errors stand to those of the kernels before (see there).
+template <int NW>
+hipError_t launch_rows32_by_k(const GemmArgs& a, hipStream_t stream)
+{
+    return a.K < 288 ? launch_rows32_as<NW, 4>(a, stream) : a.K < 800 ? launch_rows32_as<NW, 2>(a, stream) : launch_rows32_as<NW, 1>(a, stream);
+}
+
+hipError_t launch_rows32(const GemmArgs& a, int64_t tiles, hipStream_t stream)
+{
+    return tiles <= 256 || a.K >= 1024 ? launch_rows32_by_k<8>(a, stream) : launch_rows32_by_k<4>(a, stream);
+}
+
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs& args, hipStream_t stream)
@@ -489,7 +517,7 @@ hipError_t launch_gemm(const GemmArgs& args, hipStream_t stream)
         if (a.K == 512) return launch_ksplit<1, 16>(a, stream);
     }
 
-    hipError_t err;
+    hipError_t err = hipSuccess;
     // 32-bit byte offsets inside one matrix, grid limits
     const int64_t a_ext = (int64_t)(a.M - 1) * a.lda + a.K;
     const int64_t b_ext = a.b_is_nk ? (int64_t)(a.N - 1) * a.ldb + a.K : (int64_t)(a.K - 1) * a.ldb + a.N;
@@ -497,7 +525,13 @@ hipError_t launch_gemm(const GemmArgs& args, hipStream_t stream)
     const int64_t tiles64 = (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch;
     const bool offsets32 = a_ext < ((int64_t)1 << 29) && b_ext < ((int64_t)1 << 29) && tiles64 < ((int64_t)1 << 22);
     bool piped = false;
-    err = hipSuccess;
+    // Few 32 x 32 tiles: gemm_rows32_kernel, whatever the alignment.  Up to a tile per CU from K = 65 on (283 x 821 x 83
+    // 6.6 -> 4.8 us, 449 x 450 x 1920 36 -> 17), or from 97 where the pipelined kernel can load the operands (2560 x 32 x
+    // 96 5.1 -> 5.5), up to two from 97 (1422 x 200 x 510 15.2 -> 13.1, 192 x 2464 x 320 10.1 -> 10.0); past that each CU has
+    // more work than its own chain and larger tiles reuse more (520 tiles, K = 384, 11.6 -> 13.3).
+    const int64_t tiles_rows32 = (int64_t)((a.M + 31) / 32) * ((a.N + 31) / 32) * a.batch;
+    if (offsets32 && !a.b_is_nk && !a.softmax_rows && a.batch_inner == 1 && a.K > (tiles_rows32 <= 256 && !vec ? 64 : 96) && tiles_rows32 <= 512)
+        return launch_rows32(a, tiles_rows32, stream);
     if (offsets32 && vec && !a.b_is_nk) err = launch_pipe(a, stream, &piped);
     if (err != hipSuccess) return err;
     // A k-major B is read a whole chunk of rows and a pair of columns at a time.  Operands the pipelined kernel
