@@ -1,6 +1,7 @@
 // Tile and split-K selection and launch of the general implicit-GEMM convolution (kernels
 // and their description in conv_gather_kernel.h).
 #include <algorithm>
+#include <cmath>
 #include "conv_gather_kernel.h"
 
 namespace anr {
@@ -269,6 +270,13 @@ size_t conv2d_gather_workspace_bytes(const ConvArgs& a)
 {
     Plan g;
     return make_plan(a, &g) && choose_tile(a, &g) ? plan_workspace(g) : 0;
+}
+
+double conv2d_gather_estimate_us(const ConvArgs& a)
+{
+    Plan g;
+    if (!(make_plan(a, &g) && choose_tile(a, &g)) || g.taps != 9) return INFINITY;
+    return estimate_taps_us(g, a, g.ksplit);
 }
 
 bool describe_conv2d_gather(const ConvArgs& a, ConvRoute* r)

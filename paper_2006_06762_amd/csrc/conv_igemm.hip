@@ -71,10 +71,61 @@ int select_variant(const ConvArgs& a, Geom* g, size_t* lds)
 constexpr int kMinTunedWorkGroups = 112;
 
 struct IgemmPlan {
-    int variant;     // 0 V224x64, 1 V224x32, 2 V128x64, 3 V64x64; -1: the kernel does not take the call
+    int variant;     // 0 V224x64, 1 V224x32, 2 V128x64, 3 V64x64, 4 the bf16-split form at any width; -1: the kernel does not take the call
     Geom g;
     size_t lds;
+    int cap;         // variant 4: patch pixels it needs room for (512 or 768)
 };
+
+// The bf16-split 224 x 64 tile without the fp32 forms' conditions (it loads single floats, so any width, alignment
+// and row stride): stride 1, whole chunks of sixteen channels, a patch that fits whatever pixel a tile starts at.  An
+// image's virtual rows are the zero rows above it and its own; the zero rows below it are the next image's.
+// (A pack in the fp32 form's order is not for it.)
+bool plan_wide(const ConvArgs& a, IgemmPlan* p)
+{
+    constexpr int BM = psplit::BM, BN = 64;
+    if (a.wpack || a.R != 3 || a.S != 3 || a.C % 16 != 0 || a.groups != 1 || a.stride_h != 1 || a.stride_w != 1 || a.dil_h != 1 || a.dil_w != 1 ||
+        a.pad_h > 2 || a.OW < 24)
+        return false;
+    const int64_t x_extent = (int64_t)(a.N - 1) * a.xs[0] + (int64_t)(a.C - 1) * a.xs[1] + (int64_t)(a.H - 1) * a.xs[2] + a.W;
+    const int64_t w_extent = (int64_t)a.K * a.C * 9, ohow = (int64_t)a.OH * a.OW;
+    if (x_extent >= (int64_t)1 << 29 || w_extent >= (int64_t)1 << 29 || a.N * ohow >= (int64_t)1 << 30) return false;
+    Geom* g = &p->g;
+    *g = Geom{};
+    g->Mtot = (int)(a.N * ohow);
+    g->ohow = (int)ohow;
+    g->HV = a.H + a.pad_h;
+    const int64_t rows = (BM - 1 + a.OW - 1) / a.OW + 1, crossings = (BM - 1 + ohow - 1) / ohow;
+    const int64_t vr = rows + crossings * (g->HV > a.OH ? g->HV - a.OH : 0) + 2, px = vr * (a.OW + 2);
+    if (px > 768 || (int64_t)(a.N + 1) * g->HV + vr >= (int64_t)1 << 31) return false;
+    g->VR = (int)vr;
+    p->cap = px <= 512 ? 512 : 768;
+    g->vec_store = (ohow % 4 == 0) && a.ys[2] == a.OW && (a.ys[0] % 4 == 0) && (a.ys[1] % 4 == 0) && is_aligned16(a.y);
+    g->d_ow = make_fastdiv(a.OW);
+    g->d_oh = make_fastdiv(a.OH);
+    g->d_hv = make_fastdiv(g->HV);
+    g->x_bytes = (uint32_t)(4 * x_extent);
+    g->w_bytes = (uint32_t)(4 * w_extent);
+    g->tiles_m = (g->Mtot + BM - 1) / BM;
+    g->tiles_n = (a.K + BN - 1) / BN;
+    g->d_tiles_m = make_fastdiv(g->tiles_m);
+    g->d_sub_n = make_fastdiv(1);
+    return (int64_t)g->tiles_m * g->tiles_n < ((int64_t)1 << 31);
+}
+
+// Time estimates (us) of that form and of the fp32 tiles it competes with: rounds of one work-group per CU, each a
+// fixed part and its channels.  Within 8 % of 90 layers of 16 to 512 channels on maps of 24 to 224 pixels.
+double wide_us(const ConvArgs& a, const IgemmPlan& p)
+{
+    const double rounds = (double)(((int64_t)p.g.tiles_m * p.g.tiles_n + 255) / 256);
+    return 2.0 + rounds * (4.5 + a.C / 16 * (p.cap == 512 ? 5.8 : 6.2));
+}
+
+double fp32_us(const ConvArgs& a, const Geom& g, int variant)
+{
+    const double rounds = (double)(((int64_t)g.tiles_m * g.tiles_n + 255) / 256);
+    return 2.0 + rounds * (variant == 2 ? 4.0 + 0.274 * a.C : 2.5 + 0.145 * a.C);
+}
 
 // The one planning pass of a call: variant, geometry and LDS size, with the descriptor's route
 // applied (1: whenever a variant runs the shape; 2: never; 0: with enough output tiles).  Depends
@@ -85,9 +136,22 @@ void plan_igemm(const ConvArgs& a, IgemmPlan* p)
     p->variant = -1;
     if (a.route == 2) return;
     const int best = select_variant(a, &p->g, &p->lds);
-    if (best < 0) return;
-    if (a.route != 1 && (int64_t)p->g.tiles_m * p->g.tiles_n < kMinTunedWorkGroups) return;
-    p->variant = best;
+    const bool tuned = best >= 0 && (a.route == 1 || (int64_t)p->g.tiles_m * p->g.tiles_n >= kMinTunedWorkGroups);
+    if (tuned && (best < 2 || a.route == 1)) {
+        p->variant = best;
+        return;
+    }
+    // The bf16-split tile at any width, where its estimate is the shorter one by the estimates' spread (81 x 81, 512 -> 96, batch
+    // 4, 304 -> 207 us; 57 x 57, 64 -> 512, batch 4, 81 -> 61; 42 x 42, 128 -> 160, batch 32, 211 -> 169; 124 x 124, 32 -> 512, batch
+    // 7, 468 -> 282; on average 0.82 of the time of the layers that take it).  Few or half-filled rounds, channels far from a
+    // multiple of 64 and few input channels leave it behind (38 x 38, 128 -> 64, batch 16, 42 against 51).
+    IgemmPlan wide;
+    if (plan_wide(a, &wide) && wide_us(a, wide) < 0.93 * (tuned ? fp32_us(a, p->g, best) : conv2d_gather_estimate_us(a))) {
+        *p = wide;
+        p->variant = 4;
+        return;
+    }
+    if (tuned) p->variant = best;
 }
 
 // Patch pixels the bf16-split form of a 224-pixel tile needs room for (512 or 1024), 0 if it does not take
@@ -133,6 +197,7 @@ hipError_t launch_igemm_plan(const ConvArgs& a, const IgemmPlan& p, hipStream_t 
             if (try_fixed<V224x32, 3, 36, 432, 3>(a, g, lds, stream, &err)) return err;     // 28x28 maps, stride 1
             if (try_fixed<V224x32, 8, 32, 1088, 3>(a, g, lds, stream, &err)) return err;    // 28x28 maps, stride 2
             return V224x32::launch(a, g, lds, stream);
+        case 4: return p.cap == 512 ? launch_patch_split<64, 512>(a, g, a.OW + 2, stream) : launch_patch_split<64, 768>(a, g, a.OW + 2, stream);
         case 2: return V128x64::launch(a, g, lds, stream);
         default: return V64x64::launch(a, g, lds, stream);
     }
@@ -202,7 +267,7 @@ bool describe_conv2d_igemm(const ConvArgs& a, ConvRoute* r)
     IgemmPlan p;
     plan_igemm(a, &p);
     if (p.variant < 0) return false;
-    static const int kTileM[5] = {224, 224, 128, 64, 224}, kTileN[5] = {64, 32, 64, 64, 32};
+    static const int kTileM[5] = {224, 224, 128, 64, 224}, kTileN[5] = {64, 32, 64, 64, 64};
     r->kernel = 1;
     r->tile_m = kTileM[p.variant];
     r->tile_n = kTileN[p.variant];
@@ -249,7 +314,7 @@ ConvPackLayout conv2d_pack_layout(const ConvArgs& a)
     plan_igemm(b, &p);
     int bn = 0, ck = 0;
     const int64_t pf = packed_floats(b, p, &bn, &ck);
-    l.patch_layout = p.variant >= 0 && pf < ((int64_t)1 << 30);
+    l.patch_layout = p.variant >= 0 && p.variant < 4 && pf < ((int64_t)1 << 30);
     l.w_floats = l.patch_layout ? (size_t)pf : (size_t)a.K * (a.C / a.groups) * a.R * a.S;
     return l;
 }

@@ -1,5 +1,6 @@
 // The 3 x 3 patch kernel on the bf16 matrix pipes, fp32 as three bf16 pieces (split_bf16.h): the tile of
-// conv_igemm_kernel's 224-pixel variants, planned by the same code.
+// conv_igemm_kernel's 224-pixel variants, planned by the same code, and at stride 1 the tile of 224 pixels x 64 channels for
+// any width (plan_wide in conv_igemm.hip).
 //
 // Splitting costs vector-ALU time beside the matrix instructions, so it pays where a split float is used
 // often: an input element of the staged patch serves nine taps, a weight 224 pixels.  A chunk is sixteen
@@ -30,7 +31,7 @@ constexpr uint32_t kPastExtent = 0x80000000u;       // byte offset beyond any de
 constexpr int T = 512;
 constexpr int MB = 7, BM = 32 * MB;
 
-// BN output channels (64 or 32), CAP patch pixels (a multiple of T).
+// BN output channels (64 or 32), CAP patch pixels (a multiple of 64).
 template <int BN, int CAP>
 struct Lds {
     static constexpr int XKQ = CAP * 16, XPLANE = 2 * XKQ;      // bytes
@@ -52,7 +53,7 @@ __device__ __forceinline__ bool compute_tile(const ConvArgs& p, const igemm::Geo
     using L = Lds<BN, CAP>;
     constexpr int XKQ = L::XKQ, XPLANE = L::XPLANE, WKQ = L::WKQ, WTAP = L::WTAP, WPLANE = L::WPLANE;
     constexpr int NB = BN / 32, MG = 8 / NB, BLK = MG == 4 ? 2 : 1;      // blocks of 32 pixels of a wave
-    constexpr int PX = CAP / T;                                          // patch pixels of a thread
+    constexpr int PX = (CAP + T - 1) / T;                                // patch pixels of a thread
     extern __shared__ __attribute__((aligned(16))) char plds[];
     char* const lx = plds;
     char* const lw = plds + 3 * XPLANE;
@@ -88,9 +89,11 @@ __device__ __forceinline__ bool compute_tile(const ConvArgs& p, const igemm::Geo
     //      its input offset; weight unit (row r of the kernel, eight channels, output channel)
     const int px0 = (tid + T - 6 * BN) & (T - 1);
     uint32_t xoff[PX];
+    bool stages[PX];                               // (uniform over the wave) it has pixels of the patch there
 #pragma unroll
     for (int i = 0; i < PX; ++i) {
         const int px = px0 + T * i;
+        stages[i] = (CAP % T == 0 || i + 1 < PX || px < CAP) && (i == 0 || __builtin_amdgcn_readfirstlane(px) < g.VR * wp);
         const int vr = px / wp, col = px - vr * wp;
         const int v = v0 + vr;
         const int n = g.d_hv.div(v), ih = v - n * g.HV - p.pad_h, iw = col - p.pad_w;
@@ -116,11 +119,13 @@ __device__ __forceinline__ bool compute_tile(const ConvArgs& p, const igemm::Geo
     auto load_chunk = [&](int ck) {
 #pragma unroll
         for (int i = 0; i < PX; ++i)
+            if (i == 0 || stages[i]) {
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
+                for (int k = 0; k < 2; ++k)
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    rx[i][k][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)xoff[i], (int)((uint32_t)(16 * ck + 8 * k + e) * xs1b), 0));
+                    for (int e = 0; e < 8; ++e)
+                        rx[i][k][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)xoff[i], (int)((uint32_t)(16 * ck + 8 * k + e) * xs1b), 0));
+            }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             typedef float f32x3 __attribute__((ext_vector_type(3)));
@@ -137,6 +142,7 @@ __device__ __forceinline__ bool compute_tile(const ConvArgs& p, const igemm::Geo
             for (int i = 0; i < PX; ++i)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
+                    if (i > 0 && !stages[i]) break;
                     const float* const v = rx[i][u / 2] + 4 * (u % 2);
                     *reinterpret_cast<f32x4*>(dx + u * XKQ + T * 16 * i) = f32x4{v[0], v[1], v[2], v[3]};
                 }
@@ -153,6 +159,7 @@ __device__ __forceinline__ bool compute_tile(const ConvArgs& p, const igemm::Geo
         for (int i = 0; i < PX; ++i)
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
+                if (i > 0 && !stages[i]) break;
                 u32x4 s[3];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {

@@ -1,0 +1,81 @@
+"""3 x 3 layers of any width on the bf16-split tile of 224 pixels: tiles that start anywhere in a row and cross
+images, both patch sizes, paddings, channel counts past a tile, views of any alignment, packed weights, values the pieces
+cannot carry."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2006_06762_amd import inputs as I
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+GUARD = 12345.0
+# (N, C, H, W, K, pad): patches of at most 512 pixels and of more, the widest row that fits, images smaller than a tile
+SHAPES = [(5, 32, 37, 53, 320, 1), (8, 16, 33, 27, 400, 1), (4, 32, 90, 71, 384, 1), (3, 32, 126, 125, 384, 1), (3, 48, 61, 77, 250, 0),
+          (6, 16, 30, 31, 512, 2), (18, 32, 7, 25, 1000, 1), (25, 64, 26, 26, 100, 1), (13, 32, 31, 29, 200, 2)]
+
+
+def tensors(shape, seed, ints, start, gap):
+    N, C, H, W, K, pad = shape
+    s = I.ConvShape(N, C, H, W, K, 3, 3, (1, 1), (pad, pad))
+    x, w = I.conv_inputs(s, seed, ints=ints)
+    xbuf = torch.full((x.size // W * (W + gap) + 8,), float("nan"), device="cuda")
+    xv = xbuf[start:start + x.size // W * (W + gap)].view(N, C, H, W + gap)[..., :W]
+    xv.copy_(torch.from_numpy(x))
+    ybuf = torch.full((N * K * s.OH * (s.OW + gap) + 128,), GUARD, device="cuda")
+    wide = ybuf[64 + start:64 + start + N * K * s.OH * (s.OW + gap)].view(N, K, s.OH, s.OW + gap)
+    return s, x, w, xv, torch.from_numpy(w).cuda(), ybuf, wide
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("start,gap", [(0, 0), (1, 0), (2, 3)])
+def test_whole_numbers(shape, start, gap):
+    from paper_2006_06762_amd import binding as anr
+    s, x, w, xv, wd, ybuf, wide = tensors(shape, 5000 + shape[2], True, start, gap)
+    assert anr.conv2d_route(anr.conv_desc(x.shape, s.K, 3, 3, s.stride, s.pad)).tile_m == 224
+    y = wide[..., :s.OW]
+    anr.conv2d(xv, wd, y, s.stride, s.pad)
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).cuda().double(), wd.double(), padding=s.pad)
+    assert torch.equal(y.double(), ref)
+    assert np.array_equal(y[:1].cpu().numpy().astype(np.float64), oracle.conv2d(x[:1], w, s.stride, s.pad))
+    assert bool((wide[..., s.OW:] == GUARD).all()) and bool((ybuf[:64 + start] == GUARD).all()) and bool((ybuf[-32:] == GUARD).all())
+
+
+@pytest.mark.parametrize("shape", SHAPES[:4])
+def test_fused_and_packed(shape):
+    """Sums within the bound of an fp32 sum, the fused epilogue, and the pack's results bit for bit."""
+    from paper_2006_06762_amd import binding as anr
+    s, x, w, xv, wd, ybuf, wide = tensors(shape, 5100, False, 0, 0)
+    anr.conv2d(xv, wd, wide, s.stride, s.pad)
+    xd = xv.double()
+    ref = torch.nn.functional.conv2d(xd, wd.double(), padding=s.pad)
+    size = torch.nn.functional.conv2d(xd.abs(), wd.double().abs(), padding=s.pad)
+    assert bool(((wide.double() - ref).abs() <= (9 * s.C + 2) * 2.0 ** -24 * size).all())
+    bn = [torch.from_numpy(v).cuda() for v in I.bn_inputs(s.K, 5101)]
+    y = torch.empty_like(wide)
+    anr.conv_bn_relu(xv, wd, *bn, I.BN_EPS, y, s.stride, s.pad)
+    desc, pack = anr.conv2d_pack_weights(x.shape, wd, s.stride, s.pad, bn=bn, eps=I.BN_EPS)
+    y2 = torch.empty_like(wide)
+    anr.conv_bn_relu_packed(desc, xv, pack, y2)
+    assert torch.equal(y, y2)
+    g, b, m, v = (t.double().view(1, -1, 1, 1) for t in bn)
+    want = torch.relu((ref - m) * g / (v + I.BN_EPS).sqrt() + b)
+    assert float(((y.double() - want).abs() / want.abs().clamp(min=1.0)).max()) <= 1e-5
+    anr.conv2d_packed(desc, xv, pack, y2)
+    assert torch.equal(wide, y2)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 2.0 ** -120, 3.4e38])
+def test_values_the_pieces_cannot_carry(value):
+    from paper_2006_06762_amd import binding as anr
+    s, x, w, xv, wd, ybuf, wide = tensors(SHAPES[2], 5200, True, 0, 0)
+    xv[1, 3, 40, 35] = value
+    xv[2, 31, 0, 70] = value
+    anr.conv2d(xv, wd, wide, s.stride, s.pad)
+    ref = torch.nn.functional.conv2d(xv.cpu(), wd.cpu(), padding=s.pad)
+    got = wide.cpu()
+    assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf())
+    ok = ref.isfinite()
+    exact = torch.nn.functional.conv2d(xv.double(), wd.double(), padding=s.pad).cpu()
+    assert bool(((got.double() - exact).abs()[ok] <= 1e-6 * exact.abs().clamp(min=1.0)[ok]).all())
