@@ -408,18 +408,18 @@ hipError_t launch_variant(const GemmArgs& a, hipStream_t stream)
 }
 
 
-template <int BM, int WM, int WN, int NWG, bool NT>
+template <int BM, int WM, int WN, int NWG, bool SPEC, bool NT>
 hipError_t launch_split(const GemmArgs& a, hipStream_t stream)
 {
     const gsplit::Grid g{(a.M + BM - 1) / BM, (a.N + BM - 1) / BM, 8};
-    constexpr size_t lds_bytes = gsplit::lds_bytes<BM, BM, NWG>();
-    auto kern = gsplit::gemm_split_kernel<BM, BM, WM, WN, NWG, 2, NT>;
+    constexpr size_t lds_bytes = gsplit::lds_bytes<BM, BM, NWG, SPEC>();
+    auto kern = gsplit::gemm_split_kernel<BM, BM, WM, WN, NWG, SPEC, 2, NT>;
     if (lds_bytes > 48 * 1024) {
         static LdsLimit granted;
         hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_bytes, granted);
         if (e != hipSuccess) return e;
     }
-    return launch_kernel(kern, dim3((unsigned)((int64_t)g.tiles_m * g.tiles_n * a.batch)), dim3(64 * WM * WN * NWG), lds_bytes,
+    return launch_kernel(kern, dim3((unsigned)((int64_t)g.tiles_m * g.tiles_n * a.batch)), dim3(64 * WM * WN * (SPEC ? 2 : NWG)), lds_bytes,
                          stream, a, g);
 }
 
@@ -428,11 +428,11 @@ hipError_t launch_split_any(const GemmArgs& a, hipStream_t stream)
 {
     static_assert(gsplit::kVariantCount == 5, "one launch per variant");
     switch (gsplit::choose_variant(a.M, a.N, a.K, a.batch)) {
-        case 0: return launch_split<128, 2, 2, 1, NT>(a, stream);
-        case 1: return launch_split<128, 2, 2, 2, NT>(a, stream);
-        case 2: return launch_split<64, 2, 1, 1, NT>(a, stream);
-        case 3: return launch_split<64, 2, 1, 2, NT>(a, stream);
-        default: return launch_split<64, 2, 1, 4, NT>(a, stream);
+        case 0: return launch_split<128, 2, 2, 1, false, NT>(a, stream);
+        case 1: return launch_split<128, 2, 2, 1, true, NT>(a, stream);
+        case 2: return launch_split<64, 2, 1, 1, false, NT>(a, stream);
+        case 3: return launch_split<64, 2, 1, 2, false, NT>(a, stream);
+        default: return launch_split<64, 2, 1, 4, false, NT>(a, stream);
     }
 }
 

@@ -10,6 +10,14 @@
 // order of k is a valid reduction order as long as both operands use it).  Units are 64 bytes further
 // apart than their rows need: those two lanes then write to different banks.
 //
+// SPEC, for products with about one tile of 128 x 128 per CU: four waves only load, split and store, four only multiply,
+// and a chunk has a buffer to itself, so there is one barrier per 32 k.  Vector-ALU and matrix instructions of
+// different waves run side by side (probe: 256 us of matrix instructions with 232 us of splitting in the other waves take
+// 306), and a work-group alone on its CU has no second one whose products cover its splitting.  Two groups that
+// took turns at both, each with a barrier per 16 k, against it: 512^3 x16 37.2 -> 31.8 us, 512 x 512 x 2048 x16 122 -> 106,
+// 2048^3 119 -> 104, 2038 x 1861 x 473 33.9 -> 28.4.  With several tiles per CU two work-groups of the other form cover
+// each other (4096^2 x 512 109 against 116).  Two chunks of loads in flight: 3 to 8 % slower.
+//
 // B is k-major in memory.  A staging piece is four k of two neighbouring columns: 8-byte loads (the
 // address unit takes a load instruction's 64 lanes in 16 cycles whatever their width, and 4-byte loads
 // cost a quarter of the time of a work-group alone on its CU), and packing pairs of k transposes for
@@ -19,7 +27,7 @@
 // Bound: large products by the matrix pipes' power (eight bf16 products per fp32 one at 181 TFLOP/s are
 // 1.45 PFLOP/s, what a large bf16 product of the library reaches on the card is 1.3); work-groups alone on their
 // CU by the chain load - split - LDS - multiply.  Measured against the fp32 kernels this one took over from:
-// 4096^3 976 -> 765-889 us (by card), 2048^3 133 -> 113, 1024^3 x16 257 -> 204, 512^3 x16 38.6 -> 33.3,
+// 4096^3 976 -> 765-889 us (by card), 2048^3 133 -> 104, 1024^3 x16 257 -> 204, 512^3 x16 38.6 -> 31.8,
 // 1009 x 1531 x 771 x3 (4-byte aligned rows) 167 -> 70, 1024^3 22.7 -> 22.4.  Tried and dropped: the split
 // between the matrix instructions, v_dot2 for its subtractions, wave groups in opposite order (all slower);
 // 256 x 256 tiles, which leave no registers for the second set of sums (six products in one set, 4096^3 in
@@ -40,10 +48,11 @@ struct Plane {
     static constexpr int BYTES = 2 * UNIT;
 };
 
-template <int BM, int BN, int NWG>
+// SPEC: whole chunks in two buffers, four halves, for one group of waves that multiplies.
+template <int BM, int BN, int NWG, bool SPEC>
 constexpr size_t lds_bytes()
 {
-    return NWG * 2 * 3 * (size_t)(Plane<BM>::BYTES + Plane<BN>::BYTES) + 16;      // and a flag
+    return (SPEC ? 2 : NWG) * 2 * 3 * (size_t)(Plane<BM>::BYTES + Plane<BN>::BYTES) + 16;      // and flags
 }
 
 // Chunk-invariant description of a launch (what the host works out once).
@@ -54,7 +63,7 @@ struct Grid {
 
 // One tile of a work-group: as bf16 pieces, or PLAIN, with the fp32 instruction.  False if it met a value that the
 // pieces cannot carry: then nothing is stored.
-template <int BM, int BN, int WM, int WN, int NWG, bool NT, bool PLAIN>
+template <int BM, int BN, int WM, int WN, int NWG, bool SPEC, bool NT, bool PLAIN>
 __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, const int thread)
 {
     constexpr int T = 64 * WM * WN;                  // threads of a wave group
@@ -68,9 +77,11 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
 
     extern __shared__ __attribute__((aligned(16))) char slds[];
 
+    static_assert(!SPEC || NWG == 1, "one group multiplies, the other one stages");
     const int wgrp = NWG > 1 ? __builtin_amdgcn_readfirstlane(thread / T) : 0;
+    const bool stager = SPEC && __builtin_amdgcn_readfirstlane(thread / T) != 0;
     char* const region = slds + wgrp * 2 * BUF;
-    int* const flag = reinterpret_cast<int*>(slds + NWG * 2 * BUF);     // a value was met that the pieces cannot carry
+    int* const flag = reinterpret_cast<int*>(slds + (SPEC ? 2 : NWG) * 2 * BUF);     // a value was met that the pieces cannot carry
     const int tid = thread % T;
     const int lane = tid & 63, wave = tid >> 6;
     const int r32 = lane & 31, h = lane >> 5;
@@ -165,21 +176,22 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
             if (NT) rb[f][e] = in ? rb[f][e] : 0.f;
         }
     };
+    int at_buf = 0;                                  // SPEC: the chunk's buffer, bytes
     auto split_pair = [&](auto f_c, int i) {
         constexpr int f = decltype(f_c)::value;
         if (i < 4) split2(ra[f][2 * i], ra[f][2 * i + 1], sp[0][i], sp[1][i], sp[2][i], lost);
         else split2(rb[f][2 * (i - 4)], rb[f][2 * (i - 4) + 1], sp[0][i], sp[1][i], sp[2][i], lost);
         if (i == 3) {
 #pragma unroll
-            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(wa + f * BUF + q * PA) = u32x4{sp[q][0], sp[q][1], sp[q][2], sp[q][3]};
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(wa + at_buf + f * BUF + q * PA) = u32x4{sp[q][0], sp[q][1], sp[q][2], sp[q][3]};
         }
         if (NT && i == 7) {
 #pragma unroll
-            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(wb + f * BUF + q * PB) = u32x4{sp[q][4], sp[q][5], sp[q][6], sp[q][7]};
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(wb + at_buf + f * BUF + q * PB) = u32x4{sp[q][4], sp[q][5], sp[q][6], sp[q][7]};
         }
         if (!NT && (i == 5 || i == 7)) {
 #pragma unroll
-            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2*>(wb + f * BUF + q * PB + (i == 7 ? BN * 8 : 0)) = u32x2{sp[q][i - 1], sp[q][i]};
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2*>(wb + at_buf + f * BUF + q * PB + (i == 7 ? BN * 8 : 0)) = u32x2{sp[q][i - 1], sp[q][i]};
         }
     };
     // For the fp32 instruction the half goes as it is: units of four k, 16 bytes a row
@@ -193,31 +205,38 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
         if constexpr (PLAIN) {
             const float* const x = ra[f];
             const float* const y = rb[f];
-            *reinterpret_cast<f32x4*>(fa + f * BUF) = f32x4{x[0], x[1], x[2], x[3]};
-            *reinterpret_cast<f32x4*>(fa + f * BUF + 2 * QA) = f32x4{x[4], x[5], x[6], x[7]};
-            *reinterpret_cast<f32x4*>(fb + f * BUF) = f32x4{y[0], y[1], y[2], y[3]};
-            *reinterpret_cast<f32x4*>(fb + f * BUF + (NT ? 2 * QB : BN * 8)) = f32x4{y[4], y[5], y[6], y[7]};
+            *reinterpret_cast<f32x4*>(fa + at_buf + f * BUF) = f32x4{x[0], x[1], x[2], x[3]};
+            *reinterpret_cast<f32x4*>(fa + at_buf + f * BUF + 2 * QA) = f32x4{x[4], x[5], x[6], x[7]};
+            *reinterpret_cast<f32x4*>(fb + at_buf + f * BUF) = f32x4{y[0], y[1], y[2], y[3]};
+            *reinterpret_cast<f32x4*>(fb + at_buf + f * BUF + (NT ? 2 * QB : BN * 8)) = f32x4{y[4], y[5], y[6], y[7]};
         } else {
 #pragma unroll
             for (int i = 0; i < 8; ++i) split_pair(f_c, i);
         }
     };
 
-    // the products of the first pieces (or of the floats themselves), and the other seven
-    f32x16 acc[MB][2], low[MB][2];
+    // the products of the first pieces (or of the floats themselves), with SPEC a sum for each half of the chunks as two
+    // groups would have, and the other seven
+    constexpr int SUMS = SPEC ? 2 : 1;
+    f32x16 sums_of[SUMS][MB][2], low[MB][2];
+    f32x16 (&acc)[MB][2] = sums_of[0];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mb][nb][r] = low[mb][nb][r] = 0.f;
+            for (int r = 0; r < 16; ++r) {
+                low[mb][nb][r] = 0.f;
+#pragma unroll
+                for (int i = 0; i < SUMS; ++i) sums_of[i][mb][nb][r] = 0.f;
+            }
 
     auto multiply = [&](auto f_c) {
         constexpr int f = decltype(f_c)::value;
         if constexpr (PLAIN) {
             // the wave's half h takes the units 2q + h, element by element
-            const char* a = region + f * BUF + h * QA + (wm * MB * 32 + r32) * 16;
-            const char* b = region + f * BUF + 3 * PA + h * QB + (wn * 32 + r32) * 16;
+            const char* a = region + at_buf + f * BUF + h * QA + (wm * MB * 32 + r32) * 16;
+            const char* b = region + at_buf + f * BUF + 3 * PA + h * QB + (wn * 32 + r32) * 16;
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 f32x4 av[MB], bv[2];
@@ -230,11 +249,11 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
 #pragma unroll
                     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                        for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = mfma32(av[mb][e], bv[nb][e], acc[mb][nb]);
+                        for (int nb = 0; nb < 2; ++nb) sums_of[f % SUMS][mb][nb] = mfma32(av[mb][e], bv[nb][e], sums_of[f % SUMS][mb][nb]);
             }
         } else {
-            const char* a = region + f * BUF + h * Plane<BM>::UNIT + (wm * MB * 32 + r32) * 16;
-            const char* b = region + f * BUF + 3 * PA + h * Plane<BN>::UNIT + (wn * 32 + r32) * 16;
+            const char* a = region + at_buf + f * BUF + h * Plane<BM>::UNIT + (wm * MB * 32 + r32) * 16;
+            const char* b = region + at_buf + f * BUF + 3 * PA + h * Plane<BN>::UNIT + (wn * 32 + r32) * 16;
             u32x4 bv[3][2];
 #pragma unroll
             for (int q = 0; q < 3; ++q)
@@ -249,7 +268,7 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
                 for (int t = 0; t < kProducts; ++t)
 #pragma unroll
                     for (int nb = 0; nb < 2; ++nb) {
-                        f32x16& sum = t < kProducts - 1 ? low[mb][nb] : acc[mb][nb];
+                        f32x16& sum = t < kProducts - 1 ? low[mb][nb] : sums_of[f % SUMS][mb][nb];
                         sum = mfma_bf16(av[kPieceA[t]], bv[kPieceB[t]][nb], sum);
                     }
             }
@@ -268,34 +287,78 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
         load_a(c_load, G{});
         load_b(c_load, G{});
     };
-    if (!PLAIN && thread == 0) *flag = 0;
-    load_a(wgrp, F0{});
-    load_b(wgrp, F0{});
-    load_a(wgrp, F1{});
-    load_b(wgrp, F1{});
-    store_half(F0{}, wgrp);
-    load_a(wgrp + NWG, F0{});
-    load_b(wgrp + NWG, F0{});
-    int end = (nchunks + NWG - 1) / NWG * NWG;       // the barriers are the work-group's
+    if constexpr (SPEC) {
+        // Barrier c: chunk c is staged and chunk c - 1 multiplied.  A value that the pieces cannot carry is noted before it,
+        // in the chunk's flag, and every wave leaves before the next one.
+        if (stager) {
+            load_a(0, F0{});
+            load_b(0, F0{});
+            load_a(0, F1{});
+            load_b(0, F1{});
+        } else if (!PLAIN && thread == 0) {
+            flag[0] = flag[1] = 0;
+        }
+        if (!PLAIN) __syncthreads();
+        if (stager) {
 #pragma unroll 1
-    for (int c = wgrp; c < end; c += NWG) {
-        __syncthreads();
-        // set between the barriers of a round and read behind the second, so every wave reads the same
-        if (!PLAIN && lost_bits(lost)) *flag = 1;
-        half(F0{}, c, c + NWG);
-        __syncthreads();
-        const int stop = PLAIN ? 0 : *flag;
-        half(F1{}, c + NWG, c + 2 * NWG);
-        if (!PLAIN && __builtin_amdgcn_readfirstlane(stop)) end = 0;
+            for (int c = 0, stop = 0; c < nchunks; ++c) {
+                at_buf = (c & 1) * 2 * BUF;
+                store_half(F0{}, c);
+                load_a(c + 1, F0{});
+                load_b(c + 1, F0{});
+                store_half(F1{}, c);
+                load_a(c + 1, F1{});
+                load_b(c + 1, F1{});
+                __builtin_amdgcn_sched_barrier(0);
+                if (!PLAIN) {
+                    if (__builtin_amdgcn_readfirstlane(stop)) break;
+                    if (lost_bits(lost)) flag[c & 1] = 1;
+                }
+                __syncthreads();
+                if (!PLAIN) stop = flag[c & 1];
+            }
+        } else {
+#pragma unroll 1
+            for (int c = 0, stop = 0; c < nchunks; ++c) {
+                if (!PLAIN && __builtin_amdgcn_readfirstlane(stop)) break;
+                __syncthreads();
+                at_buf = (c & 1) * 2 * BUF;
+                if (!PLAIN) stop = flag[c & 1];
+                multiply(F0{});
+                multiply(F1{});
+            }
+        }
+    } else {
+        if (!PLAIN && thread == 0) *flag = 0;
+        load_a(wgrp, F0{});
+        load_b(wgrp, F0{});
+        load_a(wgrp, F1{});
+        load_b(wgrp, F1{});
+        store_half(F0{}, wgrp);
+        load_a(wgrp + NWG, F0{});
+        load_b(wgrp + NWG, F0{});
+        int end = (nchunks + NWG - 1) / NWG * NWG;       // the barriers are the work-group's
+#pragma unroll 1
+        for (int c = wgrp; c < end; c += NWG) {
+            __syncthreads();
+            // set between the barriers of a round and read behind the second, so every wave reads the same
+            if (!PLAIN && lost_bits(lost)) *flag = 1;
+            half(F0{}, c, c + NWG);
+            __syncthreads();
+            const int stop = PLAIN ? 0 : *flag;
+            half(F1{}, c + NWG, c + 2 * NWG);
+            if (!PLAIN && __builtin_amdgcn_readfirstlane(stop)) end = 0;
+        }
     }
-    if (!PLAIN) {
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
+        for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[mb][nb][r] += low[mb][nb][r];
-    }
+            for (int r = 0; r < 16; ++r) {
+                if (!PLAIN) acc[mb][nb][r] += low[mb][nb][r];
+                if (SPEC) acc[mb][nb][r] += sums_of[SUMS - 1][mb][nb][r];
+            }
     if (NWG > 1) {
         // every staging buffer is free: groups 1 .. NWG-1 leave their accumulators there, group 0 adds
         // them in group order
@@ -332,7 +395,7 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
             for (int nb = 0; nb < 2; ++nb) sums.check(acc[mb][nb]);
         if (__syncthreads_or(lost_bits(lost) || sums.refused())) return false;
     }
-    if (NWG > 1 && wgrp > 0) return true;
+    if (stager || (NWG > 1 && wgrp > 0)) return true;
 
     // accumulator register r of lane (h, r32): row 8*(r/4) + 4*h + r%4 of block mb, columns 2*(wn*32 + r32) + nb:
     // 32 lanes write 256 contiguous bytes of a row, and C is not read again (non-temporal)
@@ -364,13 +427,13 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
 // kernels did (4096^3, probabilities of a steep softmax: 1050 to 1080 us against 1003); infinities, NaN and a last
 // chunk's lost pieces cost both tries (1870).  Operand by operand, without staging, it was 5020.  The flag costs an
 // ordinary product 1.4 % (set at the end of a round instead, where it cuts the schedule in two, 6 %).
-template <int BM, int BN, int WM, int WN, int NWG, int MINW, bool NT>
-__global__ __launch_bounds__(64 * WM * WN * NWG, MINW) void gemm_split_kernel(const GemmArgs p, const Grid g)
+template <int BM, int BN, int WM, int WN, int NWG, bool SPEC, int MINW, bool NT>
+__global__ __launch_bounds__(64 * WM * WN * (SPEC ? 2 : NWG), MINW) void gemm_split_kernel(const GemmArgs p, const Grid g)
 {
     int thread = threadIdx.x;
-    if (compute_tile<BM, BN, WM, WN, NWG, NT, false>(p, g, thread)) return;
+    if (compute_tile<BM, BN, WM, WN, NWG, SPEC, NT, false>(p, g, thread)) return;
     asm("" : "+v"(thread));                          // nothing of the second try is held through the first
-    compute_tile<BM, BN, WM, WN, NWG, NT, true>(p, g, thread);
+    compute_tile<BM, BN, WM, WN, NWG, SPEC, NT, true>(p, g, thread);
 }
 
 }  // namespace gsplit

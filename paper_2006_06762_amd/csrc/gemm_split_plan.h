@@ -42,11 +42,12 @@ constexpr bool second_of_pair(int col, int N) { return col == N - 1; }
 // more CUs, and wave groups shorten the chain of chunks where there are not enough tiles even so.  The figures
 // are those that chose best among all five variants timed on 550 products of 32 to 4096 (0.2 % slower than the
 // best one on average, 12 % at most), near a least-squares fit of the estimate itself.
+// 128 with two groups is the form whose second group of waves stages what the first one multiplies.
 struct Variant {
     int tile, groups;
     double base, round, busy, ends;      // us
 };
-constexpr Variant kVariants[] = {{128, 1, 5.5, 2.64, 1.49, 1.36}, {128, 2, 1.2, 1.30, 1.53, 8.91}, {64, 1, 4.9, 1.88, 0.46, 0.42},
+constexpr Variant kVariants[] = {{128, 1, 5.5, 2.64, 1.49, 1.36}, {128, 2, 3.8, 1.56, 1.555, 3.2}, {64, 1, 4.9, 1.88, 0.46, 0.42},
                                  {64, 2, 6.3, 1.48, 0.44, 0.94}, {64, 4, 2.4, 1.79, 0.44, 6.24}};
 constexpr int kVariantCount = sizeof(kVariants) / sizeof(kVariants[0]);
 
