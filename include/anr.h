@@ -285,7 +285,8 @@ enum {
     ANR_CONV_KERNEL_BIGTAPS = 3,   /* 5x5 / 7x7 kernels: one channel per chunk, or the stem kernel  */
     ANR_CONV_KERNEL_GATHER = 4,    /* any-geometry gather kernel                                  */
     ANR_CONV_KERNEL_DIRECT = 5,    /* one thread per output (extents beyond 32-bit offsets)       */
-    ANR_CONV_KERNEL_POINTWISE = 6  /* streaming 1x1 kernel for layers with few channels           */
+    ANR_CONV_KERNEL_POINTWISE = 6  /* 1x1: streaming kernel for layers with few channels, or the
+                                      GEMM of weights and images (its tile is square)             */
 };
 typedef struct {
     int32_t kernel;                /* ANR_CONV_KERNEL_*                                           */

@@ -63,8 +63,14 @@ struct GemmArgs {
     int64_t sAo, sAi, sBo, sBi, sCo, sCi;
     bool b_is_nk;
     bool softmax_rows;   // TBS: softmax over each output row (requires N <= 1024)
+    // launch_gemm_split only: batch norm and ReLU per row of C, as in ConvArgs (null: none)
+    const float *gamma, *beta, *mean, *var, *scale_shift;
+    float eps;
 };
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream);
+// The bf16-split GEMM alone (A.B with K >= 32, N >= 2, extents below 2^29 floats), and the edge of its tile.
+hipError_t launch_gemm_split(const GemmArgs& a, hipStream_t stream);
+int gemm_split_tile(const GemmArgs& a);
 // The TBS batch matmul (a.b_is_nk set, batch = B*H, batch_inner = H), optionally followed by the
 // row softmax; picks the dedicated tile kernel when the operands allow it.
 hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream);

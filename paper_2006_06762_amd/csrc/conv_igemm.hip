@@ -280,7 +280,7 @@ bool describe_conv2d_igemm(const ConvArgs& a, ConvRoute* r)
 
 void describe_conv2d(const ConvArgs& a, ConvRoute* r)
 {
-    if (describe_conv2d_igemm(a, r) || describe_conv2d_pointwise(a, r) || describe_conv2d_stem(a, r) || describe_conv2d_gather(a, r))
+    if (describe_conv2d_igemm(a, r) || describe_conv2d_pointwise(a, r) || describe_conv2d_pointwise_gemm(a, r) || describe_conv2d_stem(a, r) || describe_conv2d_gather(a, r))
         return;
     *r = ConvRoute{5, 0, 0, 1, 1, 0, 0};
 }
@@ -297,7 +297,7 @@ size_t conv2d_workspace_bytes(const ConvArgs& a)
 {
     if (conv2d_igemm_takes(a)) return 0;
     ConvRoute r;
-    if (describe_conv2d_pointwise(a, &r) || describe_conv2d_stem(a, &r)) return 0;
+    if (describe_conv2d_pointwise(a, &r) || describe_conv2d_pointwise_gemm(a, &r) || describe_conv2d_stem(a, &r)) return 0;
     return conv2d_gather_workspace_bytes(a);
 }
 
@@ -348,6 +348,8 @@ hipError_t launch_conv2d(const ConvArgs& a, hipStream_t stream, int* ws_fault)
     hipError_t err = launch_conv2d_igemm(a, stream, &taken);
     if (taken || err != hipSuccess) return err;
     err = launch_conv2d_pointwise(a, stream, &taken);
+    if (taken || err != hipSuccess) return err;
+    err = launch_conv2d_pointwise_gemm(a, stream, &taken);
     if (taken || err != hipSuccess) return err;
     err = launch_conv2d_stem(a, stream, &taken);
     if (taken || err != hipSuccess) return err;

@@ -26,15 +26,19 @@ double conv2d_gather_estimate_us(const ConvArgs& a);
 // Streaming kernel for pointwise layers with few channels (conv_pointwise_kernel.h); same contract.
 hipError_t launch_conv2d_pointwise(const ConvArgs& a, hipStream_t stream, bool* taken);
 
-// Kernel for images of two or three channels with 7 x 7 kernels (conv_stem.hip); same contract.
-hipError_t launch_conv2d_stem(const ConvArgs& a, hipStream_t stream, bool* taken);
-
 // What a launch would do, for introspection (nothing is launched).
 struct ConvRoute {
     int kernel;          // 1 patch-staging, 2 taps, 3 bigtaps, 4 gather, 5 direct, 6 pointwise stream (the public ANR_CONV_KERNEL_* values)
     int tile_m, tile_n, ksplit, wave_groups, work_groups;
     size_t workspace_bytes;
 };
+// Pointwise layers as a batched GEMM, weights times image, on planes that are no whole 16-byte units; same contract.
+hipError_t launch_conv2d_pointwise_gemm(const ConvArgs& a, hipStream_t stream, bool* taken);
+bool describe_conv2d_pointwise_gemm(const ConvArgs& a, ConvRoute* r);
+
+// Kernel for images of two or three channels with 7 x 7 kernels (conv_stem.hip); same contract.
+hipError_t launch_conv2d_stem(const ConvArgs& a, hipStream_t stream, bool* taken);
+
 bool describe_conv2d_igemm(const ConvArgs& a, ConvRoute* r);
 bool describe_conv2d_gather(const ConvArgs& a, ConvRoute* r);
 bool describe_conv2d_pointwise(const ConvArgs& a, ConvRoute* r);

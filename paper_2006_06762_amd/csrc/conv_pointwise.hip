@@ -60,4 +60,62 @@ hipError_t launch_conv2d_pointwise(const ConvArgs& a, hipStream_t stream, bool* 
     }
 }
 
+namespace {
+
+// y[n] = w . x[n] on the bf16-split GEMM (M = K output channels, N = a plane, K = C; batch norm and ReLU per row where it
+// stores), once there are tiles for most of the chip.  On planes that are no multiple of four pixels the convolution
+// kernels store four bytes at a time: from 170 tiles of 64 x 64 on (batch 16, 48 -> 160 on 171 x 171 323 -> 156 us, batch 32, 64 ->
+// 384 on 45 x 45 87 -> 43, batch 16, 64 -> 64 on 29 x 29 8.1 -> 7.4; 128 tiles 10.9 -> 11.1, 20 to 40 tiles 8.2 -> 9.4).  On others from
+// 700 on and 96 channels (batch 16, 256 -> 256 on 84 x 84 148 -> 113, batch 32, 512 -> 256 on 20 x 20 41 -> 33; 288 tiles 13.7 ->
+// 16.2, 504 tiles 15.5 -> 15.7); fewer channels were not tried there.
+bool pointwise_gemm(const ConvArgs& a, GemmArgs* g)
+{
+    const int64_t plane = (int64_t)a.H * a.W;
+    if (a.route != 0 || a.R != 1 || a.S != 1 || a.stride_h != 1 || a.stride_w != 1 || a.pad_h != 0 || a.pad_w != 0 || a.groups != 1 ||
+        a.xs[2] != a.W || a.ys[2] != a.OW || plane < 256 || plane >= ((int64_t)1 << 29) || a.C < 32 || a.K < 48)
+        return false;
+    if ((int64_t)a.K * a.C >= ((int64_t)1 << 29) || (int64_t)(a.C - 1) * a.xs[1] + plane >= ((int64_t)1 << 29)) return false;
+    const int64_t tiles = (int64_t)((a.K + 63) / 64) * ((plane + 63) / 64) * a.N;
+    if (tiles < (plane % 4 ? 170 : 700) || (plane % 4 == 0 && (a.C < 96 || a.K < 96)) || tiles >= ((int64_t)1 << 22)) return false;
+    *g = GemmArgs{};
+    g->A = a.w;
+    g->B = a.x;
+    g->C = a.y;
+    g->M = a.K;
+    g->N = (int)plane;
+    g->K = a.C;
+    g->lda = a.C;
+    g->ldb = a.xs[1];
+    g->ldc = a.ys[1];
+    g->batch = a.N;
+    g->batch_inner = 1;
+    g->sBo = a.xs[0];
+    g->sCo = a.ys[0];
+    g->gamma = a.gamma;
+    g->beta = a.beta;
+    g->mean = a.mean;
+    g->var = a.var;
+    g->scale_shift = a.scale_shift;
+    g->eps = a.eps;
+    return true;
+}
+
+}  // namespace
+
+bool describe_conv2d_pointwise_gemm(const ConvArgs& a, ConvRoute* r)
+{
+    GemmArgs g;
+    if (!pointwise_gemm(a, &g)) return false;
+    const int tile = gemm_split_tile(g);
+    *r = ConvRoute{6, tile, tile, 1, 1, (int)(((int64_t)(g.M + tile - 1) / tile) * ((g.N + tile - 1) / tile) * g.batch), 0};
+    return true;
+}
+
+hipError_t launch_conv2d_pointwise_gemm(const ConvArgs& a, hipStream_t stream, bool* taken)
+{
+    GemmArgs g;
+    *taken = pointwise_gemm(a, &g);
+    return *taken ? launch_gemm_split(g, stream) : hipSuccess;
+}
+
 }  // namespace anr

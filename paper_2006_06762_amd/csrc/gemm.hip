@@ -561,6 +561,10 @@ hipError_t launch_gemm(const GemmArgs& args, hipStream_t stream)
     return err;
 }
 
+hipError_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) { return launch_split_any<false>(a, stream); }
+
+int gemm_split_tile(const GemmArgs& a) { return gsplit::kVariants[gsplit::choose_variant(a.M, a.N, a.K, a.batch)].tile; }
+
 hipError_t launch_softmax_rows(const GemmArgs& a, hipStream_t stream)
 {
     const int64_t rows = (int64_t)a.batch * a.M;

@@ -73,6 +73,7 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
     constexpr int PA = Plane<BM>::BYTES, PB = Plane<BN>::BYTES;
     constexpr int BUF = 3 * (PA + PB);
     constexpr int RED = BM * BN * 4;                 // a group's accumulators
+    static_assert(BM <= T, "a thread per row");
     static_assert(NWG == 1 || (NWG - 1) * RED <= NWG * 2 * BUF, "the groups' sums meet in the staging buffers");
 
     extern __shared__ __attribute__((aligned(16))) char slds[];
@@ -395,6 +396,18 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
             for (int nb = 0; nb < 2; ++nb) sums.check(acc[mb][nb]);
         if (__syncthreads_or(lost_bits(lost) || sums.refused())) return false;
     }
+    // scale and shift of the tile's rows
+    float* const row_scale = reinterpret_cast<float*>(slds);
+    if (p.gamma) {
+        __syncthreads();                             // the staging buffers are free
+        if (thread < BM) {
+            const int row = min(m0 + thread, M - 1);
+            const float scale = p.scale_shift ? p.scale_shift[row] : p.gamma[row] / sqrtf(p.var[row] + p.eps);
+            row_scale[thread] = scale;
+            row_scale[BM + thread] = p.scale_shift ? p.scale_shift[M + row] : p.beta[row] - p.mean[row] * scale;
+        }
+        __syncthreads();
+    }
     if (stager || (NWG > 1 && wgrp > 0)) return true;
 
     // accumulator register r of lane (h, r32): row 8*(r/4) + 4*h + r%4 of block mb, columns 2*(wn*32 + r32) + nb:
@@ -411,9 +424,14 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
             for (int r = 0; r < 16; ++r) {
                 const int dr = 8 * (r / 4) + (r % 4);
                 float* const d = c + (int64_t)dr * p.ldc;
-                const pair v = {acc[mb][0][r], acc[mb][1][r]};
+                pair v = {acc[mb][0][r], acc[mb][1][r]};
+                if (p.gamma) {
+                    const float scale = row_scale[row0 - m0 + dr], shift = row_scale[BM + row0 - m0 + dr];
+                    v[0] = fmaxf(fmaf(v[0], scale, shift), 0.f);
+                    v[1] = fmaxf(fmaf(v[1], scale, shift), 0.f);
+                }
                 if (whole || (row0 + dr < M && col + 1 < N)) __builtin_nontemporal_store(v, reinterpret_cast<pair*>(d));
-                else if (row0 + dr < M && col < N) *d = acc[mb][!NT && second_of_pair(col, N)][r];
+                else if (row0 + dr < M && col < N) *d = v[!NT && second_of_pair(col, N)];
             }
         }
     };

@@ -51,22 +51,20 @@ constexpr Variant kVariants[] = {{128, 1, 5.5, 2.64, 1.49, 1.36}, {128, 2, 3.8, 
                                  {64, 2, 6.3, 1.48, 0.44, 0.94}, {64, 4, 2.4, 1.79, 0.44, 6.24}};
 constexpr int kVariantCount = sizeof(kVariants) / sizeof(kVariants[0]);
 
-constexpr int choose_variant(int64_t M, int64_t N, int64_t K, int64_t batch)
+constexpr double estimate_us(const Variant& t, int64_t M, int64_t N, int64_t K, int64_t batch)
 {
     const int64_t chunks = (K + KC - 1) / KC;
+    const int64_t tiles = ((M + t.tile - 1) / t.tile) * ((N + t.tile - 1) / t.tile) * batch;
+    const double chain = (double)((chunks + t.groups - 1) / t.groups) * t.round;
+    const double work = (double)((tiles + 255) / 256) * ((double)chunks * t.busy + t.ends);
+    return t.base + (work > chain ? work : chain);
+}
+
+constexpr int choose_variant(int64_t M, int64_t N, int64_t K, int64_t batch)
+{
     int best = 0;
-    double best_us = 0.0;
-    for (int v = 0; v < kVariantCount; ++v) {
-        const Variant& t = kVariants[v];
-        const int64_t tiles = ((M + t.tile - 1) / t.tile) * ((N + t.tile - 1) / t.tile) * batch;
-        const double chain = (double)((chunks + t.groups - 1) / t.groups) * t.round;
-        const double work = (double)((tiles + 255) / 256) * ((double)chunks * t.busy + t.ends);
-        const double us = t.base + (work > chain ? work : chain);
-        if (v == 0 || us < best_us) {
-            best = v;
-            best_us = us;
-        }
-    }
+    for (int v = 1; v < kVariantCount; ++v)
+        if (estimate_us(kVariants[v], M, N, K, batch) < estimate_us(kVariants[best], M, N, K, batch)) best = v;
     return best;
 }
 
