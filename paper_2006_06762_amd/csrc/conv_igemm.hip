@@ -142,8 +142,8 @@ void plan_igemm(const ConvArgs& a, IgemmPlan* p)
         return;
     }
     // The bf16-split tile at any width, where its estimate is the shorter one by the estimates' spread (81 x 81, 512 -> 96, batch
-    // 4, 304 -> 207 us; 57 x 57, 64 -> 512, batch 4, 81 -> 61; 42 x 42, 128 -> 160, batch 32, 211 -> 169; 124 x 124, 32 -> 512, batch
-    // 7, 468 -> 282; on average 0.82 of the time of the layers that take it).  Few or half-filled rounds, channels far from a
+    // 4, 307 -> 215 us; 57 x 57, 64 -> 512, batch 4, 81 -> 65; 42 x 42, 128 -> 160, batch 32, 214 -> 184; 124 x 124, 32 -> 512, batch
+    // 7, 452 -> 318, weights not packed; on average 0.82 of the time of the layers that take it).  Few or half-filled rounds, channels far from a
     // multiple of 64 and few input channels leave it behind (38 x 38, 128 -> 64, batch 16, 42 against 51).
     IgemmPlan wide;
     if (plan_wide(a, &wide) && wide_us(a, wide) < 0.93 * (tuned ? fp32_us(a, p->g, best) : conv2d_gather_estimate_us(a))) {

@@ -64,9 +64,9 @@ namespace {
 
 // y[n] = w . x[n] on the bf16-split GEMM (M = K output channels, N = a plane, K = C; batch norm and ReLU per row where it
 // stores), once there are tiles for most of the chip.  On planes that are no multiple of four pixels the convolution
-// kernels store four bytes at a time: from 170 tiles of 64 x 64 on (batch 16, 48 -> 160 on 171 x 171 323 -> 156 us, batch 32, 64 ->
-// 384 on 45 x 45 87 -> 43, batch 16, 64 -> 64 on 29 x 29 8.1 -> 7.4; 128 tiles 10.9 -> 11.1, 20 to 40 tiles 8.2 -> 9.4).  On others from
-// 700 on and 96 channels (batch 16, 256 -> 256 on 84 x 84 148 -> 113, batch 32, 512 -> 256 on 20 x 20 41 -> 33; 288 tiles 13.7 ->
+// kernels store four bytes at a time: from 170 tiles of 64 x 64 on (batch 16, 48 -> 160 on 171 x 171 310 -> 161 us, batch 32, 64 ->
+// 384 on 45 x 45 87 -> 46, batch 16, 64 -> 64 on 29 x 29 7.8 -> 7.5; 128 tiles 10.9 -> 11.1, 20 to 40 tiles 8.2 -> 9.4).  On others from
+// 700 on and 96 channels (batch 16, 256 -> 256 on 84 x 84 150 -> 118, batch 32, 512 -> 256 on 20 x 20 41 -> 32; 288 tiles 13.7 ->
 // 16.2, 504 tiles 15.5 -> 15.7); fewer channels were not tried there.
 bool pointwise_gemm(const ConvArgs& a, GemmArgs* g)
 {

@@ -381,7 +381,7 @@ __global__ __launch_bounds__(256) void dwconv_small_planes_kernel(const ConvArgs
 // once and by consecutive lanes, and a thread walks down kBandRows outputs of one column, so that an output costs
 // S + (R - stride) * S / kBandRows LDS reads.  The taps of an output are added in the order of the direct kernel
 // (same bits).  Bound: memory for 3 x 3, LDS reads for 5 x 5.  One thread per output / this: 141 x 141 x 104, batch
-// 32, 564 / 150 us; 115 x 115 x 343, batch 16, 616 / 156 (3.7 TB/s); 95 x 95 x 304, stride 2, batch 32, 228 / 106;
+// 32, 563 / 156 us; 115 x 115 x 343, batch 16, 616 / 154 (3.8 TB/s); 95 x 95 x 304, stride 2, batch 32, 228 / 106;
 // 68 x 68 x 924, 5 x 5, batch 16, 1094 / 175.
 constexpr int kBandRows = 8;          // outputs of a thread's walk
 

@@ -1,7 +1,8 @@
 // fp32 GEMM on the MFMA units of gfx950: the GMM operator (C = A.B, Sec. 4.1 of
 // arXiv 2006.06762) and the batch matmul of the TBS subgraph (Sec. 7.2) in its
-// A.B^T form.  Four kernels, chosen in launch_gemm: the wave-split-K kernel below for small
-// products of K = 128, 256 and 512, gemm_pipe_kernel for other small aligned ones,
+// A.B^T form.  Five kernels, chosen in launch_gemm: the wave-split-K kernel below for small
+// aligned products of K = 128, 256 and 512, gemm_rows32_kernel for others of few 32 x 32 tiles,
+// gemm_pipe_kernel for aligned ones of few 64 x 64 tiles and a short reduction,
 // gemm_split_kernel for everything larger, and gemm_kernel for what those leave (extents beyond
 // 32-bit offsets, unaligned products of few tiles and a short reduction).
 //
@@ -526,8 +527,8 @@ hipError_t launch_gemm(const GemmArgs& args, hipStream_t stream)
     const bool offsets32 = a_ext < ((int64_t)1 << 29) && b_ext < ((int64_t)1 << 29) && tiles64 < ((int64_t)1 << 22);
     bool piped = false;
     // Few 32 x 32 tiles: gemm_rows32_kernel, whatever the alignment.  Up to a tile per CU from K = 65 on (283 x 821 x 83
-    // 6.6 -> 4.8 us, 449 x 450 x 1920 36 -> 17), or from 97 where the pipelined kernel can load the operands (2560 x 32 x
-    // 96 5.1 -> 5.5), up to two from 97 (1422 x 200 x 510 15.2 -> 13.1, 192 x 2464 x 320 10.1 -> 10.0); past that each CU has
+    // 6.9 -> 5.6 us, 449 x 450 x 1920 36 -> 16), or from 97 where the pipelined kernel can load the operands (2560 x 32 x
+    // 96 5.1 -> 5.5), up to two from 97 (1422 x 200 x 510 14.7 -> 12.5, 192 x 2464 x 320 10.1 -> 10.0); past that each CU has
     // more work than its own chain and larger tiles reuse more (520 tiles, K = 384, 11.6 -> 13.3).
     const int64_t tiles_rows32 = (int64_t)((a.M + 31) / 32) * ((a.N + 31) / 32) * a.batch;
     if (offsets32 && !a.b_is_nk && !a.softmax_rows && a.batch_inner == 1 && a.K > (tiles_rows32 <= 256 && !vec ? 64 : 96) && tiles_rows32 <= 512)

@@ -6,8 +6,8 @@
 //
 // Bound: a chain of latencies per wave (load, LDS, sixteen matrix instructions) with the waves of a SIMD in
 // different places of theirs.  The kernels with 64-wide tiles, which these products took before, leave most CUs idle and
-// walk the chunks with a barrier each: 32 x 512 x 1408 26 -> 12 us, 96 x 1088 x 3648 63 -> 27, 553 x 420 x 1298 29 -> 13, 16 x
-// 130 x 68 x 3577 62 -> 27, 192 x 1408 x 864 20 -> 14.
+// walk the chunks with a barrier each: 32 x 512 x 1408 27 -> 12 us, 96 x 1088 x 3648 63 -> 26, 553 x 420 x 1298 29 -> 14, 16 x
+// 130 x 68 x 3577 62 -> 28, 192 x 1408 x 864 20 -> 14.
 //
 // The sums of short runs of k meet in a compensated one, so the error does not grow with K: relative to the exact
 // results 6.0e-8 (four or two runs a chunk), 8.5e-8 (one); with the bf16-split GEMM it was 5.7e-8 at K = 165, 7.0e-8

@@ -38,7 +38,7 @@ __device__ __forceinline__ float block_sum(float v, float* red)
 // PACKED: rows back to back, so a slice is one contiguous run whatever its alignment: up to three floats, 16-byte units,
 // up to three floats.  Otherwise a thread steps through the flattened matrix by carrying row and column along.
 // One element and one 64-bit division at a time, as both had it unless everything was a multiple of four, 16 matrices of
-// 131 x 161 took 13.2 us, of 177 x 999 26.2, of 3651 x 86 28.2; PACKED 7.1, 7.2 and 9.4.
+// 131 x 161 took 13.1 us, of 177 x 999 26.1, of 3651 x 86 28.3; PACKED 7.2, 7.1 and 7.8.
 template <bool PACKED, bool ONCE>
 __global__ __launch_bounds__(kNT) void nrm_partial_kernel(const NrmArgs p, int64_t per_part, int parts)
 {

@@ -94,8 +94,8 @@ hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
     // 152).  The split GEMM keeps its sizes: its scores are the closer ones, and those tbg gives for them.  A
     // work-group walks the keys in a row, so with few work-groups and a long walk the two kernels are faster (8 heads of
     // 300 x 300 x 128 11.1 / 16.1, x 64 9.8 / 10.4, x 32 9.7 / 8.5; 12 heads of 492 x 492 x 128 19.4 / 21.9, 16 of 400 x
-    // 400 x 128 23.8 / 21.0), and so they
-    // are for wide heads with a third of the last keys missing (64 of 300 x 300 x 128 39.0 / 41.7).
+    // 400 x 128 23.8 / 21.0), and so they are for wide heads with a third of the last keys missing (64 of 300 x 300 x 128
+    // 39.0 / 41.7).
     const int64_t long_items = (int64_t)a.batch * ((a.M + 31) / 32);
     const int long_chunks = (a.M + 127) / 128;
     const bool long_pays = (long_items > (a.K > 96 ? 200 : 160) || long_chunks * a.K <= 128) && !(a.K > 96 && long_chunks == 3 && long_items < 1024);
