@@ -13,8 +13,9 @@ constexpr uint32_t kOutOfRange = 0x80000000u;        // byte offset beyond any d
 constexpr int smaller(int a, int b) { return a < b ? a : b; }
 
 // First k that chunk c loads.  The last chunk of a K that is no multiple of 32 starts at K - 32, inside the
-// matrix, and what an earlier chunk has counted is cleared in A (`counts`).  A K below 32 comes in the A.B^T form
-// only: the chunk starts at zero, and what its rows read past K is cleared in both operands.
+// matrix, and what an earlier chunk has counted is cleared in A (`counts`), in the A.B^T form and in the fp32
+// instruction's try in B too.  A K below 32 comes in the A.B^T form only: the chunk starts at zero, and what its rows
+// read past K is cleared in both operands.
 constexpr int chunk_k0(int c, int K) { return K < KC ? 0 : smaller(c * KC, K - KC); }
 constexpr bool counts(int c, int k, int K) { return k >= c * KC && k < K; }
 

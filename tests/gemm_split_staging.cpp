@@ -1,6 +1,7 @@
 // Walks what every thread of a work-group of the bf16-split GEMM loads, tile by tile and chunk by chunk, with
 // the arithmetic the kernel itself uses, and multiplies what it stages.  Prints one line and exits non-zero if
-// a load touches an element outside its matrix or the products are not those of whole numbers.
+// a load touches an element outside its matrix, the products are not those of whole numbers, or something that is
+// not counted is multiplied.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -37,7 +38,7 @@ int main(int argc, char** argv)
         for (int k = 0; k < K; ++k) B[nt ? (size_t)j * ldb + k : (size_t)k * ldb + j] = (j * 13 + k * 7) % 19 - 9;
 
     const int nchunks = (K + KC - 1) / KC, iters = (nchunks + groups - 1) / groups;
-    long wrong = 0;
+    long wrong = 0, kept = 0;
     std::vector<int> sa((size_t)tile * KC), sb((size_t)tile * KC);          // [row or column position][k of a chunk]
     std::vector<long> acc((size_t)tile * tile);
     for (int m0 = 0; m0 < M; m0 += tile)
@@ -66,10 +67,17 @@ int main(int argc, char** argv)
                                     const int64_t lane = (int64_t)piece_k(bt, at) * ldb + piece_col(n0 + 2 * pair, N) + b;
                                     const int step = k0 + piece_step(f, e);
                                     const int v = load(B, lane + (c < nchunks ? 0 : (int64_t)1 << 40), (int64_t)step * ldb);
-                                    sb[(size_t)(2 * pair + b) * KC + piece_k(bt, at) + piece_step(f, e)] = v;
+                                    const int off = piece_k(bt, at) + piece_step(f, e);
+                                    const bool in = c * KC + KC <= K || counts(c, k0 + off, K);
+                                    sb[(size_t)(2 * pair + b) * KC + off] = in ? v : 0;
                                 }
                         }
                     }
+                    // as the try with the fp32 instruction stages it, whatever is not counted is zero on both sides: one of
+                    // them may hold an infinity
+                    for (int r = 0; r < tile; ++r)
+                        for (int k = 0; k < KC; ++k)
+                            if (c < nchunks && !counts(c, k0 + k, K)) kept += (sa[(size_t)r * KC + k] != 0) + (sb[(size_t)r * KC + k] != 0);
                     for (int r = 0; r < tile; ++r)
                         for (int j = 0; j < tile; ++j)
                             for (int k = 0; k < KC; ++k) acc[(size_t)r * tile + j] += (long)sa[(size_t)r * KC + k] * sb[(size_t)j * KC + k];
@@ -84,6 +92,6 @@ int main(int argc, char** argv)
                     wrong += acc[(size_t)(r - m0) * tile + (held - n0)] != want;
                 }
         }
-    printf("%ld outside, %ld wrong\n", outside, wrong);
-    return outside != 0 || wrong != 0;
+    printf("%ld outside, %ld wrong, %ld kept\n", outside, wrong, kept);
+    return outside != 0 || wrong != 0 || kept != 0;
 }

@@ -86,3 +86,20 @@ def test_values_the_pieces_cannot_carry(value):
     ok = ok.cuda() & fused.isfinite()                    # (a scale above one takes 3.4e38 past the largest float)
     assert torch.equal(y2.isinf(), fused.isinf())
     assert bool(((y2 - fused).abs()[ok] <= 1e-4 * fused.abs().clamp(min=1.0)[ok]).all())
+
+
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[1] % 32])
+@pytest.mark.parametrize("value", [float("inf"), -float("inf")])
+def test_an_infinite_pixel_in_channels_that_two_chunks_load(shape, value):
+    """C is no multiple of 32, so the last chunk starts at C - 32: an infinite pixel there is multiplied by its own
+    weights alone, and the fused form keeps what survives the ReLU."""
+    from paper_2006_06762_amd import binding as anr
+    s, x, w, xv, wd, ybuf, y = tensors(shape, 6300, False, 0, 0)
+    xv[s.N - 1, s.C // 32 * 32 - 1, 7, 5] = value
+    anr.conv2d(xv, wd, y)
+    at = y[s.N - 1, :, 7, 5]
+    want = torch.sign(wd[:, s.C // 32 * 32 - 1, 0, 0]) * value
+    assert torch.equal(at, want) and int((~y.isfinite()).sum()) == s.K
+    bn = [torch.from_numpy(v).cuda() for v in I.bn_inputs(s.K, 6301)]
+    anr.conv_bn_relu(xv, wd, *bn, I.BN_EPS, y)
+    assert torch.equal(y[s.N - 1, :, 7, 5], torch.relu(want * bn[0])) and int((~y.isfinite()).sum()) == int((want * bn[0] > 0).sum())

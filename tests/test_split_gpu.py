@@ -163,6 +163,19 @@ def test_split_gemm_variants(anr, variant, what):
     assert bool((buf[:64] == 7.0).all()) and bool((buf[-64:] == 7.0).all())
 
 
+# A last chunk that is no whole one starts at K - 32 and passes over what was counted: values there are multiplied once,
+# with their own partners alone, whichever operand and order of infinities
+@pytest.mark.parametrize("batch,M,N,K", [*VARIANTS.values(), (1, 1100, 1000, 333), (1, 2000, 1900, 200), (2, 1040, 1050, 63)])
+def test_split_gemm_infinities_in_the_last_chunks_overlap(anr, batch, M, N, K):
+    A, B = uniform(51, batch, M, K), uniform(52, batch, K, N)
+    B[0, K // 32 * 32 - 1, N - 1] = float("inf")
+    B[batch - 1, K - 32, 0] = -float("inf")
+    A[batch - 1, M // 2, max(K // 32 * 32 - 9, K - 32)] = float("inf")
+    C = torch.empty(batch, M, N, device="cuda")
+    anr.gemm(A, B, C)
+    assert_product(C, A, B)
+
+
 # ... and scores that the dispatch takes from the tile kernels: heads of 256 and more in whole chunks, parts of one
 # (K below the 32 of a chunk) and a ragged last tile
 @pytest.mark.parametrize("B,S,H,D", [*SCORES.values(), (16, 256, 8, 32), (16, 256, 8, 24), (16, 256, 8, 128), (16, 360, 8, 96)])
