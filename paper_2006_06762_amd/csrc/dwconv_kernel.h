@@ -380,9 +380,9 @@ __global__ __launch_bounds__(256) void dwconv_small_planes_kernel(const ConvArgs
 // output rows (or G whole planes), brings the input rows they need to LDS with their padding as zeros, every element
 // once and by consecutive lanes, and a thread walks down kBandRows outputs of one column, so that an output costs
 // S + (R - stride) * S / kBandRows LDS reads.  The taps of an output are added in the order of the direct kernel
-// (same bits).  Bound: memory for 3 x 3, LDS reads for 5 x 5.  One thread per output / this: 141 x 141 x 104, batch
-// 32, 563 / 156 us; 115 x 115 x 343, batch 16, 616 / 154 (3.8 TB/s); 95 x 95 x 304, stride 2, batch 32, 228 / 106;
-// 68 x 68 x 924, 5 x 5, batch 16, 1094 / 175.
+// (same bits, whatever the weights: see below).  Bound: memory for 3 x 3, LDS reads for 5 x 5.  One thread per output / this: 141 x 141 x 104, batch
+// 32, 563 / 121 us; 115 x 115 x 343, batch 16, 616 / 122 (4.8 TB/s); 95 x 95 x 304, stride 2, batch 32, 228 / 94;
+// 68 x 68 x 924, 5 x 5, batch 16, 1094 / 134.  (Before the test of the weights ahead of a walk 155, 153, 106 and 172.)
 constexpr int kBandRows = 8;          // outputs of a thread's walk
 
 struct Band {
@@ -447,6 +447,27 @@ __global__ __launch_bounds__(256) void dwconv_band_kernel(const ConvArgs p, cons
         const float* const in = dlds + pl * g.per_plane + oh * ST * g.wl + ow * ST;
         float* const out = p.y + n * p.ys[0] + c * p.ys[1] + (int64_t)(oh0 + oh) * p.ys[2] + ow;
         const int left = min(g.rows, p.OH - oh0) - oh;       // outputs of this walk
+        // zeros stand for the padding, which an infinite or NaN weight must not meet: its channel is summed tap by tap, as
+        // the direct kernel does
+        float none = 0.f;
+#pragma unroll
+        for (int i = 0; i < K_ * K_; ++i) none = fmaf(w[i], 0.f, none);
+        if (none != 0.f) {
+#pragma unroll 1
+            for (int i = 0; i < min(left, kBandRows); ++i) {
+                float acc = 0.f;
+#pragma unroll
+                for (int r = 0; r < K_; ++r)
+#pragma unroll
+                    for (int s = 0; s < K_; ++s) {
+                        const int ih = row0 + (oh + i) * ST + r, iw = ow * ST + s - p.pad_w;
+                        if (((unsigned)ih < (unsigned)p.H) & ((unsigned)iw < (unsigned)p.W))
+                            acc = fmaf(in[(i * ST + r) * g.wl + s], w[r * K_ + s], acc);
+                    }
+                out[i * p.ys[2]] = acc;
+            }
+            continue;
+        }
         float win[K_][K_];
 #pragma unroll
         for (int r = 0; r < K_ - ST; ++r)

@@ -12,10 +12,13 @@ pytestmark = pytest.mark.gpu
 GUARD = 12345.0
 
 
-def run(s, seed, start=0, gap=0):
-    """start: floats x and y begin past an aligned address; gap: floats between the rows of x and of y."""
+def run(s, seed, start=0, gap=0, values=()):
+    """start: floats x and y begin past an aligned address; gap: floats between the rows of x and of y; values: (value, tap)
+    for every third channel's weights."""
     from paper_2006_06762_amd import binding as anr
     x, w = I.dwconv_inputs(s, seed, ints=True)
+    for value, tap in values:
+        w[tap % 3::3].reshape(-1, s.R * s.R)[:, tap] = value
     xbuf = torch.full((s.N * s.C * s.H * (s.W + gap) + 8,), float("nan"), device="cuda")
     xv = xbuf[start:start + s.N * s.C * s.H * (s.W + gap)].view(s.N, s.C, s.H, s.W + gap)[..., :s.W]
     xv.copy_(torch.from_numpy(x))
@@ -23,7 +26,7 @@ def run(s, seed, start=0, gap=0):
     ybuf = torch.full((n + 128,), GUARD, device="cuda")
     wide = ybuf[64 + start:64 + start + n].view(s.N, s.C, s.OH, s.OW + gap)
     anr.dwconv(xv, torch.from_numpy(w).cuda(), wide[..., :s.OW], s.stride, s.pad)
-    assert np.array_equal(wide[..., :s.OW].cpu().numpy().astype(np.float64), oracle.dwconv(x, w, s.stride, s.pad)), s
+    assert np.array_equal(wide[..., :s.OW].cpu().numpy().astype(np.float64), oracle.dwconv(x, w, s.stride, s.pad), equal_nan=True), s
     assert bool((wide[..., s.OW:] == GUARD).all()) and bool((ybuf[:64 + start] == GUARD).all())
     assert bool((ybuf[64 + start + n:] == GUARD).all())
 
@@ -42,3 +45,14 @@ def test_planes_in_groups_views_and_padding(H, W, R, stride, pad, start, gap):
     """Planes that are unaligned or whose rows lie apart: several to a work-group, or one."""
     s = I.ConvShape(5, 3001 if H * W < 300 else 901, H, W, 3001 if H * W < 300 else 901, R, R, (stride, stride), (pad, pad))
     run(s, 3100 + H, start, gap)
+
+
+@pytest.mark.parametrize("R", [3, 5])
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("H, W, planes, pad, start, gap", [(47, 61, 400, 1, 0, 0), (64, 67, 400, 2, 1, 3), (9, 259, 900, 0, 0, 0), (57, 57, 1100, 4, 0, 0),
+                                                           (14, 14, 8000, 1, 1, 0)])
+def test_weights_that_are_not_finite(R, stride, H, W, planes, pad, start, gap):
+    """A tap outside the image is no product: an infinite weight leaves the outputs whose tap it is there as they are."""
+    planes *= stride * stride
+    s = I.ConvShape(2, planes // 2, H, W, planes // 2, R, R, (stride, stride), (pad, pad))
+    run(s, 3200 + H, start, gap, [(float("inf"), 0), (float("nan"), R * R - 1), (-float("inf"), R // 2)])
