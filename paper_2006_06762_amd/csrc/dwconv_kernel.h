@@ -345,8 +345,9 @@ __global__ __launch_bounds__(256) void dwconv_small_planes_kernel(const ConvArgs
                     for (int s = 0; s < S_; ++s) {
                         const int ih = ih0 + r * p.dil_h, iw = iw0 + s * p.dil_w;
                         const bool ok = ((unsigned)ih < (unsigned)p.H) & ((unsigned)iw < (unsigned)p.W);
-                        const float v = xin[ok ? ih * p.W + iw : 0];
-                        acc = fmaf(ok ? v : 0.f, wt[r * S_ + s], acc);
+                        // a tap outside the image is passed over (zero times an infinite weight is not zero)
+                        const float with = fmaf(xin[ok ? ih * p.W + iw : 0], wt[r * S_ + s], acc);
+                        acc = ok ? with : acc;
                     }
             } else {
                 for (int r = 0; r < p.R; ++r)

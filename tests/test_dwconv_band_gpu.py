@@ -56,3 +56,9 @@ def test_weights_that_are_not_finite(R, stride, H, W, planes, pad, start, gap):
     planes *= stride * stride
     s = I.ConvShape(2, planes // 2, H, W, planes // 2, R, R, (stride, stride), (pad, pad))
     run(s, 3200 + H, start, gap, [(float("inf"), 0), (float("nan"), R * R - 1), (-float("inf"), R // 2)])
+
+
+@pytest.mark.parametrize("N, C, H, W, R, stride", [(2, 100, 7, 7, 3, 1), (3, 33, 14, 14, 5, 1), (2, 40, 13, 9, 3, 2), (1, 30, 7, 9, 7, 1)])
+def test_small_planes_pass_over_taps_outside_too(N, C, H, W, R, stride):
+    s = I.ConvShape(N, C, H, W, C, R, R, (stride, stride), (R // 2, R // 2))
+    run(s, 3300 + H, 0, 0, [(float("inf"), 0), (float("nan"), R * R - 1), (-float("inf"), R // 2)])
