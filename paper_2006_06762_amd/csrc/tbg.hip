@@ -90,8 +90,8 @@ hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
                        (double)a.M * a.M >= 0.6 * tiles128 * tiles128 * 128 * 128 && (double)a.M * a.M * a.batch >= 384.0 * 128 * 128 &&
                        (a.K >= 48 || a.M % tbg::kTile == 0) && !(whole && a.K <= tbg::kChunk);
     // What is left with a softmax and up to 512 keys: one kernel that keeps the scores on the chip (16 x 16 heads, two
-    // kernels / one: 160 x 160 x 64 52 / 29 us, 256 x 256 x 64 71 / 39, 481 x 481 x 32 203 / 128, 512 x 512 x 64 209 /
-    // 152).  The split GEMM keeps its sizes: its scores are the closer ones, and those tbg gives for them.  A
+    // kernels / one: 160 x 160 x 64 52 / 28 us, 256 x 256 x 64 74 / 42, 481 x 481 x 32 193 / 131, 512 x 512 x 64 198 /
+    // 158).  The split GEMM keeps its sizes: its scores are the closer ones, and those tbg gives for them.  A
     // work-group walks the keys in a row, so with few work-groups and a long walk the two kernels are faster (8 heads of
     // 300 x 300 x 128 11.1 / 16.1, x 64 9.8 / 10.4, x 32 9.7 / 8.5; 12 heads of 492 x 492 x 128 19.4 / 21.9, 16 of 400 x
     // 400 x 128 23.8 / 21.0), and so they are for wide heads with a third of the last keys missing (64 of 300 x 300 x 128

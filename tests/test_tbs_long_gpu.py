@@ -75,3 +75,19 @@ def test_values_that_are_not_finite():
     ok[100] = False                      # scores of 1e38: the largest alone survives
     assert float((got[ok] - ref[ok]).abs().max()) <= TOL
     assert got[100].argmax() == ref[100].argmax()
+
+
+@pytest.mark.parametrize("S, D", [(160, 40), (256, 64), (300, 40), (511, 64), (512, 64)])
+def test_small_probabilities(S, D):
+    """Whole numbers, so the scores and their distances from the row's maximum are exact: what is left is the exponential and
+    the division (a few units), at most 16 + 3 additions in a lane and 5 between lanes, and half the smallest denormal."""
+    from paper_2006_06762_amd import binding as anr
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(S)
+    q, k = (torch.randint(-3, 4, (1, S, 24, D), device="cuda", generator=gen).float() for _ in range(2))
+    out = torch.empty((1, 24, S, S), device="cuda")
+    anr.tbs(q, k, out)
+    scores = q.permute(0, 2, 1, 3).contiguous().double() @ k.permute(0, 2, 3, 1).contiguous().double()
+    want = torch.softmax(scores, -1)
+    assert bool(((want > 0) & (want < 2.0 ** -126)).any())
+    assert bool(((out.double() - want).abs() <= 32 * 2.0 ** -24 * want + 2.0 ** -149).all())
