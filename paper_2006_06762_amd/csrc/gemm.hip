@@ -1,6 +1,6 @@
 // fp32 GEMM on the MFMA units of gfx950: the GMM operator (C = A.B, Sec. 4.1 of
 // arXiv 2006.06762) and the batch matmul of the TBS subgraph (Sec. 7.2) in its
-// A.B^T form.  Five kernels, chosen in launch_gemm: the wave-split-K kernel below for small
+// A.B^T form.  Five kernels, chosen by gemm_dispatch.h: the wave-split-K kernel below for small
 // aligned products of K = 128, 256 and 512, gemm_rows32_kernel for others of few 32 x 32 tiles,
 // gemm_pipe_kernel for aligned ones of few 64 x 64 tiles and a short reduction,
 // gemm_split_kernel for everything larger, and gemm_kernel for what those leave (extents beyond
@@ -15,6 +15,7 @@
 // consecutive k of "its" row with one ds_read_b128 and spends them on four MFMAs.
 #include "anr_device.h"
 #include "anr_kernels.h"
+#include "gemm_dispatch.h"
 #include "gemm_pipe_kernel.h"
 #include "gemm_rows32_kernel.h"
 #include "gemm_split_kernel.h"
@@ -437,19 +438,10 @@ hipError_t launch_split_any(const GemmArgs& a, hipStream_t stream)
     }
 }
 
-// The fp32 pipelined kernel where it is the faster one: a short reduction over few 64 x 64 tiles, so that the
-// time is a chain of latencies (splitting adds an LDS round trip to every chunk).  At most one tile per CU:
-// 512^2 x 96 5.1 against 7.3 us, 1024^2 x 480 12.8 against 13.9, x 608 15.3 against 16.2 (past 704 four
-// wave groups of the split kernel come level, and only they keep up with a longer chain).  Up to three tiles
-// per CU and the seven chunks of one wave group: 1536 x 1024 x 160 9.2 against 10.7, 1536^2 x 224 15.3 against
-// 16.1; x 256 18.6 against 17.1, and 16 x 512^2 x 128 14.3 against 12.7.  Up to four and two chunks: 2048^2 x 64
-// 10.6 against 12.7.  The split kernel starts at one chunk.
-hipError_t launch_pipe(const GemmArgs& a, hipStream_t stream, bool* taken)
+hipError_t launch_pipe(const GemmArgs& a, hipStream_t stream)
 {
+    static_assert(gpipe::KC == 32, "gemm_pipe_takes counts its chunks");
     const int tiles_m = (a.M + 63) / 64, tiles_n = (a.N + 63) / 64;
-    const int64_t tiles = (int64_t)tiles_m * tiles_n * a.batch;
-    *taken = tiles <= 256 ? a.K <= 704 : tiles <= 768 ? a.K <= 7 * gpipe::KC : tiles <= 1024 ? a.K <= 64 : a.K < gsplit::KC;
-    if (!*taken) return hipSuccess;
     const dim3 grid((unsigned)(tiles_m * tiles_n), 1, a.batch);
     // a longer chain of chunks is shared by two groups of waves
     if (a.K > 7 * gpipe::KC) {
@@ -505,56 +497,41 @@ hipError_t launch_gemm(const GemmArgs& args, hipStream_t stream)
                (a.K % 4 == 0) && (a.lda % 4 == 0) && (a.ldb % 4 == 0) && (a.ldc % 4 == 0);
     if (!a.b_is_nk) vec = vec && (a.N % 4 == 0);
 
-    const int64_t tiles128 = (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch;
-    const bool big = tiles128 >= 192;   // enough 128x128 tiles to occupy most of the 256 CUs
-
-    // few tiles and a long reduction: one 32x32 tile per work-group, K split over its waves
-    const int64_t tiles32 = (int64_t)(a.M / 32) * (a.N / 32) * a.batch;
-    if (!a.b_is_nk && !a.softmax_rows && (a.M % 32 == 0) && (a.N % 32 == 0) && tiles32 <= 1024 &&
-        a.batch_inner == 1 && is_aligned16(a.A) && is_aligned16(a.B) && (a.lda % 4 == 0) && (a.ldb % 4 == 0) &&
-        (a.sAo % 4 == 0) && (a.sBo % 4 == 0) && a.batch <= 65535) {
-        if (a.K == 128) return launch_ksplit<1, 4>(a, stream);
-        if (a.K == 256) return launch_ksplit<1, 8>(a, stream);
-        if (a.K == 512) return launch_ksplit<1, 16>(a, stream);
-    }
-
-    hipError_t err = hipSuccess;
-    // 32-bit byte offsets inside one matrix, grid limits
+    GemmProblem q{};
+    q.M = a.M; q.N = a.N; q.K = a.K; q.batch = a.batch;
+    q.nk = a.b_is_nk;
+    q.one_level = !a.softmax_rows && a.batch_inner == 1;
+    q.lines = is_aligned16(a.A) && is_aligned16(a.B) && (a.lda % 4 == 0) && (a.ldb % 4 == 0) && (a.sAo % 4 == 0) &&
+              (a.sBo % 4 == 0) && a.batch <= 65535;
+    q.vec = vec;
+    // 32-bit byte offsets inside one matrix, and work-items in one grid dimension below 2^32: a 64 x 64 tile has 128 to
+    // 512 of them
     const int64_t a_ext = (int64_t)(a.M - 1) * a.lda + a.K;
     const int64_t b_ext = a.b_is_nk ? (int64_t)(a.N - 1) * a.ldb + a.K : (int64_t)(a.K - 1) * a.ldb + a.N;
-    // (work-items in one grid dimension stay below 2^32: a 64 x 64 tile has 128 to 512 of them)
-    const int64_t tiles64 = (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch;
-    const bool offsets32 = a_ext < ((int64_t)1 << 29) && b_ext < ((int64_t)1 << 29) && tiles64 < ((int64_t)1 << 22);
-    bool piped = false;
-    // Few 32 x 32 tiles: gemm_rows32_kernel, whatever the alignment.  Up to a tile per CU from K = 65 on (283 x 821 x 83
-    // 6.9 -> 5.6 us, 449 x 450 x 1920 36 -> 16), or from 97 where the pipelined kernel can load the operands (2560 x 32 x
-    // 96 5.1 -> 5.5), up to two from 97 (1422 x 200 x 510 14.7 -> 12.5, 192 x 2464 x 320 10.1 -> 10.0); past that each CU has
-    // more work than its own chain and larger tiles reuse more (520 tiles, K = 384, 11.6 -> 13.3).
-    const int64_t tiles_rows32 = (int64_t)((a.M + 31) / 32) * ((a.N + 31) / 32) * a.batch;
-    if (offsets32 && !a.b_is_nk && !a.softmax_rows && a.batch_inner == 1 && a.K > (tiles_rows32 <= 256 && !vec ? 64 : 96) && tiles_rows32 <= 512)
-        return launch_rows32(a, tiles_rows32, stream);
-    if (offsets32 && vec && !a.b_is_nk) err = launch_pipe(a, stream, &piped);
-    if (err != hipSuccess) return err;
-    // A k-major B is read a whole chunk of rows and a pair of columns at a time.  Operands the pipelined kernel
-    // cannot load, few tiles and a short reduction: the plain kernel's prologue is the shortest (up to a tile per
-    // CU K = 32 to 47 0.73 of the split kernel's time, 81 to 96 0.82, 129 to 160 0.94, 161 to 224 1.11; up to two
-    // 48 to 80 0.89, 81 to 96 0.97, 129 to 160 1.16; three to four tiles per CU 48 to 64 1.13).
-    const bool split = offsets32 && (a.b_is_nk || (a.N >= 2 && a.K >= gsplit::KC)) &&
-                       a.K > (tiles64 <= 256 ? 160 : tiles64 <= 512 ? 96 : 0);
-    if (piped) {
-        // enqueued
-    } else if (split) {
-        err = a.b_is_nk ? launch_split_any<true>(a, stream) : launch_split_any<false>(a, stream);
-    } else if (a.b_is_nk) {
-        if (big) err = vec ? launch_variant<128, 128, 16, true, true>(a, stream)
-                           : launch_variant<128, 128, 16, true, false>(a, stream);
-        else     err = vec ? launch_variant<64, 64, 16, true, true>(a, stream)
-                           : launch_variant<64, 64, 16, true, false>(a, stream);
-    } else {
-        if (big) err = vec ? launch_variant<128, 128, 16, false, true>(a, stream)
-                           : launch_variant<128, 128, 16, false, false>(a, stream);
-        else     err = vec ? launch_variant<64, 64, 16, false, true>(a, stream)
-                           : launch_variant<64, 64, 16, false, false>(a, stream);
+    q.offsets32 = a_ext < ((int64_t)1 << 29) && b_ext < ((int64_t)1 << 29) && gemm_tiles(q, 64) < ((int64_t)1 << 22);
+
+    hipError_t err = hipSuccess;
+    switch (choose_gemm(q)) {
+        case GemmKernel::ksplit:
+            err = a.K == 128 ? launch_ksplit<1, 4>(a, stream) : a.K == 256 ? launch_ksplit<1, 8>(a, stream) : launch_ksplit<1, 16>(a, stream);
+            break;
+        case GemmKernel::rows32: err = launch_rows32(a, gemm_tiles(q, 32), stream); break;
+        case GemmKernel::pipe: err = launch_pipe(a, stream); break;
+        case GemmKernel::split: err = a.b_is_nk ? launch_split_any<true>(a, stream) : launch_split_any<false>(a, stream); break;
+        case GemmKernel::plain: {
+            const bool big = gemm_tiles(q, 128) >= 192;   // enough 128x128 tiles to occupy most of the 256 CUs
+            if (a.b_is_nk) {
+                if (big) err = vec ? launch_variant<128, 128, 16, true, true>(a, stream)
+                                   : launch_variant<128, 128, 16, true, false>(a, stream);
+                else     err = vec ? launch_variant<64, 64, 16, true, true>(a, stream)
+                                   : launch_variant<64, 64, 16, true, false>(a, stream);
+            } else {
+                if (big) err = vec ? launch_variant<128, 128, 16, false, true>(a, stream)
+                                   : launch_variant<128, 128, 16, false, false>(a, stream);
+                else     err = vec ? launch_variant<64, 64, 16, false, true>(a, stream)
+                                   : launch_variant<64, 64, 16, false, false>(a, stream);
+            }
+        }
     }
     if (err != hipSuccess) return err;
 

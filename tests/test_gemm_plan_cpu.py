@@ -27,23 +27,60 @@ def test_split_gemm_staging_stays_inside_and_counts_once(staging, tile, groups, 
     assert res.returncode == 0, res.stdout + res.stderr
 
 
-def test_variant_shapes_select_their_variants(tmp_path):
-    """The GPU tests' shapes run the tile and wave groups they are listed for, and every variant has one."""
-    torch_tests = pytest.importorskip("test_split_gpu")
-    src = tmp_path / "choose.cpp"
-    src.write_text("""
+@pytest.fixture(scope="module")
+def dispatch(tmp_path_factory):
+    """What launch_gemm runs for a product in packed tensors (all of them 16-byte aligned): kernel, tile and wave groups of
+    the split GEMM, and how many such variants there are."""
+    where = tmp_path_factory.mktemp("dispatch")
+    (where / "choose.cpp").write_text("""
 #include <cstdio>
 #include <cstdlib>
-#include "gemm_split_plan.h"
+#include "gemm_dispatch.h"
+using namespace anr;
 int main(int, char** v)
 {
-    const auto& c = anr::gsplit::kVariants[anr::gsplit::choose_variant(atoi(v[2]), atoi(v[3]), atoi(v[4]), atoi(v[1]))];
-    printf("%d %d %d", c.tile, c.groups, anr::gsplit::kVariantCount);
+    GemmProblem p{};
+    p.batch = atoi(v[1]); p.M = atoi(v[2]); p.N = atoi(v[3]); p.K = atoi(v[4]); p.nk = atoi(v[5]);
+    p.one_level = !p.nk;
+    p.offsets32 = true;
+    p.lines = p.K % 4 == 0 && p.N % 4 == 0;
+    p.vec = p.K % 4 == 0 && p.N % 4 == 0;
+    const char* const names[] = {"ksplit", "rows32", "pipe", "split", "plain"};
+    const auto& c = gsplit::kVariants[gsplit::choose_variant(p.M, p.N, p.K, p.batch)];
+    printf("%s %d %d %d", names[(int)choose_gemm(p)], c.tile, c.groups, gsplit::kVariantCount);
 }
 """)
-    subprocess.run(["g++", "-std=c++17", "-I", CSRC, str(src), "-o", str(tmp_path / "choose")], check=True)
-    choose = lambda shape: tuple(map(int, subprocess.check_output([str(tmp_path / "choose"), *map(str, shape)]).split()))
-    for variant, shape in torch_tests.VARIANTS.items():
-        assert choose(shape) == (*variant, len(torch_tests.VARIANTS))
-    for variant, (B, S, H, D) in torch_tests.SCORES.items():
-        assert choose((B * H, S, S, D)) == (*variant, len(torch_tests.SCORES)) and D % 4 != 0
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-I", CSRC, str(where / "choose.cpp"), "-o", str(where / "choose")], check=True)
+
+    def choose(batch, M, N, K, nk=0):
+        kernel, *rest = subprocess.check_output([str(where / "choose"), *map(str, (batch, M, N, K, nk))], text=True).split()
+        return (kernel, *map(int, rest))
+    return choose
+
+
+def test_shapes_of_the_gpu_tests_run_what_they_are_listed_for(dispatch):
+    """Kernel, tile and wave groups, and every variant of the split GEMM has a shape."""
+    split = pytest.importorskip("test_split_gpu")
+    rows32 = pytest.importorskip("test_gemm_rows32_gpu")
+    for variant, shape in split.VARIANTS.items():
+        assert dispatch(*shape) == ("split", *variant, len(split.VARIANTS)), shape
+    for variant, (B, S, H, D) in split.SCORES.items():
+        assert dispatch(B * H, S, S, D, 1) == ("split", *variant, len(split.SCORES)) and D % 4 != 0
+    # (views of odd strides: never aligned, here by their odd extents; 700 x 700 x 545 has 484 tiles)
+    assert [dispatch(1, *shape)[0] for shape in split.UNALIGNED] == ["rows32", "rows32", "split", "split", "split"]
+    assert {dispatch(1, *shape)[1:3] for shape in split.UNALIGNED[2:]} >= {(64, 4), (128, 2)}
+    for M, N in rows32.EDGES:
+        for K in rows32.EDGES_K:
+            # past 256 tiles it starts at 97: those two lengths are the other side of the line
+            want = "ksplit" if (M, N, K) == (32, 32, 128) else "plain" if M == 129 and K < 97 else "rows32"
+            assert dispatch(1, M, N, K)[0] == want, (M, N, K)
+    for shape in rows32.VIEWS:
+        assert dispatch(*shape)[0] == "rows32"
+
+
+def test_dispatch_at_its_lines(dispatch):
+    """256 and 512 tiles of 32 x 32, the shortest reductions on either side."""
+    for (M, N, K), want in {(511, 512 - 1, 65): "rows32", (511, 511, 64): "plain", (512, 512, 96): "pipe", (512, 512, 100): "rows32",
+                            (511, 1023, 97): "rows32", (511, 1023, 96): "plain", (511, 1025, 333): "split", (512, 1028, 300): "pipe",
+                            (512, 1024, 128): "ksplit", (1024, 1024, 256): "ksplit", (1024, 1056, 256): "split"}.items():
+        assert dispatch(1, M, N, K)[0] == want, (M, N, K)

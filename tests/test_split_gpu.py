@@ -53,7 +53,11 @@ def test_split_gemm_edges(anr, batch, M, N, K):
     assert bool((buf[:64] == 7.0).all()) and bool((buf[-64:] == 7.0).all())
 
 
-@pytest.mark.parametrize("M,N,K", [(300, 260, 333), (700, 700, 545), (2100, 1900, 200)])
+# the first two are products of few 32 x 32 tiles (gemm_rows32_kernel), the others the split GEMM's
+UNALIGNED = [(300, 260, 333), (700, 700, 545), (2100, 1900, 200), (1100, 1000, 333), (547, 1037, 1025)]
+
+
+@pytest.mark.parametrize("M,N,K", UNALIGNED)
 def test_split_gemm_strided_unaligned_views(anr, M, N, K):
     A = uniform(1, M, K + 5)[:, 3:K + 3]
     B = uniform(2, K, N + 7)[:, 1:N + 1]
@@ -75,7 +79,7 @@ def test_gemm_of_a_single_column(anr, batch, M, K, ldb, ldc):
     assert bool((C[:, :, 1:] == 7.0).all())
 
 
-@pytest.mark.parametrize("M,N,K", [(300, 260, 333), (700, 700, 545), (2100, 1900, 200)])
+@pytest.mark.parametrize("M,N,K", UNALIGNED)
 @pytest.mark.parametrize("what", ["inf", "nan", "huge", "overflow", "denormal", "tiny", "past_k"])
 def test_split_gemm_values_the_pieces_cannot_carry(anr, M, N, K, what):
     A, B = uniform(3, M, K), uniform(4, K, N)
@@ -120,7 +124,7 @@ def test_split_scores(anr, B, S, H, D):
 
 # one shape per variant of the split GEMM (tile, wave groups), each with remainders in M, N and K
 VARIANTS = {(128, 1): (1, 3971, 4033, 545), (128, 2): (8, 505, 900, 515), (64, 1): (8, 257, 900, 161), (64, 2): (12, 505, 511, 1509),
-            (64, 4): (1, 257, 511, 515)}
+            (64, 4): (1, 545, 943, 963)}
 
 # Units of 2^-24 of a product: what the products add beside the roundings of the large sum.  The seven small ones
 # make at most 2^-7 of a product, rounded seven times; ll, which is left out, at most 2^-10 of a unit.
