@@ -469,15 +469,22 @@ hipError_t launch_rows32_as(const GemmArgs& a, hipStream_t stream)
 }
 
 // Eight waves to a work-group, with more than one work-group per CU and a short reduction four (1422 x 200 x 510 12.1
-// against 12.7 us); the number of folds by K as their errors stand to those of the kernels before (see there).
+// against 12.7 us); the number of folds by K so that no error is above the split GEMM's (see there).
 template <int NW>
 hipError_t launch_rows32_by_k(const GemmArgs& a, hipStream_t stream)
 {
-    return a.K < 288 ? launch_rows32_as<NW, 4>(a, stream) : a.K < 800 ? launch_rows32_as<NW, 2>(a, stream) : launch_rows32_as<NW, 1>(a, stream);
+    return a.K < 288   ? launch_rows32_as<NW, 4>(a, stream)
+           : a.K < 800 ? launch_rows32_as<NW, 2>(a, stream)
+           : a.K < 864 ? launch_rows32_as<NW, 1>(a, stream)
+                       : launch_rows32_as<NW, 0>(a, stream);
 }
 
-hipError_t launch_rows32(const GemmArgs& a, int64_t tiles, hipStream_t stream)
+hipError_t launch_rows32(const GemmArgs& a, const GemmProblem& q, hipStream_t stream)
 {
+    const int64_t tiles = gemm_tiles(q, 32);
+    // short sums that the split GEMM would take (many small unaligned matrices) are closer there than with four folds:
+    // 300 x 29 x 31 x 97 8.1 us, with four 6.5, the split GEMM 9.9
+    if (a.K <= 128 && gemm_split_takes(q) && !gemm_pipe_takes(q)) return launch_rows32_as<4, 8>(a, stream);
     return tiles <= 256 || a.K >= 1024 ? launch_rows32_by_k<8>(a, stream) : launch_rows32_by_k<4>(a, stream);
 }
 
@@ -515,7 +522,7 @@ hipError_t launch_gemm(const GemmArgs& args, hipStream_t stream)
         case GemmKernel::ksplit:
             err = a.K == 128 ? launch_ksplit<1, 4>(a, stream) : a.K == 256 ? launch_ksplit<1, 8>(a, stream) : launch_ksplit<1, 16>(a, stream);
             break;
-        case GemmKernel::rows32: err = launch_rows32(a, gemm_tiles(q, 32), stream); break;
+        case GemmKernel::rows32: err = launch_rows32(a, q, stream); break;
         case GemmKernel::pipe: err = launch_pipe(a, stream); break;
         case GemmKernel::split: err = a.b_is_nk ? launch_split_any<true>(a, stream) : launch_split_any<false>(a, stream); break;
         case GemmKernel::plain: {

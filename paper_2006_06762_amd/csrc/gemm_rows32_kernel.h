@@ -10,9 +10,10 @@
 // 130 x 68 x 3577 62 -> 28, 192 x 1408 x 864 20 -> 14.
 //
 // The sums of short runs of k meet in a compensated one, so the error does not grow with K: relative to the exact
-// results 6.0e-8 (four or two runs a chunk), 8.5e-8 (one); with the bf16-split GEMM it was 5.7e-8 at K = 165, 7.0e-8
-// at 441, 8.3e-8 at 800 and 1.6e-7 at 3500, with the fp32 kernels 2.5e-7 at 320.  Sixteen waves gained 3 % at K above
-// 3000 and lost 5 to 30 below; sums in fp64 instead took up to 1.2 times as long.
+// results 4.55e-8 (eight runs a chunk), 5.15e-8 (four), 6.3e-8 (two), 8.05e-8 (one), 8.5e-8 (one, both accumulators
+// added up first).  The split GEMM has 5.0e-8 at K = 97, 5.3e-8 at 129, 5.7e-8 at 161, 6.35e-8 at 289, 8.3e-8 at 801, 8.5e-8
+// at 864 and 9.9e-8 at 1281, the fp32 kernels 18e-8 at 97 and 34e-8 at 704.  Sixteen waves gained 3 % at K above 3000
+// and lost 5 to 30 below; sums in fp64 instead took up to 1.2 times as long.
 #pragma once
 #include "anr_device.h"
 #include "anr_kernels.h"
@@ -42,7 +43,7 @@ struct Sum16 {
     }
 };
 
-// FOLDS 4, 2: both accumulators join the sum every 8 or 16 k; 1: their sum does every 32.
+// FOLDS 8, 4, 2, 1: both accumulators join the sum every 4, 8, 16 or 32 k; 0: their sum does every 32.
 template <int NW, int FOLDS>
 __global__ __launch_bounds__(64 * NW) void gemm_rows32_kernel(const GemmArgs p, int tiles_m, int tiles_n)
 {
@@ -124,29 +125,36 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows32_kernel(const GemmArgs p, 
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         __builtin_amdgcn_sched_barrier(0);       // the loads stay ahead of the products
         f32x16 acc, acc2;
+        auto clear = [&] {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = acc2[r] = 0.f;
+        };
+        auto fold = [&] {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                sum.add(r, acc[r]);
+                sum.add(r, acc2[r]);
+            }
+        };
+        constexpr int kRun = FOLDS == 0 ? 4 : FOLDS > 4 ? 1 : 4 / FOLDS;      // steps of eight k
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            if (kk % (4 / FOLDS) == 0) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[r] = acc2[r] = 0.f;
-            }
+            if (kk % kRun == 0) clear();
             const f32x4 av = *reinterpret_cast<const f32x4*>(&st[r32 * LD + kk * 8 + 4 * h]);
             float bv[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) bv[e] = st[32 * LD + (kk * 8 + 4 * h + e) * LD + r32];
             acc = mfma32(av[0], bv[0], acc);
             acc2 = mfma32(av[1], bv[1], acc2);
+            if (FOLDS == 8) {
+                fold();
+                clear();
+            }
             acc = mfma32(av[2], bv[2], acc);
             acc2 = mfma32(av[3], bv[3], acc2);
-            if (FOLDS > 1 && (kk + 1) % (4 / FOLDS) == 0) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    sum.add(r, acc[r]);
-                    sum.add(r, acc2[r]);
-                }
-            }
+            if (FOLDS > 0 && (kk + 1) % kRun == 0) fold();
         }
-        if (FOLDS == 1) {
+        if (FOLDS == 0) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) sum.add(r, acc[r] + acc2[r]);
         }

@@ -79,3 +79,22 @@ def test_error_does_not_grow_with_the_reduction(K):
     anr.gemm(A, B, C)
     ref = A.double() @ B.double()
     assert float((C.double() - ref).norm() / ref.norm()) <= 1.1e-7          # sqrt(6.5 / 3) * 2^-24 = 8.8e-8
+
+
+@pytest.mark.parametrize("batch,M,N,K,steps", [(1, 256, 259, 97, 2), (1, 256, 259, 165, 2), (1, 256, 259, 287, 2), (1, 256, 259, 289, 4),
+                                               (1, 256, 259, 513, 4), (1, 256, 259, 801, 8), (1, 256, 259, 861, 8), (1, 256, 259, 865, 8),
+                                               (300, 29, 31, 97, 1), (300, 29, 31, 127, 1), (300, 29, 31, 129, 2)])
+def test_error_by_the_length_of_a_run(batch, M, N, K, steps):
+    """A run adds `steps` instructions of two products to each of two sums: in units of a rounding of the result, the squares
+    of these roundings (each of a part of the run's half that grows to the whole) make steps + 1/2 in all, the term that
+    enters the compensated sum one, the result itself one, and from K = 864 on, where the two halves are added first,
+    that addition one.  A rounding is evenly spread over 2^-24 of a number's power of two, 0.541 of the square of its own
+    size on average.  The split GEMM, which took the products of K = 801 and 861 and the many small ones before, is at
+    8.3e-8, 8.5e-8 and, for K = 97, 5.0e-8."""
+    from paper_2006_06762_amd import binding as anr
+    A, B = uniform(7, batch, M, K), uniform(8, batch, K, N)
+    C = torch.empty(batch, M, N, device="cuda")
+    anr.gemm(A, B, C)
+    ref = A.double() @ B.double()
+    roundings = steps + 2.5 + (K >= 864)
+    assert float((C.double() - ref).norm() / ref.norm()) <= (0.541 * roundings / 3) ** 0.5 * 2.0 ** -24
