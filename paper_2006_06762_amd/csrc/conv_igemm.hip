@@ -128,7 +128,7 @@ double fp32_us(const ConvArgs& a, const Geom& g, int variant)
 }
 
 // The one planning pass of a call: variant, geometry and LDS size, with the descriptor's route
-// applied (1: whenever a variant runs the shape; 2: never; 0: with enough output tiles).  Depends
+// applied (1: whenever a variant runs the shape, the fp32 ones first; 2: never; 0: with enough output tiles).  Depends
 // on the descriptor and on the alignment of x and w only (null pointers count as aligned), so a
 // pack made for a descriptor fits every later call with it.
 void plan_igemm(const ConvArgs& a, IgemmPlan* p)
@@ -146,7 +146,7 @@ void plan_igemm(const ConvArgs& a, IgemmPlan* p)
     // 7, 452 -> 318, weights not packed; on average 0.82 of the time of the layers that take it).  Few or half-filled rounds, channels far from a
     // multiple of 64 and few input channels leave it behind (38 x 38, 128 -> 64, batch 16, 42 against 51).
     IgemmPlan wide;
-    if (plan_wide(a, &wide) && wide_us(a, wide) < 0.93 * (tuned ? fp32_us(a, p->g, best) : conv2d_gather_estimate_us(a))) {
+    if (plan_wide(a, &wide) && (a.route == 1 || wide_us(a, wide) < 0.93 * (tuned ? fp32_us(a, p->g, best) : conv2d_gather_estimate_us(a)))) {
         *p = wide;
         p->variant = 4;
         return;

@@ -301,7 +301,13 @@ def test_conv_route_follows_the_descriptor_field():
     # the workspace figure is the plan's own need, route by route
     assert B.workspace_size(B.ANR_OP_CONV2D, auto) == ra.workspace_bytes > 0
     assert B.workspace_size(B.ANR_OP_CONV2D, patch) == 0
-    # a shape the patch kernel cannot run (width not a multiple of 4) takes the general one under any route
+    # any width from 24 on and whole chunks of sixteen channels, however few tiles there are
+    for x in ((1, 16, 30, 31), (1, 64, 24, 25), (1, 512, 29, 33)):
+        auto, patch = (B.conv2d_route(B.conv_desc(x, 100, 3, 3, (1, 1), (1, 1), route=r)) for r in (B.ANR_CONV_ROUTE_AUTO, B.ANR_CONV_ROUTE_PATCH))
+        assert auto.kernel == B.ANR_CONV_KERNEL_TAPS
+        assert (patch.kernel, patch.tile_m, patch.tile_n, patch.ksplit, patch.workspace_bytes) == (B.ANR_CONV_KERNEL_PATCH, 224, 64, 1, 0)
+    assert B.conv2d_route(B.conv_desc((1, 24, 30, 31), 64, 3, 3, (1, 1), (1, 1), route=B.ANR_CONV_ROUTE_PATCH)).kernel == B.ANR_CONV_KERNEL_TAPS
+    # a shape the patch kernel cannot run (width not a multiple of 4 and below 24) takes the general one under any route
     odd = B.conv_desc((16, 64, 14, 14), 64, 3, 3, (1, 1), (1, 1), route=B.ANR_CONV_ROUTE_PATCH)
     assert B.conv2d_route(odd).kernel == B.ANR_CONV_KERNEL_TAPS
 

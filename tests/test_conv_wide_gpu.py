@@ -42,6 +42,21 @@ def test_whole_numbers(shape, start, gap):
     assert bool((wide[..., s.OW:] == GUARD).all()) and bool((ybuf[:64 + start] == GUARD).all()) and bool((ybuf[-32:] == GUARD).all())
 
 
+@pytest.mark.parametrize("shape", [(1, 16, 30, 31, 100, 1), (1, 48, 24, 24, 7, 0), (1, 32, 5, 125, 70, 2)])
+def test_few_tiles_when_asked_for(shape):
+    """The route that asks for the patch kernel gets it whatever the estimates say, packed weights too."""
+    from paper_2006_06762_amd import binding as anr
+    s, x, w, xv, wd, ybuf, wide = tensors(shape, 5050, True, 1, 2)
+    y = wide[..., :s.OW]
+    anr.conv2d(xv, wd, y, s.stride, s.pad, route=anr.ANR_CONV_ROUTE_PATCH)
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).cuda().double(), wd.double(), padding=s.pad)
+    assert torch.equal(y.double(), ref)
+    desc, pack = anr.conv2d_pack_weights(x.shape, wd, s.stride, s.pad, route=anr.ANR_CONV_ROUTE_PATCH)
+    z = torch.empty(y.shape, device="cuda")
+    anr.conv2d_packed(desc, torch.from_numpy(x).cuda(), pack, z)
+    assert torch.equal(z, y)
+
+
 @pytest.mark.parametrize("shape", SHAPES[:4])
 def test_fused_and_packed(shape):
     """Sums within the bound of an fp32 sum, the fused epilogue, and the pack's results bit for bit."""
