@@ -144,7 +144,9 @@ void plan_igemm(const ConvArgs& a, IgemmPlan* p)
     // The bf16-split tile at any width, where its estimate is the shorter one by the estimates' spread (81 x 81, 512 -> 96, batch
     // 4, 307 -> 215 us; 57 x 57, 64 -> 512, batch 4, 81 -> 65; 42 x 42, 128 -> 160, batch 32, 214 -> 184; 124 x 124, 32 -> 512, batch
     // 7, 452 -> 318, weights not packed; on average 0.82 of the time of the layers that take it).  Few or half-filled rounds, channels far from a
-    // multiple of 64 and few input channels leave it behind (38 x 38, 128 -> 64, batch 16, 42 against 51).
+    // multiple of 64 and few input channels leave it behind (38 x 38, 128 -> 64, batch 16, 42 against 51).  Weights that are
+    // not 16-byte aligned cost the general kernels more, so more layers take it (16 x 25 x 25, 256 -> 256, 156 -> 107; a
+    // single 24 x 24, 512 -> 64, stays: 155 against 186).
     IgemmPlan wide;
     if (plan_wide(a, &wide) && (a.route == 1 || wide_us(a, wide) < 0.93 * (tuned ? fp32_us(a, p->g, best) : conv2d_gather_estimate_us(a)))) {
         *p = wide;

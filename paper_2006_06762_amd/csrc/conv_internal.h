@@ -20,7 +20,8 @@ bool conv2d_igemm_takes(const ConvArgs& a);
 // *ws_fault as in launch_conv2d.
 hipError_t launch_conv2d_gather(const ConvArgs& a, hipStream_t stream, bool* taken, int* ws_fault);
 size_t conv2d_gather_workspace_bytes(const ConvArgs& a);
-// Its estimated time for a 3 x 3 layer (conv_taps_kernel) in microseconds; infinite where it does not take the call.
+// Its estimated time for a 3 x 3 layer in microseconds (conv_taps_kernel, or conv_gather_kernel where the weights are not
+// 16-byte aligned); infinite where it does not take the call.
 double conv2d_gather_estimate_us(const ConvArgs& a);
 
 // Streaming kernel for pointwise layers with few channels (conv_pointwise_kernel.h); same contract.

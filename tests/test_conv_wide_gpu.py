@@ -94,3 +94,22 @@ def test_values_the_pieces_cannot_carry(value):
     ok = ref.isfinite()
     exact = torch.nn.functional.conv2d(xv.double(), wd.double(), padding=s.pad).cpu()
     assert bool(((got.double() - exact).abs()[ok] <= 1e-6 * exact.abs().clamp(min=1.0)[ok]).all())
+
+
+@pytest.mark.parametrize("shape,wide_tile", [((1, 512, 30, 30, 512, 1), False), ((1, 512, 24, 24, 64, 1), False), ((2, 128, 41, 41, 128, 1), False),
+                                             ((4, 64, 30, 30, 64, 1), False), ((8, 128, 33, 33, 128, 1), True), ((16, 128, 53, 53, 128, 1), True),
+                                             ((4, 64, 57, 57, 512, 1), True)])
+def test_weights_that_are_not_aligned(shape, wide_tile):
+    """Few tiles leave such a layer to the general kernel (the same bits as the route that asks for it), many do not."""
+    from paper_2006_06762_amd import binding as anr
+    s, x, w, xv, wd, ybuf, wide = tensors(shape, 5300, False, 0, 0)
+    buf = torch.empty(wd.numel() + 1, device="cuda")
+    wu = buf[1:].view(wd.shape)
+    wu.copy_(wd)
+    general = torch.empty_like(wide)
+    anr.conv2d(xv, wu, wide, s.stride, s.pad)
+    anr.conv2d(xv, wu, general, s.stride, s.pad, route=anr.ANR_CONV_ROUTE_GENERAL)
+    assert torch.equal(wide, general) == (not wide_tile)
+    ref = torch.nn.functional.conv2d(xv.double(), wd.double(), padding=s.pad)
+    size = torch.nn.functional.conv2d(xv.double().abs(), wd.double().abs(), padding=s.pad)
+    assert bool(((wide.double() - ref).abs() <= (9 * s.C + 2) * 2.0 ** -24 * size).all())
