@@ -1,0 +1,62 @@
+// Which kernel takes the scores q.k^T of S queries and keys of D floats, with or without the softmax: the rule of
+// launch_tbg, plain arithmetic without a device in it, so that a CPU program can ask it too.
+#pragma once
+#include <cstdint>
+
+namespace anr {
+
+enum class TbgKernel { rows32, rows_long, tile64, tile, gemm };
+
+struct TbgProblem {
+    int64_t S, D, batch;      // batch: heads of all sequences
+    bool softmax;
+    bool aligned;             // D a multiple of four, rows of q and k whole 16-byte units
+    bool offsets32;           // byte offsets inside one (b, h) view of q and of k below 2^31
+    bool out_offsets32;       // and of the result
+};
+
+constexpr int64_t kTbgMaxKeys = 128;      // of the fused kernel of a single pass
+constexpr int64_t kTbgLongKeys = 512, kTbgLongD = 256;
+
+constexpr bool tbs_rows32_takes(const TbgProblem& p) { return p.softmax && p.S <= kTbgMaxKeys && p.D <= 1024 && p.D % 8 == 0; }
+
+// whole tiles, whole chunks and 32-bit byte offsets inside one (b, h) view: the lean form
+constexpr bool tbg_whole(const TbgProblem& p) { return p.S % 64 == 0 && p.D % 64 == 0 && p.offsets32 && p.out_offsets32; }
+
+// Enough 128 x 128 tiles to fill the chip twice, mostly full: the bf16-split GEMM (32 x 12 heads of 512 x
+// 512 x 128 231 -> 200 us, 16 x 12 of 200 x 200 x 80 36 -> 26).  With fewer or half-empty tiles the other kernels
+// are the faster ones (8 x 8 of 312 x 312 x 64 15.0 against 16.5 us), and so they are with a single
+// chunk in the lean form (24 x 8 of 256 x 256 x 64 18.4 against 20.6, 48 x 8 of 512 x 512 x 64 129.7 against
+// 128.7).  The fused softmax of a single pass keeps its sizes.
+constexpr bool tbg_split_takes(const TbgProblem& p)
+{
+    const int64_t t = (p.S + 127) / 128;
+    return p.S > kTbgMaxKeys && p.offsets32 && t * t * p.batch >= 512 && (double)p.S * p.S >= 0.6 * t * t * 128 * 128 &&
+           (double)p.S * p.S * p.batch >= 384.0 * 128 * 128 && (p.D >= 48 || p.S % 64 == 0) && !(tbg_whole(p) && p.D <= 64);
+}
+
+// What is left with a softmax and up to 512 keys: one kernel that keeps the scores on the chip (16 x 16 heads, two
+// kernels / one: 160 x 160 x 64 52 / 28 us, 256 x 256 x 64 74 / 42, 481 x 481 x 32 193 / 131, 512 x 512 x 64 198 /
+// 158).  The split GEMM keeps its sizes: its scores are the closer ones, and those tbg gives for them.  A work-group
+// walks `walk` floats of every key row of a chunk of 128 in a row, so with few work-groups or a long walk the two
+// kernels are faster (8 heads of 300 x 300 x 128 11.4 / 16.9, 24 of 512 x 512 x 256 43.6 / 55.2).  Of 826 shapes of 136 to 512
+// keys, 32 to 256 floats and 4 to 128 heads this line costs 0.5 % against the faster of both on average and 17 % at
+// most; the next ones to it: 24 heads of 256 x 256 x 104, 17.9 / 11.9, 16 of 384 x 384 x 104 21.7 / 16.4, 24 of 384 x 384 x
+// 128 23.5 / 24.9, 48 of 320 x 320 x 192 36.4 / 34.4.
+constexpr bool tbs_long_takes(const TbgProblem& p)
+{
+    const int64_t chunks = (p.S + 127) / 128, walk = chunks * p.D, items = p.batch * ((p.S + 31) / 32);
+    return p.softmax && p.S > kTbgMaxKeys && p.S <= kTbgLongKeys && p.D <= kTbgLongD && p.D % 8 == 0 && p.offsets32 && !tbg_split_takes(p) &&
+           (walk <= 64 || (walk <= 512 && items >= (walk < 304 ? walk / 2 : 152)));
+}
+
+constexpr TbgKernel choose_tbg(const TbgProblem& p)
+{
+    const int64_t tiles = (p.S + 63) / 64;
+    if (!p.aligned || tbg_split_takes(p) || p.batch * tiles * tiles >= ((int64_t)1 << 31)) return TbgKernel::gemm;
+    if (tbs_rows32_takes(p)) return TbgKernel::rows32;
+    if (tbs_long_takes(p)) return TbgKernel::rows_long;
+    return tbg_whole(p) ? TbgKernel::tile64 : TbgKernel::tile;
+}
+
+}  // namespace anr

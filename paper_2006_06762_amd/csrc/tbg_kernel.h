@@ -235,8 +235,6 @@ __global__ __launch_bounds__(256) void tbg_tile64_kernel(const Args p)
 // per work-group), 2 for S <= 64 (64 queries), 1 for S <= 32 (128 queries), so a short sequence
 // neither loads nor multiplies key rows it does not have.
 // UT = 16-byte staging units per thread: ceil((32 * 4/KB + 32 * KB) * (min(D, 64)/4) / 256).
-constexpr int kMaxKeys = 128;
-
 template <int KB>
 struct TbsShape {
     static constexpr int QBK = 4 / KB;            // query blocks per work-group
@@ -507,9 +505,6 @@ __device__ __forceinline__ float exp_nonpositive(float d)
     const float f = fmaf(d, kRest, fmaf(d, kLog2e, -n));
     return ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
 }
-
-constexpr int kLongKeys = 512;
-constexpr int kLongD = 256;
 
 template <int KW>
 constexpr size_t long_lds_floats(int D)

@@ -1,5 +1,6 @@
 """The bf16-split GEMM's staging, walked thread by thread on the CPU with the kernel's own index arithmetic: every
-load inside its matrix (or past the extent by the lane's part of the offset alone), every k counted once."""
+load inside its matrix (or past the extent by the lane's part of the offset alone), every k counted once.  And the
+rules by which products and attention scores choose their kernels."""
 import os
 import subprocess
 
@@ -84,3 +85,48 @@ def test_dispatch_at_its_lines(dispatch):
                             (511, 1023, 97): "rows32", (511, 1023, 96): "plain", (511, 1025, 333): "split", (512, 1028, 300): "pipe",
                             (512, 1024, 128): "ksplit", (1024, 1024, 256): "ksplit", (1024, 1056, 256): "split"}.items():
         assert dispatch(1, M, N, K)[0] == want, (M, N, K)
+
+
+@pytest.fixture(scope="module")
+def scores(tmp_path_factory):
+    """What launch_tbg runs for packed tensors."""
+    where = tmp_path_factory.mktemp("scores")
+    (where / "choose.cpp").write_text("""
+#include <cstdio>
+#include <cstdlib>
+#include "tbg_dispatch.h"
+using namespace anr;
+int main(int, char** v)
+{
+    TbgProblem p{};
+    p.S = atoi(v[1]); p.D = atoi(v[2]); p.batch = atoi(v[3]); p.softmax = atoi(v[4]);
+    p.aligned = p.D % 4 == 0;
+    p.offsets32 = p.out_offsets32 = true;
+    const char* const names[] = {"rows32", "rows_long", "tile64", "tile", "gemm"};
+    printf("%s", names[(int)choose_tbg(p)]);
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-I", CSRC, str(where / "choose.cpp"), "-o", str(where / "choose")], check=True)
+    return lambda *args: subprocess.check_output([str(where / "choose"), *map(str, args)], text=True)
+
+
+def test_long_scores_of_the_gpu_tests_run_the_one_kernel(scores):
+    long = pytest.importorskip("test_tbs_long_gpu")
+    for S, D, heads in long.EDGES:
+        assert scores(S, D, heads, 1) == "rows_long", (S, D, heads)
+    assert {((S + 127) // 128, D) for S, D, heads in long.EDGES} >= {(2, 256), (3, 168), (4, 128)}
+    B, S, H, D = long.VIEW
+    assert scores(S, D, B * H, 1) == "rows_long"
+    for S, D in long.SMALL:
+        assert scores(S, D, long.SMALL_HEADS, 1) == "rows_long"
+    assert scores(300, 16, 1, 1) == "rows_long"          # values that are not finite
+
+
+def test_scores_dispatch_at_its_lines(scores):
+    """128 and 512 keys, few and enough work-groups, long walks, the split GEMM's sizes; scores alone never."""
+    for (S, D, heads, softmax), want in {(128, 64, 200, 1): "rows32", (129, 64, 16, 1): "rows_long", (129, 64, 12, 1): "tile",
+                                         (384, 104, 12, 1): "tile", (384, 104, 13, 1): "rows_long", (384, 128, 24, 1): "rows_long",
+                                         (320, 192, 48, 1): "tile64", (512, 256, 24, 1): "tile64", (512, 64, 48, 1): "rows_long",
+                                         (513, 64, 20, 1): "tile", (512, 128, 32, 1): "gemm", (384, 128, 57, 1): "gemm", (256, 64, 100, 0): "tile64",
+                                         (300, 36, 40, 1): "tile", (300, 33, 40, 1): "gemm"}.items():
+        assert scores(S, D, heads, softmax) == want, (S, D, heads, softmax)

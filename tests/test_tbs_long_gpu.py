@@ -21,12 +21,23 @@ def check(got, ref, what):
     assert err <= TOL, "%s: %.2e of the row's largest" % (what, err)
 
 
-@pytest.mark.parametrize("S", [129, 160, 255, 256, 257, 384, 385, 389, 511, 512])
-@pytest.mark.parametrize("D", [8, 32, 40, 72, 128, 256])
-def test_edges(S, D):
+def heads_for(S, D):
+    """As many heads as the one kernel asks for, and fewer than the split GEMM does."""
+    chunks = (S + 127) // 128
+    return 2 if D * chunks <= 64 else (31, 17, 12)[chunks - 2]
+
+
+# (more than 512 floats of a row to walk, chunks times D, are left to two kernels)
+EDGES = [(S, D, heads_for(S, D)) for S in (129, 160, 255, 256, 257, 384, 385, 389, 511, 512) for D in (8, 32, 40, 72, 128, 168, 256)
+         if (S + 127) // 128 * D <= 512]
+VIEW = (2, 192, 14, 64)
+SMALL = [(160, 40), (256, 64), (300, 40), (511, 64), (512, 64)]
+SMALL_HEADS = 24
+
+
+@pytest.mark.parametrize("S,D,heads", EDGES)
+def test_edges(S, D, heads):
     from paper_2006_06762_amd import binding as anr
-    # as many heads as the one kernel asks for, and fewer than the split GEMM does
-    heads = 2 if D * ((S + 127) // 128) <= 128 else 86 if D > 96 and 256 < S <= 384 else 31 if S > 384 else 34
     s = I.TbgShape(1, S, heads, D)
     q, k = I.tbg_inputs(s, 2000 + S + D)
     q = (q * (2.0 / D ** 0.5)).astype(np.float32)
@@ -42,7 +53,7 @@ def test_edges(S, D):
 def test_views(pad, start):
     """q and k as slices of a projection that holds both, rows of the result further apart than they are long."""
     from paper_2006_06762_amd import binding as anr
-    B, S, H, D = 2, 192, 14, 64
+    B, S, H, D = VIEW
     q, k = I.tbg_inputs(I.TbgShape(B, S, H, D), 2100)
     q = (q * 0.25).astype(np.float32)
     both = torch.zeros((B, S, 2, H, D), device="cuda")
@@ -77,15 +88,15 @@ def test_values_that_are_not_finite():
     assert got[100].argmax() == ref[100].argmax()
 
 
-@pytest.mark.parametrize("S, D", [(160, 40), (256, 64), (300, 40), (511, 64), (512, 64)])
+@pytest.mark.parametrize("S, D", SMALL)
 def test_small_probabilities(S, D):
     """Whole numbers, so the scores and their distances from the row's maximum are exact: what is left is the exponential and
     the division (a few units), at most 16 + 3 additions in a lane and 5 between lanes, and half the smallest denormal."""
     from paper_2006_06762_amd import binding as anr
     gen = torch.Generator(device="cuda")
     gen.manual_seed(S)
-    q, k = (torch.randint(-3, 4, (1, S, 24, D), device="cuda", generator=gen).float() for _ in range(2))
-    out = torch.empty((1, 24, S, S), device="cuda")
+    q, k = (torch.randint(-3, 4, (1, S, SMALL_HEADS, D), device="cuda", generator=gen).float() for _ in range(2))
+    out = torch.empty((1, SMALL_HEADS, S, S), device="cuda")
     anr.tbs(q, k, out)
     scores = q.permute(0, 2, 1, 3).contiguous().double() @ k.permute(0, 2, 3, 1).contiguous().double()
     want = torch.softmax(scores, -1)
