@@ -119,7 +119,7 @@ hipError_t launch_bands_as(const ConvArgs& a, hipStream_t stream, bool* taken)
     const int64_t planes = (int64_t)a.N * a.C;
     const int64_t wl = (int64_t)(a.OW - 1) * ST + K_, x_plane = (int64_t)(a.H - 1) * a.xs[2] + a.W;
     auto rows_in = [&](int rows) { return (int64_t)(rows - 1) * ST + K_; };
-    constexpr int64_t kRoom = 7 * 1024;                      // floats: five work-groups per CU
+    constexpr int64_t kRoom = 7 * 1024;                      // floats: five work-groups per CU (rows too wide for it: two)
     if (planes >= ((int64_t)1 << 30) || x_plane >= ((int64_t)1 << 28) || a.xs[2] >= ((int64_t)1 << 28) ||
         wl * rows_in(dw::kBandRows) > 2 * kRoom || a.OH > (1 << 20))
         return hipSuccess;
@@ -159,8 +159,14 @@ hipError_t launch_bands_as(const ConvArgs& a, hipStream_t stream, bool* taken)
     g.d_strips = make_fastdiv(g.strips);
     g.d_c = make_fastdiv(a.C);
     *taken = true;
-    return launch_kernel(dw::dwconv_band_kernel<K_, ST>, dim3((unsigned)(groups * g.bands)), dim3(256),
-                         sizeof(float) * (size_t)g.G * g.per_plane, stream, a, g);
+    const size_t lds_bytes = sizeof(float) * (size_t)g.G * g.per_plane;
+    auto kern = dw::dwconv_band_kernel<K_, ST>;
+    if (lds_bytes > 48 * 1024) {
+        static LdsLimit granted;
+        hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_bytes, granted);
+        if (e != hipSuccess) return e;
+    }
+    return launch_kernel(kern, dim3((unsigned)(groups * g.bands)), dim3(256), lds_bytes, stream, a, g);
 }
 
 hipError_t launch_bands(const ConvArgs& a, hipStream_t stream, bool* taken)

@@ -39,6 +39,15 @@ def test_bands(R, stride, H, W, planes):
     run(I.ConvShape(2, planes // 2, H, W, planes // 2, R, R, (stride, stride), (R // 2, R // 2)), 3000 + H + R)
 
 
+@pytest.mark.parametrize("R, stride, W, planes", [(3, 1, 1399, 20), (3, 1, 1431, 20), (3, 2, 830, 90), (5, 1, 1190, 10), (5, 2, 747, 40)])
+def test_wide_rows(R, stride, W, planes):
+    """Eight rows of outputs whose input rows take more than 48 KB of LDS, up to the 56 KB where the direct kernel takes over."""
+    s = I.ConvShape(1, planes, 37, W, planes, R, R, (stride, stride), (R // 2, R // 2))
+    lds = 4 * ((s.OW - 1) * stride + R) * (7 * stride + R)
+    assert 48 * 1024 < lds <= 56 * 1024 and planes * s.OH * s.OW * R * R >= 4000000
+    run(s, 3050 + W)
+
+
 @pytest.mark.parametrize("H, W, R, stride, pad, start, gap", [(13, 13, 3, 1, 1, 1, 0), (14, 14, 5, 1, 2, 3, 0), (7, 9, 3, 1, 1, 2, 0),
                                                               (20, 20, 3, 1, 0, 0, 3), (30, 31, 3, 2, 3, 0, 1), (16, 12, 5, 2, 4, 1, 0)])
 def test_planes_in_groups_views_and_padding(H, W, R, stride, pad, start, gap):
