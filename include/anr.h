@@ -279,7 +279,9 @@ anr_status anr_workspace_size(int op, const void *desc, size_t *bytes);
  * callers that want to know why a layer takes the time it does, and for tests of the
  * selection logic.  tile_m x tile_n is the work-group's output tile (pixels x channels),
  * ksplit the number of work-groups that share a tile's reduction through the workspace,
- * wave_groups the groups of four waves inside a work-group that share its chunk chain. */
+ * wave_groups the groups of waves inside a work-group (of four; in the 64 x 64 tiles of the
+ * pointwise GEMM of two) that share its chunk chain, or one of which stages what the other
+ * one multiplies (two of the pointwise GEMM's 128 x 128 tiles). */
 enum {
     ANR_CONV_KERNEL_PATCH = 1,     /* 3x3 patch-staging kernel tuned on the ResNet-style layers   */
     ANR_CONV_KERNEL_TAPS = 2,      /* 3x3 / 1x1 gather kernel with compile-time taps              */

@@ -68,9 +68,10 @@ struct GemmArgs {
     float eps;
 };
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream);
-// The bf16-split GEMM alone (A.B with K >= 32, N >= 2, extents below 2^29 floats), and the edge of its tile.
+// The bf16-split GEMM alone (A.B with K >= 32, N >= 2, extents below 2^29 floats), and the edge of its tile and the
+// groups of waves in a work-group.
 hipError_t launch_gemm_split(const GemmArgs& a, hipStream_t stream);
-int gemm_split_tile(const GemmArgs& a);
+void gemm_split_variant(const GemmArgs& a, int* tile, int* groups);
 // The TBS batch matmul (a.b_is_nk set, batch = B*H, batch_inner = H), optionally followed by the
 // row softmax; picks the dedicated tile kernel when the operands allow it.
 hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream);

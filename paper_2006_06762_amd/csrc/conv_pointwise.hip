@@ -106,8 +106,9 @@ bool describe_conv2d_pointwise_gemm(const ConvArgs& a, ConvRoute* r)
 {
     GemmArgs g;
     if (!pointwise_gemm(a, &g)) return false;
-    const int tile = gemm_split_tile(g);
-    *r = ConvRoute{6, tile, tile, 1, 1, (int)(((int64_t)(g.M + tile - 1) / tile) * ((g.N + tile - 1) / tile) * g.batch), 0};
+    int tile = 0, groups = 0;
+    gemm_split_variant(g, &tile, &groups);
+    *r = ConvRoute{6, tile, tile, 1, groups, (int)(((int64_t)(g.M + tile - 1) / tile) * ((g.N + tile - 1) / tile) * g.batch), 0};
     return true;
 }
 

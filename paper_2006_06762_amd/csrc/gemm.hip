@@ -548,7 +548,12 @@ hipError_t launch_gemm(const GemmArgs& args, hipStream_t stream)
 
 hipError_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) { return launch_split_any<false>(a, stream); }
 
-int gemm_split_tile(const GemmArgs& a) { return gsplit::kVariants[gsplit::choose_variant(a.M, a.N, a.K, a.batch)].tile; }
+void gemm_split_variant(const GemmArgs& a, int* tile, int* groups)
+{
+    const gsplit::Variant& v = gsplit::kVariants[gsplit::choose_variant(a.M, a.N, a.K, a.batch)];
+    *tile = v.tile;
+    *groups = v.groups;
+}
 
 hipError_t launch_softmax_rows(const GemmArgs& a, hipStream_t stream)
 {

@@ -130,3 +130,18 @@ def test_scores_dispatch_at_its_lines(scores):
                                          (513, 64, 20, 1): "tile", (512, 128, 32, 1): "gemm", (384, 128, 57, 1): "gemm", (256, 64, 100, 0): "tile64",
                                          (300, 36, 40, 1): "tile", (300, 33, 40, 1): "gemm"}.items():
         assert scores(S, D, heads, softmax) == want, (S, D, heads, softmax)
+
+
+def test_pointwise_route_reports_the_gemm_it_runs(dispatch):
+    """Tile, wave groups and work-groups of a pointwise layer that runs as a GEMM: the variant of weights times image."""
+    from paper_2006_06762_amd import binding as B
+    gpu = pytest.importorskip("test_conv_pointwise_gemm_gpu")
+    seen = set()
+    for N, C, H, W, K in [*gpu.SHAPES, (16, 512, 45, 45, 256), (1, 2000, 57, 57, 512), (2, 700, 61, 61, 200), (32, 64, 85, 85, 384)]:
+        r = B.conv2d_route(B.conv_desc((N, C, H, W), K, 1, 1))
+        _, tile, groups, _ = dispatch(N, K, H * W, C)
+        assert r.kernel == B.ANR_CONV_KERNEL_POINTWISE
+        assert (r.tile_m, r.tile_n, r.wave_groups) == (tile, tile, groups)
+        assert r.work_groups == N * -(-K // tile) * -(-H * W // tile)
+        seen.add((tile, groups))
+    assert len(seen) >= 4 and max(g for _, g in seen) > 1
