@@ -191,8 +191,9 @@ anr_status anr_conv2d_noalloc(const anr_conv_desc *desc, const float *x, const f
  *                            only, `route` included).
  *   anr_conv2d_pack_weights  writes the pack: the weights w (OIHW [K, C/groups, R, S]) in
  *                            the order in which the kernel planned for `desc` stages them
- *                            (for the 3x3 patch-staging kernel: per channel tile and chunk
- *                            of input channels one contiguous image of its LDS buffer; for
+ *                            (for the 3x3 patch-staging kernel, on layers whose width and
+ *                            strides are multiples of 4: per channel tile and chunk of
+ *                            input channels one contiguous image of its LDS buffer; for
  *                            every other plan a plain copy), preceded by scale[K], shift[K]
  *                            = gamma/sqrt(var+eps), beta - mean*scale in fp32 when the four
  *                            batch-norm vectors are given (all four or none; none: that part
@@ -207,7 +208,8 @@ anr_status anr_conv2d_noalloc(const anr_conv_desc *desc, const float *x, const f
  *                            vectors.  A pack in the patch kernel's order presumes that
  *                            kernel's alignment rules for x (16-byte aligned pointer,
  *                            strides multiples of 4): a call with another x returns
- *                            ANR_ERR_INVALID_ARG.
+ *                            ANR_ERR_INVALID_ARG unless the kernel planned for `desc` is
+ *                            its form for any width, which reads any x.
  */
 anr_status anr_conv2d_packed_size(const anr_conv_desc *desc, size_t *bytes);
 anr_status anr_conv2d_pack_weights(const anr_conv_desc *desc, const float *w,

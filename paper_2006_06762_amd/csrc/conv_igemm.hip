@@ -75,21 +75,23 @@ struct IgemmPlan {
     Geom g;
     size_t lds;
     int cap;         // variant 4: patch pixels it needs room for (512 or 768)
+    bool patch_order;      // variant 4: an fp32 form runs the layer too, so its pack has the order they share
 };
 
 // The bf16-split 224 x 64 tile without the fp32 forms' conditions (it loads single floats, so any width, alignment
 // and row stride): stride 1, whole chunks of sixteen channels, a patch that fits whatever pixel a tile starts at.  An
 // image's virtual rows are the zero rows above it and its own; the zero rows below it are the next image's.
-// (A pack in the fp32 form's order is not for it.)
+static_assert(V224x64::BN == 64 && V128x64::BN == 64 && V64x64::BN == 64 && V224x64::CK == V128x64::CK && V224x64::CK == V64x64::CK &&
+              V224x64::CK == 8, "one order of packed weights for all tiles of 64 channels");
 bool plan_wide(const ConvArgs& a, IgemmPlan* p)
 {
     constexpr int BM = psplit::BM, BN = 64;
-    if (a.wpack || a.R != 3 || a.S != 3 || a.C % 16 != 0 || a.groups != 1 || a.stride_h != 1 || a.stride_w != 1 || a.dil_h != 1 || a.dil_w != 1 ||
+    if (a.R != 3 || a.S != 3 || a.C % 16 != 0 || a.groups != 1 || a.stride_h != 1 || a.stride_w != 1 || a.dil_h != 1 || a.dil_w != 1 ||
         a.pad_h > 2 || a.OW < 24)
         return false;
     const int64_t x_extent = (int64_t)(a.N - 1) * a.xs[0] + (int64_t)(a.C - 1) * a.xs[1] + (int64_t)(a.H - 1) * a.xs[2] + a.W;
-    const int64_t w_extent = (int64_t)a.K * a.C * 9, ohow = (int64_t)a.OH * a.OW;
-    if (x_extent >= (int64_t)1 << 29 || w_extent >= (int64_t)1 << 29 || a.N * ohow >= (int64_t)1 << 30) return false;
+    const int64_t w_extent = (int64_t)a.K * a.C * 9, ohow = (int64_t)a.OH * a.OW, pack = V224x64::packed_floats(a);
+    if (x_extent >= (int64_t)1 << 29 || w_extent >= (int64_t)1 << 29 || pack >= (int64_t)1 << 29 || a.N * ohow >= (int64_t)1 << 30) return false;
     Geom* g = &p->g;
     *g = Geom{};
     g->Mtot = (int)(a.N * ohow);
@@ -106,6 +108,7 @@ bool plan_wide(const ConvArgs& a, IgemmPlan* p)
     g->d_hv = make_fastdiv(g->HV);
     g->x_bytes = (uint32_t)(4 * x_extent);
     g->w_bytes = (uint32_t)(4 * w_extent);
+    g->wpack_bytes = (uint32_t)(4 * pack);
     g->tiles_m = (g->Mtot + BM - 1) / BM;
     g->tiles_n = (a.K + BN - 1) / BN;
     g->d_tiles_m = make_fastdiv(g->tiles_m);
@@ -134,7 +137,16 @@ double fp32_us(const ConvArgs& a, const Geom& g, int variant)
 void plan_igemm(const ConvArgs& a, IgemmPlan* p)
 {
     p->variant = -1;
+    p->patch_order = false;
     if (a.route == 2) return;
+    if (a.wpack && !is_aligned16(a.x)) {
+        // a pack is for the plan of aligned pointers; of its kernels only the form for any width reads this x
+        ConvArgs b = a;
+        b.x = nullptr;
+        plan_igemm(b, p);
+        if (p->variant != 4) p->variant = -1;
+        return;
+    }
     const int best = select_variant(a, &p->g, &p->lds);
     const bool tuned = best >= 0 && (a.route == 1 || (int64_t)p->g.tiles_m * p->g.tiles_n >= kMinTunedWorkGroups);
     if (tuned && (best < 2 || a.route == 1)) {
@@ -151,6 +163,7 @@ void plan_igemm(const ConvArgs& a, IgemmPlan* p)
     if (plan_wide(a, &wide) && (a.route == 1 || wide_us(a, wide) < 0.93 * (tuned ? fp32_us(a, p->g, best) : conv2d_gather_estimate_us(a)))) {
         *p = wide;
         p->variant = 4;
+        p->patch_order = tuned;
         return;
     }
     if (tuned) p->variant = best;
@@ -205,10 +218,11 @@ hipError_t launch_igemm_plan(const ConvArgs& a, const IgemmPlan& p, hipStream_t 
     }
 }
 
-// Floats of the packed weights of plan p, and its channel tile and chunk (output channels x input channels).
+// Floats of the packed weights of plan p, and its channel tile and chunk (output channels x input channels); none for
+// plans whose pack is a plain copy.  Plans 0, 2, 3 and 4 share one order.
 int64_t packed_floats(const ConvArgs& a, const IgemmPlan& p, int* bn, int* ck)
 {
-    switch (p.variant) {
+    switch (p.variant == 4 && p.patch_order ? 0 : p.variant) {
         case 0: *bn = V224x64::BN; *ck = V224x64::CK; return V224x64::packed_floats(a);
         case 1: *bn = V224x32::BN; *ck = V224x32::CK; return V224x32::packed_floats(a);
         case 2: *bn = V128x64::BN; *ck = V128x64::CK; return V128x64::packed_floats(a);
@@ -316,7 +330,7 @@ ConvPackLayout conv2d_pack_layout(const ConvArgs& a)
     plan_igemm(b, &p);
     int bn = 0, ck = 0;
     const int64_t pf = packed_floats(b, p, &bn, &ck);
-    l.patch_layout = p.variant >= 0 && p.variant < 4 && pf < ((int64_t)1 << 30);
+    l.patch_layout = pf > 0 && pf < ((int64_t)1 << 30);
     l.w_floats = l.patch_layout ? (size_t)pf : (size_t)a.K * (a.C / a.groups) * a.R * a.S;
     return l;
 }

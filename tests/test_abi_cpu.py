@@ -320,6 +320,19 @@ def test_no_environment_variable_steers_the_library():
         assert "getenv" not in text and "environ" not in text, name
 
 
+@pytest.mark.parametrize("x,K", [((7, 32, 124, 124), 512), ((4, 32, 80, 80), 384), ((8, 128, 96, 96), 128), ((32, 512, 24, 24), 512),
+                                 ((16, 64, 56, 56), 64), ((16, 64, 64, 64), 64)])
+def test_packed_weights_keep_the_patch_order_whatever_tile_runs(x, K):
+    """Layers that a patch kernel with aligned rows can run have their pack in its order, per 64 output and 8 input channels
+    64 rows of 76 floats, also where the 224-pixel tile for any width is the faster one: packs that a program keeps stay valid."""
+    d = B.conv_desc(x, K, 3, 3, (1, 1), (1, 1))
+    r = B.conv2d_route(d)
+    assert r.kernel == B.ANR_CONV_KERNEL_PATCH and r.tile_n == 64
+    assert B.conv2d_packed_size(d) == 4 * ((2 * K + 63) // 64 * 64 + -(-K // 64) * (x[1] // 8) * 64 * 76)
+    # (odd widths: a plain copy)
+    assert B.conv2d_packed_size(B.conv_desc((x[0], x[1], x[2], x[3] + 1), K, 3, 3, (1, 1), (1, 1))) == 4 * ((2 * K + 63) // 64 * 64 + K * x[1] * 9)
+
+
 def test_conv_route_large_batch_without_split_keeps_the_mfma_kernels():
     # a VGG-style stem at batch 32: 3 channels rule out the tap kernels, and the cap on the split-K
     # workspace must not apply to plans that do not split

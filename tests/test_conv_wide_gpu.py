@@ -113,3 +113,44 @@ def test_weights_that_are_not_aligned(shape, wide_tile):
     ref = torch.nn.functional.conv2d(xv.double(), wd.double(), padding=s.pad)
     size = torch.nn.functional.conv2d(xv.double().abs(), wd.double().abs(), padding=s.pad)
     assert bool(((wide.double() - ref).abs() <= (9 * s.C + 2) * 2.0 ** -24 * size).all())
+
+
+# layers that an fp32 patch kernel with aligned rows runs too, and that this tile takes
+ALIGNED = [(7, 32, 124, 124, 190, 1), (4, 32, 80, 80, 384, 1), (8, 128, 96, 96, 100, 1), (16, 64, 24, 24, 320, 1), (8, 32, 100, 36, 500, 1)]
+
+
+@pytest.mark.parametrize("shape", ALIGNED)
+def test_packs_in_the_patch_order(shape):
+    """A pack written by hand as the header describes it (per 64 output and 8 input channels 64 rows of 72 weights and four
+    floats of padding, behind scale and shift) gives what the library's own pack and the call without one give, and so does
+    an x that is not aligned."""
+    from paper_2006_06762_amd import binding as anr
+    s, x, w, xv, wd, ybuf, wide = tensors(shape, 5400, False, 0, 0)
+    bn = [torch.from_numpy(v).cuda() for v in I.bn_inputs(s.K, 5401)]
+    desc, pack = anr.conv2d_pack_weights(x.shape, wd, s.stride, s.pad, bn=bn, eps=I.BN_EPS)
+    r = anr.conv2d_route(desc)
+    assert (r.kernel, r.tile_m, r.tile_n) == (anr.ANR_CONV_KERNEL_PATCH, 224, 64)
+    tiles, chunks, head = -(-s.K // 64), s.C // 8, (2 * s.K + 63) // 64 * 64
+    image = torch.zeros((tiles * 64, chunks, 76), device="cuda")
+    image[:s.K, :, :72] = wd.reshape(s.K, chunks, 72)
+    byhand = torch.zeros(head + tiles * chunks * 64 * 76, device="cuda")
+    byhand[head:] = image.view(tiles, 64, chunks, 76).permute(0, 2, 1, 3).reshape(-1)
+    assert pack.numel() == 4 * byhand.numel() and torch.equal(pack.view(torch.float32)[head:], byhand[head:])
+    anr.conv2d(xv, wd, wide, s.stride, s.pad)
+    z = torch.empty_like(wide)
+    anr.conv2d_packed(desc, xv, byhand.view(torch.uint8), z)
+    assert torch.equal(z, wide)
+    buf = torch.empty(xv.numel() + 1, device="cuda")
+    xu = buf[1:].view(xv.shape)
+    xu.copy_(xv)
+    z.zero_()
+    anr.conv2d_packed(desc, xu, pack, z)
+    assert torch.equal(z, wide)
+    anr.conv_bn_relu(xv, wd, *bn, I.BN_EPS, wide, s.stride, s.pad)
+    anr.conv_bn_relu_packed(desc, xu, pack, z)
+    assert torch.equal(z, wide)
+    xv[1, 3, 5, 7], wd[2, 1, 0, 2] = float("inf"), 2.0 ** -120          # the second try reads the pack too
+    desc, pack = anr.conv2d_pack_weights(x.shape, wd, s.stride, s.pad)
+    anr.conv2d(xv, wd, wide, s.stride, s.pad)
+    anr.conv2d_packed(desc, xv, pack, z)
+    assert torch.equal(z.nan_to_num(1.5), wide.nan_to_num(1.5))
