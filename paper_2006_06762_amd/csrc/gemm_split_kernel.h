@@ -405,9 +405,9 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
             for (int nb = 0; nb < 2; ++nb) sums.check(acc[mb][nb]);
         if (__syncthreads_or(lost_bits(lost) || sums.refused())) return false;
     }
-    // scale and shift of the tile's rows
+    // scale and shift of the tile's rows (a convolution's, which is A.B)
     float* const row_scale = reinterpret_cast<float*>(slds);
-    if (p.gamma) {
+    if (!NT && p.gamma) {
         __syncthreads();                             // the staging buffers are free
         if (thread < BM) {
             const int row = min(m0 + thread, M - 1);
@@ -434,7 +434,7 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
                 const int dr = 8 * (r / 4) + (r % 4);
                 float* const d = c + (int64_t)dr * p.ldc;
                 pair v = {acc[mb][0][r], acc[mb][1][r]};
-                if (p.gamma) {
+                if (!NT && p.gamma) {
                     const float scale = row_scale[row0 - m0 + dr], shift = row_scale[BM + row0 - m0 + dr];
                     v[0] = fmaxf(fmaf(v[0], scale, shift), 0.f);
                     v[1] = fmaxf(fmaf(v[1], scale, shift), 0.f);
