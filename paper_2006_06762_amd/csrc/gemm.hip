@@ -410,12 +410,12 @@ hipError_t launch_variant(const GemmArgs& a, hipStream_t stream)
 }
 
 
-template <int BM, int WM, int WN, int NWG, bool SPEC, bool NT>
+template <int BM, int WM, int WN, int NWG, bool SPEC, bool NT, bool FUSED>
 hipError_t launch_split(const GemmArgs& a, hipStream_t stream)
 {
     const gsplit::Grid g{(a.M + BM - 1) / BM, (a.N + BM - 1) / BM, 8};
     constexpr size_t lds_bytes = gsplit::lds_bytes<BM, BM, NWG, SPEC>();
-    auto kern = gsplit::gemm_split_kernel<BM, BM, WM, WN, NWG, SPEC, 2, NT>;
+    auto kern = gsplit::gemm_split_kernel<BM, BM, WM, WN, NWG, SPEC, 2, NT, FUSED>;
     if (lds_bytes > 48 * 1024) {
         static LdsLimit granted;
         hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_bytes, granted);
@@ -425,16 +425,16 @@ hipError_t launch_split(const GemmArgs& a, hipStream_t stream)
                          stream, a, g);
 }
 
-template <bool NT>
+template <bool NT, bool FUSED = false>
 hipError_t launch_split_any(const GemmArgs& a, hipStream_t stream)
 {
     static_assert(gsplit::kVariantCount == 5, "one launch per variant");
     switch (gsplit::choose_variant(a.M, a.N, a.K, a.batch)) {
-        case 0: return launch_split<128, 2, 2, 1, false, NT>(a, stream);
-        case 1: return launch_split<128, 2, 2, 1, true, NT>(a, stream);
-        case 2: return launch_split<64, 2, 1, 1, false, NT>(a, stream);
-        case 3: return launch_split<64, 2, 1, 2, false, NT>(a, stream);
-        default: return launch_split<64, 2, 1, 4, false, NT>(a, stream);
+        case 0: return launch_split<128, 2, 2, 1, false, NT, FUSED>(a, stream);
+        case 1: return launch_split<128, 2, 2, 1, true, NT, FUSED>(a, stream);
+        case 2: return launch_split<64, 2, 1, 1, false, NT, FUSED>(a, stream);
+        case 3: return launch_split<64, 2, 1, 2, false, NT, FUSED>(a, stream);
+        default: return launch_split<64, 2, 1, 4, false, NT, FUSED>(a, stream);
     }
 }
 
@@ -546,7 +546,10 @@ hipError_t launch_gemm(const GemmArgs& args, hipStream_t stream)
     return err;
 }
 
-hipError_t launch_gemm_split(const GemmArgs& a, hipStream_t stream) { return launch_split_any<false>(a, stream); }
+hipError_t launch_gemm_split(const GemmArgs& a, hipStream_t stream)
+{
+    return a.gamma ? launch_split_any<false, true>(a, stream) : launch_split_any<false>(a, stream);
+}
 
 void gemm_split_variant(const GemmArgs& a, int* tile, int* groups)
 {

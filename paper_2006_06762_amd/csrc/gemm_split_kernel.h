@@ -63,7 +63,7 @@ struct Grid {
 
 // One tile of a work-group: as bf16 pieces, or PLAIN, with the fp32 instruction.  False if it met a value that the
 // pieces cannot carry: then nothing is stored.
-template <int BM, int BN, int WM, int WN, int NWG, bool SPEC, bool NT, bool PLAIN>
+template <int BM, int BN, int WM, int WN, int NWG, bool SPEC, bool NT, bool FUSED, bool PLAIN>
 __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, const int thread)
 {
     constexpr int T = 64 * WM * WN;                  // threads of a wave group
@@ -405,9 +405,9 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
             for (int nb = 0; nb < 2; ++nb) sums.check(acc[mb][nb]);
         if (__syncthreads_or(lost_bits(lost) || sums.refused())) return false;
     }
-    // scale and shift of the tile's rows (a convolution's, which is A.B)
+    // scale and shift of the tile's rows
     float* const row_scale = reinterpret_cast<float*>(slds);
-    if (!NT && p.gamma) {
+    if (FUSED) {
         __syncthreads();                             // the staging buffers are free
         if (thread < BM) {
             const int row = min(m0 + thread, M - 1);
@@ -434,7 +434,7 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
                 const int dr = 8 * (r / 4) + (r % 4);
                 float* const d = c + (int64_t)dr * p.ldc;
                 pair v = {acc[mb][0][r], acc[mb][1][r]};
-                if (!NT && p.gamma) {
+                if (FUSED) {
                     const float scale = row_scale[row0 - m0 + dr], shift = row_scale[BM + row0 - m0 + dr];
                     v[0] = fmaxf(fmaf(v[0], scale, shift), 0.f);
                     v[1] = fmaxf(fmaf(v[1], scale, shift), 0.f);
@@ -454,13 +454,15 @@ __device__ __forceinline__ bool compute_tile(const GemmArgs& p, const Grid& g, c
 // kernels did (4096^3, probabilities of a steep softmax: 1050 to 1080 us against 1003); infinities, NaN and a last
 // chunk's lost pieces cost both tries (1870).  Operand by operand, without staging, it was 5020.  The flag costs an
 // ordinary product 1.4 % (set at the end of a round instead, where it cuts the schedule in two, 6 %).
-template <int BM, int BN, int WM, int WN, int NWG, bool SPEC, int MINW, bool NT>
+// FUSED: batch norm and ReLU per row of C (a pointwise convolution's).  Forms of their own: asked of every product, they
+// cost short reductions 3 to 5 % (3 x 1312 x 384 x 151 11.1 -> 11.7 us, 192 heads of 249 x 249 x 80 67.9 -> 70.7).
+template <int BM, int BN, int WM, int WN, int NWG, bool SPEC, int MINW, bool NT, bool FUSED>
 __global__ __launch_bounds__(64 * WM * WN * (SPEC ? 2 : NWG), MINW) void gemm_split_kernel(const GemmArgs p, const Grid g)
 {
     int thread = threadIdx.x;
-    if (compute_tile<BM, BN, WM, WN, NWG, SPEC, NT, false>(p, g, thread)) return;
+    if (compute_tile<BM, BN, WM, WN, NWG, SPEC, NT, FUSED, false>(p, g, thread)) return;
     asm("" : "+v"(thread));                          // nothing of the second try is held through the first
-    compute_tile<BM, BN, WM, WN, NWG, SPEC, NT, true>(p, g, thread);
+    compute_tile<BM, BN, WM, WN, NWG, SPEC, NT, FUSED, true>(p, g, thread);
 }
 
 }  // namespace gsplit

@@ -40,14 +40,14 @@ constexpr bool tbg_split_takes(const TbgProblem& p)
 // 158).  The split GEMM keeps its sizes: its scores are the closer ones, and those tbg gives for them.  A work-group
 // walks `walk` floats of every key row of a chunk of 128 in a row, so with few work-groups or a long walk the two
 // kernels are faster (8 heads of 300 x 300 x 128 11.4 / 16.9, 24 of 512 x 512 x 256 43.6 / 55.2).  Of 826 shapes of 136 to 512
-// keys, 32 to 256 floats and 4 to 128 heads this line costs 0.5 % against the faster of both on average and 17 % at
-// most; the next ones to it: 24 heads of 256 x 256 x 104, 17.9 / 11.9, 16 of 384 x 384 x 104 21.7 / 16.4, 24 of 384 x 384 x
+// keys, 32 to 256 floats and 4 to 128 heads this line costs 0.4 % against the faster of both on average and 17 % at
+// most; the next ones to it: 24 heads of 256 x 256 x 104 17.9 / 11.9, 16 of 384 x 384 x 104 21.7 / 16.4, 24 of 384 x 384 x
 // 128 23.5 / 24.9, 48 of 320 x 320 x 192 36.4 / 34.4.
 constexpr bool tbs_long_takes(const TbgProblem& p)
 {
     const int64_t chunks = (p.S + 127) / 128, walk = chunks * p.D, items = p.batch * ((p.S + 31) / 32);
     return p.softmax && p.S > kTbgMaxKeys && p.S <= kTbgLongKeys && p.D <= kTbgLongD && p.D % 8 == 0 && p.offsets32 && !tbg_split_takes(p) &&
-           (walk <= 64 || (walk <= 512 && items >= (walk < 304 ? walk / 2 : 152)));
+           (walk <= 64 || (walk <= 512 && items >= (walk < 320 ? 11 * walk / 20 : 176)));
 }
 
 constexpr TbgKernel choose_tbg(const TbgProblem& p)

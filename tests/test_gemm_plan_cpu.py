@@ -125,7 +125,7 @@ def test_long_scores_of_the_gpu_tests_run_the_one_kernel(scores):
 def test_scores_dispatch_at_its_lines(scores):
     """128 and 512 keys, few and enough work-groups, long walks, the split GEMM's sizes; scores alone never."""
     for (S, D, heads, softmax), want in {(128, 64, 200, 1): "rows32", (129, 64, 16, 1): "rows_long", (129, 64, 12, 1): "tile",
-                                         (384, 104, 12, 1): "tile", (384, 104, 13, 1): "rows_long", (384, 128, 24, 1): "rows_long",
+                                         (384, 104, 14, 1): "tile", (384, 104, 15, 1): "rows_long", (136, 80, 17, 1): "tile", (136, 80, 18, 1): "rows_long", (384, 128, 24, 1): "rows_long",
                                          (320, 192, 48, 1): "tile64", (512, 256, 24, 1): "tile64", (512, 64, 48, 1): "rows_long",
                                          (513, 64, 20, 1): "tile", (512, 128, 32, 1): "gemm", (384, 128, 57, 1): "gemm", (256, 64, 100, 0): "tile64",
                                          (300, 36, 40, 1): "tile", (300, 33, 40, 1): "gemm"}.items():

@@ -24,7 +24,7 @@ def check(got, ref, what):
 def heads_for(S, D):
     """As many heads as the one kernel asks for, and fewer than the split GEMM does."""
     chunks = (S + 127) // 128
-    return 2 if D * chunks <= 64 else (31, 17, 12)[chunks - 2]
+    return 2 if D * chunks <= 64 else (36, 20, 14)[chunks - 2]
 
 
 # (more than 512 floats of a row to walk, chunks times D, are left to two kernels)
