@@ -124,8 +124,8 @@ hipError_t launch_bands_as(const ConvArgs& a, hipStream_t stream, bool* taken)
         wl * rows_in(dw::kBandRows) > 2 * kRoom || a.OH > (1 << 20))
         return hipSuccess;
     // One thread per output needs no second trip (load, LDS, weights, store): below some four million products it is
-    // the faster one (335 planes of 58 x 58, stride 2, 5.2 against 5.7 us; 408 of 29 x 29 5.1 against 5.9; 636 of 77 x
-    // 77, stride 2, 11.4 against 7.8).
+    // level or the faster one for 3 x 3 (393 planes of 27 x 27, 2.6 million, 4.9 against 5.6 us; 277 of 35 x 35, 3.1 million, 5.0
+    // against 5.2; 674 of 27 x 27, 4.4 million, 5.8 against 5.4; 225 of 111 x 111, stride 2, 6.4 million, 7.7 against 5.9).
     if (planes * a.OH * a.OW * (K_ * K_) < 4000000) return hipSuccess;
     dw::Band g{};
     // the fewest bands that fit, and smaller ones until the chip has four work-groups per CU
