@@ -48,8 +48,8 @@ constexpr bool gemm_split_takes(const GemmProblem& p)
 // 96 5.1 -> 5.5), up to two from 97 (1422 x 200 x 510 14.7 -> 12.5, 192 x 2464 x 320 10.1 -> 10.0); past that each CU has
 // more work than its own chain and larger tiles reuse more (520 tiles, K = 384, 11.6 -> 13.3).  Where the pipelined kernel
 // could load them, products of 257 to 512 tiles are level at K = 100 to 128, slower up to 288 (3 x 120 x 784 x 144 6.7 ->
-// 8.4, 624 x 672 x 228 8.6 -> 9.5) and faster from 320 on (855 x 544 x 452 12.9 -> 11.4): they stay here for their sums, 5.2e-8
-// of the exact results where the pipelined kernel's are 2.0e-7 to 2.5e-7.
+// 8.4, 624 x 672 x 228 8.6 -> 9.5) and faster from 330 on (1861 x 160 x 452 12.9 -> 11.4): they stay here for their sums, 5.2e-8
+// of the exact results where the pipelined kernel's are 1.8e-7 (K = 97) to 3.4e-7 (704).
 constexpr bool gemm_rows32_takes(const GemmProblem& p)
 {
     const int64_t tiles = gemm_tiles(p, 32);
