@@ -315,14 +315,21 @@ def conv2d_pack_weights(x_shape, w, stride=(1, 1), pad=(0, 0), bn=None, eps=0.0,
 
 def _run_packed(fn, name, op, desc, x, pack, y, ws):
     d = ConvDesc.from_buffer_copy(desc)
-    d.x_stride = _conv_strides(x)
+    xs = d.x_stride = _conv_strides(x)
+    if xs is not _NO_STRIDES and (xs[0] % 4 or xs[1] % 4 or xs[2] % 4 or xs[0] * x.shape[0] >= 1 << 29):
+        # The order of a pack goes by its descriptor's strides: a view that would have made another one is copied
+        # (the two orders always differ in size).
+        if conv2d_packed_size(d) != conv2d_packed_size(desc):
+            x = x.contiguous()
+            d.x_stride = _NO_STRIDES
     d.y_stride = _conv_strides(y)
     _with_workspace(fn, name, op, bytes(d), (_ptr(x), pack.data_ptr(), _ptr(y)), ws)
     return y
 
 
 def conv2d_packed(desc, x, pack, y, ws=None):
-    """conv2d with weights from conv2d_pack_weights (desc: the descriptor it returned)."""
+    """conv2d with weights from conv2d_pack_weights (desc: the descriptor it returned).  x may be a strided view; one
+    whose rows are no whole 16-byte units is copied first where the pack is in the patch kernel's order."""
     return _run_packed(_fast.anr_conv2d_packed, "anr_conv2d_packed", ANR_OP_CONV2D, desc, x, pack, y, ws)
 
 

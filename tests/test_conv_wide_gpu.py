@@ -154,3 +154,22 @@ def test_packs_in_the_patch_order(shape):
     anr.conv2d(xv, wd, wide, s.stride, s.pad)
     anr.conv2d_packed(desc, xv, pack, z)
     assert torch.equal(z.nan_to_num(1.5), wide.nan_to_num(1.5))
+
+
+@pytest.mark.parametrize("N,C,H,K", [(16, 64, 56, 64), (16, 64, 28, 128), (4, 32, 80, 384), (16, 64, 64, 64), (4, 64, 57, 512), (2, 64, 14, 64)])
+@pytest.mark.parametrize("gap", [1, 2, 4])
+def test_packed_calls_on_strided_views(N, C, H, K, gap):
+    """A pack made for packed rows, x with rows that lie apart: whole 16-byte units or not, the same results."""
+    from paper_2006_06762_amd import binding as anr
+    gen = torch.Generator(device="cuda").manual_seed(5500)
+    x = torch.empty((N, C, H, H + gap), device="cuda").uniform_(-1, 1, generator=gen)[..., :H]
+    w = torch.empty((K, C, 3, 3), device="cuda").uniform_(-1, 1, generator=gen)
+    bn = [torch.from_numpy(v).cuda() for v in I.bn_inputs(K, 5501)]
+    desc, pack = anr.conv2d_pack_weights(x.shape, w, (1, 1), (1, 1), bn=bn, eps=I.BN_EPS)
+    y, want = torch.zeros((2, N, K, H, H), device="cuda")
+    for run in (anr.conv2d_packed, anr.conv_bn_relu_packed):
+        run(desc, x.contiguous(), pack, want)
+        run(desc, x, pack, y)
+        # (another kernel may run where the pack is a plain copy: the same products in another order)
+        assert float((y - want).abs().max()) <= 1e-4 * float(want.abs().max())
+        assert torch.equal(y, want) or anr.conv2d_packed_size(desc) == 4 * ((2 * K + 63) // 64 * 64 + K * C * 9)
