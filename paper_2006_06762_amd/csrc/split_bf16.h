@@ -76,8 +76,10 @@ struct SumCheck {
     {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            not_finite = fmaf(a[r], 0.f, not_finite);
-            smallest = min(smallest, (__builtin_bit_cast(uint32_t, a[r]) << 1) - 1u);
+            // (a copy: the compiler's bit cast of a vector's element takes the first one whatever its index)
+            const float sum = a[r];
+            not_finite = fmaf(sum, 0.f, not_finite);
+            smallest = min(smallest, (__builtin_bit_cast(uint32_t, sum) << 1) - 1u);
         }
     }
     __device__ __forceinline__ bool refused() const

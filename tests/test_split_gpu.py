@@ -239,6 +239,22 @@ def test_split_gemm_results_near_the_smallest_normal(anr, variant):
     assert float(units.max()) <= 1.0 + SMALL, float(units.max())
 
 
+@pytest.mark.parametrize("variant", VARIANTS)
+def test_split_gemm_single_rows_near_the_smallest_normal(anr, variant):
+    """The same where only some rows of a tile are that small: rows of every accumulator register."""
+    batch, M, N, K = VARIANTS[variant]
+    B = uniform(29, batch, K, N)
+    B = torch.where(B < 0, B * 0.5 - 1.0, B * 0.5 + 1.0) * 2.0 ** -60
+    C = torch.empty(batch, M, N, device="cuda")
+    for first in (1, 6, 11, 16):
+        A = few_terms(27, 1, batch, M, K)
+        A[:, first::29] *= 2.0 ** -64
+        anr.gemm(A, B, C)
+        ref = A.double() @ B.double()
+        units = ((C.double() - ref).abs() / ref.abs() * 2.0 ** 24)[:, first::29]
+        assert float(units.max()) <= 1.0 + SMALL, float(units.max())
+
+
 def conv_reference(x, w, stride, pad, dil=1, groups=1):
     """Convolution and the convolution of the absolute values, in 64 bits, tap by tap."""
     N, C, H, W = x.shape
