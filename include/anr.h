@@ -35,7 +35,9 @@
  *     partial sums of a matrix's slices.  Its contents on entry do not
  *     matter and are undefined on return.  A call that needs more than it
  *     is given returns ANR_ERR_WORKSPACE.  Calls that share one workspace
- *     must be ordered (same stream).
+ *     must be ordered (same stream).  Convolutions that are given
+ *     anr_conv2d_fast_workspace_size() bytes run the fastest kernel, which for
+ *     larger layers keeps more there; its sums are taken in another order.
  *   - Errors are return codes.  All argument checks happen on the host before
  *     anything is launched, so an invalid call has no effect on the device.
  *   - Thread-safe and re-entrant.  The library reads no environment variable
@@ -162,8 +164,8 @@ anr_status anr_conv2d(const anr_conv_desc *desc, const float *x, const float *w,
 
 /* anr_conv2d for callers that cannot allocate device memory, and so cannot bring a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc.  Same arguments, kernels and results as anr_conv2d (bit for bit), but the
- * partial tiles of a split reduction go to a fixed array of
+ * hipMalloc.  Same arguments, kernels and results as anr_conv2d with a workspace of
+ * anr_workspace_size() bytes (bit for bit), but the partial tiles of a split reduction go to a fixed array of
  * ANR_STATIC_SCRATCH_BYTES that the library holds in the memory of every GPU it is
  * loaded on, from load time until the process ends.  The call allocates and frees
  * nothing and synchronises nothing.  A descriptor whose plan needs more
@@ -276,8 +278,15 @@ anr_status anr_nrm(const anr_nrm_desc *desc, const float *x, float *out,
  * way the operation does. */
 anr_status anr_workspace_size(int op, const void *desc, size_t *bytes);
 
+/* Bytes of workspace with which anr_conv2d, anr_conv_bn_relu and their packed forms run `desc`
+ * fastest: for layers that gain from it, room for the operands as three bf16 pieces each (at
+ * most 256 MB), which are made once per call there instead of once per output tile
+ * (conv_pieces_kernel.h), else anr_workspace_size().  May be less than that; a call that is
+ * given less than both returns ANR_ERR_WORKSPACE, one given less than this runs another kernel. */
+anr_status anr_conv2d_fast_workspace_size(const anr_conv_desc *desc, size_t *bytes);
+
 /* Which kernel anr_conv2d / anr_conv_bn_relu would run for `desc` with 16-byte aligned
- * pointers, and how (host-side planning only: nothing is launched, no GPU is needed).  For
+ * pointers and anr_workspace_size() bytes of workspace, and how (host-side planning only: nothing is launched, no GPU is needed).  For
  * callers that want to know why a layer takes the time it does, and for tests of the
  * selection logic.  tile_m x tile_n is the work-group's output tile (pixels x channels),
  * ksplit the number of work-groups that share a tile's reduction through the workspace,

@@ -30,7 +30,7 @@ ANR_OP_GEMM, ANR_OP_CONV2D, ANR_OP_CONV_BN_RELU, ANR_OP_DWCONV, ANR_OP_TBG, ANR_
 
 EXPORTS = ("anr_gemm", "anr_conv2d", "anr_conv2d_noalloc", "anr_conv2d_packed_size", "anr_conv2d_pack_weights",
            "anr_conv2d_packed", "anr_conv_bn_relu_packed", "anr_conv_bn_relu", "anr_dwconv", "anr_tbg", "anr_tbs", "anr_nrm",
-           "anr_workspace_size", "anr_conv2d_route", "anr_status_string", "anr_version", "anr_last_hip_error",
+           "anr_workspace_size", "anr_conv2d_fast_workspace_size", "anr_conv2d_route", "anr_status_string", "anr_version", "anr_last_hip_error",
            "anr_last_hip_error_string")
 
 
@@ -90,10 +90,11 @@ _lib.anr_tbg.argtypes = [ctypes.POINTER(TbgDesc), _vp, _vp, _vp, _vp, ctypes.c_s
 _lib.anr_tbs.argtypes = [ctypes.POINTER(TbgDesc), _vp, _vp, _vp, _vp, ctypes.c_size_t, _vp]
 _lib.anr_nrm.argtypes = [ctypes.POINTER(NrmDesc), _vp, _vp, _vp, ctypes.c_size_t, _vp]
 _lib.anr_workspace_size.argtypes = [ctypes.c_int, _vp, ctypes.POINTER(ctypes.c_size_t)]
+_lib.anr_conv2d_fast_workspace_size.argtypes = [ctypes.POINTER(ConvDesc), ctypes.POINTER(ctypes.c_size_t)]
 _lib.anr_conv2d_route.argtypes = [ctypes.POINTER(ConvDesc), ctypes.POINTER(ConvRoute)]
 for _name in ("anr_gemm", "anr_conv2d", "anr_conv2d_noalloc", "anr_conv2d_packed_size", "anr_conv2d_pack_weights",
               "anr_conv2d_packed", "anr_conv_bn_relu_packed", "anr_conv_bn_relu", "anr_dwconv", "anr_tbg", "anr_tbs",
-              "anr_workspace_size"):
+              "anr_workspace_size", "anr_conv2d_fast_workspace_size"):
     getattr(_lib, _name).restype = ctypes.c_int
 _lib.anr_status_string.argtypes = [ctypes.c_int]
 _lib.anr_status_string.restype = ctypes.c_char_p
@@ -203,34 +204,60 @@ def conv2d_route(desc: ConvDesc) -> ConvRoute:
     return r
 
 
+def conv2d_fast_workspace_size(desc: ConvDesc) -> int:
+    """Bytes of workspace with which the convolutions run `desc` fastest."""
+    n = ctypes.c_size_t(0)
+    _check(_lib.anr_conv2d_fast_workspace_size(ctypes.byref(desc), ctypes.byref(n)), "anr_conv2d_fast_workspace_size")
+    return int(n.value)
+
+
 _workspaces = {}
+_fast_sizes = {}        # descriptor of a convolution, packed -> conv2d_fast_workspace_size
+
+
+def _fast_size(desc):
+    size = _fast_sizes.get(desc)
+    if size is None:
+        if len(_fast_sizes) >= 4096:
+            _fast_sizes.clear()
+        n = ctypes.c_size_t(0)
+        # (a descriptor that is refused here is refused by the call itself)
+        size = n.value if _lib.anr_conv2d_fast_workspace_size(ctypes.byref(ConvDesc.from_buffer_copy(desc)), ctypes.byref(n)) == ANR_OK else 0
+        _fast_sizes[desc] = size
+    return size
 
 
 def _with_workspace(fn, name, op, desc, args, ws, desc_type=ConvDesc):
     """Calls fn(desc, *args, workspace, bytes, stream).  The workspace is the caller's tensor, else a buffer
     kept per (device, stream) and grown on demand (calls on one stream run in order, so they can share it; a
-    call never synchronises).  Without the caller's tensor the call itself says whether the buffer it is
-    handed will do: a refused call has had no effect, and is made again with one that is large enough."""
+    call never synchronises).  Without the caller's tensor a convolution gets what it runs fastest with, at most
+    256 MB; for the other operation the call itself says whether the buffer it is handed will do: a refused call
+    has had no effect, and is made again with one that is large enough."""
     stream = _stream()
     if ws is None:
         key = (torch._C._cuda_getDevice(), stream)
         ws = _workspaces.get(key)
-        if ws is None:
-            status = fn(desc, *args, None, 0, stream)
-        else:
-            status = fn(desc, *args, ws.data_ptr(), ws.numel(), stream)
+        have = 0 if ws is None else ws.numel()
+        if desc_type is ConvDesc:
+            need = _fast_size(desc)
+            if need > have:
+                ws = _workspaces[key] = torch.empty(need, dtype=torch.uint8, device="cuda")
+                have = need
+        status = fn(desc, *args, ws.data_ptr() if have else None, have, stream)
         if status == ANR_ERR_WORKSPACE:
             ws = torch.empty(workspace_size(op, desc_type.from_buffer_copy(desc)), dtype=torch.uint8, device="cuda")
             _workspaces[key] = ws
             status = fn(desc, *args, ws.data_ptr(), ws.numel(), stream)
     else:
         need = workspace_size(op, desc_type.from_buffer_copy(desc))
-        if need == 0:
+        size = ws.numel() * ws.element_size()
+        fast = _fast_size(desc) if desc_type is ConvDesc else 0
+        if ws.is_cuda and ws.is_contiguous() and (size >= need > 0 or size >= fast > 0):
+            status = fn(desc, *args, ws.data_ptr(), size, stream)
+        elif need == 0:
             status = fn(desc, *args, None, 0, stream)
         else:
-            if not ws.is_cuda or not ws.is_contiguous() or ws.numel() * ws.element_size() < need:
-                raise ValueError("workspace must be a contiguous CUDA tensor of at least %d bytes" % need)
-            status = fn(desc, *args, ws.data_ptr(), ws.numel() * ws.element_size(), stream)
+            raise ValueError("workspace must be a contiguous CUDA tensor of at least %d bytes" % need)
     if status != ANR_OK:
         raise AnrError(status, name)
 

@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libanr.so")
 
-SOURCES = ["api.cpp", "gemm.hip", "tbg.hip", "conv_direct.hip", "conv_igemm.hip", "conv_gather.hip", "conv_pointwise.hip", "conv_stem.hip", "dwconv.hip", "nrm.hip", "static_scratch.hip"]
+SOURCES = ["api.cpp", "gemm.hip", "tbg.hip", "conv_direct.hip", "conv_igemm.hip", "conv_gather.hip", "conv_pieces.hip", "conv_pointwise.hip", "conv_stem.hip", "dwconv.hip", "nrm.hip", "static_scratch.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
@@ -33,6 +33,7 @@ FLAGS = [
 FILE_FLAGS = {
     "conv_igemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "conv_gather.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "conv_pieces.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "conv_stem.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "gemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }

@@ -109,6 +109,9 @@ struct ConvArgs {
 // Workspace the convolution of `a` needs (0 for most shapes): that of the plan for 16-byte
 // aligned x and w (null pointers count as aligned); plans for less aligned pointers need none.
 size_t conv2d_workspace_bytes(const ConvArgs& a);
+// Workspace with which the fastest kernel runs: more than the above for layers that gain from their operands' pieces being
+// made once per call, which run another kernel where they are given less.
+size_t conv2d_fast_workspace_bytes(const ConvArgs& a);
 // Plans once, checks a.ws / a.ws_bytes against the plan, launches.  *ws_fault: 0 fine, 1 the
 // workspace is missing or too small, 2 it is not 16-byte aligned (nothing is enqueued then).
 hipError_t launch_conv2d(const ConvArgs& a, hipStream_t stream, int* ws_fault);

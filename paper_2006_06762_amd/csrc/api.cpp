@@ -245,12 +245,14 @@ anr_status anr_conv2d_noalloc(const anr_conv_desc* d, const float* x, const floa
     if (!x || !w || !y) return ANR_ERR_NULL;
     anr::ConvArgs a = make_conv_args(d, g, x, w, y);
     // plans that need no workspace never touch the array (nor the runtime, to look it up)
-    if (anr::conv2d_workspace_bytes(a) == 0) return run_conv2d(&a, nullptr, 0, hip_stream);
+    const size_t need = anr::conv2d_workspace_bytes(a);
+    if (need == 0) return run_conv2d(&a, nullptr, 0, hip_stream);
     void* scratch = nullptr;
     size_t scratch_bytes = 0;
     const hipError_t e = anr::static_scratch(&scratch, &scratch_bytes);
     if (e != hipSuccess) return launch_status(e);
-    return run_conv2d(&a, scratch, scratch_bytes, hip_stream);
+    // (no more than the need: a larger workspace may select another kernel)
+    return run_conv2d(&a, scratch, need < scratch_bytes ? need : scratch_bytes, hip_stream);
 }
 
 anr_status anr_conv2d_packed_size(const anr_conv_desc* d, size_t* bytes)
@@ -409,6 +411,16 @@ anr_status anr_workspace_size(int op, const void* desc, size_t* bytes)
         const anr::ConvArgs a = make_conv_args(static_cast<const anr_conv_desc*>(desc), cg, nullptr, nullptr, nullptr);
         *bytes = anr::conv2d_workspace_bytes(a);
     }
+    return ANR_OK;
+}
+
+anr_status anr_conv2d_fast_workspace_size(const anr_conv_desc* d, size_t* bytes)
+{
+    if (!d || !bytes) return ANR_ERR_NULL;
+    ConvGeom g;
+    const anr_status st = check_conv(d, false, &g);
+    if (st != ANR_OK) return st;
+    *bytes = anr::conv2d_fast_workspace_bytes(make_conv_args(d, g, nullptr, nullptr, nullptr));
     return ANR_OK;
 }
 

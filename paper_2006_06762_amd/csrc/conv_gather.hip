@@ -9,6 +9,8 @@ namespace {
 
 using namespace gconv;
 
+constexpr int kCUs = 256;
+
 struct Tile {
     int bm, bn;
     double chunk_us;    // CU time per chunk and work-group when the CU is saturated with work-groups
@@ -16,11 +18,14 @@ struct Tile {
     int occupancy;      // work-groups one CU holds (LDS, registers)
 };
 constexpr Tile kTiles[] = {{128, 128, 3.2, 2.8, 2}, {128, 64, 1.6, 1.9, 3}, {64, 64, 0.8, 1.1, 4}};
-constexpr int kCUs = 256;
 constexpr double kLaunchUs = 2.0;            // launch plus prologue and epilogue
 constexpr double kWsBytesPerUs = 3.0e6;      // workspace traffic, bytes per microsecond
 
-bool make_plan(const ConvArgs& a, Plan* g, bool allow_taps = true)
+}  // namespace
+
+namespace gconv {
+
+bool make_plan(const ConvArgs& a, Plan* g, bool allow_taps)
 {
     const int64_t x_extent = (int64_t)(a.N - 1) * a.xs[0] + (int64_t)(a.C - 1) * a.xs[1] +
                              (int64_t)(a.H - 1) * a.xs[2] + a.W;
@@ -115,6 +120,10 @@ void set_tile(const ConvArgs& a, Plan* g, int bm, int bn, int ks)
     g->rblocks = (g->Mpad / 4 * reduce_lanes(g->ksplit) + 255) / 256;
     g->d_rblocks = make_fastdiv(g->rblocks);
 }
+
+}  // namespace gconv
+
+namespace {
 
 // Estimated run time in microseconds of tile t with the reduction split ks ways.  Two bounds:
 // the work of the busiest CU when it is saturated (work-groups are dealt evenly over the CUs
@@ -276,7 +285,7 @@ double conv2d_gather_estimate_us(const ConvArgs& a)
 {
     Plan g;
     if (!(make_plan(a, &g) && choose_tile(a, &g))) return INFINITY;
-    if (g.taps) return estimate_taps_us(g, a, g.ksplit);
+    if (g.taps) return estimate_taps_us(g, a, g.ksplit);        // (6 and, for the large kernels, 4 % too short over 220 layers)
     // Weights that are not 16-byte aligned: the form without compile-time taps, which loads them one by one; its own
     // estimate, for tiles that it compares with each other, is too short by a quarter (110 layers of 16 to 512 channels on maps of
     // 24 to 150 pixels: with this the choice is within 0.6 % of the better kernel's time on average, 15 % at most).
@@ -335,7 +344,11 @@ hipError_t launch_gather_plan(const ConvArgs& a, const Plan& g, hipStream_t stre
     } else if (g.bm == 128 && g.bn == 128) err = launch_tile<128, 128>(a, g, stream);
     else if (g.bm == 128) err = launch_tile<128, 64>(a, g, stream);
     else err = launch_tile<64, 64>(a, g, stream);
-    if (err != hipSuccess || g.ksplit == 1) return err;
+    return err != hipSuccess || g.ksplit == 1 ? err : gconv::launch_splitk_reduce(a, g, stream);
+}
+
+hipError_t gconv::launch_splitk_reduce(const ConvArgs& a, const Plan& g, hipStream_t stream)
+{
     const dim3 rgrid((unsigned)((int64_t)a.K * g.rblocks));
     switch (reduce_lanes(g.ksplit)) {
         case 8: return launch_kernel(conv_splitk_reduce_kernel<8>, rgrid, dim3(256), 0, stream, a, g);

@@ -63,6 +63,12 @@ struct Plan {
     FastDiv d_rblocks;
 };
 
+// Host side (conv_gather.hip): the geometry of a call, false where it is outside what the kernels support; a tile and a split of
+// the reduction for it; the sum of a split reduction's partial tiles, with the epilogue.
+bool make_plan(const ConvArgs& a, Plan* g, bool allow_taps = true);
+void set_tile(const ConvArgs& a, Plan* g, int bm, int bn, int ks);
+hipError_t launch_splitk_reduce(const ConvArgs& a, const Plan& g, hipStream_t stream);
+
 // Inference batch norm of output channel co as one multiply-add: y = v * scale + shift.
 __device__ __forceinline__ void bn_constants(const ConvArgs& p, int co, float* scale, float* shift)
 {

@@ -24,6 +24,19 @@ size_t conv2d_gather_workspace_bytes(const ConvArgs& a);
 // 16-byte aligned); infinite where it does not take the call.
 double conv2d_gather_estimate_us(const ConvArgs& a);
 
+// Estimated time of the kernel that the library's choice of a.route runs without a workspace for pieces, in microseconds;
+// zero where that choice is to stand.  Pointers are taken as aligned and absent.
+double conv2d_estimate_us(const ConvArgs& a);
+
+// Order of a pack that a patch kernel reads: output channels per tile and input channels per chunk, rows of a chunk's weights
+// four floats apart; false where the pack is a plain copy.
+bool conv2d_pack_order(const ConvArgs& a, int* tile, int* channels);
+
+// The general convolution on pieces made once per call (conv_pieces_kernel.h).  Bytes of workspace it needs, zero where
+// another kernel is the faster one; *taken false: that, or a.ws is smaller or not aligned.
+size_t conv2d_pieces_workspace_bytes(const ConvArgs& a);
+hipError_t launch_conv2d_pieces(const ConvArgs& a, hipStream_t stream, bool* taken);
+
 // Streaming kernel for pointwise layers with few channels (conv_pointwise_kernel.h); same contract.
 hipError_t launch_conv2d_pointwise(const ConvArgs& a, hipStream_t stream, bool* taken);
 

@@ -463,3 +463,27 @@ def test_tbg_sizes_beyond_the_descriptor_are_refused_by_the_library(fn):
     q = torch.empty((2 ** 31, 1, 1, 4), device="meta")
     d = B.TbgDesc.from_buffer_copy(B._tbg_desc(q, q, torch.empty((2 ** 31, 1, 1, 1), device="meta")))
     assert getattr(B.raw(), fn)(ctypes.byref(d), DUMMY, DUMMY, DUMMY, None, 0, None) == B.ANR_ERR_INVALID_ARG
+
+
+def test_fast_workspace_size():
+    n = ctypes.c_size_t(0)
+    lib = B.raw()
+    assert lib.anr_conv2d_fast_workspace_size(None, ctypes.byref(n)) == B.ANR_ERR_NULL
+    bad = B.conv_desc((1, 4, 8, 8), 8, 3, 3, (0, 1))
+    assert lib.anr_conv2d_fast_workspace_size(ctypes.byref(bad), ctypes.byref(n)) == B.ANR_ERR_INVALID_ARG
+    # the pieces of both operands, 6 bytes a float, and nothing on the route that asks for the patch kernel
+    shape = (16, 256, 14, 14)
+    d = B.conv_desc(shape, 256, 3, 3, (1, 1), (1, 1))
+    assert B.conv2d_fast_workspace_size(d) == 6 * (16 * 256 * 14 * 14 + 256 * 256 * 9) < B.workspace_size(B.ANR_OP_CONV2D, d)
+    d = B.conv_desc((16, 32, 81, 81), 32, 5, 5, (1, 1), (2, 2))
+    assert B.conv2d_fast_workspace_size(d) > 6 * 16 * 32 * 81 * 81 > B.workspace_size(B.ANR_OP_CONV2D, d) == 0
+    d.route = B.ANR_CONV_ROUTE_PATCH
+    assert B.conv2d_fast_workspace_size(d) == 0
+    # few pixels, pointwise layers, the stem, the patch kernels' own layers: what another kernel needs
+    for args in [((1, 512, 7, 7), 512, 3, 3, (1, 1), (1, 1)), ((16, 64, 56, 56), 256, 1, 1), ((16, 3, 224, 224), 64, 7, 7, (2, 2), (3, 3)),
+                 ((16, 64, 56, 56), 64, 3, 3, (1, 1), (1, 1))]:
+        d = B.conv_desc(*args)
+        assert B.conv2d_fast_workspace_size(d) == B.workspace_size(B.ANR_OP_CONV2D, d)
+    # a layer whose pieces are more than 256 MB
+    d = B.conv_desc((32, 256, 112, 112), 256, 5, 5, (1, 1), (2, 2))
+    assert B.conv2d_fast_workspace_size(d) == B.workspace_size(B.ANR_OP_CONV2D, d)
