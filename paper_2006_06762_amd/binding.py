@@ -1,4 +1,5 @@
-"""ctypes binding of libanr.so: argument marshalling only.
+"""Binding of libanr.so: argument marshalling only, in Python over ctypes and, for the operators' usual calls, in the
+extension module ``_native`` (csrc/binding_native.cpp).
 
 Function names and arguments mirror ``include/anr.h``.  Every tensor argument
 is a torch CUDA tensor (float32); torch is used for device memory and for the
@@ -17,12 +18,14 @@ import torch  # noqa: F401
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libanr.so")
 
-if not os.path.exists(LIB_PATH):
+if not all(os.path.exists(p) for p in (LIB_PATH, os.path.join(_HERE, "_native.so"))):
     raise ImportError(
-        "%s is missing: build it with `python -m paper_2006_06762_amd.build` "
+        "%s or _native.so is missing: build it with `python -m paper_2006_06762_amd.build` "
         "(there is no fallback path)" % LIB_PATH)
 
 _lib = ctypes.CDLL(LIB_PATH)
+
+from paper_2006_06762_amd import _native  # noqa: E402
 
 ANR_OK, ANR_ERR_NULL, ANR_ERR_INVALID_ARG, ANR_ERR_UNSUPPORTED, ANR_ERR_WORKSPACE, ANR_ERR_LAUNCH = range(6)
 ANR_LAYOUT_NCHW = 0
@@ -262,7 +265,7 @@ def _with_workspace(fn, name, op, desc, args, ws, desc_type=ConvDesc):
         raise AnrError(status, name)
 
 
-def gemm(A, B, C):
+def _gemm(A, B, C):
     """C = A.B.  A [M,K] / [b,M,K], B [K,N] / [b,K,N], C [M,N] / [b,M,N]; last dim contiguous."""
     sa, sb, sc = A.stride(), B.stride(), C.stride()
     if len(sa) == 2:
@@ -299,7 +302,7 @@ def _conv_packed_desc(x, w, y, stride, pad, dil, groups, route):
         return bytes(conv_desc((N, C, H, W), K, R, S, stride, pad, xs, ys, dil=dil, groups=groups, route=route))
 
 
-def conv2d(x, w, y, stride=(1, 1), pad=(0, 0), ws=None, dil=(1, 1), groups=1, route=ANR_CONV_ROUTE_AUTO):
+def _conv2d(x, w, y, stride=(1, 1), pad=(0, 0), ws=None, dil=(1, 1), groups=1, route=ANR_CONV_ROUTE_AUTO):
     """y = conv2d(x, w); x [N,C,H,W], w [K,C/groups,R,S] packed, y [N,K,OH,OW] (may be strided views).
     ws: optional workspace tensor of at least workspace_size(ANR_OP_CONV2D, desc) bytes."""
     d = _conv_packed_desc(x, w, y, stride, pad, dil, groups, route)
@@ -354,18 +357,18 @@ def _run_packed(fn, name, op, desc, x, pack, y, ws):
     return y
 
 
-def conv2d_packed(desc, x, pack, y, ws=None):
+def _conv2d_packed(desc, x, pack, y, ws=None):
     """conv2d with weights from conv2d_pack_weights (desc: the descriptor it returned).  x may be a strided view; one
     whose rows are no whole 16-byte units is copied first where the pack is in the patch kernel's order."""
     return _run_packed(_fast.anr_conv2d_packed, "anr_conv2d_packed", ANR_OP_CONV2D, desc, x, pack, y, ws)
 
 
-def conv_bn_relu_packed(desc, x, pack, y, ws=None):
+def _conv_bn_relu_packed(desc, x, pack, y, ws=None):
     """conv + batch norm + ReLU with a pack made with bn=(gamma, beta, mean, var)."""
     return _run_packed(_fast.anr_conv_bn_relu_packed, "anr_conv_bn_relu_packed", ANR_OP_CONV_BN_RELU, desc, x, pack, y, ws)
 
 
-def conv_bn_relu(x, w, gamma, beta, mean, var, eps, y, stride=(1, 1), pad=(0, 0), ws=None, dil=(1, 1), groups=1,
+def _conv_bn_relu(x, w, gamma, beta, mean, var, eps, y, stride=(1, 1), pad=(0, 0), ws=None, dil=(1, 1), groups=1,
                  route=ANR_CONV_ROUTE_AUTO):
     if not w.is_contiguous():
         raise ValueError("weights must be packed")
@@ -379,7 +382,7 @@ def conv_bn_relu(x, w, gamma, beta, mean, var, eps, y, stride=(1, 1), pad=(0, 0)
     return y
 
 
-def dwconv(x, w, y, stride=(1, 1), pad=(0, 0), dil=(1, 1)):
+def _dwconv(x, w, y, stride=(1, 1), pad=(0, 0), dil=(1, 1)):
     d = _conv_packed_desc(x, w, y, stride, pad, dil, 1, ANR_CONV_ROUTE_AUTO)
     _check(_fast.anr_dwconv(d, _ptr(x), _ptr(w), _ptr(y), None, 0, _stream()), "anr_dwconv")
     return y
@@ -394,19 +397,19 @@ def _tbg_desc(q, k, out):
         return bytes(TbgDesc(B, S, H, D, *strides))
 
 
-def tbg(q, k, out):
+def _tbg(q, k, out):
     """out[b,h,i,j] = sum_d q[b,i,h,d] k[b,j,h,d]; q,k [B,S,H,D], out [B,H,S,S]."""
     _check(_fast.anr_tbg(_tbg_desc(q, k, out), _ptr(q), _ptr(k), _ptr(out), None, 0, _stream()), "anr_tbg")
     return out
 
 
-def tbs(q, k, out):
+def _tbs(q, k, out):
     """tbg followed by a softmax over the last axis."""
     _check(_fast.anr_tbs(_tbg_desc(q, k, out), _ptr(q), _ptr(k), _ptr(out), None, 0, _stream()), "anr_tbs")
     return out
 
 
-def nrm(x, out, ws=None):
+def _nrm(x, out, ws=None):
     """out[b] = sqrt(sum of squares of x[b]).  x [N,M] or [b,N,M] with unit column stride, out [1] / [b]."""
     if x.dim() == 2:
         N, M = x.shape
@@ -419,3 +422,14 @@ def nrm(x, out, ws=None):
     d = _pack_nrm(N, M, st[1], b, st[0] if b > 1 else 0)
     _with_workspace(_fast.anr_nrm, "anr_nrm", ANR_OP_NRM, d, (_ptr(x), _ptr(out)), ws, NrmDesc)
     return out
+
+
+# The operators as programs call them: the functions above without Python's part in the usual case.
+_OPERATORS = ("gemm", "conv2d", "conv_bn_relu", "conv2d_packed", "conv_bn_relu_packed", "dwconv", "tbg", "tbs", "nrm")
+for _name in _OPERATORS:
+    globals()["_" + _name].__name__ = globals()["_" + _name].__qualname__ = _name      # (what their errors say)
+_native.setup(tuple(globals()["_" + n] for n in _OPERATORS), _workspaces,
+              tuple(ctypes.cast(getattr(_fast, "anr_" + n), _vp).value for n in _OPERATORS),
+              ctypes.cast(_fast.anr_conv2d_fast_workspace_size, _vp).value)
+from paper_2006_06762_amd._native import (gemm, conv2d, conv_bn_relu, conv2d_packed, conv_bn_relu_packed, dwconv, tbg, tbs,  # noqa: E402
+                                          nrm)

@@ -1,4 +1,4 @@
-"""Compile the HIP sources under csrc/ into paper_2006_06762_amd/libanr.so for gfx950.
+"""Compile the HIP sources under csrc/ into paper_2006_06762_amd/libanr.so for gfx950, and the binding's extension module.
 
 Run as ``python -m paper_2006_06762_amd.build`` (hipcc cross-compiles without a GPU).
 """
@@ -6,6 +6,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -13,6 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libanr.so")
+NATIVE = os.path.join(HERE, "_native.so")       # the binding's extension module (csrc/binding_native.cpp)
 
 SOURCES = ["api.cpp", "gemm.hip", "tbg.hip", "conv_direct.hip", "conv_igemm.hip", "conv_gather.hip", "conv_pieces.hip", "conv_pointwise.hip", "conv_stem.hip", "dwconv.hip", "nrm.hip", "static_scratch.hip"]
 
@@ -54,22 +56,36 @@ def _compile(src, verbose, extra):
     return out
 
 
+def _build_native(verbose):
+    import torch
+    at = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-isystem", os.path.join(at, "include"), "-isystem", "/opt/rocm/include",
+           "-isystem", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "binding_native.cpp"),
+           "-o", NATIVE, "-L", os.path.join(at, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+
+
 def build(verbose: bool = False, extra=()) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        native = ex.submit(_build_native, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose, extra), SOURCES))
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    native.result()
     return LIB
 
 
 def _stale() -> bool:
-    """True when the library is missing or older than any source it is built from."""
-    if not os.path.exists(LIB):
+    """True when the library or the extension module is missing or older than any source they are built from."""
+    if not all(os.path.exists(f) for f in (LIB, NATIVE)):
         return True
-    built = os.path.getmtime(LIB)
+    built = min(os.path.getmtime(f) for f in (LIB, NATIVE))
     srcs = [os.path.join(CSRC, f) for f in os.listdir(CSRC)]
     inc = os.path.join(ROOT, "include")
     srcs += [os.path.join(inc, f) for f in os.listdir(inc)]
@@ -82,9 +98,9 @@ def ensure_built(verbose: bool = False) -> str:
     if not _stale():
         return LIB
     if not shutil.which("hipcc"):
-        if os.path.exists(LIB):
+        if os.path.exists(LIB) and os.path.exists(NATIVE):
             return LIB      # a box without the compiler runs what was shipped
-        raise RuntimeError("libanr.so is missing and hipcc is not on PATH")
+        raise RuntimeError("libanr.so or _native.so is missing and hipcc is not on PATH")
     return build(verbose=verbose)
 
 
