@@ -74,12 +74,19 @@ struct SumCheck {
 
     __device__ __forceinline__ void check(const f32x16& a)
     {
+        bool small = false;                // or zero: most tiles have neither, and a comparison is half of what the exact answer costs
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            // (a copy: the compiler's bit cast of a vector's element takes the first one whatever its index)
-            const float sum = a[r];
+            const float sum = a[r];        // (a copy: the compiler's bit cast of a vector's element takes the first one whatever its index)
             not_finite = fmaf(sum, 0.f, not_finite);
-            smallest = min(smallest, (__builtin_bit_cast(uint32_t, sum) << 1) - 1u);
+            small = small || fabsf(sum) < 0x1p-118f;
+        }
+        if (__any(small)) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float sum = a[r];
+                smallest = min(smallest, (__builtin_bit_cast(uint32_t, sum) << 1) - 1u);
+            }
         }
     }
     __device__ __forceinline__ bool refused() const
