@@ -2,6 +2,7 @@
 // general batched GEMM for operands that do not allow 16-byte loads.
 #include "tbg_dispatch.h"
 #include "tbg_kernel.h"
+#include "tbs_split_kernel.h"
 
 namespace anr {
 namespace {
@@ -66,6 +67,25 @@ hipError_t launch_tbs_long(const tbg::Args& t0, int batch, int vec_store, hipStr
     return launch_kernel(kern, dim3((unsigned)items), dim3(64 * KW), lds_bytes, stream, t, vec_store);
 }
 
+template <int W>
+hipError_t launch_tbs_split(const tbg::Args& t0, int batch, int vec_store, bool as_gemm, hipStream_t stream)
+{
+    tbg::Args t = t0;
+    t.tiles_i = (t.S + tbg::kSplitQueries - 1) / tbg::kSplitQueries;
+    const int64_t items = (int64_t)batch * t.tiles_i;
+    t.xcd_chunk = (items % 8 == 0) ? (int)(items / 8) : 0;
+    t.d_tiles_i = make_fastdiv(t.tiles_i);
+    t.d_h = make_fastdiv(t.H);
+    const size_t lds_bytes = tbg::split_lds_bytes(t.D, W);
+    auto kern = tbg::tbs_split_kernel<W>;
+    if (lds_bytes > 48 * 1024) {
+        static LdsLimit granted;
+        hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_bytes, granted);
+        if (e != hipSuccess) return e;
+    }
+    return launch_kernel(kern, dim3((unsigned)items), dim3(64 * W), lds_bytes, stream, t, vec_store, (int)as_gemm);
+}
+
 }  // namespace
 
 hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
@@ -81,7 +101,8 @@ hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
     p.offsets32 = (int64_t)(a.M - 1) * a.lda + a.K < ((int64_t)1 << 29) && (int64_t)(a.N - 1) * a.ldb + a.K < ((int64_t)1 << 29);
     p.out_offsets32 = (int64_t)(a.M - 1) * a.ldc + a.N < ((int64_t)1 << 29);
     const TbgKernel kernel = choose_tbg(p);
-    if (kernel == TbgKernel::gemm) return launch_gemm(a, stream);
+    const bool split = tbs_split_takes(p);
+    if (kernel == TbgKernel::gemm && !split) return launch_gemm(a, stream);
     const int tiles = (a.M + tbg::kTile - 1) / tbg::kTile;
     const int64_t blocks = (int64_t)a.batch * tiles * tiles;
     tbg::Args t{};
@@ -99,11 +120,17 @@ hipError_t launch_tbg(const GemmArgs& a, hipStream_t stream)
         if (a.M <= 64) return launch_tbs_by_d<2>(t, a.batch, vec_store, stream);
         return launch_tbs_by_d<4>(t, a.batch, vec_store, stream);
     }
-    if (kernel == TbgKernel::rows_long) {
+    if (split || kernel == TbgKernel::rows_long) {
         // 1: rows of 16-byte units, 2: and every store a whole line (see stg4_nt)
         const bool units = is_aligned16(a.C) && (a.ldc % 4 == 0) && (a.sCo % 4 == 0) && (a.sCi % 4 == 0);
         const bool lines = units && (reinterpret_cast<uintptr_t>(a.C) & 127) == 0 && (a.ldc % 32 == 0) && (a.sCo % 32 == 0) && (a.sCi % 32 == 0);
         const int vec_store = lines ? 2 : units ? 1 : 0;
+        if (split) {
+            const bool as_gemm = tbg_split_takes(p);
+            if (t.S <= 256) return launch_tbs_split<8>(t, a.batch, vec_store, as_gemm, stream);
+            if (t.S <= 384) return launch_tbs_split<12>(t, a.batch, vec_store, as_gemm, stream);
+            return launch_tbs_split<16>(t, a.batch, vec_store, as_gemm, stream);
+        }
         if (t.S <= 256) return launch_tbs_long<4, 2>(t, a.batch, vec_store, stream);
         if (t.S <= 384) return launch_tbs_long<4, 3>(t, a.batch, vec_store, stream);
         return launch_tbs_long<4, 4>(t, a.batch, vec_store, stream);

@@ -50,6 +50,25 @@ constexpr bool tbs_long_takes(const TbgProblem& p)
            (walk <= 64 || (walk <= 512 && items >= (walk < 320 ? 11 * walk / 20 : 176)));
 }
 
+// Softmax, 129 to 512 keys: the kernel on bf16 pieces that keeps 64 rows of scores on the chip (tbs_split_kernel.h),
+// in place of whichever of the three above would run.  Lines from 900 shapes of 129 to 512 keys, 16 to 256 floats and
+// 8 to 512 heads, new / old time:
+//  - split GEMM and softmax kernel: always (0.33 to 0.91; 16 x 8 heads of 484 x 484 x 80 129 / 77 us);
+//  - one kernel on fp32 products: its sums of more than 80 floats, or of a number that is no whole step of 16, are
+//    the closer ones (error against 64 bits new / old 0.72 at 16 floats, 0.98 at 64, 1.00 at 80, 1.015 at 56, 1.07
+//    at 96), so it keeps those.  Up to 64 floats it also keeps few work-groups (to 128 of them 0.92 to 1.09, from 144
+//    0.73 to 0.97; to 160 keys a third block of queries and three waves idle: to 288 of them 1.06 to 1.23, 768 0.72 to
+//    0.80); longer rows are always faster here (0.59 to 0.98);
+//  - two kernels: from 88 work-groups (0.56 to 0.97; 60 to 84 0.78 to 1.31).
+constexpr bool tbs_split_takes(const TbgProblem& p)
+{
+    if (!p.softmax || !p.aligned || !p.offsets32 || p.S <= kTbgMaxKeys || p.S > kTbgLongKeys || p.D > kTbgLongD) return false;
+    if (tbg_split_takes(p)) return true;
+    const int64_t groups = p.batch * ((p.S + 63) / 64);
+    if (!tbs_long_takes(p)) return groups >= 88;
+    return p.D % 16 == 0 && p.D <= 80 && (p.D > 64 || groups >= (p.S > 160 ? 144 : 512));
+}
+
 constexpr TbgKernel choose_tbg(const TbgProblem& p)
 {
     const int64_t tiles = (p.S + 63) / 64;
