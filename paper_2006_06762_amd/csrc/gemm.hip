@@ -17,6 +17,7 @@
 #include "anr_kernels.h"
 #include "gemm_dispatch.h"
 #include "gemm_pipe_kernel.h"
+#include "gemm_rows16_kernel.h"
 #include "gemm_rows32_kernel.h"
 #include "gemm_split_kernel.h"
 
@@ -479,8 +480,19 @@ hipError_t launch_rows32_by_k(const GemmArgs& a, hipStream_t stream)
                        : launch_rows32_as<NW, 0>(a, stream);
 }
 
+// A fold per instruction to where gemm_rows32_kernel's sums are runs of more than eight k, so that no error is above its.
+template <int RUN>
+hipError_t launch_rows16(const GemmArgs& a, hipStream_t stream)
+{
+    constexpr int NW = 8;
+    const int tiles_m = (a.M + 15) / 16, tiles_n = (a.N + 15) / 16;
+    return launch_kernel(grows::gemm_rows16_kernel<NW, RUN>, dim3((unsigned)((int64_t)tiles_m * tiles_n * a.batch)), dim3(64 * NW), 0, stream, a,
+                         tiles_m, tiles_n);
+}
+
 hipError_t launch_rows32(const GemmArgs& a, const GemmProblem& q, hipStream_t stream)
 {
+    if (gemm_rows16_takes(q)) return a.K < 800 ? launch_rows16<1>(a, stream) : launch_rows16<4>(a, stream);
     const int64_t tiles = gemm_tiles(q, 32);
     // short sums that the split GEMM would take (many small unaligned matrices) are closer there than with four folds:
     // 300 x 29 x 31 x 97 8.1 us, with four 6.5, the split GEMM 9.9

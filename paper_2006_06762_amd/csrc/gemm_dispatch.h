@@ -56,6 +56,12 @@ constexpr bool gemm_rows32_takes(const GemmProblem& p)
     return p.offsets32 && !p.nk && p.one_level && tiles <= 512 && p.K > (tiles <= 256 && !p.vec ? 64 : 96);
 }
 
+// Of these the fewest, by 16 x 16 tiles (gemm_rows16_kernel): to 64 tiles of 32 x 32 every CU has at most one of 16 x 16.
+// Of 400 products of 1 to 256 tiles, new / old time: to 64 tiles 0.47 to 0.90 (64 x 64 x 2720 19.9 / 10.0 us, 200 x 130 x 300
+// 6.3 / 4.6), 65 to 128 0.61 to 1.13, then 0.75 to 1.34, past 192 1.12 to 1.76: the matrix cores of all CUs are busy then, and larger
+// tiles read less.
+constexpr bool gemm_rows16_takes(const GemmProblem& p) { return gemm_rows32_takes(p) && gemm_tiles(p, 32) <= 64; }
+
 constexpr GemmKernel choose_gemm(const GemmProblem& p)
 {
     // few whole tiles and a reduction of 128, 256 or 512: one 32x32 tile per work-group, K split over its waves

@@ -1,4 +1,5 @@
-// GMM for few output tiles and a long reduction, any M, N, K and alignment: a work-group owns one 32 x 32 tile of C
+// GMM for few output tiles (more than 64: gemm_rows16_kernel has the fewest) and a long reduction, any M, N, K and
+// alignment: a work-group owns one 32 x 32 tile of C
 // and its NW waves share the reduction, wave w taking the 32-wide chunks w, w + NW, ...  As in
 // gemm_tile32_ksplit_kernel (whole tiles, one chunk per wave) a wave stages its chunk of A and B through a region of
 // LDS of its own, so that there is no barrier before the sums meet; here the next chunk's loads are in flight while
@@ -6,7 +7,7 @@
 //
 // Bound: a chain of latencies per wave (load, LDS, sixteen matrix instructions) with the waves of a SIMD in
 // different places of theirs.  The kernels with 64-wide tiles, which these products took before, leave most CUs idle and
-// walk the chunks with a barrier each: 32 x 512 x 1408 27 -> 12 us, 96 x 1088 x 3648 63 -> 26, 553 x 420 x 1298 29 -> 14, 16 x
+// walk the chunks with a barrier each: 96 x 1088 x 3648 63 -> 26 us, 553 x 420 x 1298 29 -> 14, 16 x
 // 130 x 68 x 3577 62 -> 28, 192 x 1408 x 864 20 -> 14.
 //
 // The sums of short runs of k meet in a compensated one, so the error does not grow with K: relative to the exact
