@@ -36,8 +36,10 @@
  *     matter and are undefined on return.  A call that needs more than it
  *     is given returns ANR_ERR_WORKSPACE.  Calls that share one workspace
  *     must be ordered (same stream).  Convolutions that are given
- *     anr_conv2d_fast_workspace_size() bytes run the fastest kernel, which for
- *     larger layers keeps more there; its sums are taken in another order.
+ *     anr_conv2d_fast_workspace_size() bytes or more run the fastest kernel, which for
+ *     many larger layers keeps its operands there in another form and takes its
+ *     sums in another order; with less they run the kernel that
+ *     anr_conv2d_route reports.
  *   - Errors are return codes.  All argument checks happen on the host before
  *     anything is launched, so an invalid call has no effect on the device.
  *   - Thread-safe and re-entrant.  The library reads no environment variable
@@ -281,12 +283,15 @@ anr_status anr_workspace_size(int op, const void *desc, size_t *bytes);
 /* Bytes of workspace with which anr_conv2d, anr_conv_bn_relu and their packed forms run `desc`
  * fastest: for layers that gain from it, room for the operands as three bf16 pieces each (at
  * most 256 MB), which are made once per call there instead of once per output tile
- * (conv_pieces_kernel.h), else anr_workspace_size().  May be less than that; a call that is
- * given less than both returns ANR_ERR_WORKSPACE, one given less than this runs another kernel. */
+ * (conv_pieces_kernel.h), and then always more than anr_workspace_size(); else just that.  A
+ * call that is given less than this, anr_workspace_size() bytes among them, runs the kernel that
+ * anr_conv2d_route reports. */
 anr_status anr_conv2d_fast_workspace_size(const anr_conv_desc *desc, size_t *bytes);
 
 /* Which kernel anr_conv2d / anr_conv_bn_relu would run for `desc` with 16-byte aligned
- * pointers and anr_workspace_size() bytes of workspace, and how (host-side planning only: nothing is launched, no GPU is needed).  For
+ * pointers and anr_workspace_size() bytes of workspace, and how (host-side planning only: nothing
+ * is launched, no GPU is needed).  Layers whose anr_conv2d_fast_workspace_size() is more run on
+ * pieces where they are given as much.  For
  * callers that want to know why a layer takes the time it does, and for tests of the
  * selection logic.  tile_m x tile_n is the work-group's output tile (pixels x channels),
  * ksplit the number of work-groups that share a tile's reduction through the workspace,

@@ -247,12 +247,12 @@ anr_status anr_conv2d_noalloc(const anr_conv_desc* d, const float* x, const floa
     // plans that need no workspace never touch the array (nor the runtime, to look it up)
     const size_t need = anr::conv2d_workspace_bytes(a);
     if (need == 0) return run_conv2d(&a, nullptr, 0, hip_stream);
+    if (need > anr::kStaticScratchBytes) return ANR_ERR_WORKSPACE;
     void* scratch = nullptr;
     size_t scratch_bytes = 0;
     const hipError_t e = anr::static_scratch(&scratch, &scratch_bytes);
     if (e != hipSuccess) return launch_status(e);
-    // (no more than the need: a larger workspace may select another kernel)
-    return run_conv2d(&a, scratch, need < scratch_bytes ? need : scratch_bytes, hip_stream);
+    return run_conv2d(&a, scratch, need, hip_stream);           // (a larger workspace may select another kernel)
 }
 
 anr_status anr_conv2d_packed_size(const anr_conv_desc* d, size_t* bytes)

@@ -281,10 +281,12 @@ size_t conv2d_gather_workspace_bytes(const ConvArgs& a)
     return make_plan(a, &g) && choose_tile(a, &g) ? plan_workspace(g) : 0;
 }
 
-double conv2d_gather_estimate_us(const ConvArgs& a)
+double conv2d_gather_estimate_us(const ConvArgs& a, size_t* workspace)
 {
     Plan g;
+    if (workspace) *workspace = 0;
     if (!(make_plan(a, &g) && choose_tile(a, &g))) return INFINITY;
+    if (workspace) *workspace = plan_workspace(g);
     if (g.taps) return estimate_taps_us(g, a, g.ksplit);        // (6 and, for the large kernels, 4 % too short over 220 layers)
     // Weights that are not 16-byte aligned: the form without compile-time taps, which loads them one by one; its own
     // estimate, for tiles that it compares with each other, is too short by a quarter (110 layers of 16 to 512 channels on maps of

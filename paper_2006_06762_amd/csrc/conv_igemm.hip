@@ -271,14 +271,15 @@ __global__ __launch_bounds__(256) void conv_pack_bn_kernel(const float* __restri
 
 }  // namespace
 
-double conv2d_estimate_us(const ConvArgs& call)
+double conv2d_estimate_us(const ConvArgs& call, size_t* workspace)
 {
+    *workspace = 0;
     ConvArgs a = call;
     a.x = a.w = a.wpack = nullptr;
     IgemmPlan p;
     plan_igemm(a, &p);
     ConvRoute r;
-    if (p.variant < 0) return describe_conv2d_stem(a, &r) ? 0. : 1.05 * conv2d_gather_estimate_us(a);
+    if (p.variant < 0) return describe_conv2d_stem(a, &r) ? 0. : 1.05 * conv2d_gather_estimate_us(a, workspace);
     int wp;
     const double rounds = (double)(((int64_t)p.g.tiles_m * p.g.tiles_n + 255) / 256);
     switch (p.variant) {

@@ -21,19 +21,21 @@ bool conv2d_igemm_takes(const ConvArgs& a);
 hipError_t launch_conv2d_gather(const ConvArgs& a, hipStream_t stream, bool* taken, int* ws_fault);
 size_t conv2d_gather_workspace_bytes(const ConvArgs& a);
 // Its estimated time for a 3 x 3 layer in microseconds (conv_taps_kernel, or conv_gather_kernel where the weights are not
-// 16-byte aligned); infinite where it does not take the call.
-double conv2d_gather_estimate_us(const ConvArgs& a);
+// 16-byte aligned) and the bytes of its workspace; infinite where it does not take the call.
+double conv2d_gather_estimate_us(const ConvArgs& a, size_t* workspace = nullptr);
 
 // Estimated time of the kernel that the library's choice of a.route runs without a workspace for pieces, in microseconds;
-// zero where that choice is to stand.  Pointers are taken as aligned and absent.
-double conv2d_estimate_us(const ConvArgs& a);
+// zero where that choice is to stand, and the bytes of that kernel's workspace (conv2d_workspace_bytes of any layer that is
+// not pointwise).  Pointers are taken as aligned and absent.
+double conv2d_estimate_us(const ConvArgs& a, size_t* workspace);
 
 // Order of a pack that a patch kernel reads: output channels per tile and input channels per chunk, rows of a chunk's weights
 // four floats apart; false where the pack is a plain copy.
 bool conv2d_pack_order(const ConvArgs& a, int* tile, int* channels);
 
-// The general convolution on pieces made once per call (conv_pieces_kernel.h).  Bytes of workspace it needs, zero where
-// another kernel is the faster one; *taken false: that, or a.ws is smaller or not aligned.
+// The general convolution on pieces made once per call (conv_pieces_kernel.h).  Bytes of workspace with which it runs, zero
+// where another kernel is the faster one; *taken false: that, or a.ws is smaller or not aligned.  Always more than
+// conv2d_workspace_bytes, so that a call which is given exactly those runs the kernel that needs them.
 size_t conv2d_pieces_workspace_bytes(const ConvArgs& a);
 hipError_t launch_conv2d_pieces(const ConvArgs& a, hipStream_t stream, bool* taken);
 

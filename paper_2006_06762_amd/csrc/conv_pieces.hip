@@ -41,7 +41,7 @@ double estimate_us(const ConvArgs& a, const Plan& g, int cg8, int steps, const V
 
 size_t partial_bytes(const Plan& g) { return g.ksplit > 1 ? sizeof(float) * (size_t)g.ksplit * g.Kpad * g.Mpad : 0; }
 
-// The plan of a call and the bytes of its workspace; false where the kernels do not take it or another one is faster.  Depends on
+// The plan of a call and the bytes of workspace with which it is taken; false where the kernels do not take it or another one is faster.  Depends on
 // the descriptor alone, not on pointers (but for the general route's choice between two kernels), so packed, unpacked and unaligned calls of a layer add the same products in the same
 // order.
 bool plan(const ConvArgs& a, Plan* g, Pieces* z, const Variant** variant, size_t* bytes)
@@ -74,9 +74,10 @@ bool plan(const ConvArgs& a, Plan* g, Pieces* z, const Variant** variant, size_t
             }
         }
     }
+    size_t least;                // that other kernel's workspace
     // Both estimates are off by 8 to 15 %: with a tenth between them 2 % of 240 layers lost more than 3 % and the gain of
     // all was 1.080 of the 1.106 that the faster of the two would give.
-    if (!best || best_us > 0.88 * conv2d_estimate_us(a)) return false;
+    if (!best || best_us > 0.88 * conv2d_estimate_us(a, &least)) return false;
     g->taps = 0;
     g->nchunks = steps;
     gconv::set_tile(a, g, BP, best->channels, best_ks);
@@ -91,6 +92,7 @@ bool plan(const ConvArgs& a, Plan* g, Pieces* z, const Variant** variant, size_t
     z->x_bytes = 3 * z->plane;
     z->w_bytes = (uint32_t)(g->tiles_n * (best->channels / 32)) * (uint32_t)steps * 3072;
     *bytes = partial_bytes(*g) + z->x_bytes + z->w_bytes;
+    if (*bytes <= least) *bytes = least + 16;
     *variant = best;
     return true;
 }

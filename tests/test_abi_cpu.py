@@ -471,10 +471,11 @@ def test_fast_workspace_size():
     assert lib.anr_conv2d_fast_workspace_size(None, ctypes.byref(n)) == B.ANR_ERR_NULL
     bad = B.conv_desc((1, 4, 8, 8), 8, 3, 3, (0, 1))
     assert lib.anr_conv2d_fast_workspace_size(ctypes.byref(bad), ctypes.byref(n)) == B.ANR_ERR_INVALID_ARG
-    # the pieces of both operands, 6 bytes a float, and nothing on the route that asks for the patch kernel
+    # the pieces of both operands, 6 bytes a float, and more than what the kernel without them needs (which a call that is
+    # given exactly that runs), and nothing on the route that asks for the patch kernel
     shape = (16, 256, 14, 14)
     d = B.conv_desc(shape, 256, 3, 3, (1, 1), (1, 1))
-    assert B.conv2d_fast_workspace_size(d) == 6 * (16 * 256 * 14 * 14 + 256 * 256 * 9) < B.workspace_size(B.ANR_OP_CONV2D, d)
+    assert 6 * (16 * 256 * 14 * 14 + 256 * 256 * 9) < B.conv2d_fast_workspace_size(d) == B.workspace_size(B.ANR_OP_CONV2D, d) + 16
     d = B.conv_desc((16, 32, 81, 81), 32, 5, 5, (1, 1), (2, 2))
     assert B.conv2d_fast_workspace_size(d) > 6 * 16 * 32 * 81 * 81 > B.workspace_size(B.ANR_OP_CONV2D, d) == 0
     d.route = B.ANR_CONV_ROUTE_PATCH
