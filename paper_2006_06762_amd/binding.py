@@ -214,7 +214,6 @@ def conv2d_fast_workspace_size(desc: ConvDesc) -> int:
     return int(n.value)
 
 
-_workspaces = {}
 _fast_sizes = {}        # descriptor of a convolution, packed -> conv2d_fast_workspace_size
 
 
@@ -230,27 +229,27 @@ def _fast_size(desc):
     return size
 
 
+def _least_size(op, desc):
+    """anr_workspace_size of a packed descriptor, zero for one that is refused (by the call itself then, too)."""
+    n = ctypes.c_size_t(0)
+    return n.value if _lib.anr_workspace_size(op, desc, ctypes.byref(n)) == ANR_OK else 0
+
+
 def _with_workspace(fn, name, op, desc, args, ws, desc_type=ConvDesc):
-    """Calls fn(desc, *args, workspace, bytes, stream).  The workspace is the caller's tensor, else a buffer
-    kept per (device, stream) and grown on demand (calls on one stream run in order, so they can share it; a
-    call never synchronises).  Without the caller's tensor a convolution gets what it runs fastest with, at most
-    256 MB; for the other operation the call itself says whether the buffer it is handed will do: a refused call
-    has had no effect, and is made again with one that is large enough."""
+    """Calls fn(desc, *args, workspace, bytes, stream).  The workspace is the caller's tensor, else memory of torch's
+    allocator for this call alone, with which a convolution runs fastest (at most 256 MB).  It goes back as soon as
+    the launches are enqueued: the allocator gives it to nothing but later work on the same stream, or on a capture's
+    stream to later work of the same graph.  (Not a buffer kept for the stream: a call is several launches, and another
+    thread's may come between them.)"""
     stream = _stream()
     if ws is None:
-        key = (torch._C._cuda_getDevice(), stream)
-        ws = _workspaces.get(key)
-        have = 0 if ws is None else ws.numel()
-        if desc_type is ConvDesc:
-            need = _fast_size(desc)
-            if need > have:
-                ws = _workspaces[key] = torch.empty(need, dtype=torch.uint8, device="cuda")
-                have = need
-        status = fn(desc, *args, ws.data_ptr() if have else None, have, stream)
-        if status == ANR_ERR_WORKSPACE:
-            ws = torch.empty(workspace_size(op, desc_type.from_buffer_copy(desc)), dtype=torch.uint8, device="cuda")
-            _workspaces[key] = ws
-            status = fn(desc, *args, ws.data_ptr(), ws.numel(), stream)
+        need = _fast_size(desc) if desc_type is ConvDesc else _least_size(op, desc)
+        buffer = torch.cuda.caching_allocator_alloc(need, stream=stream) if need else None
+        try:
+            status = fn(desc, *args, buffer, need, stream)
+        finally:
+            if buffer:
+                torch.cuda.caching_allocator_delete(buffer)
     else:
         need = workspace_size(op, desc_type.from_buffer_copy(desc))
         size = ws.numel() * ws.element_size()
@@ -428,8 +427,8 @@ def _nrm(x, out, ws=None):
 _OPERATORS = ("gemm", "conv2d", "conv_bn_relu", "conv2d_packed", "conv_bn_relu_packed", "dwconv", "tbg", "tbs", "nrm")
 for _name in _OPERATORS:
     globals()["_" + _name].__name__ = globals()["_" + _name].__qualname__ = _name      # (what their errors say)
-_native.setup(tuple(globals()["_" + n] for n in _OPERATORS), _workspaces,
+_native.setup(tuple(globals()["_" + n] for n in _OPERATORS),
               tuple(ctypes.cast(getattr(_fast, "anr_" + n), _vp).value for n in _OPERATORS),
-              ctypes.cast(_fast.anr_conv2d_fast_workspace_size, _vp).value)
+              ctypes.cast(_fast.anr_conv2d_fast_workspace_size, _vp).value, ctypes.cast(_fast.anr_workspace_size, _vp).value)
 from paper_2006_06762_amd._native import (gemm, conv2d, conv_bn_relu, conv2d_packed, conv_bn_relu_packed, dwconv, tbg, tbs,  # noqa: E402
                                           nrm)

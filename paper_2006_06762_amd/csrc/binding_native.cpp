@@ -1,5 +1,5 @@
 // The operators of binding.py for the calls that programs make over and over: plain float32 GPU tensors, a descriptor within
-// its fields' ranges, a workspace that is there.  Anything else (and every error) goes to the Python function of the same
+// its fields' ranges.  Anything else (and every error) goes to the Python function of the same
 // name, so what is accepted, refused and raised is decided there.
 //
 // Marshalling in Python took 1.6 to 2.2 us of a call, more than the launch: back to back on the GPU 128 x 128 x 128 ran every 4.6
@@ -8,6 +8,7 @@
 #include <Python.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -21,16 +22,17 @@
 
 namespace {
 
-// ---- what binding.py hands over (setup): its functions, its workspaces, the library's entry points
+// ---- what binding.py hands over (setup): its functions, the library's entry points
 enum Op { GEMM, CONV2D, CONV_BN_RELU, CONV2D_PACKED, CONV_BN_RELU_PACKED, DWCONV, TBG, TBS, NRM, OPS };
 PyObject* g_python[OPS];
-PyObject* g_workspaces;
 using Call3 = anr_status (*)(const void*, const void*, const void*, void*, void*, size_t, void*);
 using CallBn = anr_status (*)(const void*, const void*, const void*, const void*, const void*, const void*, const void*, float, void*, void*, size_t, void*);
 using CallNrm = anr_status (*)(const void*, const void*, void*, void*, size_t, void*);
-using CallSize = anr_status (*)(const void*, size_t*);
+using CallFastSize = anr_status (*)(const void*, size_t*);
+using CallSize = anr_status (*)(int, const void*, size_t*);
 void* g_entry[OPS];
-CallSize g_fast_size;
+CallFastSize g_fast_size;
+CallSize g_size;
 
 // A tensor that is memory on a GPU and nothing else: no subclass, no wrapper of a transform, float32.
 const at::Tensor* plain(PyObject* o, at::ScalarType type = at::kFloat)
@@ -102,23 +104,18 @@ struct Stream {
     hipStream_t stream = c10::hip::getCurrentHIPStream(device).stream();
 };
 
-// The buffer that binding.py keeps for the stream, held while the call is made; none: null and zero.
+// Memory for the launches of one call (see _with_workspace in binding.py); none of zero bytes.
 struct Workspace {
-    at::Tensor tensor;
-    void* ptr = nullptr;
-    size_t bytes = 0;
+    void* const ptr;
+    const size_t bytes;
 
-    explicit Workspace(const Stream& s)
+    Workspace(size_t need, const Stream& s) : ptr(need ? c10::hip::HIPCachingAllocator::raw_alloc_with_stream(need, s.stream) : nullptr), bytes(need) {}
+    ~Workspace()
     {
-        PyObject* const key = Py_BuildValue("(iN)", (int)s.device, PyLong_FromVoidPtr(s.stream));
-        if (!key) return;
-        PyObject* const ws = PyDict_GetItem(g_workspaces, key);
-        Py_DECREF(key);
-        if (!ws || !THPVariable_Check(ws)) return;
-        tensor = THPVariable_Unpack(ws);
-        ptr = tensor.mutable_data_ptr();
-        bytes = (size_t)tensor.numel();
+        if (ptr) c10::hip::HIPCachingAllocator::raw_delete(ptr);
     }
+    Workspace(const Workspace&) = delete;
+    Workspace& operator=(const Workspace&) = delete;
 };
 
 // Other threads run while the library is called, as they do around a ctypes call: a launch may wait for room in its queue.
@@ -192,8 +189,8 @@ bool run_conv2d(PyObject* const* a)
     anr_conv_desc d;
     if (!x || !w || !y || (a[5] && a[5] != Py_None) || !conv_desc(x, w, y, a[3], a[4], a[6], a[7], a[8], &d)) return false;
     const Stream s;
-    const Workspace ws(s);
-    return fast_size(d) <= ws.bytes && accepted<Call3>(CONV2D, &d, data(x), data(w), data(y), ws.ptr, ws.bytes, s.stream);
+    const Workspace ws(fast_size(d), s);
+    return accepted<Call3>(CONV2D, &d, data(x), data(w), data(y), ws.ptr, ws.bytes, s.stream);
 }
 
 bool run_conv_bn_relu(PyObject* const* a)
@@ -208,9 +205,8 @@ bool run_conv_bn_relu(PyObject* const* a)
         bn[i] = data(v);
     }
     const Stream s;
-    const Workspace ws(s);
-    return fast_size(d) <= ws.bytes && accepted<CallBn>(CONV_BN_RELU, &d, data(x), data(w), bn[0], bn[1], bn[2], bn[3], (float)PyFloat_AS_DOUBLE(a[6]), data(y),
-                                                        ws.ptr, ws.bytes, s.stream);
+    const Workspace ws(fast_size(d), s);
+    return accepted<CallBn>(CONV_BN_RELU, &d, data(x), data(w), bn[0], bn[1], bn[2], bn[3], (float)PyFloat_AS_DOUBLE(a[6]), data(y), ws.ptr, ws.bytes, s.stream);
 }
 
 bool run_packed(Op op, PyObject* const* a)
@@ -230,8 +226,8 @@ bool run_packed(Op op, PyObject* const* a)
     for (int i = 0; i < 4; ++i) d.x_stride[i] = 0;
     strides4(y, d.y_stride);
     const Stream s;
-    const Workspace ws(s);
-    return fast_size(d) <= ws.bytes && accepted<Call3>(op, &d, data(x), data(pack), data(y), ws.ptr, ws.bytes, s.stream);
+    const Workspace ws(fast_size(d), s);
+    return accepted<Call3>(op, &d, data(x), data(pack), data(y), ws.ptr, ws.bytes, s.stream);
 }
 
 bool run_dwconv(PyObject* const* a)
@@ -267,8 +263,10 @@ bool run_nrm(PyObject* const* a)
     d.batch = n == 3 ? x->size(0) : 1;
     d.stride = d.batch > 1 ? x->stride(0) : 0;
     if (out->numel() != d.batch) return false;
+    size_t need = 0;
+    if (g_size(ANR_OP_NRM, &d, &need) != ANR_OK) return false;
     const Stream s;
-    const Workspace ws(s);
+    const Workspace ws(need, s);
     return accepted<CallNrm>(NRM, &d, data(x), data(out), ws.ptr, ws.bytes, s.stream);
 }
 
@@ -291,7 +289,7 @@ PyObject* call(const char* const (&names)[N], int required, int result, Run run,
             return a[result];
         }
     } catch (...) {
-        // (a tensor whose memory cannot be had: Python raises it)
+        // (memory that cannot be had: Python raises it)
     }
     if (PyErr_Occurred()) PyErr_Clear();
     return PyObject_Vectorcall(g_python[OP], args, (size_t)n, kwnames);
@@ -313,11 +311,11 @@ ANR_OPERATOR(py_tbs, TBS, kScores, 3, 2, run_scores(TBS, a))
 ANR_OPERATOR(py_nrm, NRM, kNrm, 2, 1, run_nrm(a))
 #undef ANR_OPERATOR
 
-// setup(functions, workspaces, entries, fast_size): tuples in the order of the operators, entry points as integers.
+// setup(functions, entries, fast_size, size): tuples in the order of the operators, entry points as integers.
 PyObject* py_setup(PyObject*, PyObject* args)
 {
-    PyObject *functions, *workspaces, *entries, *size;
-    if (!PyArg_ParseTuple(args, "O!O!O!O", &PyTuple_Type, &functions, &PyDict_Type, &workspaces, &PyTuple_Type, &entries, &size)) return nullptr;
+    PyObject *functions, *entries, *fast_size, *size;
+    if (!PyArg_ParseTuple(args, "O!O!OO", &PyTuple_Type, &functions, &PyTuple_Type, &entries, &fast_size, &size)) return nullptr;
     if (PyTuple_GET_SIZE(functions) != OPS || PyTuple_GET_SIZE(entries) != OPS) {
         PyErr_SetString(PyExc_ValueError, "one function and one entry point per operator");
         return nullptr;
@@ -330,9 +328,9 @@ PyObject* py_setup(PyObject*, PyObject* args)
         }
         Py_XSETREF(g_python[i], Py_NewRef(PyTuple_GET_ITEM(functions, i)));
     }
-    g_fast_size = reinterpret_cast<CallSize>(PyLong_AsVoidPtr(size));
-    if (!g_fast_size) return nullptr;
-    Py_XSETREF(g_workspaces, Py_NewRef(workspaces));
+    g_fast_size = reinterpret_cast<CallFastSize>(PyLong_AsVoidPtr(fast_size));
+    g_size = reinterpret_cast<CallSize>(PyLong_AsVoidPtr(size));
+    if (!g_fast_size || !g_size) return nullptr;
     Py_RETURN_NONE;
 }
 

@@ -3,6 +3,7 @@ runtime's entry points."""
 import ctypes
 import subprocess
 import sys
+import threading
 
 import pytest
 
@@ -106,3 +107,75 @@ def test_noalloc_refuses_what_is_more_than_its_array():
     assert B.workspace_size(B.ANR_OP_CONV2D, desc(l)) > B.STATIC_SCRATCH_BYTES
     at = ctypes.c_void_p(0x10000)
     assert B.raw().anr_conv2d_noalloc(ctypes.byref(desc(l)), at, at, at, None) == B.ANR_ERR_WORKSPACE
+
+
+# ------------------------------------------------------------------ the binding's workspaces
+class Allocator:
+    """Stands for torch's: addresses in use are never handed out twice."""
+
+    def __init__(self, monkeypatch):
+        self.used, self.next, self.most = {}, 1 << 20, 1 << 40
+        monkeypatch.setattr(B, "_stream", lambda: 7)
+        monkeypatch.setattr(B.torch.cuda, "caching_allocator_alloc", self.alloc)
+        monkeypatch.setattr(B.torch.cuda, "caching_allocator_delete", self.delete)
+
+    def alloc(self, size, device=None, stream=None):
+        assert stream == 7 and size > 0
+        free = self.next if not self.used else max(p + n for p, n in self.used.items())
+        self.used[free] = size
+        return free
+
+    def delete(self, ptr):
+        del self.used[ptr]
+
+
+def packed(l):
+    return bytes(desc(l))
+
+
+NORM = bytes(B.NrmDesc(4096, 4096, 4096, 1, 0))
+
+
+def test_calls_of_two_threads_have_workspaces_of_their_own(monkeypatch):
+    """A call is several launches: another thread's on the same stream may come between them."""
+    allocator, met, seen = Allocator(monkeypatch), threading.Barrier(2, timeout=20), []
+
+    def fn(d, *args):
+        met.wait()                       # both calls are under way
+        seen.append((args[-3], args[-3] + args[-2], args[-1]))
+        met.wait()
+        return B.ANR_OK
+
+    for calls in ([(B.ANR_OP_CONV2D, packed(LAYERS[0]), B.ConvDesc)] * 2, [(B.ANR_OP_NRM, NORM, B.NrmDesc)] * 2,
+                  [(B.ANR_OP_CONV2D, packed(LAYERS[2]), B.ConvDesc), (B.ANR_OP_NRM, NORM, B.NrmDesc)]):
+        seen.clear()
+        threads = [threading.Thread(target=B._with_workspace, args=(fn, "fn", op, d, (1, 2, 3), None, t)) for op, d, t in calls]
+        [t.start() for t in threads]
+        [t.join() for t in threads]
+        (a, a_end, s), (b, b_end, t) = seen
+        assert s == t == 7 and (a_end <= b or b_end <= a)
+        assert not allocator.used
+
+
+@pytest.mark.parametrize("op, d, t, need", [(B.ANR_OP_CONV2D, packed(LAYERS[0]), B.ConvDesc, B.conv2d_fast_workspace_size(desc(LAYERS[0]))),
+                                            (B.ANR_OP_CONV2D, packed((1, 512, 7, 7, 512, 3, 3, (1, 1), (1, 1), (1, 1), 1)), B.ConvDesc, None),
+                                            (B.ANR_OP_CONV2D, packed((2, 16, 8, 8, 16, 3, 3, (1, 1), (1, 1), (1, 1), 1)), B.ConvDesc, 0),
+                                            (B.ANR_OP_NRM, NORM, B.NrmDesc, 4096), (B.ANR_OP_NRM, bytes(B.NrmDesc(8, 8, 8, 1, 0)), B.NrmDesc, 0),
+                                            (B.ANR_OP_NRM, bytes(B.NrmDesc(0, 8, 8, 1, 0)), B.NrmDesc, 0)])
+def test_a_call_is_given_what_it_needs_and_gives_it_back(monkeypatch, op, d, t, need):
+    allocator = Allocator(monkeypatch)
+    if need is None:
+        need = B.workspace_size(op, B.ConvDesc.from_buffer_copy(d))
+        assert need > 0
+
+    def fn(_, x, ws, size, stream):
+        assert (x, size, stream) == (1, need, 7) and (ws is None) == (need == 0)
+        assert list(allocator.used.items()) == ([(ws, need)] if need else [])
+        return status
+    for status in (B.ANR_OK, B.ANR_ERR_LAUNCH):
+        if status == B.ANR_OK:
+            B._with_workspace(fn, "fn", op, d, (1,), None, t)
+        else:
+            with pytest.raises(B.AnrError, match="fn"):
+                B._with_workspace(fn, "fn", op, d, (1,), None, t)
+        assert not allocator.used
