@@ -235,12 +235,20 @@ def _least_size(op, desc):
     return n.value if _lib.anr_workspace_size(op, desc, ctypes.byref(n)) == ANR_OK else 0
 
 
+def _only_replays_hold(buffer):
+    """True in a capture that is not torch's own, whose graph has no pool: nothing but its replays knows of the buffer."""
+    return torch.cuda.is_current_stream_capturing() and not any(
+        s["address"] <= buffer < s["address"] + s["total_size"] for s in torch.cuda.memory_snapshot() if tuple(s["segment_pool_id"]) != (0, 0))
+
+
 def _with_workspace(fn, name, op, desc, args, ws, desc_type=ConvDesc):
     """Calls fn(desc, *args, workspace, bytes, stream).  The workspace is the caller's tensor, else memory of torch's
     allocator for this call alone, with which a convolution runs fastest (at most 256 MB).  It goes back as soon as
-    the launches are enqueued: the allocator gives it to nothing but later work on the same stream, or on a capture's
-    stream to later work of the same graph.  (Not a buffer kept for the stream: a call is several launches, and another
-    thread's may come between them.)"""
+    the launches are enqueued: the allocator gives it to nothing but later work on the same stream, and what
+    is captured by torch (torch.cuda.graph) has it from the graph's own pool, where nothing but the graph's later work gets
+    it.  What another program captures keeps its memory for good; such callers better bring a workspace.  (Not a buffer
+    kept for the stream: a call is several launches, and another thread's may come between them; and a captured call would
+    go on using it when it is replaced by a larger one, or when two graphs run at once.)"""
     stream = _stream()
     if ws is None:
         need = _fast_size(desc) if desc_type is ConvDesc else _least_size(op, desc)
@@ -248,7 +256,7 @@ def _with_workspace(fn, name, op, desc, args, ws, desc_type=ConvDesc):
         try:
             status = fn(desc, *args, buffer, need, stream)
         finally:
-            if buffer:
+            if buffer and not _only_replays_hold(buffer):
                 torch.cuda.caching_allocator_delete(buffer)
     else:
         need = workspace_size(op, desc_type.from_buffer_copy(desc))

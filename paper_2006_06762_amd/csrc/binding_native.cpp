@@ -102,14 +102,25 @@ void strides4(const at::Tensor* t, int64_t* out)
 struct Stream {
     c10::DeviceIndex device = c10::hip::current_device();
     hipStream_t stream = c10::hip::getCurrentHIPStream(device).stream();
+
+    bool capturing() const
+    {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        return hipStreamIsCapturing(stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+    }
 };
 
-// Memory for the launches of one call (see _with_workspace in binding.py); none of zero bytes.
+// Memory for the launches of one call (see _with_workspace in binding.py); none of zero bytes, and not in a capture, where
+// Python looks after it.
 struct Workspace {
+    const bool here;
     void* const ptr;
     const size_t bytes;
 
-    Workspace(size_t need, const Stream& s) : ptr(need ? c10::hip::HIPCachingAllocator::raw_alloc_with_stream(need, s.stream) : nullptr), bytes(need) {}
+    Workspace(size_t need, const Stream& s)
+        : here(need == 0 || !s.capturing()), ptr(need && here ? c10::hip::HIPCachingAllocator::raw_alloc_with_stream(need, s.stream) : nullptr), bytes(need)
+    {
+    }
     ~Workspace()
     {
         if (ptr) c10::hip::HIPCachingAllocator::raw_delete(ptr);
@@ -190,7 +201,7 @@ bool run_conv2d(PyObject* const* a)
     if (!x || !w || !y || (a[5] && a[5] != Py_None) || !conv_desc(x, w, y, a[3], a[4], a[6], a[7], a[8], &d)) return false;
     const Stream s;
     const Workspace ws(fast_size(d), s);
-    return accepted<Call3>(CONV2D, &d, data(x), data(w), data(y), ws.ptr, ws.bytes, s.stream);
+    return ws.here && accepted<Call3>(CONV2D, &d, data(x), data(w), data(y), ws.ptr, ws.bytes, s.stream);
 }
 
 bool run_conv_bn_relu(PyObject* const* a)
@@ -206,7 +217,8 @@ bool run_conv_bn_relu(PyObject* const* a)
     }
     const Stream s;
     const Workspace ws(fast_size(d), s);
-    return accepted<CallBn>(CONV_BN_RELU, &d, data(x), data(w), bn[0], bn[1], bn[2], bn[3], (float)PyFloat_AS_DOUBLE(a[6]), data(y), ws.ptr, ws.bytes, s.stream);
+    return ws.here && accepted<CallBn>(CONV_BN_RELU, &d, data(x), data(w), bn[0], bn[1], bn[2], bn[3], (float)PyFloat_AS_DOUBLE(a[6]), data(y), ws.ptr,
+                                       ws.bytes, s.stream);
 }
 
 bool run_packed(Op op, PyObject* const* a)
@@ -227,7 +239,7 @@ bool run_packed(Op op, PyObject* const* a)
     strides4(y, d.y_stride);
     const Stream s;
     const Workspace ws(fast_size(d), s);
-    return accepted<Call3>(op, &d, data(x), data(pack), data(y), ws.ptr, ws.bytes, s.stream);
+    return ws.here && accepted<Call3>(op, &d, data(x), data(pack), data(y), ws.ptr, ws.bytes, s.stream);
 }
 
 bool run_dwconv(PyObject* const* a)
@@ -267,7 +279,7 @@ bool run_nrm(PyObject* const* a)
     if (g_size(ANR_OP_NRM, &d, &need) != ANR_OK) return false;
     const Stream s;
     const Workspace ws(need, s);
-    return accepted<CallNrm>(NRM, &d, data(x), data(out), ws.ptr, ws.bytes, s.stream);
+    return ws.here && accepted<CallNrm>(NRM, &d, data(x), data(out), ws.ptr, ws.bytes, s.stream);
 }
 
 // Parameters of each operator, the required ones first, and which of them it returns.

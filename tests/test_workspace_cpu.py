@@ -114,8 +114,12 @@ class Allocator:
     """Stands for torch's: addresses in use are never handed out twice."""
 
     def __init__(self, monkeypatch):
-        self.used, self.next, self.most = {}, 1 << 20, 1 << 40
+        self.used, self.next = {}, 1 << 20
+        self.capture = None              # or the pool that the capture in progress allocates from
         monkeypatch.setattr(B, "_stream", lambda: 7)
+        monkeypatch.setattr(B.torch.cuda, "is_current_stream_capturing", lambda: self.capture is not None)
+        monkeypatch.setattr(B.torch.cuda, "memory_snapshot", lambda: [{"address": p, "total_size": n, "segment_pool_id": self.capture or (0, 0)}
+                                                                      for p, n in self.used.items()])
         monkeypatch.setattr(B.torch.cuda, "caching_allocator_alloc", self.alloc)
         monkeypatch.setattr(B.torch.cuda, "caching_allocator_delete", self.delete)
 
@@ -179,3 +183,28 @@ def test_a_call_is_given_what_it_needs_and_gives_it_back(monkeypatch, op, d, t, 
             with pytest.raises(B.AnrError, match="fn"):
                 B._with_workspace(fn, "fn", op, d, (1,), None, t)
         assert not allocator.used
+
+
+def test_a_captured_call_keeps_its_workspace_from_others(monkeypatch):
+    """From the graph's pool it goes back there; without one it is never handed out again, as the graph's replays use it."""
+    allocator, seen = Allocator(monkeypatch), []
+
+    def fn(_, x, ws, size, stream):
+        seen.append((ws, ws + size))
+        return B.ANR_OK
+
+    def call(l):
+        B._with_workspace(fn, "fn", B.ANR_OP_CONV2D, packed(l), (1,), None)
+        return seen[-1]
+
+    call(LAYERS[0])
+    allocator.capture = (0, 3)
+    call(LAYERS[0])
+    assert not allocator.used
+    allocator.capture = (0, 0)
+    captured = [call(LAYERS[0]), call(LAYERS[1])]
+    allocator.capture = None
+    later = [call(LAYERS[0]), call(LAYERS[3])]
+    spans = sorted(captured) + [max(later)]
+    assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:])) and min(later)[0] >= spans[1][1]
+    assert sorted(allocator.used.items()) == [(a, b - a) for a, b in sorted(captured)]

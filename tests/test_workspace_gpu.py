@@ -1,4 +1,6 @@
-"""Calls without a workspace of the caller's: several threads on one stream, each with operands of its own."""
+"""Calls without a workspace of the caller's: several threads on one stream, each with operands of its own; graphs, whose
+replays go on while the stream that they were captured on does other work and while each other's run."""
+import ctypes
 import threading
 
 import pytest
@@ -53,3 +55,85 @@ def test_threads_on_one_stream(own):
     [t.start() for t in threads]
     [t.join() for t in threads]
     assert not wrong
+
+
+class Captured:
+    """A call captured by torch, its output and what that is to be."""
+
+    def __init__(self, call, y, stream):
+        torch.cuda.synchronize()         # (the operands are the default stream's work)
+        with torch.cuda.stream(stream):
+            call()                       # (what a kernel's first launch sets up)
+        stream.synchronize()
+        self.call, self.y, self.want, self.graph = call, y, y.clone(), torch.cuda.CUDAGraph()      # (the call holds its operands)
+        with torch.cuda.graph(self.graph, stream=stream):
+            call()
+        torch.cuda.synchronize()
+
+    def right(self):
+        return torch.equal(self.y, self.want)
+
+
+@pytest.mark.parametrize("name", list(CALLS))
+def test_a_graph_has_memory_of_its_own(name):
+    """A larger layer and tensors of every size afterwards on the stream of the capture: the replays write to none of them."""
+    from paper_2006_06762_amd import binding as anr
+    stream = torch.cuda.Stream()
+    g = Captured(*CALLS[name](anr, 60), stream)
+    larger, z = conv(anr, 61, 16, 128, 40, 96, 5)
+    torch.cuda.synchronize()
+    for i in range(3):
+        with torch.cuda.stream(stream):
+            larger()
+            want = z.clone()
+            others = [torch.full((n,), 7.0, device="cuda") for n in (1 << 10, 1 << 18, 1 << 20, 1 << 21, 1 << 22, 1 << 23, 1 << 24)]
+            g.y.fill_(float("nan"))
+            g.graph.replay()
+            assert g.right() and all(bool((t == 7.0).all()) for t in others)
+            larger()
+            assert torch.equal(z, want)
+            del others
+
+
+@pytest.mark.parametrize("name", list(CALLS))
+def test_graphs_captured_on_one_stream_run_at_once(name):
+    from paper_2006_06762_amd import binding as anr
+    stream = torch.cuda.Stream()
+    graphs = [Captured(*CALLS[name](anr, 70 + i), stream) for i in range(3)]
+    streams = [torch.cuda.Stream() for _ in graphs]
+    for _ in range(5):
+        for g in graphs:
+            g.y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for _ in range(20):
+            for g, s in zip(graphs, streams):
+                with torch.cuda.stream(s):
+                    g.graph.replay()
+        torch.cuda.synchronize()
+        assert all(g.right() for g in graphs)
+
+
+def test_a_capture_that_is_not_torchs():
+    """Replays write to memory that nothing else is given."""
+    from paper_2006_06762_amd import binding as anr
+    hip = ctypes.CDLL("libamdhip64.so.7")         # (the one that torch has loaded)
+    stream = torch.cuda.Stream()
+    call, y = CALLS["pieces split"](anr, 80)
+    at, graph, program = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p(), ctypes.c_void_p()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        call()
+        want = y.clone()
+        torch.cuda.synchronize()
+        relaxed = 2
+        assert hip.hipStreamBeginCapture(at, relaxed) == 0
+        call()
+        assert hip.hipStreamEndCapture(at, ctypes.byref(graph)) == 0
+        assert hip.hipGraphInstantiate(ctypes.byref(program), graph, None, None, 0) == 0
+        others = [torch.full((n,), 7.0, device="cuda") for n in (1 << 18, 1 << 20, 1 << 21, 1 << 22, 1 << 23)]
+        for _ in range(3):
+            y.fill_(float("nan"))
+            assert hip.hipGraphLaunch(program, at) == 0
+            assert torch.equal(y, want) and all(bool((t == 7.0).all()) for t in others)
+        torch.cuda.synchronize()
+        assert hip.hipGraphExecDestroy(program) == 0 and hip.hipGraphDestroy(graph) == 0
