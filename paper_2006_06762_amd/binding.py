@@ -235,6 +235,19 @@ def _least_size(op, desc):
     return n.value if _lib.anr_workspace_size(op, desc, ctypes.byref(n)) == ANR_OK else 0
 
 
+def _allocate(need, op, desc, stream):
+    """(address, bytes) of a workspace of `need` bytes, or where those cannot be had of anr_workspace_size."""
+    if not need:
+        return None, 0
+    try:
+        return torch.cuda.caching_allocator_alloc(need, stream=stream), need
+    except torch.OutOfMemoryError:
+        least = _least_size(op, desc)
+        if least >= need:
+            raise
+    return _allocate(least, op, desc, stream)
+
+
 def _only_replays_hold(buffer):
     """True in a capture that is not torch's own, whose graph has no pool: nothing but its replays knows of the buffer."""
     return torch.cuda.is_current_stream_capturing() and not any(
@@ -243,7 +256,8 @@ def _only_replays_hold(buffer):
 
 def _with_workspace(fn, name, op, desc, args, ws, desc_type=ConvDesc):
     """Calls fn(desc, *args, workspace, bytes, stream).  The workspace is the caller's tensor, else memory of torch's
-    allocator for this call alone, with which a convolution runs fastest (at most 256 MB).  It goes back as soon as
+    allocator for this call alone, with which a convolution runs fastest (at most 256 MB), or if there is no such room
+    what it cannot do without.  It goes back as soon as
     the launches are enqueued: the allocator gives it to nothing but later work on the same stream, and what
     is captured by torch (torch.cuda.graph) has it from the graph's own pool, where nothing but the graph's later work gets
     it.  What another program captures keeps its memory for good; such callers better bring a workspace.  (Not a buffer
@@ -252,7 +266,7 @@ def _with_workspace(fn, name, op, desc, args, ws, desc_type=ConvDesc):
     stream = _stream()
     if ws is None:
         need = _fast_size(desc) if desc_type is ConvDesc else _least_size(op, desc)
-        buffer = torch.cuda.caching_allocator_alloc(need, stream=stream) if need else None
+        buffer, need = _allocate(need, op, desc, stream)
         try:
             status = fn(desc, *args, buffer, need, stream)
         finally:

@@ -115,6 +115,7 @@ class Allocator:
 
     def __init__(self, monkeypatch):
         self.used, self.next = {}, 1 << 20
+        self.most = 1 << 40              # that can be had at once
         self.capture = None              # or the pool that the capture in progress allocates from
         monkeypatch.setattr(B, "_stream", lambda: 7)
         monkeypatch.setattr(B.torch.cuda, "is_current_stream_capturing", lambda: self.capture is not None)
@@ -125,6 +126,8 @@ class Allocator:
 
     def alloc(self, size, device=None, stream=None):
         assert stream == 7 and size > 0
+        if size > self.most:
+            raise B.torch.OutOfMemoryError("no room")
         free = self.next if not self.used else max(p + n for p, n in self.used.items())
         self.used[free] = size
         return free
@@ -208,3 +211,22 @@ def test_a_captured_call_keeps_its_workspace_from_others(monkeypatch):
     spans = sorted(captured) + [max(later)]
     assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:])) and min(later)[0] >= spans[1][1]
     assert sorted(allocator.used.items()) == [(a, b - a) for a, b in sorted(captured)]
+
+
+@pytest.mark.parametrize("layer", LAYERS)
+def test_without_room_for_the_pieces_a_layer_runs_without_them(monkeypatch, layer):
+    allocator, sizes = Allocator(monkeypatch), []
+
+    def fn(_, x, ws, size, stream):
+        assert (ws is None) == (size == 0)
+        sizes.append(size)
+        return B.ANR_OK
+
+    least, fast = B.workspace_size(B.ANR_OP_CONV2D, desc(layer)), B.conv2d_fast_workspace_size(desc(layer))
+    for allocator.most in (fast, fast - 1, least):
+        B._with_workspace(fn, "fn", B.ANR_OP_CONV2D, packed(layer), (1,), None)
+    assert sizes == [fast, least, least] and not allocator.used
+    if least:
+        allocator.most = least - 1
+        with pytest.raises(B.torch.OutOfMemoryError):
+            B._with_workspace(fn, "fn", B.ANR_OP_CONV2D, packed(layer), (1,), None)

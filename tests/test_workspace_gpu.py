@@ -18,7 +18,7 @@ def conv(anr, seed, N, C, H, K, R, packed=False):
     if packed:
         desc, pack = anr.conv2d_pack_weights(x.shape, w, (1, 1), pad)
         return lambda: anr.conv2d_packed(desc, x, pack, y), y
-    return lambda: anr.conv2d(x, w, y, (1, 1), pad), y
+    return lambda ws=None: anr.conv2d(x, w, y, (1, 1), pad, ws=ws), y
 
 
 def norm(anr, seed):
@@ -137,3 +137,29 @@ def test_a_capture_that_is_not_torchs():
             assert torch.equal(y, want) and all(bool((t == 7.0).all()) for t in others)
         torch.cuda.synchronize()
         assert hip.hipGraphExecDestroy(program) == 0 and hip.hipGraphDestroy(graph) == 0
+
+
+@pytest.mark.parametrize("N,C,H,K,R", [(16, 256, 56, 64, 5), (16, 64, 150, 96, 5)])
+def test_a_layer_runs_where_there_is_no_room_for_its_pieces(N, C, H, K, R):
+    """The process is allowed little more than it has: the kernel that needs no workspace, as with an empty one."""
+    from paper_2006_06762_amd import binding as anr
+    call, y = conv(anr, 90, N, C, H, K, R)
+    d = anr.conv_desc((N, C, H, H), K, R, R, (1, 1), (R // 2, R // 2))
+    assert anr.workspace_size(anr.ANR_OP_CONV2D, d) == 0 and anr.conv2d_fast_workspace_size(d) > 64 << 20
+    call(torch.empty(0, dtype=torch.uint8, device="cuda"))
+    want = y.clone()
+    call()
+    pieces = y.clone()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    try:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (8 << 20)) / total)
+        y.fill_(float("nan"))
+        call()
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(y, want) and not torch.equal(want, pieces)
+    call()
+    assert torch.equal(y, pieces)
