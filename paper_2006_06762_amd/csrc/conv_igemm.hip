@@ -271,13 +271,14 @@ __global__ __launch_bounds__(256) void conv_pack_bn_kernel(const float* __restri
 
 }  // namespace
 
-double conv2d_estimate_us(const ConvArgs& call, size_t* workspace)
+double conv2d_estimate_us(const ConvArgs& call, size_t* workspace, PackOrder* pack)
 {
     *workspace = 0;
     ConvArgs a = call;
     a.x = a.w = a.wpack = nullptr;
     IgemmPlan p;
     plan_igemm(a, &p);
+    packed_floats(a, p, &pack->tile, &pack->channels);
     ConvRoute r;
     if (p.variant < 0) return describe_conv2d_stem(a, &r) ? 0. : 1.05 * conv2d_gather_estimate_us(a, workspace);
     int wp;
@@ -289,15 +290,6 @@ double conv2d_estimate_us(const ConvArgs& call, size_t* workspace)
         case 4: return wide_us(a, p);
         default: return 1.1 * fp32_us(a, p.g, p.variant);
     }
-}
-
-bool conv2d_pack_order(const ConvArgs& call, int* tile, int* channels)
-{
-    ConvArgs a = call;
-    a.x = a.w = a.wpack = nullptr;
-    IgemmPlan p;
-    plan_igemm(a, &p);
-    return packed_floats(a, p, tile, channels) > 0;
 }
 
 bool conv2d_igemm_takes(const ConvArgs& a)

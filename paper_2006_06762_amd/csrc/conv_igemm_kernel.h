@@ -60,6 +60,7 @@
 #include <type_traits>
 
 #include "anr_device.h"
+#include "conv_igemm_plan.h"
 #include "conv_internal.h"
 
 namespace anr {
@@ -607,32 +608,6 @@ void conv_igemm_kernel(const ConvArgs p, const Geom g)
     }
 }
 
-// Largest number of virtual rows any M-tile of BM pixels needs.  What a whole tile needs
-// depends only on where in an image it starts, m0 mod OH*OW, and that repeats after
-// OH*OW / gcd(BM, OH*OW) tiles; the clipped last tile needs no more than a whole one at the
-// same start.  So one period is scanned, not every tile of a large batch.
-inline int max_virtual_rows(const ConvArgs& a, int BM, int HV)
-{
-    const int64_t Mtot = (int64_t)a.N * a.OH * a.OW;
-    const int64_t ohow = (int64_t)a.OH * a.OW;
-    int64_t x = BM, y = ohow;
-    while (y) { const int64_t t = x % y; x = y; y = t; }
-    const int64_t period = ohow / x;                      // tiles until the start offset repeats
-    const int64_t tiles = (Mtot + BM - 1) / BM;
-    const int64_t scan = tiles < period ? tiles : period;
-    int vr = 0;
-    for (int64_t t = 0; t < scan; ++t) {
-        const int64_t m0 = t * BM;
-        const int64_t m1 = (m0 + BM < Mtot ? m0 + BM : Mtot) - 1;
-        const int64_t g0 = m0 / a.OW, g1 = m1 / a.OW;
-        const int64_t va = (g0 / a.OH) * HV + (g0 % a.OH) * a.stride_h;
-        const int64_t vb = (g1 / a.OH) * HV + (g1 % a.OH) * a.stride_h;
-        const int need = (int)(vb - va) + a.R;
-        if (need > vr) vr = need;
-    }
-    return vr;
-}
-
 template <int WM_BLK, int WN_BLK, int WAVES_M, int WAVES_N, int KSPLIT, int R_, int S_, int CPH>
 struct Variant {
     static constexpr int NT = 64 * WAVES_M * WAVES_N * KSPLIT;
@@ -657,7 +632,7 @@ struct Variant {
         g->Mtot = a.N * a.OH * a.OW;
         g->ohow = a.OH * a.OW;
         g->HV = (a.OH - 1) * a.stride_h + a.R;
-        g->VR = max_virtual_rows(a, BM, g->HV);
+        g->VR = max_virtual_rows(a.N, a.OH, a.OW, a.stride_h, a.R, BM, g->HV);
         g->XC = (a.pad_w + 3) / 4 * 4;
         const int wv = (a.OW - 1) * a.stride_w + a.S;           // virtual row width
         const int need_cols = g->XC - a.pad_w + (wv > a.W + a.pad_w ? wv : a.W + a.pad_w);

@@ -25,13 +25,13 @@ size_t conv2d_gather_workspace_bytes(const ConvArgs& a);
 double conv2d_gather_estimate_us(const ConvArgs& a, size_t* workspace = nullptr);
 
 // Estimated time of the kernel that the library's choice of a.route runs without a workspace for pieces, in microseconds;
-// zero where that choice is to stand, and the bytes of that kernel's workspace (conv2d_workspace_bytes of any layer that is
-// not pointwise).  Pointers are taken as aligned and absent.
-double conv2d_estimate_us(const ConvArgs& a, size_t* workspace);
-
-// Order of a pack that a patch kernel reads: output channels per tile and input channels per chunk, rows of a chunk's weights
-// four floats apart; false where the pack is a plain copy.
-bool conv2d_pack_order(const ConvArgs& a, int* tile, int* channels);
+// zero where that choice is to stand, the bytes of that kernel's workspace (conv2d_workspace_bytes of any layer that is
+// not pointwise) and the order of a pack.  Pointers are taken as aligned and absent.
+struct PackOrder {
+    int tile, channels;      // of a pack that a patch kernel reads: output channels per tile, input channels per chunk, rows of a
+                             // chunk's weights four floats apart; zero where the pack is a plain copy
+};
+double conv2d_estimate_us(const ConvArgs& a, size_t* workspace, PackOrder* pack);
 
 // The general convolution on pieces made once per call (conv_pieces_kernel.h).  Bytes of workspace with which it runs, zero
 // where another kernel is the faster one; *taken false: that, or a.ws is smaller or not aligned.  Always more than

@@ -44,7 +44,7 @@ size_t partial_bytes(const Plan& g) { return g.ksplit > 1 ? sizeof(float) * (siz
 // The plan of a call and the bytes of workspace with which it is taken; false where the kernels do not take it or another one is faster.  Depends on
 // the descriptor alone, not on pointers (but for the general route's choice between two kernels), so packed, unpacked and unaligned calls of a layer add the same products in the same
 // order.
-bool plan(const ConvArgs& a, Plan* g, Pieces* z, const Variant** variant, size_t* bytes)
+bool plan(const ConvArgs& a, Plan* g, Pieces* z, const Variant** variant, PackOrder* pack, size_t* bytes)
 {
     const int RS = a.R * a.S;
     // (below 0.4 GFLOP two launches and the split pass are as long as the whole layer on any kernel)
@@ -77,7 +77,7 @@ bool plan(const ConvArgs& a, Plan* g, Pieces* z, const Variant** variant, size_t
     size_t least;                // that other kernel's workspace
     // Both estimates are off by 8 to 15 %: with a tenth between them 2 % of 240 layers lost more than 3 % and the gain of
     // all was 1.080 of the 1.106 that the faster of the two would give.
-    if (!best || best_us > 0.88 * conv2d_estimate_us(a, &least)) return false;
+    if (!best || best_us > 0.88 * conv2d_estimate_us(a, &least, pack)) return false;
     g->taps = 0;
     g->nchunks = steps;
     gconv::set_tile(a, g, BP, best->channels, best_ks);
@@ -118,8 +118,9 @@ size_t conv2d_pieces_workspace_bytes(const ConvArgs& a)
     Plan g;
     Pieces z;
     const Variant* v;
+    PackOrder pack;
     size_t bytes;
-    return plan(a, &g, &z, &v, &bytes) ? bytes : 0;
+    return plan(a, &g, &z, &v, &pack, &bytes) ? bytes : 0;
 }
 
 hipError_t launch_conv2d_pieces(const ConvArgs& a, hipStream_t stream, bool* taken)
@@ -128,23 +129,25 @@ hipError_t launch_conv2d_pieces(const ConvArgs& a, hipStream_t stream, bool* tak
     Plan g;
     Pieces z;
     const Variant* v;
+    PackOrder pack;
     size_t bytes;
-    if (a.ws == nullptr || !is_aligned16(a.ws) || !plan(a, &g, &z, &v, &bytes) || a.ws_bytes < bytes) return hipSuccess;
+    // (less room than the pieces of x alone: not planned; planning takes the host a microsecond or two)
+    if (a.ws == nullptr || !is_aligned16(a.ws) || a.ws_bytes < 6. * a.N * a.C * a.H * a.W || !plan(a, &g, &z, &v, &pack, &bytes) || a.ws_bytes < bytes)
+        return hipSuccess;
     z.at = reinterpret_cast<char*>(a.ws) + partial_bytes(g);
     z.d_hw = make_fastdiv(a.H * a.W);
     z.d_w = make_fastdiv(a.W);
     z.d_cg8g = make_fastdiv(z.cg8 * g.groups);
     z.d_cg8 = make_fastdiv(z.cg8);
     z.rs_mul = (uint32_t)((((uint64_t)1 << 31) + g.RS - 1) / g.RS);
-    int tile = 0, channels = 0;
     if (a.wpack) {
-        if (!conv2d_pack_order(a, &tile, &channels) || channels != 8) return hipSuccess;
+        if (pack.channels != 8) return hipSuccess;
         z.w = a.wpack;
-        z.w_tile = tile;
+        z.w_tile = pack.tile;
         z.w_row = 8 * g.RS + 4;
-        z.w_unit = tile * z.w_row;
+        z.w_unit = pack.tile * z.w_row;
         z.w_tile_step = z.cg8 * z.w_unit;
-        z.w_in_bytes = 4u * (uint32_t)(ceil_div(a.K, tile) * z.w_tile_step);
+        z.w_in_bytes = 4u * (uint32_t)(ceil_div(a.K, pack.tile) * z.w_tile_step);
     } else {
         z.w = a.w;
         z.w_tile = 1;

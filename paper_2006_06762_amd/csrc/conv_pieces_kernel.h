@@ -40,7 +40,7 @@ using gconv::Plan;
 constexpr int BP = 64;               // pixels of a tile
 constexpr int kMaxTaps = 49;
 
-// Where the pieces lie, and where w is read from (host side: make_pieces in conv_pieces.hip).
+// Where the pieces lie, and where w is read from (host side: plan and launch_conv2d_pieces in conv_pieces.hip).
 struct Pieces {
     char* at;                    // in the workspace, behind the partial tiles
     const float* w;              // row of output channel co: w + (co / w_tile) * w_tile_step + co % w_tile * w_row
