@@ -75,8 +75,13 @@ bool plan(const ConvArgs& a, Plan* g, Pieces* z, const Variant** variant, PackOr
         }
     }
     size_t least;                // that other kernel's workspace
-    // Both estimates are off by 8 to 15 %: with a tenth between them 2 % of 240 layers lost more than 3 % and the gain of
-    // all was 1.080 of the 1.106 that the faster of the two would give.
+    // Four groups of waves and a split reduction leave a wave few rounds, and what is around those, the groups' meeting in LDS
+    // above all, is 1 to 4 us longer than the estimate has it (318 layers; with this 5 % rms, without 9).  Only for the comparison
+    // with the other kernel: among the variants it was still the best one where it was taken for that.
+    if (best && best->groups == 4 && best_ks > 1) best_us = 0.9 * best_us + 4.0;
+    // Both estimates are off by 5 to 10 %.  Of 3500 layers of 0.4 GFLOP and more (3 x 3 to 7 x 7, 16 to 512 channels) whose estimate
+    // is below 0.88 of the other kernel's, 18 are slower by more than 3 %, half of them by 5 to 12 (without the line above 46, up to
+    // 20: 4 x 256 x 8 x 123 -> 32 19.4 -> 23.3 us); 26 that gain 4 % are not taken for it.  All together run 1.31 times as fast.
     if (!best || best_us > 0.88 * conv2d_estimate_us(a, &least, pack)) return false;
     g->taps = 0;
     g->nchunks = steps;

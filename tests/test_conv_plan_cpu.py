@@ -2,6 +2,7 @@
 import random
 import subprocess
 
+from paper_2006_06762_amd import binding as B
 from test_gemm_plan_cpu import CSRC
 
 
@@ -31,3 +32,14 @@ int main()
         want.append(most + R)
     text = "\n".join(" ".join(map(str, c)) for c in cases)
     assert list(map(int, subprocess.check_output([str(tmp_path / "rows")], input=text, text=True).split())) == want
+
+
+def test_layers_that_the_pieces_would_slow_down():
+    """Few rounds for each of four groups of waves and a split reduction: with the pieces 19.0 -> 23.3, 20.0 -> 23.7, 17.2 -> 19.8 and
+    23.6 -> 25.3 us, so these are not given room for them; one with more rounds (37.8 -> 33.9) and one without a split
+    (20.0 -> 18.2) are."""
+    def more(x, K, R, groups=1):
+        d = B.conv_desc(x, K, R, R, (1, 1), (R // 2, R // 2), groups=groups)
+        return B.conv2d_fast_workspace_size(d) - B.workspace_size(B.ANR_OP_CONV2D, d)
+    assert [more((4, 256, 8, 123), 32, 3), more((1, 512, 45, 45), 32, 3), more((16, 100, 12, 41), 32, 3), more((1, 256, 21, 99), 96, 3)] == [0] * 4
+    assert more((32, 512, 7, 7), 160, 3) > 0 and more((3, 32, 40, 40), 128, 7, 4) > 0
