@@ -1,4 +1,4 @@
-"""The binding's kept workspace: absent, too small and large enough, on a stream of its own."""
+"""Calls that need more and less workspace than the one before on their stream, and a caller's that is too small."""
 import pytest
 
 torch = pytest.importorskip("torch")

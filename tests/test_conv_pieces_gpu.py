@@ -1,5 +1,6 @@
 """Convolutions on pieces made once per call: every tile and group count, split reductions, channels and output channels that
-are no whole units, an odd number of units, groups, strides, dilations, odd planes, views, packs of both orders, values the
+are no whole units, an odd number of units, groups, strides, dilations, rows and columns that differ in all of these, odd planes,
+views, operands and workspaces that start anywhere, packs of both orders, values the
 pieces cannot carry, and what a call does with less workspace."""
 import numpy as np
 import pytest
@@ -176,3 +177,95 @@ def test_replays_of_a_captured_call():
         torch.cuda.synchronize()
         anr.conv2d(xd, wd, ref, s.stride, s.pad)
         assert torch.equal(y, ref)
+
+
+# (N, C, H, W, K, R, S, stride, pad, dil, groups): rows and columns of the kernel, the steps, the padding and the dilation that differ
+OBLONG = [
+    (8, 64, 40, 50, 96, 3, 5, (1, 2), (1, 2), (1, 1), 1),
+    (8, 64, 37, 45, 96, 5, 3, (2, 1), (0, 1), (1, 2), 1),
+    (8, 96, 30, 61, 64, 1, 9, (1, 1), (0, 4), (1, 1), 1),
+    (8, 96, 61, 30, 64, 9, 1, (1, 1), (4, 0), (1, 1), 1),
+    (8, 100, 33, 70, 80, 7, 4, (1, 3), (6, 1), (2, 1), 4),
+    (6, 40, 29, 83, 72, 2, 7, (1, 1), (2, 0), (1, 3), 2),
+    (4, 48, 57, 31, 40, 4, 12, (1, 1), (3, 11), (1, 1), 1),
+]
+
+
+def oblong(shape, seed, ints):
+    N, C, H, W, K, R, S, stride, pad, dil, groups = shape
+    s = I.ConvShape(N, C, H, W, K, R, S, stride, pad, dil, groups)
+    x, w = I.conv_inputs(s, seed, ints=ints)
+    return s, x, w
+
+
+def exact_oblong(s, x, w):
+    """As exact(), for any geometry."""
+    G, Cg, Kg = s.groups, s.C // s.groups, s.K // s.groups
+    xp = torch.nn.functional.pad(x.double(), (s.pad[1], s.pad[1], s.pad[0], s.pad[0]))
+    y = torch.zeros(2, s.N, G, Kg, s.OH * s.OW, device="cuda", dtype=torch.float64)
+    for r in range(s.R):
+        for t in range(s.S):
+            part = xp[:, :, r * s.dil[0]:r * s.dil[0] + s.stride[0] * (s.OH - 1) + 1:s.stride[0],
+                      t * s.dil[1]:t * s.dil[1] + s.stride[1] * (s.OW - 1) + 1:s.stride[1]].reshape(s.N, G, Cg, -1).contiguous()
+            wt = w.double()[:, :, r, t].reshape(G, Kg, Cg)
+            y[0] += wt @ part
+            y[1] += wt.abs() @ part.abs()
+    return y.reshape(2, s.N, s.K, s.OH, s.OW)
+
+
+@pytest.mark.parametrize("shape", OBLONG)
+def test_rows_and_columns_that_differ(shape):
+    """Whole numbers exactly, others to one rounding per sixteen products; weights and an x that are no whole 16-byte units,
+    images further apart than they are long, and the fused form of a pack."""
+    from paper_2006_06762_amd import binding as anr
+    for ints in (True, False):
+        s, x, w = oblong(shape, 7400, ints)
+        assert sizes(anr, s)[0] < sizes(anr, s)[1]
+        run = dict(dil=s.dil, groups=s.groups)
+        xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+        ref, magnitudes = exact_oblong(s, xd, wd)
+        y = torch.full(ref.shape, float("nan"), device="cuda")
+        anr.conv2d(xd, wd, y, s.stride, s.pad, **run)
+        if ints:
+            assert torch.equal(y.double(), ref)
+            assert np.array_equal(ref[:1].cpu().numpy(), oracle.conv2d_general(x[:1], w, s.stride, s.pad, s.dil, s.groups))
+            continue
+        worst = float(((y - ref).abs() / magnitudes.clamp(min=1e-30)).max())
+        assert worst <= (2 + (s.C // s.groups * s.R * s.S / 16) ** .5) * 2.0 ** -24
+        # the same bits from operands that start anywhere
+        wu = torch.empty(w.size + 1, device="cuda")[1:].view(w.shape).copy_(wd)
+        xu = torch.full((x.size + s.N * 5 + 3,), float("nan"), device="cuda")[3:].view(s.N, -1)[:, :x[0].size].view(x.shape).copy_(xd)
+        assert xu.stride(0) == x[0].size + 5 and xu.data_ptr() % 16 and wu.data_ptr() % 16
+        out = torch.full((s.N, s.K + 1, s.OH, s.OW), 12345.0, device="cuda")
+        anr.conv2d(xu, wu, out[:, :s.K], s.stride, s.pad, **run)
+        assert torch.equal(out[:, :s.K], y) and bool((out[:, s.K] == 12345.0).all())
+        bn = [torch.from_numpy(v).cuda() for v in I.bn_inputs(s.K, 7401)]
+        desc, pack = anr.conv2d_pack_weights(x.shape, wd, s.stride, s.pad, bn=bn, eps=I.BN_EPS, **run)
+        z = torch.empty_like(y)
+        anr.conv_bn_relu(xd, wd, *bn, I.BN_EPS, y, s.stride, s.pad, **run)
+        anr.conv_bn_relu_packed(desc, xd, pack, z)
+        assert torch.equal(z, y)
+        gamma, beta, mean, var = (v.double().view(1, -1, 1, 1) for v in bn)
+        want = torch.relu(gamma * (ref - mean) / torch.sqrt(var + I.BN_EPS) + beta)
+        assert float((y - want).abs().max()) <= 1e-4 * max(1.0, float(want.abs().max()))
+
+
+@pytest.mark.parametrize("shape", [OBLONG[0], OBLONG[5]])
+def test_a_workspace_that_is_not_aligned(shape):
+    """The pieces are left out where nothing else needs a workspace; a split reduction refuses it as ever."""
+    from paper_2006_06762_amd import binding as anr
+    s, x, w = oblong(shape, 7500, True)
+    run = dict(dil=s.dil, groups=s.groups)
+    xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    least, fast = sizes(anr, s)
+    ws = torch.full((fast + 64,), 0xff, dtype=torch.uint8, device="cuda")
+    y = torch.full((s.N, s.K, s.OH, s.OW), float("nan"), device="cuda")
+    for start in (4, 8):
+        if least:
+            with pytest.raises(anr.AnrError):
+                anr.conv2d(xd, wd, y, s.stride, s.pad, ws=ws[start:], **run)
+            assert bool(y.isnan().all())
+        else:
+            anr.conv2d(xd, wd, y, s.stride, s.pad, ws=ws[start:], **run)
+            assert torch.equal(y.double(), exact_oblong(s, xd, wd)[0])
+        assert bool((ws == 0xff).all())

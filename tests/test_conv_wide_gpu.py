@@ -16,6 +16,11 @@ SHAPES = [(5, 32, 37, 53, 320, 1), (8, 16, 33, 27, 400, 1), (4, 32, 90, 71, 384,
           (6, 16, 30, 31, 512, 2), (18, 32, 7, 25, 1000, 1), (25, 64, 26, 26, 100, 1), (13, 32, 31, 29, 200, 2)]
 
 
+def least_workspace(anr, x, K, pad):
+    """With this and no more a layer runs the kernel that its route names, not the one on pieces made once per call."""
+    return torch.empty(anr.workspace_size(anr.ANR_OP_CONV2D, anr.conv_desc(x.shape, K, 3, 3, (1, 1), pad)), dtype=torch.uint8, device="cuda")
+
+
 def tensors(shape, seed, ints, start, gap):
     N, C, H, W, K, pad = shape
     s = I.ConvShape(N, C, H, W, K, 3, 3, (1, 1), (pad, pad))
@@ -106,9 +111,11 @@ def test_weights_that_are_not_aligned(shape, wide_tile):
     buf = torch.empty(wd.numel() + 1, device="cuda")
     wu = buf[1:].view(wd.shape)
     wu.copy_(wd)
-    general = torch.empty_like(wide)
-    anr.conv2d(xv, wu, wide, s.stride, s.pad)
-    anr.conv2d(xv, wu, general, s.stride, s.pad, route=anr.ANR_CONV_ROUTE_GENERAL)
+    general, ws = torch.empty_like(wide), least_workspace(anr, xv, s.K, s.pad)
+    anr.conv2d(xv, wu, wide, s.stride, s.pad, ws=ws)
+    ws = torch.empty(anr.workspace_size(anr.ANR_OP_CONV2D, anr.conv_desc(xv.shape, s.K, 3, 3, s.stride, s.pad, route=anr.ANR_CONV_ROUTE_GENERAL)),
+                     dtype=torch.uint8, device="cuda")
+    anr.conv2d(xv, wu, general, s.stride, s.pad, ws=ws, route=anr.ANR_CONV_ROUTE_GENERAL)
     assert torch.equal(wide, general) == (not wide_tile)
     ref = torch.nn.functional.conv2d(xv.double(), wd.double(), padding=s.pad)
     size = torch.nn.functional.conv2d(xv.double().abs(), wd.double().abs(), padding=s.pad)
@@ -130,29 +137,30 @@ def test_packs_in_the_patch_order(shape):
     desc, pack = anr.conv2d_pack_weights(x.shape, wd, s.stride, s.pad, bn=bn, eps=I.BN_EPS)
     r = anr.conv2d_route(desc)
     assert (r.kernel, r.tile_m, r.tile_n) == (anr.ANR_CONV_KERNEL_PATCH, 224, 64)
+    ws = least_workspace(anr, xv, s.K, s.pad)
     tiles, chunks, head = -(-s.K // 64), s.C // 8, (2 * s.K + 63) // 64 * 64
     image = torch.zeros((tiles * 64, chunks, 76), device="cuda")
     image[:s.K, :, :72] = wd.reshape(s.K, chunks, 72)
     byhand = torch.zeros(head + tiles * chunks * 64 * 76, device="cuda")
     byhand[head:] = image.view(tiles, 64, chunks, 76).permute(0, 2, 1, 3).reshape(-1)
     assert pack.numel() == 4 * byhand.numel() and torch.equal(pack.view(torch.float32)[head:], byhand[head:])
-    anr.conv2d(xv, wd, wide, s.stride, s.pad)
+    anr.conv2d(xv, wd, wide, s.stride, s.pad, ws=ws)
     z = torch.empty_like(wide)
-    anr.conv2d_packed(desc, xv, byhand.view(torch.uint8), z)
+    anr.conv2d_packed(desc, xv, byhand.view(torch.uint8), z, ws=ws)
     assert torch.equal(z, wide)
     buf = torch.empty(xv.numel() + 1, device="cuda")
     xu = buf[1:].view(xv.shape)
     xu.copy_(xv)
     z.zero_()
-    anr.conv2d_packed(desc, xu, pack, z)
+    anr.conv2d_packed(desc, xu, pack, z, ws=ws)
     assert torch.equal(z, wide)
-    anr.conv_bn_relu(xv, wd, *bn, I.BN_EPS, wide, s.stride, s.pad)
-    anr.conv_bn_relu_packed(desc, xu, pack, z)
+    anr.conv_bn_relu(xv, wd, *bn, I.BN_EPS, wide, s.stride, s.pad, ws=ws)
+    anr.conv_bn_relu_packed(desc, xu, pack, z, ws=ws)
     assert torch.equal(z, wide)
     xv[1, 3, 5, 7], wd[2, 1, 0, 2] = float("inf"), 2.0 ** -120          # the second try reads the pack too
     desc, pack = anr.conv2d_pack_weights(x.shape, wd, s.stride, s.pad)
-    anr.conv2d(xv, wd, wide, s.stride, s.pad)
-    anr.conv2d_packed(desc, xv, pack, z)
+    anr.conv2d(xv, wd, wide, s.stride, s.pad, ws=ws)
+    anr.conv2d_packed(desc, xv, pack, z, ws=ws)
     assert torch.equal(z.nan_to_num(1.5), wide.nan_to_num(1.5))
 
 
