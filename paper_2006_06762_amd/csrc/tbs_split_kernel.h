@@ -10,8 +10,9 @@
 // first product and the last, and the waves of a SIMD split and multiply in turn.  (Keys two steps ahead, whole lines of
 // them, spill: 16 x 8 heads of 484 x 484 x 80 138 us against 83.)
 //
-// Where scores alone would be the split GEMM's (as_gemm), these are the same to the last bit: the same products in the same
-// order, in the same sums.  (Otherwise two roundings are saved, see `step`.)
+// Where scores alone would be the split GEMM's (as_gemm), these are the same products in the same order, in the same sums.
+// (Otherwise two roundings are saved, see `step`.)  A value that the pieces cannot carry has 64 queries x all keys done again
+// with the fp32 instruction here, the GEMM's own tile there.
 //
 // The heads of a sequence go round fastest among the work-groups: all query blocks of one head at a time would ask one
 // channel of the L2 for their keys where rows are whole multiples of its interleaving (4 x 16 heads of 512 x 512 x 64 54 us

@@ -151,3 +151,78 @@ def test_its_scores_are_those_of_the_scores_alone(S, D, heads):
     out = run(q, k).double()
     # the exponential 1.5 units, its argument's two roundings, the sum of up to 512 as a tree, the division; all of a few units
     assert bool(((out - want).abs() <= (16 - 2 * below) * 2.0 ** -24 * want + 2.0 ** -148).all())
+
+
+# ------------------------------------------------------------------ every product of pieces that is formed
+PAIRS = [("h", "m"), ("m", "h"), ("m", "m"), ("h", "l"), ("l", "h"), ("m", "l"), ("l", "m")]
+PIECES = {"h": 1.0, "m": 2.0 ** -9, "l": 2.0 ** -18}
+
+
+def up_to(piece):
+    return sum(v for p, v in PIECES.items() if "hml".index(p) <= "hml".index(piece))
+
+
+def one_product(pair, S, heads, D, at):
+    """q and k whose scores are the product of one piece of each: three columns from `at` on, in which all else cancels and every
+    partial sum is exact.  Both, and the factors that are left: +-1 a query, 0, +-1 or +-2 a key."""
+    a, b = pair
+    rng = np.random.default_rng(S + D + at)
+    left, right = rng.choice([-1.0, 1.0], (S, heads)), rng.choice([-2.0, -1.0, 0.0, 1.0, 2.0], (S, heads))
+    q, k = np.zeros((2, 1, S, heads, D))
+    q[0, :, :, at:at + 3] = left[..., None] * [up_to(a), PIECES[a] - up_to(a), -PIECES[a]] / PIECES[a]
+    k[0, :, :, at:at + 3] = right[..., None] * [up_to(b), up_to(b), up_to(b) - PIECES[b]] / PIECES[b]
+    return q.astype(np.float32), k.astype(np.float32), left, right
+
+
+def split(x):
+    """The three bf16 pieces of a float32 array, each rounded to nearest, as float64."""
+    t = torch.from_numpy(x)
+    out = []
+    for _ in range(3):
+        piece = t.to(torch.bfloat16).float()
+        out.append(piece.double().numpy())
+        t = t - piece
+    return out
+
+
+@pytest.mark.parametrize("pair", PAIRS)
+def test_one_product_tells_all(pair):
+    """The model of the kernel's sum gives those scores, and none where that product is left out."""
+    q, k, left, right = one_product(pair, 130, 2, 40, 33)
+    pq, pk = split(q), split(k)
+    want = np.einsum("ih,jh->hij", left, right)
+    for left_out in (None, pair):
+        s = sum(np.einsum("bihd,bjhd->hij", pq[i], pk[j]) for i, p in enumerate("hml") for j, r in enumerate("hml")
+                if p + r != "ll" and (p, r) != left_out)
+        assert np.array_equal(s, want if left_out is None else np.zeros_like(want))
+    assert {-2.0, 0.0, 2.0} <= set(np.unique(want))
+
+
+# (keys, floats, heads), and whether the scores alone are the split GEMM's
+SUMS = [(257, 36, 18, 0), (257, 80, 15, 0), (385, 100, 16, 0), (416, 252, 14, 0), (192, 64, 48, 0), (512, 128, 34, 1), (250, 80, 150, 1)]
+
+
+def test_sums_of_both_orders_are_among_them(tmp_path):
+    text = (tmp_path / "takes.cpp")
+    assert all(split_takes(tmp_path, [(*s[:3], 1, 1, 1) for s in SUMS]))
+    text.write_text(text.read_text().replace("tbs_split_takes(p)", "tbg_split_takes(p)"))
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-I", CSRC, str(text), "-o", str(tmp_path / "takes")], check=True)
+    lines = "\n".join("%d %d %d 1 1 1" % s[:3] for s in SUMS)
+    assert subprocess.check_output([str(tmp_path / "takes")], input=lines, text=True) == "".join(str(s[3]) for s in SUMS)
+
+
+@gpu
+@pytest.mark.parametrize("S, D, heads, as_gemm", SUMS)
+@pytest.mark.parametrize("pair", PAIRS)
+def test_every_product_of_pieces_is_in_the_scores(S, D, heads, as_gemm, pair):
+    """Columns of the first step, of one in the middle and of the last: the scores are exact, what is left is the exponential (a
+    few units) and a tree of at most 512 equal-signed terms, 6 roundings of lanes and waves.  Not those of 2^-27 of the largest
+    products in the last step of sums which have the small products' sum added ahead of its large ones: one instruction then
+    adds both, with a rounding of 2^-24."""
+    last = [D - 3] if as_gemm or pair not in (("m", "l"), ("l", "m")) else []
+    for at in (0, D // 2 // 16 * 16 + 5, *last):
+        q, k, left, right = one_product(pair, S, heads, D, at)
+        out = run(torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda())[0]
+        scores = torch.from_numpy(np.einsum("ih,jh->hij", left, right)).cuda()
+        want = torch.softmax(scores, -1)
+        assert bool(((out.double() - want).abs() <= 32 * 2.0 ** -24 * want).all()), at
