@@ -454,3 +454,5 @@ _native.setup(tuple(globals()["_" + n] for n in _OPERATORS),
               ctypes.cast(_fast.anr_conv2d_fast_workspace_size, _vp).value, ctypes.cast(_fast.anr_workspace_size, _vp).value)
 from paper_2006_06762_amd._native import (gemm, conv2d, conv_bn_relu, conv2d_packed, conv_bn_relu_packed, dwconv, tbg, tbs,  # noqa: E402
                                           nrm)
+for _name in _OPERATORS:
+    globals()[_name].__module__ = __name__          # (where a pickle of one finds it again, in a process that has not imported torch)

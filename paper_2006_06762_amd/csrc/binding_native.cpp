@@ -295,6 +295,10 @@ template <int OP, int N, typename Run>
 PyObject* call(const char* const (&names)[N], int required, int result, Run run, PyObject* const* args, Py_ssize_t n, PyObject* kwnames)
 {
     PyObject* a[N];
+    if (!g_python[OP]) {
+        PyErr_SetString(PyExc_RuntimeError, "the operators are those of paper_2006_06762_amd.binding, which is not imported");
+        return nullptr;
+    }
     try {
         if (!at::impl::torch_function_mode_enabled() && arguments(names, required, args, n, kwnames, a) && run(a)) {
             Py_INCREF(a[result]);

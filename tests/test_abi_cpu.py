@@ -465,6 +465,23 @@ def test_tbg_sizes_beyond_the_descriptor_are_refused_by_the_library(fn):
     assert getattr(B.raw(), fn)(ctypes.byref(d), DUMMY, DUMMY, DUMMY, None, 0, None) == B.ANR_ERR_INVALID_ARG
 
 
+def test_operators_reach_another_process():
+    """As names of the binding: a process that has imported nothing gets them with torch and all they need."""
+    import pickle
+    import subprocess
+    import sys
+    names = ("gemm", "conv2d", "conv_bn_relu", "conv2d_packed", "conv_bn_relu_packed", "dwconv", "tbg", "tbs", "nrm")
+    assert all(pickle.loads(pickle.dumps(getattr(B, n))) is getattr(B, n) for n in names)
+    there = "import pickle, sys\nfor f in pickle.load(sys.stdin.buffer):\n    try: f(1, 2, 3)\n    except Exception as e: print(type(e).__name__)"
+    out = subprocess.run([sys.executable, "-c", there], input=pickle.dumps([getattr(B, n) for n in names]), capture_output=True, check=True,
+                         cwd=B.os.path.dirname(B._HERE)).stdout.decode().split()
+    assert len(out) == len(names) and set(out) <= {"AttributeError", "TypeError"}
+    # the extension module alone says what is missing
+    alone = "import torch\nimport paper_2006_06762_amd._native as native\ntry: native.gemm(1, 2, 3)\nexcept RuntimeError as e: print(e)"
+    out = subprocess.run([sys.executable, "-c", alone], capture_output=True, check=True, cwd=B.os.path.dirname(B._HERE)).stdout.decode()
+    assert "binding" in out
+
+
 def test_fast_workspace_size():
     n = ctypes.c_size_t(0)
     lib = B.raw()
