@@ -200,8 +200,9 @@ def workspace_size(op: int, desc) -> int:
 
 
 def conv2d_route(desc: ConvDesc) -> ConvRoute:
-    """Which kernel anr_conv2d would run for the descriptor (aligned pointers assumed), its tile,
-    split and workspace need; host-side planning only."""
+    """Which kernel anr_conv2d would run for the descriptor (aligned pointers assumed) with workspace_size bytes,
+    its tile, split and workspace need; host-side planning only.  The operators here give a layer
+    conv2d_fast_workspace_size bytes: where that is more, it runs on pieces instead."""
     r = ConvRoute()
     _check(_lib.anr_conv2d_route(ctypes.byref(desc), ctypes.byref(r)), "anr_conv2d_route")
     return r
@@ -262,7 +263,8 @@ def _with_workspace(fn, name, op, desc, args, ws, desc_type=ConvDesc):
     is captured by torch (torch.cuda.graph) has it from the graph's own pool, where nothing but the graph's later work gets
     it.  What another program captures keeps its memory for good; such callers better bring a workspace.  (Not a buffer
     kept for the stream: a call is several launches, and another thread's may come between them; and a captured call would
-    go on using it when it is replaced by a larger one, or when two graphs run at once.)"""
+    go on using it when it is replaced by a larger one, or when two graphs run at once.  The extension module keeps those
+    of up to 8 MB for a thread and stream, outside captures.)"""
     stream = _stream()
     if ws is None:
         need = _fast_size(desc) if desc_type is ConvDesc else _least_size(op, desc)
@@ -325,7 +327,8 @@ def _conv_packed_desc(x, w, y, stride, pad, dil, groups, route):
 
 def _conv2d(x, w, y, stride=(1, 1), pad=(0, 0), ws=None, dil=(1, 1), groups=1, route=ANR_CONV_ROUTE_AUTO):
     """y = conv2d(x, w); x [N,C,H,W], w [K,C/groups,R,S] packed, y [N,K,OH,OW] (may be strided views).
-    ws: optional workspace tensor of at least workspace_size(ANR_OP_CONV2D, desc) bytes."""
+    ws: optional workspace tensor of at least workspace_size(ANR_OP_CONV2D, desc) bytes; with fewer than
+    conv2d_fast_workspace_size(desc) the kernel that conv2d_route reports runs."""
     d = _conv_packed_desc(x, w, y, stride, pad, dil, groups, route)
     _with_workspace(_fast.anr_conv2d, "anr_conv2d", ANR_OP_CONV2D, d, (_ptr(x), _ptr(w), _ptr(y)), ws)
     return y

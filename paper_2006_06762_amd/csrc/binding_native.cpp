@@ -110,23 +110,68 @@ struct Stream {
     }
 };
 
+// Smaller workspaces of a thread, one for each of the eight streams it used last: asking the allocator takes 0.9 us of a call, which
+// shows where the GPU is done before the host (norms 5.9 against 6.9 us; 1 x 32 x 28 x 28 -> 32, 1.7 MB, 7.9 against 8.3; from
+// 8 MB on calls take 15 us and more).  Not of all threads together: another one's launches may come between those of a call.
+// Given back when the thread ends.
+class Kept {
+public:
+    static constexpr size_t kMost = (size_t)8 << 20;
+
+    void* get(size_t need, const Stream& s)
+    {
+        Entry* e = entries_;
+        while (e != entries_ + kStreams && !(e->ptr && e->device == s.device && e->stream == s.stream)) ++e;
+        if (e == entries_ + kStreams) e = &entries_[next_++ % kStreams];
+        else if (e->bytes >= need) return e->ptr;
+        size_t bytes = (size_t)1 << 16;
+        while (bytes < need) bytes *= 2;
+        void* const ptr = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, s.stream);
+        if (e->ptr) c10::hip::HIPCachingAllocator::raw_delete(e->ptr);
+        *e = {s.device, s.stream, ptr, bytes};
+        return ptr;
+    }
+    ~Kept()
+    {
+        for (const Entry& e : entries_) try {
+                if (e.ptr) c10::hip::HIPCachingAllocator::raw_delete(e.ptr);
+            } catch (...) {                       // (at the end of the process)
+            }
+    }
+
+private:
+    static constexpr int kStreams = 8;
+    struct Entry {
+        c10::DeviceIndex device;
+        hipStream_t stream;
+        void* ptr;
+        size_t bytes;
+    };
+    Entry entries_[kStreams] = {};
+    unsigned next_ = 0;
+};
+thread_local Kept t_kept;
+
 // Memory for the launches of one call (see _with_workspace in binding.py); none of zero bytes, and not in a capture, where
 // Python looks after it.
 struct Workspace {
     const bool here;
-    void* const ptr;
     const size_t bytes;
+    void* const ptr;
 
-    Workspace(size_t need, const Stream& s)
-        : here(need == 0 || !s.capturing()), ptr(need && here ? c10::hip::HIPCachingAllocator::raw_alloc_with_stream(need, s.stream) : nullptr), bytes(need)
-    {
-    }
+    Workspace(size_t need, const Stream& s) : here(need == 0 || !s.capturing()), bytes(need), ptr(need && here ? take(need, s) : nullptr) {}
     ~Workspace()
     {
-        if (ptr) c10::hip::HIPCachingAllocator::raw_delete(ptr);
+        if (ptr && bytes > Kept::kMost) c10::hip::HIPCachingAllocator::raw_delete(ptr);
     }
     Workspace(const Workspace&) = delete;
     Workspace& operator=(const Workspace&) = delete;
+
+private:
+    static void* take(size_t need, const Stream& s)
+    {
+        return need > Kept::kMost ? c10::hip::HIPCachingAllocator::raw_alloc_with_stream(need, s.stream) : t_kept.get(need, s);
+    }
 };
 
 // Other threads run while the library is called, as they do around a ctypes call: a launch may wait for room in its queue.
@@ -358,7 +403,8 @@ PyMethodDef g_methods[] = {
     {"conv2d", as_cfunction(py_conv2d), METH_FASTCALL | METH_KEYWORDS,
      "conv2d(x, w, y, stride=(1, 1), pad=(0, 0), ws=None, dil=(1, 1), groups=1, route=0)\n--\n\n"
      "y = conv2d(x, w); x [N,C,H,W], w [K,C/groups,R,S] packed, y [N,K,OH,OW] (may be strided views).\n"
-     "ws: optional workspace tensor of at least workspace_size(ANR_OP_CONV2D, desc) bytes."},
+     "ws: optional workspace tensor of at least workspace_size(ANR_OP_CONV2D, desc) bytes; with fewer than\n"
+     "conv2d_fast_workspace_size(desc) the kernel that conv2d_route reports runs."},
     {"conv_bn_relu", as_cfunction(py_conv_bn_relu), METH_FASTCALL | METH_KEYWORDS,
      "conv_bn_relu(x, w, gamma, beta, mean, var, eps, y, stride=(1, 1), pad=(0, 0), ws=None, dil=(1, 1), groups=1, route=0)\n--\n\n"
      "y = relu(batch norm(conv2d(x, w))) with the batch norm's vectors of K floats."},

@@ -1,4 +1,5 @@
-"""Calls without a workspace of the caller's: several threads on one stream, each with operands of its own; graphs, whose
+"""Calls without a workspace of the caller's: several threads on one stream, each with operands of its own; more streams than
+a thread keeps buffers for, and threads that end; graphs, whose
 replays go on while the stream that they were captured on does other work and while each other's run."""
 import ctypes
 import threading
@@ -163,3 +164,39 @@ def test_a_layer_runs_where_there_is_no_room_for_its_pieces(N, C, H, K, R):
     assert torch.equal(y, want) and not torch.equal(want, pieces)
     call()
     assert torch.equal(y, pieces)
+
+
+def test_more_streams_than_a_thread_keeps_buffers_for():
+    """Needs that grow and shrink on eleven streams in turn, every call's operands other than the last one's; then again in threads
+    that end before their work is done."""
+    from paper_2006_06762_amd import binding as anr
+    streams = [torch.cuda.Stream() for _ in range(11)]
+    gen = torch.Generator(device="cuda").manual_seed(100)
+    jobs = []
+    for batch, n in ((1, 150), (70, 300), (3, 2000), (1, 300), (300, 260), (16, 700)):
+        for i in range(2):
+            x = torch.empty((batch, n, n), device="cuda").uniform_(-1, 1, generator=gen)
+            jobs.append((x, torch.empty(batch, device="cuda")))
+    need = [anr.workspace_size(anr.ANR_OP_NRM, anr.NrmDesc(x.shape[1], x.shape[2], x.shape[2], x.shape[0], x.stride(0))) for x, _ in jobs]
+    assert min(need) > 0
+    layers = [CALLS["split"](anr, 101), conv(anr, 102, 1, 64, 14, 64, 3), CALLS["split"](anr, 103)]       # 4, 1, 4 MB
+    want = [anr.nrm(*j).clone() for j in jobs] + [(c(), y.clone())[1] for c, y in layers]
+    calls = [(lambda x=x, o=o: anr.nrm(x, o), o) for x, o in jobs] + layers
+    torch.cuda.synchronize()
+
+    def work(offset):
+        for turn in range(4):
+            for i, (call, out) in enumerate(calls):
+                with torch.cuda.stream(streams[(i * 5 + turn * 3 + offset) % len(streams)]):
+                    call()
+
+    for offset in range(3):
+        for _, out in calls:
+            out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        thread = threading.Thread(target=work, args=(offset,))
+        work(offset) if offset == 0 else (thread.start(), thread.join())
+        others = [torch.full((1 << s,), 7.0, device="cuda") for s in range(12, 22)]
+        torch.cuda.synchronize()
+        assert all(torch.equal(out, w) for (_, out), w in zip(calls, want))
+        assert all(bool((t == 7.0).all()) for t in others)
