@@ -35,7 +35,8 @@
  *     partial sums of a matrix's slices.  Its contents on entry do not
  *     matter and are undefined on return.  A call that needs more than it
  *     is given returns ANR_ERR_WORKSPACE.  Calls that share one workspace
- *     must be ordered (same stream).  Convolutions that are given
+ *     must be ordered: same stream, and not made by two threads at once (a
+ *     call that uses it is two or three launches).  Convolutions that are given
  *     anr_conv2d_fast_workspace_size() bytes or more run the fastest kernel, which for
  *     many larger layers keeps its operands there in another form and takes its
  *     sums in another order; with less they run the kernel that

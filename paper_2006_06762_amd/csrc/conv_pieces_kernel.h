@@ -1,4 +1,4 @@
-// General convolution (3 x 3 to 7 x 7 kernels, any stride, padding, dilation, groups, channel count, width, strided view) on
+// General convolution (kernels of 9 to 49 taps of any form, any stride, padding, dilation, groups, channel count, width, strided view) on
 // the bf16 matrix pipes, each fp32 operand split into three bf16 pieces (split_bf16.h) once per call: split_operands_kernel
 // writes the pieces of x and w to the workspace in the order in which conv_pieces_kernel reads them.
 //
@@ -7,10 +7,11 @@
 // and a float of x once per tap and column tile.  (Measured as a kernel of its own, on the tiles of gemm_split_kernel.h:
 // 14 x 14, 256 -> 256, batch 16, no faster than the fp32 form.)  Here the loop holds loads, LDS traffic and matrix instructions
 // only, so small tiles, which fill the chip with the layers of small maps, cost no more per product than large ones.
-// Both kernels together against the forms before, batch 16 unless stated (us): 14 x 14, 256 -> 256, 3 x 3 48.5 -> 38.0; 25 x 25,
-// 64 -> 64, 5 x 5 34.8 -> 28.6; 80 x 80, 64 -> 96, 5 x 5, stride 2 126 -> 84; 87 x 87, 48 -> 32, 7 x 7, stride 2 107 -> 57; 12 x 12,
-// 192 -> 512, 5 x 5, batch 32 281 -> 154; 123 x 123, 64 -> 256, 7 x 7, batch 1 220 -> 158 (167 TFLOP/s without the split; the rate at
-// which the largest products run, where the card's power sets the clock).
+// Both kernels together against the forms without, in turn on one card, batch 16 unless stated (us): 14 x 14, 256 -> 256, 3 x 3 44.1 ->
+// 41.2; 25 x 25, 64 -> 64, 5 x 5 35.6 -> 31.0; 80 x 80, 64 -> 96, 5 x 5, stride 2 139 -> 91.5; 87 x 87, 48 -> 32, 7 x 7, stride 2 115 ->
+// 56.5; 12 x 12, 192 -> 512, 5 x 5, batch 32 307 -> 170; 123 x 123, 64 -> 256, 7 x 7, batch 1 251 -> 171; 56 x 56, 128 -> 128, 5 x 5 445 ->
+// 316.  The products alone run at 124 to 130 TFLOP/s in the last two, matrix pipes 39 % busy (170 and 77 % in the largest GEMM): a
+// barrier and 35 scalar instructions for sixteen of the matrix.
 //
 // A unit is eight input channels (of one group) at one tap, 16 bytes a piece; units are ordered (channels / 8, tap), so
 // that the taps of the same channels follow each other and find their pixels in L1.  A step is two units, sixteen k, one
@@ -73,7 +74,7 @@ __device__ __forceinline__ void split_unit(const float (&v)[8], u32x4 (&out)[3])
 
 // One launch for both operands: the first work-groups take eight output channels and eight input channels of w each, with all
 // their taps, through LDS (rows of w are contiguous in taps, units in channels), the others 256 units of x.  Bound by
-// latency: 6 to 8 us for 1.4 million floats (14 MB read and written), of which a launch and two memory round trips are 4.
+// latency: 8 us for 1.4 million floats (14 MB read and written), of which a launch and two memory round trips are 4.
 __global__ __launch_bounds__(256) void split_operands_kernel(const ConvArgs p, const Plan g, const Pieces z)
 {
     char* const ws = z.at;
