@@ -200,3 +200,40 @@ def test_more_streams_than_a_thread_keeps_buffers_for():
         torch.cuda.synchronize()
         assert all(torch.equal(out, w) for (_, out), w in zip(calls, want))
         assert all(bool((t == 7.0).all()) for t in others)
+
+
+def test_another_thread_goes_on_while_one_captures():
+    from paper_2006_06762_amd import binding as anr
+    stream = torch.cuda.Stream()
+    inside = [CALLS[n](anr, 110 + i) for i, n in enumerate(("pieces split", "norm"))]
+    beside = [CALLS[n](anr, 120 + i) for i, n in enumerate(CALLS)]
+    want = []
+    for call, y in inside + beside:
+        call()
+        want.append(y.clone())
+        y.fill_(float("nan"))
+    with torch.cuda.stream(stream):
+        [call() for call, _ in inside]
+    torch.cuda.synchronize()
+    graph, failed = torch.cuda.CUDAGraph(), []
+
+    def eager():
+        try:
+            [call() for _ in range(5) for call, _ in beside]
+        except Exception as e:
+            failed.append(e)
+
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+        inside[0][0]()
+        thread = threading.Thread(target=eager)
+        thread.start()
+        thread.join()
+        inside[1][0]()
+    assert not failed
+    for _ in range(3):
+        for _, y in inside:
+            y.fill_(float("nan"))
+        graph.replay()
+        beside[0][0]()
+        torch.cuda.synchronize()
+        assert all(torch.equal(y, w) for (_, y), w in zip(inside + beside, want))
