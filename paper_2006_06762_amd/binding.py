@@ -258,13 +258,12 @@ def _only_replays_hold(buffer):
 def _with_workspace(fn, name, op, desc, args, ws, desc_type=ConvDesc):
     """Calls fn(desc, *args, workspace, bytes, stream).  The workspace is the caller's tensor, else memory of torch's
     allocator for this call alone, with which a convolution runs fastest (at most 256 MB), or if there is no such room
-    what it cannot do without.  It goes back as soon as
-    the launches are enqueued: the allocator gives it to nothing but later work on the same stream, and what
-    is captured by torch (torch.cuda.graph) has it from the graph's own pool, where nothing but the graph's later work gets
-    it.  What another program captures keeps its memory for good; such callers better bring a workspace.  (Not a buffer
-    kept for the stream: a call is several launches, and another thread's may come between them; and a captured call would
-    go on using it when it is replaced by a larger one, or when two graphs run at once.  The extension module keeps those
-    of up to 8 MB for a thread and stream, outside captures.)"""
+    what it cannot do without.  It goes back as soon as the launches are enqueued: the allocator gives it to nothing but
+    later work on the same stream, and a call that torch captures (torch.cuda.graph) has it from the graph's own pool,
+    where nothing but the graph's later work gets it.  A call that is captured in another way keeps its memory for good;
+    it had better bring a workspace.  (Not a buffer kept for the stream: a call is several launches, and another thread's
+    may come between them; and a captured call would go on using it when it is replaced by a larger one, or when two
+    graphs run at once.  The extension module keeps those of up to 8 MB for a thread and stream, outside captures.)"""
     stream = _stream()
     if ws is None:
         need = _fast_size(desc) if desc_type is ConvDesc else _least_size(op, desc)

@@ -41,9 +41,9 @@ double estimate_us(const ConvArgs& a, const Plan& g, int cg8, int steps, const V
 
 size_t partial_bytes(const Plan& g) { return g.ksplit > 1 ? sizeof(float) * (size_t)g.ksplit * g.Kpad * g.Mpad : 0; }
 
-// The plan of a call and the bytes of workspace with which it is taken; false where the kernels do not take it or another one is faster.  Depends on
-// the descriptor alone, not on pointers (but for the general route's choice between two kernels), so packed, unpacked and unaligned calls of a layer add the same products in the same
-// order.
+// The plan of a call and the bytes of workspace with which it is taken; false where the kernels do not take it or another one
+// is faster.  Depends on the descriptor alone, not on pointers (but for the general route's choice between two kernels), so
+// packed, unpacked and unaligned calls of a layer add the same products in the same order.
 bool plan(const ConvArgs& a, Plan* g, Pieces* z, const Variant** variant, PackOrder* pack, size_t* bytes)
 {
     const int RS = a.R * a.S;
